@@ -64,7 +64,8 @@ enum { DLA_KERNEL_MM3 = 0, DLA_KERNEL_LU = 1, DLA_KERNEL_CHOLESKY = 2 };
  * computes: the paper's split factors of the y and x axes of one 3mm product
  * (code mold, parameters P0..P5).  The remaining fields are the extra knobs of
  * the native kernel.  A field set to 0 means "library default for this
- * macro-tile".
+ * macro-tile".  All six 0, or the schedule that dla_default_params() gives for
+ * the product's size, leaves tile and kernel to the library.
  */
 typedef struct {
   int tile_m, tile_n; /* workgroup macro-tile, multiples of 16                                 */

@@ -32,7 +32,14 @@ static int esize(dla_dtype dt) { return dt == DLA_F64 ? 8 : 4; }
 
 int resolve_schedule(dla_dtype dt, const dla_gemm_params* in, int op, GemmSchedule* out, int64_t m, int64_t n) {
   GemmSchedule s = {0, 0, 0, 0, 0, 0};
-  if (in) s = GemmSchedule{in->tile_m, in->tile_n, in->tile_k, in->unroll_k, in->wave_m, in->wave_n};
+  if (!in || (in->tile_m == 0 && in->tile_n == 0 && in->tile_k == 0 && in->unroll_k == 0 && in->wave_m == 0 && in->wave_n == 0)) {
+    s.own = true;
+  } else if (m > 0 && n > 0) {  // dla_default_params() spelled out is the same choice
+    GemmSchedule def;
+    s.own = resolve_schedule(dt, nullptr, op, &def, m, n) == DLA_SUCCESS && def.tm == in->tile_m && def.tn == in->tile_n &&
+            def.tk == in->tile_k && def.uk == in->unroll_k && def.wm == in->wave_m && def.wn == in->wave_n;
+  }
+  if (in) s = GemmSchedule{in->tile_m, in->tile_n, in->tile_k, in->unroll_k, in->wave_m, in->wave_n, s.own};
   if (s.tm < 0 || s.tn < 0 || s.tk < 0 || s.uk < 0 || s.wm < 0 || s.wn < 0) return DLA_ERR_UNSUPPORTED_PARAMS;
   if (s.tm == 0 && s.tn == 0) {
     // A 128x128 macro-tile needs about four tiles per compute unit to balance the 256 of them;
@@ -144,6 +151,7 @@ int run_gemm(const GemmSchedule& s, int op, const T* A, int64_t lda, const T* B,
   g.total_tiles = problem_tiles(s, op, g.prob[0]);
   const double flops = (op == OP_SUB_NT_LOWER ? 1.0 : 2.0) * (double)M * (double)N * (double)K;
   ProfileScope scope(PHASE_GEMM, flops, st);
+  if (s.own && gemm_wide_fits<T>(op, g)) return launch_gemm_wide<T>(op, g, st);
   return launch_gemm<T>(s, op, g, st);
 }
 template int run_gemm<double>(const GemmSchedule&, int, const double*, int64_t, const double*, int64_t, double*,
@@ -195,7 +203,7 @@ static int mm3_impl(const T* A, int64_t lda, const T* B, int64_t ldb, const T* C
   if (nj == 0) return fill_zero(G, ldg, ni, nl, st);  // E and F are empty: G = 0
   // E = A*B and F = C*D are independent: one grouped launch when their schedules coincide.
   const bool same = se.tm == sf.tm && se.tn == sf.tn && se.tk == sf.tk && se.uk == sf.uk && se.wm == sf.wm &&
-                    se.wn == sf.wn;
+                    se.wn == sf.wn && se.own == sf.own;
   if (nk == 0) { if ((rc = fill_zero(E, L.lde, ni, nj, st)) != DLA_SUCCESS) return rc; }
   if (nm == 0) { if ((rc = fill_zero(F, L.ldf, nj, nl, st)) != DLA_SUCCESS) return rc; }
   if (same && nk > 0 && nm > 0) {
@@ -207,7 +215,8 @@ static int mm3_impl(const T* A, int64_t lda, const T* B, int64_t ldb, const T* C
     g.total_tiles = t0 + problem_tiles(se, OP_ASSIGN, g.prob[1]);
     for (int q = 2; q < kMaxGroup; ++q) g.prob[q] = g.prob[1];
     ProfileScope scope(PHASE_GEMM, 2.0 * ((double)ni * nj * nk + (double)nj * nl * nm), st);
-    if ((rc = launch_gemm<T>(se, OP_ASSIGN, g, st)) != DLA_SUCCESS) return rc;
+    rc = se.own && gemm_wide_fits<T>(OP_ASSIGN, g) ? launch_gemm_wide<T>(OP_ASSIGN, g, st) : launch_gemm<T>(se, OP_ASSIGN, g, st);
+    if (rc != DLA_SUCCESS) return rc;
   } else {
     if (nk > 0 && (rc = run_gemm<T>(se, OP_ASSIGN, A, lda, B, ldb, E, L.lde, ni, nj, nk, st)) != DLA_SUCCESS) return rc;
     if (nm > 0 && (rc = run_gemm<T>(sf, OP_ASSIGN, C, ldc, D, ldd, F, L.ldf, nj, nl, nm, st)) != DLA_SUCCESS) return rc;
@@ -390,7 +399,7 @@ int dla_gemm(int op, const void* d_a, int64_t lda, const void* d_b, int64_t ldb,
   if (rc != DLA_SUCCESS) return rc;
   hip_clear_stale_error();
   if (op == OP_SUB_TN) {  // instantiated for the 32x32 (16x16 waves) and 64x64 (32x32 waves) macro-tiles only
-    if (!p || (p->tile_m == 0 && p->tile_n == 0)) s = GemmSchedule{64, 64, 16, 2, 32, 32};
+    if (!p || (p->tile_m == 0 && p->tile_n == 0)) s = GemmSchedule{64, 64, 16, 2, 32, 32, s.own};
     const bool ok = (s.tm == 32 && s.tn == 32 && s.wm == 16 && s.wn == 16) || (s.tm == 64 && s.tn == 64 && s.wm == 32 && s.wn == 32);
     if (!ok) return DLA_ERR_UNSUPPORTED_PARAMS;
   }

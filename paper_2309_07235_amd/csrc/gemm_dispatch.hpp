@@ -10,6 +10,7 @@ namespace dla {
 
 struct GemmSchedule {
   int tm, tn, tk, uk, wm, wn;
+  bool own = false;  // the library's own choice: gemm_wide_kernel takes the product where it can
 };
 
 constexpr int kMaxLdsBytes = 160 * 1024;  // LDS per CU on gfx950
@@ -71,6 +72,13 @@ int launch_gemm_tile(const GemmSchedule& s, int op, const GemmGroup<T>& g, hipSt
 // Returns DLA_SUCCESS, DLA_ERR_UNSUPPORTED_PARAMS or DLA_ERR_HIP.
 template <typename T>
 int launch_gemm(const GemmSchedule& s, int op, const GemmGroup<T>& g, hipStream_t st);
+
+// gemm_wide_kernel (gemm_wide.hip): C = A*B, C -= A*B and C -= A^T*B with a tile of the library's choice.  fits: the
+// products are within its limits.  launch fills in the tile fields of the group.
+template <typename T>
+bool gemm_wide_fits(int op, const GemmGroup<T>& g);
+template <typename T>
+int launch_gemm_wide(int op, GemmGroup<T>& g, hipStream_t st);
 
 // LDS bytes of a schedule (both dtypes share the formula), used for menu legality on the host.
 inline int gemm_lds_bytes(const GemmSchedule& s, bool bt, int esz) {

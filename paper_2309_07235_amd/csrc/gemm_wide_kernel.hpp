@@ -1,0 +1,293 @@
+// LDS-tiled MFMA GEMM for the products whose schedule the library picks itself: the products of 3mm (paper,
+// 3mm_basic listing) and those of the solves with many right-hand sides.  A schedule that the caller names runs on
+// gemm_kernel.
+//
+// What bounds gemm_kernel on these shapes is the round trip of a k-slab: its loads are issued one slab ahead, and with
+// the two to four workgroups per compute unit that such products have, a slab is multiplied (0.2 - 0.9 us) before the
+// next one has arrived.  Its fragment reads are also 8 bytes each (4 in fp32), its LDS writes too.  Here
+//   - two slabs are in flight: slab s + 2 is requested before slab s is multiplied, into the register set that slab s
+//     left, and slab s + 1 goes from the other set to LDS half way through the multiplication;
+//   - a slab is 128 bytes of k, and k is dealt to the lanes so that the left operand's values of a lane are one run:
+//     lane group l4 (the k index of an MFMA) takes k = KPL l4 + kk in step kk of KPL, two 16-byte LDS reads a slab and
+//     row block.  The row stride is odd in units of 16 bytes, so the 8 rows one access cycle serves use all banks;
+//   - adjacent column blocks are interleaved (block b of a pair takes the columns 2 l15 + b), so the right operand is
+//     read and the result stored 16 bytes at a time as well;
+//   - rows and columns past the edge of the matrices are clamped and only reach results that are not stored, so a
+//     ragged tile runs the interior loop without a mask; only a last, partial slab, and a ragged column tile whose
+//     width is not a multiple of 16 bytes, load element by element.
+// Eight waves per workgroup, two on each SIMD, cover each other's barrier.  Measured, back to back (before: gemm_kernel
+// with its default schedule): fp64 E|F of the extralarge 3mm 590 -> 487 us, G 255 -> 208, 4096 x 4096 x 1024 63 ->
+// 72 TFLOP/s (92 % of the matrix-pipe peak); fp32 E|F of the large 3mm 73 -> 43 us, G 57 -> 23.  Whole calls: 847 -> 710
+// and 130 -> 64 us.  Deeper slabs (256
+// bytes) are 5 % slower, shallower ones (64 bytes) 2 - 10 %, 16 waves per 64 x 64 tile 10 %.
+#pragma once
+#include <type_traits>
+#include "gemm_kernel.hpp"
+
+namespace dla {
+
+// vectors of one 16-byte access that need no more alignment than one element
+template <typename T>
+struct WideVec;
+template <>
+struct WideVec<double> {
+  typedef double v2 __attribute__((ext_vector_type(2), aligned(8)));
+  typedef v2 v16;
+  static constexpr int PER = 2;
+};
+template <>
+struct WideVec<float> {
+  typedef float v2 __attribute__((ext_vector_type(2), aligned(4)));
+  typedef float v4 __attribute__((ext_vector_type(4), aligned(4)));
+  typedef v4 v16;
+  static constexpr int PER = 4;
+};
+
+// F: adjacent blocks one lane serves from one run of contiguous elements
+template <typename T, int F>
+constexpr int wide_run() {
+  return (sizeof(T) == 4 && F % 4 == 0) ? 4 : (F % 2 == 0 ? 2 : 1);
+}
+
+template <typename T, int WM, int WN, int FM, int FN, int TK, bool AT>
+struct WideShape {
+  static constexpr int TM = WM * FM * 16, TN = WN * FN * 16;
+  static constexpr int NT = WM * WN * 64;
+  static constexpr int PER = WideVec<T>::PER;
+  static constexpr int SA = AT ? TM : TK + PER;      // LDS row stride of the left operand
+  static constexpr int SB = TN;
+  static constexpr int A_ELEMS = AT ? TK * SA : TM * SA;
+  static constexpr int B_ELEMS = TK * SB;
+  static constexpr int STAGE = A_ELEMS + B_ELEMS;
+  static constexpr int BYTES = 2 * STAGE * (int)sizeof(T);
+};
+
+// Loads a ROWS x COLS tile (COLS contiguous in memory), 16 bytes per thread and step.
+template <typename T, int ROWS, int COLS, int NT>
+struct WideLoader {
+  using V = typename WideVec<T>::v16;
+  static constexpr int PER = WideVec<T>::PER;
+  static constexpr int VPR = COLS / PER;
+  static constexpr int TOTAL = ROWS * VPR;
+  static constexpr int ITER = (TOTAL + NT - 1) / NT;
+  static_assert(COLS % PER == 0, "tile width");
+  static __device__ __forceinline__ int row_of(int idx) { return (TOTAL % NT == 0 || idx < TOTAL) ? idx / VPR : ROWS - 1; }
+  static __device__ __forceinline__ int col_of(int idx) { return (idx % VPR) * PER; }
+};
+
+template <typename T, int WM, int WN, int FM, int FN, int TK, int OP>
+__global__ void __launch_bounds__(WM * WN * 64) gemm_wide_kernel(const GemmGroup<T> g) {
+  constexpr bool AT = OP == OP_SUB_TN, SUB = OP != OP_ASSIGN;
+  using S = WideShape<T, WM, WN, FM, FN, TK, AT>;
+  constexpr int TM = S::TM, TN = S::TN, NT = S::NT, PER = S::PER;
+  constexpr int KPL = TK / 4;  // k-steps of a slab = k values per lane
+  constexpr int RA = AT ? wide_run<T, FM>() : 1, RB = wide_run<T, FN>();
+  using acc_t = typename Mfma<T>::acc_t;
+  using V = typename WideVec<T>::v16;
+  using LA = WideLoader<T, AT ? TK : TM, AT ? TM : TK, NT>;
+  using LB = WideLoader<T, TK, TN, NT>;
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  T* const smem = reinterpret_cast<T*>(smem_raw);
+
+  const int logical = xcd_contiguous_id((int)blockIdx.x, g.total_tiles);
+  int pi = 0;
+#pragma unroll
+  for (int q = 1; q < kMaxGroup; ++q)
+    if (q < g.nprob && logical >= g.prob[q].tile_begin) pi = q;
+  const GemmProblem<T>& P = g.prob[pi];
+  const int local = logical - P.tile_begin;
+  const int ti = local / P.tiles_n, tj = local % P.tiles_n;
+  const int m0 = ti * TM, n0 = tj * TN;
+  const int tid = (int)threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int l15 = lane & 15, l4 = lane >> 4;
+  const int wm0 = (wave / WN) * (FM * 16), wn0 = (wave % WN) * (FN * 16);
+  const int M = P.M, N = P.N, K = P.K;
+  const int64_t lda = P.lda, ldb = P.ldb, ldc = P.ldc;
+  const bool full_mn = m0 + TM <= M && n0 + TN <= N;
+
+  // row of the tile held by index i of row block a, column held by lane l15 of column block b
+  auto row_at = [&](int a, int i) { return wm0 + (a / RA) * 16 * RA + i * RA + a % RA; };
+  const int coll = wn0 + l15 * RB;
+  auto col_at = [&](int b) { return coll + (b / RB) * 16 * RB + b % RB; };
+
+  acc_t acc[FM][FN];
+  T* const Ct = P.C + (int64_t)m0 * ldc + n0;
+  if constexpr (SUB) {
+    const int rmax = M - 1 - m0, cmax = N - 1 - n0;
+#pragma unroll
+    for (int a = 0; a < FM; ++a)
+#pragma unroll
+      for (int b = 0; b < FN; ++b)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          const int r = row_at(a, Mfma<T>::row_of(v, lane)), c = col_at(b);
+          acc[a][b][v] = full_mn ? Ct[(int64_t)r * ldc + c] : Ct[(int64_t)(r < rmax ? r : rmax) * ldc + (c < cmax ? c : cmax)];
+        }
+  } else {
+#pragma unroll
+    for (int a = 0; a < FM; ++a)
+#pragma unroll
+      for (int b = 0; b < FN; ++b) acc[a][b] = acc_t{0, 0, 0, 0};
+  }
+
+  // ---- operand loads.  Rows and columns past the edge are clamped into the matrix: what they bring only reaches
+  // results past the edge, which are not stored.
+  const T* const Ag = AT ? P.A + m0 : P.A + (int64_t)m0 * lda;
+  const T* const Bg = P.B + n0;
+  const int a_cols = AT ? M - m0 : K, b_cols = N - n0;   // columns of memory rows that exist
+  const bool a_vec = !AT || a_cols >= LA::VPR * PER || (a_cols % PER == 0), b_vec = b_cols >= TN || (b_cols % PER == 0);
+  uint32_t aoff[LA::ITER], boff[LB::ITER];               // element offsets of slab 0
+#pragma unroll
+  for (int it = 0; it < LA::ITER; ++it) {
+    const int idx = tid + it * NT, r = LA::row_of(idx), c = LA::col_of(idx);
+    if constexpr (AT) aoff[it] = (uint32_t)(r * (uint32_t)lda + (c + PER <= a_cols ? c : (a_cols >= PER ? a_cols - PER : 0)));
+    else aoff[it] = (uint32_t)((m0 + r < M ? r : M - 1 - m0) * (uint32_t)lda + c);
+  }
+#pragma unroll
+  for (int it = 0; it < LB::ITER; ++it) {
+    const int idx = tid + it * NT, r = LB::row_of(idx), c = LB::col_of(idx);
+    boff[it] = (uint32_t)(r * (uint32_t)ldb + (c + PER <= b_cols ? c : (b_cols >= PER ? b_cols - PER : 0)));
+  }
+  V ra[2][LA::ITER], rb[2][LB::ITER];
+  auto load_full = [&](auto sc, int s) __attribute__((always_inline)) {
+    constexpr int X = decltype(sc)::value;
+    const T* const pa = AT ? Ag + (int64_t)s * TK * lda : Ag + (int64_t)s * TK;
+    const T* const pb = Bg + (int64_t)s * TK * ldb;
+#pragma unroll
+    for (int it = 0; it < LA::ITER; ++it) ra[X][it] = *reinterpret_cast<const V*>(pa + aoff[it]);
+#pragma unroll
+    for (int it = 0; it < LB::ITER; ++it) rb[X][it] = *reinterpret_cast<const V*>(pb + boff[it]);
+  };
+  // element by element, zero past the edge
+  auto load_edge = [&](auto sc, int s) __attribute__((always_inline)) {
+    constexpr int X = decltype(sc)::value;
+    const int kv = K - s * TK;
+    const T* const pa = AT ? Ag + (int64_t)s * TK * lda : Ag + (int64_t)s * TK;
+    const T* const pb = Bg + (int64_t)s * TK * ldb;
+#pragma unroll
+    for (int it = 0; it < LA::ITER; ++it) {
+      const int idx = tid + it * NT, r = LA::row_of(idx), c = LA::col_of(idx);
+      const int rv = AT ? kv : M - m0, cv = AT ? a_cols : kv;
+#pragma unroll
+      for (int e = 0; e < PER; ++e) {
+        const T x = pa[(int64_t)(r < rv ? r : rv - 1) * lda + (c + e < cv ? c + e : cv - 1)];
+        ra[X][it][e] = (r < rv && c + e < cv) ? x : T(0);
+      }
+    }
+#pragma unroll
+    for (int it = 0; it < LB::ITER; ++it) {
+      const int idx = tid + it * NT, r = LB::row_of(idx), c = LB::col_of(idx);
+#pragma unroll
+      for (int e = 0; e < PER; ++e) {
+        const T x = pb[(int64_t)(r < kv ? r : kv - 1) * ldb + (c + e < b_cols ? c + e : b_cols - 1)];
+        rb[X][it][e] = (r < kv && c + e < b_cols) ? x : T(0);
+      }
+    }
+  };
+  auto stash = [&](auto sc, int buf) __attribute__((always_inline)) {
+    constexpr int X = decltype(sc)::value;
+    T* const sa = smem + buf * S::STAGE;
+    T* const sb = sa + S::A_ELEMS;
+#pragma unroll
+    for (int it = 0; it < LA::ITER; ++it) {
+      const int idx = tid + it * NT;
+      if (LA::TOTAL % NT == 0 || idx < LA::TOTAL) *reinterpret_cast<__attribute__((aligned(16))) V*>(sa + (idx / LA::VPR) * S::SA + LA::col_of(idx)) = SUB ? -ra[X][it] : ra[X][it];
+    }
+#pragma unroll
+    for (int it = 0; it < LB::ITER; ++it) {
+      const int idx = tid + it * NT;
+      if (LB::TOTAL % NT == 0 || idx < LB::TOTAL) *reinterpret_cast<__attribute__((aligned(16))) V*>(sb + (idx / LB::VPR) * S::SB + LB::col_of(idx)) = rb[X][it];
+    }
+  };
+  // k of step kk is KPL * l4 + kk in both operands: a lane's left-operand values of a slab are contiguous
+  auto multiply = [&](int buf, auto half) __attribute__((always_inline)) {
+    constexpr int H = decltype(half)::value;
+    const T* const sa = smem + buf * S::STAGE;
+    const T* const sb = sa + S::A_ELEMS;
+    const T* const pa = AT ? sa + (KPL * l4) * S::SA + wm0 + l15 * RA : sa + (wm0 + l15) * S::SA + KPL * l4;
+    const T* const pb = sb + (KPL * l4) * S::SB + coll;
+#pragma unroll
+    for (int kk = H * (KPL / 2); kk < (H + 1) * (KPL / 2); ++kk) {
+      T fa[FM], fb[FN];
+#pragma unroll
+      for (int a = 0; a < FM; ++a) fa[a] = AT ? pa[kk * S::SA + (a / RA) * 16 * RA + a % RA] : pa[a * 16 * S::SA + kk];
+#pragma unroll
+      for (int b = 0; b < FN; ++b) fb[b] = pb[kk * S::SB + (b / RB) * 16 * RB + b % RB];
+#pragma unroll
+      for (int a = 0; a < FM; ++a)
+#pragma unroll
+        for (int b = 0; b < FN; ++b) acc[a][b] = Mfma<T>::mma(fa[a], fb[b], acc[a][b]);
+    }
+  };
+  using c0 = std::integral_constant<int, 0>;
+  using c1 = std::integral_constant<int, 1>;
+  const int nslab = (K + TK - 1) / TK;
+  const int nfull = (a_vec && b_vec) ? K / TK : 0;
+  auto load_any = [&](auto sc, int s) __attribute__((always_inline)) {
+    if (s < nfull) load_full(sc, s);
+    else if (s < nslab) load_edge(sc, s);
+  };
+  load_any(c0{}, 0);
+  load_any(c1{}, 1);
+  stash(c0{}, 0);
+  lds_barrier();
+  int s = 0;
+  for (; s + 3 < nfull; s += 2) {
+    load_full(c0{}, s + 2);
+    multiply(0, c0{});
+    stash(c1{}, 1);
+    multiply(0, c1{});
+    lds_barrier();
+    load_full(c1{}, s + 3);
+    multiply(1, c0{});
+    stash(c0{}, 0);
+    multiply(1, c1{});
+    lds_barrier();
+  }
+  for (; s < nslab; s += 2) {
+    load_any(c0{}, s + 2);
+    multiply(0, c0{});
+    if (s + 1 < nslab) stash(c1{}, 1);
+    multiply(0, c1{});
+    lds_barrier();
+    if (s + 1 >= nslab) break;
+    load_any(c1{}, s + 3);
+    multiply(1, c0{});
+    if (s + 2 < nslab) stash(c0{}, 0);
+    multiply(1, c1{});
+    lds_barrier();
+  }
+
+  auto store_to = [&](T* const D, int64_t ldd) __attribute__((always_inline)) {
+#pragma unroll
+    for (int a = 0; a < FM; ++a)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const int r = row_at(a, Mfma<T>::row_of(v, lane));
+#pragma unroll
+        for (int b = 0; b < FN; b += RB) {
+          const int c = col_at(b);
+          T* const p = D + (int64_t)r * ldd + c;
+          if (full_mn) {
+            if constexpr (RB * sizeof(T) == 16) {
+              V w;
+#pragma unroll
+              for (int e = 0; e < RB; ++e) w[e] = acc[a][b + e][v];
+              *reinterpret_cast<V*>(p) = w;
+            } else {
+#pragma unroll
+              for (int e = 0; e < RB; ++e) p[e] = acc[a][b + e][v];
+            }
+          } else {
+#pragma unroll
+            for (int e = 0; e < RB; ++e)
+              if (m0 + r < M && n0 + c + e < N) p[e] = acc[a][b + e][v];
+          }
+        }
+      }
+  };
+  store_to(Ct, ldc);
+  if (P.C2) store_to(P.C2 + (int64_t)m0 * P.ldc2 + n0, P.ldc2);
+}
+
+}  // namespace dla

@@ -101,7 +101,7 @@ struct ProductList {
     int rc;
     {
       ProfileScope scope(PHASE_GEMM, flops, st);
-      rc = launch_gemm<T>(sch, op, g, st);
+      rc = gemm_wide_fits<T>(op, g) ? launch_gemm_wide<T>(op, g, st) : launch_gemm<T>(sch, op, g, st);
     }
     np = tiles = 0;
     flops = 0.0;
@@ -143,9 +143,9 @@ int solve_impl(const T* F, int64_t n, int64_t lda, T* B, int64_t nrhs, int64_t l
   auto rows_of = [&](int i) { return n - (int64_t)i * sb < sb ? n - (int64_t)i * sb : sb; };
   auto Nf = [&](int i) { return wf + (int64_t)i * sb * sb; };
   auto Nb = [&](int i) { return wb + (int64_t)i * sb * sb; };
-  // Where the chain's launches run on the tiled GEMM (many right-hand sides) they use its 32 x 32 tiles: the
-  // products stay skinny (k <= 512), and small tiles spread them over the compute units (N = 4000, 512
-  // right-hand sides: 0.87 ms against 1.22 ms with 64 x 64 tiles; N = 8192, 1024: 4.33 against 4.63 ms).
+  // Products on the tiled GEMM (the pre-pass; the chain with many right-hand sides) take gemm_wide_kernel, whose launch
+  // picks the tile: N = 8192 with 1024 right-hand sides, fp32, 2.78 -> 2.46 ms against 32 x 32 tiles of gemm_kernel.
+  // These schedules are for leading dimensions beyond that kernel's offsets.
   const GemmSchedule small = GemmSchedule{32, 32, 16, 4, 16, 16};
   const GemmSchedule sch = small;
   const GemmSchedule wide = GemmSchedule{64, 64, 16, 4, 32, 32};  // the 256 x 512 products of the pre-pass
@@ -272,7 +272,7 @@ int solve_impl(const T* F, int64_t n, int64_t lda, T* B, int64_t nrhs, int64_t l
     g.nprob = np;
     g.total_tiles = tiles;
     ProfileScope scope(PHASE_GEMM, flops, st);
-    return launch_gemm<T>(sch, op, g, st);
+    return gemm_wide_fits<T>(op, g) ? launch_gemm_wide<T>(op, g, st) : launch_gemm<T>(sch, op, g, st);
   };
   // ---- forward.  Z_i and then Y_i live in rows i of Y; B is updated in place (part c).
   {

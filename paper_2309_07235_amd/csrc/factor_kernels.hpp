@@ -2,12 +2,19 @@
 // Section "Linear Algebra Benchmarks": A = L*U without pivoting, A = L*L^T):
 //
 //   diag_kernel   one workgroup factors the b x b diagonal block (b <= 128) held
-//                 in LDS, recursively in 16 x 16 sub-blocks: a wavefront-level
-//                 16 x 16 factorisation in registers (one matrix row per lane,
-//                 pivot row broadcast with DPP row_newbcast), register-level
-//                 triangular solves for the 16-wide inner panels, MFMA for the
-//                 inner trailing update.  It also inverts every 16 x 16
-//                 diagonal sub-block; the inverses go to the workspace.
+//                 in LDS, in stages of 16 columns: a wavefront-level 16 x 16
+//                 factorisation in registers (one matrix row per lane, pivot row
+//                 broadcast with DPP row_newbcast), the 16-wide inner panels as
+//                 four dependent MFMAs per tile (tri_slabs), MFMA for the inner
+//                 trailing update.  The identity rides along as one more panel
+//                 tile and comes out as the sub-block's inverse, which goes to
+//                 the workspace.
+// What bounds it is the chain factor -> panels -> next sub-block's update -> factor of its eight stages: about 2900,
+// 2900 and 800 cycles of a stage's 9000 (cycle counter, N = 128, fp64 LU).  fp64 multiply-adds are not the cost (4 cycles
+// each, dependent or not); wait states, selects and compares around them and LDS traffic are.  Measured on whole calls,
+// this form against panels by substitution in one column per lane, pivots tested in every step, inverses and the store
+// behind the last stage, and the first sub-block factored only once the whole block has arrived: LU N = 300 131 -> 125 us,
+// LU N = 4000 1933 -> 1901, Cholesky N = 4000 1615 -> 1560, fp32 Cholesky N = 8192 3865 -> 3770.
 // The panel solves and the look-ahead head update, which consume those inverses,
 // live in head_kernel.hpp.
 #pragma once
@@ -42,20 +49,115 @@ __device__ inline float row_bcast(float x) {
   return __builtin_amdgcn_update_dpp(x, x, 0x150 + K, 0xF, 0xF, true);
 }
 
-// acc -= (value of src in lane K of the caller's 16-lane row) * m, as one DPP multiply-add: the
+// acc -= (value of src in lane K of the caller's 16-lane row) * m, as DPP multiply-adds: the
 // negation is a source modifier of the instruction, so it adds nothing to a dependent chain.
 // The two wait states a DPP read needs after a VALU write of its source are part of the statement.
-template <int K>
-__device__ inline void fnmac_bcast(double& acc, double src, double m) {
-  asm("s_nop 1\n\tv_fmac_f64_dpp %0, -%1, %2 row_newbcast:%3 row_mask:0xf bank_mask:0xf"
-      : "+v"(acc)
-      : "v"(src), "v"(m), "n"(K));
+// They cost a wavefront more than the multiply-add itself (16 cycles for the pair, 6.3 per multiply-add when
+// four share one s_nop), so the runs below issue up to four in a statement, where no source is written by an
+// earlier instruction of it.  lu16: 2520 -> 2092 cycles, with the pivot tests taken out as well.
+#define DLA_FNMAC_BCAST(T, OP)                                                                                \
+  template <int K>                                                                                            \
+  __device__ inline void fnmac_bcast(T& acc, T src, T m) {                                                    \
+    asm("s_nop 1\n\t" OP " %0, -%1, %2 row_newbcast:%3 row_mask:0xf bank_mask:0xf"                            \
+        : "+v"(acc)                                                                                           \
+        : "v"(src), "v"(m), "n"(K));                                                                          \
+  }                                                                                                           \
+  /* accumulators that are their own source: a_q -= a_q[lane K] * m */                                        \
+  template <int K>                                                                                            \
+  __device__ inline void fnmac_self2(T& a0, T& a1, T m) {                                                     \
+    asm("s_nop 1\n\t" OP " %0, -%0, %2 row_newbcast:%3 row_mask:0xf bank_mask:0xf\n\t"                        \
+        OP " %1, -%1, %2 row_newbcast:%3 row_mask:0xf bank_mask:0xf"                                          \
+        : "+&v"(a0), "+&v"(a1)                                                                                \
+        : "v"(m), "n"(K));                                                                                    \
+  }                                                                                                           \
+  template <int K>                                                                                            \
+  __device__ inline void fnmac_self3(T& a0, T& a1, T& a2, T m) {                                              \
+    asm("s_nop 1\n\t" OP " %0, -%0, %3 row_newbcast:%4 row_mask:0xf bank_mask:0xf\n\t"                        \
+        OP " %1, -%1, %3 row_newbcast:%4 row_mask:0xf bank_mask:0xf\n\t"                                      \
+        OP " %2, -%2, %3 row_newbcast:%4 row_mask:0xf bank_mask:0xf"                                          \
+        : "+&v"(a0), "+&v"(a1), "+&v"(a2)                                                                     \
+        : "v"(m), "n"(K));                                                                                    \
+  }                                                                                                           \
+  template <int K>                                                                                            \
+  __device__ inline void fnmac_self4(T& a0, T& a1, T& a2, T& a3, T m) {                                       \
+    asm("s_nop 1\n\t" OP " %0, -%0, %4 row_newbcast:%5 row_mask:0xf bank_mask:0xf\n\t"                        \
+        OP " %1, -%1, %4 row_newbcast:%5 row_mask:0xf bank_mask:0xf\n\t"                                      \
+        OP " %2, -%2, %4 row_newbcast:%5 row_mask:0xf bank_mask:0xf\n\t"                                      \
+        OP " %3, -%3, %4 row_newbcast:%5 row_mask:0xf bank_mask:0xf"                                          \
+        : "+&v"(a0), "+&v"(a1), "+&v"(a2), "+&v"(a3)                                                          \
+        : "v"(m), "n"(K));                                                                                    \
+  }                                                                                                           \
+  /* accumulators and one source, adjacent lanes: a_q -= src[lane K + q] * m */                               \
+  template <int K>                                                                                            \
+  __device__ inline void fnmac_lanes2(T& a0, T& a1, T src, T m) {                                             \
+    asm("s_nop 1\n\t" OP " %0, -%2, %3 row_newbcast:%4 row_mask:0xf bank_mask:0xf\n\t"                        \
+        OP " %1, -%2, %3 row_newbcast:%5 row_mask:0xf bank_mask:0xf"                                          \
+        : "+&v"(a0), "+&v"(a1)                                                                                \
+        : "v"(src), "v"(m), "n"(K), "n"(K + 1));                                                              \
+  }                                                                                                           \
+  template <int K>                                                                                            \
+  __device__ inline void fnmac_lanes3(T& a0, T& a1, T& a2, T src, T m) {                                      \
+    asm("s_nop 1\n\t" OP " %0, -%3, %4 row_newbcast:%5 row_mask:0xf bank_mask:0xf\n\t"                        \
+        OP " %1, -%3, %4 row_newbcast:%6 row_mask:0xf bank_mask:0xf\n\t"                                      \
+        OP " %2, -%3, %4 row_newbcast:%7 row_mask:0xf bank_mask:0xf"                                          \
+        : "+&v"(a0), "+&v"(a1), "+&v"(a2)                                                                     \
+        : "v"(src), "v"(m), "n"(K), "n"(K + 1), "n"(K + 2));                                                  \
+  }                                                                                                           \
+  template <int K>                                                                                            \
+  __device__ inline void fnmac_lanes4(T& a0, T& a1, T& a2, T& a3, T src, T m) {                               \
+    asm("s_nop 1\n\t" OP " %0, -%4, %5 row_newbcast:%6 row_mask:0xf bank_mask:0xf\n\t"                        \
+        OP " %1, -%4, %5 row_newbcast:%7 row_mask:0xf bank_mask:0xf\n\t"                                      \
+        OP " %2, -%4, %5 row_newbcast:%8 row_mask:0xf bank_mask:0xf\n\t"                                      \
+        OP " %3, -%4, %5 row_newbcast:%9 row_mask:0xf bank_mask:0xf"                                          \
+        : "+&v"(a0), "+&v"(a1), "+&v"(a2), "+&v"(a3)                                                          \
+        : "v"(src), "v"(m), "n"(K), "n"(K + 1), "n"(K + 2), "n"(K + 3));                                      \
+  }                                                                                                           \
+  /* four of everything: a_q -= s_q[lane K_q] * m_q */                                                        \
+  template <int K0, int K1, int K2, int K3>                                                                   \
+  __device__ inline void fnmac_bcast4_each(T& a0, T& a1, T& a2, T& a3, T s0, T s1, T s2, T s3, T m0, T m1,    \
+                                           T m2, T m3) {                                                      \
+    asm("s_nop 1\n\t" OP " %0, -%4, %8 row_newbcast:%12 row_mask:0xf bank_mask:0xf\n\t"                      \
+        OP " %1, -%5, %9 row_newbcast:%13 row_mask:0xf bank_mask:0xf\n\t"                                     \
+        OP " %2, -%6, %10 row_newbcast:%14 row_mask:0xf bank_mask:0xf\n\t"                                    \
+        OP " %3, -%7, %11 row_newbcast:%15 row_mask:0xf bank_mask:0xf"                                        \
+        : "+&v"(a0), "+&v"(a1), "+&v"(a2), "+&v"(a3)                                                          \
+        : "v"(s0), "v"(s1), "v"(s2), "v"(s3), "v"(m0), "v"(m1), "v"(m2), "v"(m3), "n"(K0), "n"(K1), "n"(K2),  \
+          "n"(K3));                                                                                           \
+  }
+DLA_FNMAC_BCAST(double, "v_fmac_f64_dpp")
+DLA_FNMAC_BCAST(float, "v_fmac_f32_dpp")
+#undef DLA_FNMAC_BCAST
+
+// Runs over the columns J0 .. J1-1 of a 16-element row:
+// a[j] -= a[j][lane K] * m
+template <int K, int J0, int J1, typename T>
+__device__ inline void fnmac_run_self(T (&a)[16], T m) {
+  constexpr int N = J1 - J0;
+  if constexpr (N >= 4) {
+    fnmac_self4<K>(a[J0], a[J0 + 1], a[J0 + 2], a[J0 + 3], m);
+    fnmac_run_self<K, J0 + 4, J1>(a, m);
+  } else if constexpr (N == 3) {
+    fnmac_self3<K>(a[J0], a[J0 + 1], a[J0 + 2], m);
+  } else if constexpr (N == 2) {
+    fnmac_self2<K>(a[J0], a[J0 + 1], m);
+  } else if constexpr (N == 1) {
+    fnmac_bcast<K>(a[J0], a[J0], m);
+  }
 }
-template <int K>
-__device__ inline void fnmac_bcast(float& acc, float src, float m) {
-  asm("s_nop 1\n\tv_fmac_f32_dpp %0, -%1, %2 row_newbcast:%3 row_mask:0xf bank_mask:0xf"
-      : "+v"(acc)
-      : "v"(src), "v"(m), "n"(K));
+// a[j] -= src[lane j] * m
+template <int J0, int J1, typename T>
+__device__ inline void fnmac_run_lanes(T (&a)[16], T src, T m) {
+  constexpr int N = J1 - J0;
+  if constexpr (N >= 4) {
+    fnmac_lanes4<J0>(a[J0], a[J0 + 1], a[J0 + 2], a[J0 + 3], src, m);
+    fnmac_run_lanes<J0 + 4, J1>(a, src, m);
+  } else if constexpr (N == 3) {
+    fnmac_lanes3<J0>(a[J0], a[J0 + 1], a[J0 + 2], src, m);
+  } else if constexpr (N == 2) {
+    fnmac_lanes2<J0>(a[J0], a[J0 + 1], src, m);
+  } else if constexpr (N == 1) {
+    fnmac_bcast<J0>(a[J0], src, m);
+  }
 }
 
 __device__ inline double fma_t(double a, double b, double c) { return __builtin_fma(a, b, c); }
@@ -115,16 +217,15 @@ __device__ inline float sqrt_t(float a) { return __builtin_sqrtf(a); }
 
 // In-place LU without pivoting of the block whose row i is a[0..15].  On exit
 // a holds L (strict lower, unit diagonal implied) and U; rdiag[k] = 1/U[k][k]
-// (same value in every lane).  zero_at: first k with an exactly zero pivot, or -1.
+// (same value in every lane).  Zero pivots are found afterwards, on U's diagonal: a test in every step
+// costs as much as the step's chain (a compare, a scalar and, a select, each waiting for the last).
 // Rows that do not take part in a step use a zero multiplier instead of a select.
 template <typename T>
-__device__ inline void lu16(T (&a)[16], T (&rdiag)[16], int i, int& zero_at) {
-  zero_at = -1;
+__device__ inline void lu16(T (&a)[16], T (&rdiag)[16], int i) {
   T piv = row_bcast<0>(a[0]);
   T rp = fast_rcp(piv);
   static_for<0, 16>([&](auto kc) {
     constexpr int k = decltype(kc)::value;
-    if (piv == T(0) && zero_at < 0) zero_at = k;
     rdiag[k] = rp;
     const bool below = i > k;
     const T l = below ? a[k] * rp : T(0);
@@ -139,32 +240,31 @@ __device__ inline void lu16(T (&a)[16], T (&rdiag)[16], int i, int& zero_at) {
       // interleave the Newton steps with the row updates, a few columns per step
       constexpr int rest = 14 - k;                 // columns k+2 .. 15
       constexpr int c1 = k + 2 + (rest + 3) / 4, c2 = k + 2 + (2 * rest + 3) / 4, c3 = k + 2 + (3 * rest + 3) / 4;
-      static_for<k + 2, c1>([&](auto jc) { constexpr int j = decltype(jc)::value; fnmac_bcast<k>(a[j], a[j], l); });
+      fnmac_run_self<k, k + 2, c1>(a, l);
       __builtin_amdgcn_sched_barrier(0);
       r = rcp_refine(piv, r);
-      static_for<c1, c2>([&](auto jc) { constexpr int j = decltype(jc)::value; fnmac_bcast<k>(a[j], a[j], l); });
+      fnmac_run_self<k, c1, c2>(a, l);
       __builtin_amdgcn_sched_barrier(0);
       if constexpr (sizeof(T) == 8) r = rcp_refine(piv, r);
-      static_for<c2, c3>([&](auto jc) { constexpr int j = decltype(jc)::value; fnmac_bcast<k>(a[j], a[j], l); });
+      fnmac_run_self<k, c2, c3>(a, l);
       __builtin_amdgcn_sched_barrier(0);
-      static_for<c3, 16>([&](auto jc) { constexpr int j = decltype(jc)::value; fnmac_bcast<k>(a[j], a[j], l); });
+      fnmac_run_self<k, c3, 16>(a, l);
       rp = r;
     }
   });
 }
 
 // In-place Cholesky of the block whose lower-triangle row i is a[0..i]; a[j] for j > i is
-// scratch (never read for a result, may hold anything).  rdiag[k] = 1/L[k][k];
-// bad_at: first k whose pivot is not > 0, or -1.
+// scratch (never read for a result, may hold anything).  rdiag[k] = 1/L[k][k]; pivot[k]: its square as
+// it was found, for the test d > 0 afterwards.
 template <typename T>
-__device__ inline void chol16(T (&a)[16], T (&rdiag)[16], int i, int& bad_at) {
-  bad_at = -1;
+__device__ inline void chol16(T (&a)[16], T (&rdiag)[16], T (&pivot)[16], int i) {
   T d = row_bcast<0>(a[0]);
   T s, rs;
   fast_rsqrt(d, s, rs);
   static_for<0, 16>([&](auto kc) {
     constexpr int k = decltype(kc)::value;
-    if (!(d > T(0)) && bad_at < 0) bad_at = k;
+    pivot[k] = d;
     rdiag[k] = rs;
     const T l = (i == k) ? s : a[k] * rs;
     a[k] = (i >= k) ? l : a[k];
@@ -177,64 +277,74 @@ __device__ inline void chol16(T (&a)[16], T (&rdiag)[16], int i, int& bad_at) {
       T y = rsq_estimate(d);
       constexpr int rest = 14 - k;
       constexpr int c1 = k + 2 + (rest + 3) / 4, c2 = k + 2 + (2 * rest + 3) / 4, c3 = k + 2 + (3 * rest + 3) / 4;
-      static_for<k + 2, c1>([&](auto jc) { constexpr int j = decltype(jc)::value; fnmac_bcast<j>(a[j], a[k], a[k]); });
+      fnmac_run_lanes<k + 2, c1>(a, a[k], a[k]);
       __builtin_amdgcn_sched_barrier(0);
       y = rsq_refine(d, y);
-      static_for<c1, c2>([&](auto jc) { constexpr int j = decltype(jc)::value; fnmac_bcast<j>(a[j], a[k], a[k]); });
+      fnmac_run_lanes<c1, c2>(a, a[k], a[k]);
       __builtin_amdgcn_sched_barrier(0);
       if constexpr (sizeof(T) == 8) y = rsq_refine(d, y);
-      static_for<c2, c3>([&](auto jc) { constexpr int j = decltype(jc)::value; fnmac_bcast<j>(a[j], a[k], a[k]); });
+      fnmac_run_lanes<c2, c3>(a, a[k], a[k]);
       __builtin_amdgcn_sched_barrier(0);
       T sq = d * y;
       sq = fma_t(fma_t(-sq, sq, d), T(0.5) * y, sq);
-      static_for<c3, 16>([&](auto jc) { constexpr int j = decltype(jc)::value; fnmac_bcast<j>(a[j], a[k], a[k]); });
+      fnmac_run_lanes<c3, 16>(a, a[k], a[k]);
       s = sq;
       rs = y;
     }
   });
 }
 
-// x = row i of the inverse of the lower-triangular matrix whose row i is a[0..i];
-// UNIT: unit diagonal (a[i] ignored), else rdiag[k] = 1/diagonal.
-template <typename T, bool UNIT>
-__device__ inline void inv_lower16(const T (&a)[16], const T (&rdiag)[16], T (&x)[16], int i) {
-#pragma unroll
-  for (int j = 0; j < 16; ++j) x[j] = (j == i) ? T(1) : T(0);
-  static_for<0, 16>([&](auto kc) {
-    constexpr int k = decltype(kc)::value;
-    if (!UNIT) {
-      const T scale = (i == k) ? rdiag[k] : T(1);
-      static_for<0, k + 1>([&](auto jc) {
-        constexpr int j = decltype(jc)::value;
-        x[j] *= scale;
-      });
-    }
-    const T mult = (i > k) ? a[k] : T(0);
-    static_for<0, k + 1>([&](auto jc) {
-      constexpr int j = decltype(jc)::value;
-      fnmac_bcast<k>(x[j], x[j], mult);
-    });
-  });
+// ---- solves with a 16 x 16 lower-triangular block T as four dependent MFMAs per 16 columns ----
+//
+// T X = P by substitution in blocks of four rows: X_r = inv(T_rr) P_r, P_s -= T_sr X_r for s > r.  With
+// W_r = [inv(T_rr); -T_sr inv(T_rr)] in rows 4 r .. 15 and zeros above, step r is the one product
+// P <- W_r P_r + (P with block r taken out), 16 x 16 x 4: P_r is the right-hand operand as the accumulators hold it.
+// In the accumulators, register v of lane l holds row 4 v + l / 16 of P.  That is the fp64 layout; in fp32 the
+// instruction's row 4 (l / 16) + v stands for it, so the left operand's rows are dealt to the lanes that way.
+template <typename T>
+__host__ __device__ constexpr int tri_row(int lane15) {  // an involution: also the lane that holds a row
+  return sizeof(T) == 8 ? lane15 : 4 * (lane15 & 3) + (lane15 >> 2);
 }
 
-// x = row i of the inverse of the upper-triangular matrix whose row i is a[i..15].
-template <typename T>
-__device__ inline void inv_upper16(const T (&a)[16], const T (&rdiag)[16], T (&x)[16], int i) {
+// The left operands W_0 .. W_3.  f: row tri_row(l15) of T (only its lower part counts), rd: reciprocals of T's diagonal
+// (not read if UNIT).  A row solves w T_rr = (its four entries of T, or of the identity inside the block).
+template <typename T, bool UNIT>
+__device__ inline void tri_slabs(const T (&f)[16], const T (&rd)[16], T (&slab)[4], int l15, int l4) {
+  const int i = tri_row<T>(l15);
+  T w[4][4];  // [column of the block][block]
 #pragma unroll
-  for (int j = 0; j < 16; ++j) x[j] = (j == i) ? T(1) : T(0);
-  static_for<0, 16>([&](auto kk) {
-    constexpr int k = 15 - decltype(kk)::value;
-    const T scale = (i == k) ? rdiag[k] : T(1);
-    static_for<k, 16>([&](auto jc) {
-      constexpr int j = decltype(jc)::value;
-      x[j] *= scale;
-    });
-    const T mult = (i < k) ? a[k] : T(0);
-    static_for<k, 16>([&](auto jc) {
-      constexpr int j = decltype(jc)::value;
-      fnmac_bcast<k>(x[j], x[j], mult);
+  for (int r = 0; r < 4; ++r)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) w[q][r] = i >= 4 * r + 4 ? f[4 * r + q] : (i == 4 * r + q ? T(1) : T(0));
+  static_for<0, 4>([&](auto qc) {
+    constexpr int q = 3 - decltype(qc)::value;
+    if constexpr (!UNIT) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r) w[q][r] *= rd[4 * r + q];
+    }
+    static_for<0, q>([&](auto pc) {
+      constexpr int p = decltype(pc)::value;
+      fnmac_bcast4_each<tri_row<T>(q), tri_row<T>(4 + q), tri_row<T>(8 + q), tri_row<T>(12 + q)>(
+          w[p][0], w[p][1], w[p][2], w[p][3], f[p], f[4 + p], f[8 + p], f[12 + p], w[q][0], w[q][1], w[q][2], w[q][3]);
     });
   });
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    // column l4 (values, not elements of w, in the conditionals: those would index w in memory)
+    const T w0 = w[0][r], w1 = w[1][r], w2 = w[2][r], w3 = w[3][r];
+    T x = w0;
+    if (l4 == 1) x = w1;
+    if (l4 == 2) x = w2;
+    if (l4 == 3) x = w3;
+    slab[r] = i >= 4 * r + 4 ? -x : x;
+  }
+}
+
+template <typename T>
+__device__ inline void tri_step(const T (&slab)[4], typename Mfma<T>::acc_t& p, int r) {
+  const T x = p[r];
+  p[r] = T(0);
+  p = Mfma<T>::mma(slab[r], x, p);
 }
 
 // --------------------------------------------------------------------------------------
@@ -260,8 +370,7 @@ template <typename T, int KIND>
 __global__ void __launch_bounds__(kDiagThreads) diag_kernel(const DiagArgs<T> g) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
   T* const S = reinterpret_cast<T*>(smem_raw);  // [kNbMax + 1][kSld]: row kNbMax and column kNbMax are dump space
-  T* const sRd = S + (kNbMax + 1) * kSld;       // [kNbMax] reciprocals of the pivots
-  __shared__ int s_info;
+  T* const sRd = S + (kNbMax + 1) * kSld;       // [kNbMax] reciprocals of the diagonal, [kNbMax] Cholesky's pivots
   constexpr int NWAVES = kDiagThreads / 64;
 
   const int tid = (int)threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -271,60 +380,61 @@ __global__ void __launch_bounds__(kDiagThreads) diag_kernel(const DiagArgs<T> g)
   const int bp = nblk * kIb;  // padded size: rows/columns b..bp-1 are identity
 
   if (g.wait_counter) chain_wait(g.wait_counter, g.wait_target, g.broken, g.wait_ticks, tid);
-  if (tid == 0) s_info = 0;
-  // ---- load, padding with the identity: thread = two adjacent columns, 8 rows per pass, all
-  // loads issued before the first LDS store
-  {
-    constexpr int TPR = kNbMax / 2;             // threads per row
-    constexpr int RPP = kDiagThreads / TPR;     // rows per pass
-    constexpr int PASSES = kNbMax / RPP;
-    const int c = (tid % TPR) * 2, r0 = tid / TPR;
+  // ---- load, padding with the identity.  Wave 0 takes the first diagonal sub-block straight to registers and
+  // factors it (below) while the other waves bring the rest to LDS: a wave one row of two adjacent columns per lane,
+  // all loads issued before the first LDS store.  Addresses are clamped into the block so every load is
+  // unconditional (no branch, no wait between loads); out-of-block positions are replaced by the identity afterwards.
+  auto load_rows = [&](auto passes) {
+    constexpr int PASSES = decltype(passes)::value;
+    const int c = lane * 2, r0 = wave - 1;
     T v0[PASSES], v1[PASSES];
-    // addresses are clamped into the block so every load is unconditional (no branch, no wait
-    // between loads); out-of-block positions are replaced by the identity afterwards
     const int cc0 = c < b ? c : b - 1, cc1 = c + 1 < b ? c + 1 : b - 1;
 #pragma unroll
     for (int it = 0; it < PASSES; ++it) {
-      const int r = r0 + it * RPP;
+      const int r = r0 + it * (NWAVES - 1);
       const T* p = g.A + (int64_t)(r < b ? r : b - 1) * g.lda;
       v0[it] = p[cc0];
       v1[it] = p[cc1];
     }
 #pragma unroll
     for (int it = 0; it < PASSES; ++it) {
-      const int r = r0 + it * RPP;
+      const int r = r0 + it * (NWAVES - 1);
       if (!(r < b && c < b)) v0[it] = (r == c) ? T(1) : T(0);
       if (!(r < b && c + 1 < b)) v1[it] = (r == c + 1) ? T(1) : T(0);
     }
 #pragma unroll
     for (int it = 0; it < PASSES; ++it) {
-      const int r = r0 + it * RPP;
-      if (r < bp && c < bp) {
+      const int r = r0 + it * (NWAVES - 1);
+      if (r < bp && c < bp && (r >= kIb || c >= kIb)) {
         S[r * kSld + c] = v0[it];
         S[r * kSld + c + 1] = v1[it];
       }
     }
-  }
-  __syncthreads();
+  };
 
   // 16 x 16 diagonal sub-block at offset o: rows to registers, factor, back to LDS (one wave)
-  auto factor_sub_block = [&](int o) {
-    T a[16], rd[16];
-#pragma unroll
-    for (int j = 0; j < 16; ++j) a[j] = S[(o + l15) * kSld + o + j];
-    int bad;
-    if (KIND == KIND_LU) lu16(a, rd, l15, bad);
-    else chol16(a, rd, l15, bad);
+  auto factor_rows = [&](int o, T (&a)[16]) {
+    T rd[16], pv[KIND == KIND_CHOL ? 16 : 1];
+    if constexpr (KIND == KIND_LU) lu16(a, rd, l15);
+    else chol16(a, rd, pv, l15);
     if (lane < 16) {
 #pragma unroll
       for (int j = 0; j < 16; ++j)
-        if (KIND == KIND_LU || j <= l15) S[(o + l15) * kSld + o + j] = a[j];
+        S[(o + l15) * kSld + o + j] = a[j];  // (Cholesky: scratch above the diagonal, which nothing reads)
     }
     if (lane == 0) {
 #pragma unroll
-      for (int j = 0; j < 16; ++j) sRd[o + j] = rd[j];
-      if (bad >= 0 && o + bad < b && s_info == 0) s_info = g.k0 + o + bad + 1;
+      for (int j = 0; j < 16; ++j) {
+        sRd[o + j] = rd[j];
+        if constexpr (KIND == KIND_CHOL) sRd[kNbMax + o + j] = pv[j];
+      }
     }
+  };
+  auto factor_sub_block = [&](int o) {
+    T a[16];
+#pragma unroll
+    for (int j = 0; j < 16; ++j) a[j] = S[(o + l15) * kSld + o + j];
+    factor_rows(o, a);
   };
   // one 16 x 16 block of the inner trailing update of the stage at offset o
   auto update_block = [&](int o, int c0, int d0) {
@@ -370,66 +480,173 @@ __global__ void __launch_bounds__(kDiagThreads) diag_kernel(const DiagArgs<T> g)
     }
   };
 
-  if (wave == 0) factor_sub_block(0);
-  __syncthreads();
-
-  for (int r = 0; r + 1 < nblk; ++r) {
-    const int o = r * kIb;
-    const int rem = bp - o - kIb;  // rows/columns to the right of / below this sub-block
-    // ---- inner panels: one thread per column (row panel) or per row (column panel).  The 16 x 16
-    // factor is uniform over the panel, so each 16-lane row keeps it in registers (lane i = its
-    // row i) and feeds the substitution through DPP broadcasts instead of LDS reads.
-    if (KIND == KIND_LU && tid < 128) {
-      // threads past the padded block work on the dump column, so the arithmetic stays unconditional
-      const int col = tid < rem ? o + kIb + tid : kNbMax;
-      T f[16], x[16];
+  // LU: blocks d, d + step, ... < nrem of one block row (row c0) of the inner trailing update, two at a time
+  auto update_row = [&](int o, int c0, int d, int step, int nrem) {
+    T fa[4];
 #pragma unroll
-      for (int j = 0; j < 16; ++j) f[j] = S[(o + l15) * kSld + o + j];  // row l15 of L_rr \ U_rr
+    for (int kk = 0; kk < 4; ++kk) fa[kk] = -S[(c0 + l15) * kSld + o + kk * 4 + l4];
+    for (; d < nrem; d += 2 * step) {
+      const bool two = d + step < nrem;  // uniform
+      const int d0 = o + kIb + d * kIb, d1 = two ? d0 + step * kIb : d0;
+      typename Mfma<T>::acc_t acc0, acc1;
+      T fb0[4], fb1[4];
 #pragma unroll
-      for (int i = 0; i < 16; ++i) x[i] = S[(o + i) * kSld + col];
-      static_for<0, 15>([&](auto kc) {
-        constexpr int k = decltype(kc)::value;
-        static_for<k + 1, 16>([&](auto ic) {
-          constexpr int i = decltype(ic)::value;
-          fnmac_bcast<i>(x[i], f[k], x[k]);  // x[i] -= L[i][k] * x[k]; L[i][k] = entry k of lane i
-        });
-        __builtin_amdgcn_sched_barrier(0);  // keep the broadcasts of later steps from being hoisted (registers)
-      });
+      for (int v = 0; v < 4; ++v) {
+        acc0[v] = S[(c0 + Mfma<T>::row_of(v, lane)) * kSld + d0 + l15];
+        fb0[v] = S[(o + v * 4 + l4) * kSld + d0 + l15];
+        acc1[v] = S[(c0 + Mfma<T>::row_of(v, lane)) * kSld + d1 + l15];
+        fb1[v] = S[(o + v * 4 + l4) * kSld + d1 + l15];
+      }
+      if (two) {
 #pragma unroll
-      for (int i = 0; i < 16; ++i) S[(o + i) * kSld + col] = x[i];
-    } else if (tid >= 128 && tid < 256) {  // waves 2, 3: not the SIMDs of the row panel's waves 0, 1
-      const int t = tid - 128;
-      const int row = t < rem ? o + kIb + t : kNbMax;  // dump row for the idle threads
-      T f[16], x[16], rd[16];
+        for (int kk = 0; kk < 4; ++kk) {
+          acc0 = Mfma<T>::mma(fa[kk], fb0[kk], acc0);
+          acc1 = Mfma<T>::mma(fa[kk], fb1[kk], acc1);
+        }
 #pragma unroll
-      for (int j = 0; j < 16; ++j) {
-        f[j] = S[(o + l15) * kSld + o + j];
-        rd[j] = sRd[o + j];
+        for (int v = 0; v < 4; ++v) S[(c0 + Mfma<T>::row_of(v, lane)) * kSld + d1 + l15] = acc1[v];
+      } else {
+#pragma unroll
+        for (int kk = 0; kk < 4; ++kk) acc0 = Mfma<T>::mma(fa[kk], fb0[kk], acc0);
       }
 #pragma unroll
-      for (int j = 0; j < 16; ++j) x[j] = S[row * kSld + o + j];
-      static_for<0, 16>([&](auto jc) {
-        constexpr int j = decltype(jc)::value;
-        x[j] *= rd[j];
-        static_for<j + 1, 16>([&](auto qc) {
-          constexpr int jj = decltype(qc)::value;
-          // LU: U[j][jj] = entry jj of lane j;  Cholesky: (L^T)[j][jj] = L[jj][j] = entry j of lane jj
-          if constexpr (KIND == KIND_LU) fnmac_bcast<j>(x[jj], f[jj], x[j]);
-          else fnmac_bcast<jj>(x[jj], f[j], x[j]);
-        });
-        __builtin_amdgcn_sched_barrier(0);
-      });
-#pragma unroll
-      for (int j = 0; j < 16; ++j) S[row * kSld + o + j] = x[j];
+      for (int v = 0; v < 4; ++v) S[(c0 + Mfma<T>::row_of(v, lane)) * kSld + d0 + l15] = acc0[v];
     }
-    __syncthreads();
+  };
+  // Rows [o, o + 16) from column o on and columns [o, o + 16) below them are final once stage o's panels are solved.
+  // Waves 4 .. 7 write them out beside the next stage's panels (Cholesky: with the zeros above the diagonal, the
+  // output convention), all LDS reads first.
+  auto store_strip = [&](int o) {
+    const int w = wave - 4;
+    constexpr int CHUNKS = kNbMax / 64, BELOW = kNbMax / kIb - 1;
+    T row[4][CHUNKS], col[BELOW];
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+#pragma unroll
+      for (int h = 0; h < CHUNKS; ++h) {
+        const int c = o + lane + h * 64;
+        row[q][h] = S[(o + w * 4 + q) * kSld + (c < kNbMax ? c : kNbMax)];
+      }
+#pragma unroll
+    for (int q = 0; q < BELOW; ++q) {
+      const int r = o + kIb + q * kIb + w * 4 + l4;
+      col[q] = S[(r < kNbMax ? r : kNbMax) * kSld + o + l15];
+    }
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+#pragma unroll
+      for (int h = 0; h < CHUNKS; ++h) {
+        const int r = o + w * 4 + q, c = o + lane + h * 64;
+        if (r < b && c < b) g.A[(int64_t)r * g.lda + c] = (KIND == KIND_LU || c <= r) ? row[q][h] : T(0);
+      }
+#pragma unroll
+    for (int q = 0; q < BELOW; ++q) {
+      const int r = o + kIb + q * kIb + w * 4 + l4;
+      if (r < b) g.A[(int64_t)r * g.lda + o + l15] = col[q];
+    }
+  };
+
+  if (wave == 0) {
+    T a[16];
+    const T* p = g.A + (int64_t)(l15 < b ? l15 : b - 1) * g.lda;
+#pragma unroll
+    for (int j = 0; j < 16; ++j) a[j] = p[j < b ? j : b - 1];
+#pragma unroll
+    for (int j = 0; j < 16; ++j)
+      if (!(l15 < b && j < b)) a[j] = (l15 == j) ? T(1) : T(0);
+    factor_rows(0, a);
+  } else if (bp <= kNbMax / 2) {
+    load_rows(std::integral_constant<int, (kNbMax / 2 + NWAVES - 2) / (NWAVES - 1)>{});
+  } else {
+    load_rows(std::integral_constant<int, (kNbMax + NWAVES - 2) / (NWAVES - 1)>{});
+  }
+  __syncthreads();
+
+  // One 16-wide panel of the sub-block at offset o, in tiles of 16 columns (row panel: L X = P) or rows (column panel:
+  // X U = P or X L^T = P, solved transposed); tile nrem is the identity, which becomes the sub-block's inverse for the
+  // panel solves behind this block.  This wave's tiles are first, first + STEP, ...: at most MAXT of them.
+  auto panel_tiles = [&](auto upper_c, auto step_c, int o, int nrem, int first) {
+    constexpr bool UPPER = decltype(upper_c)::value;  // with U (transposed)
+    constexpr bool ROWP = KIND == KIND_LU && !UPPER;
+    constexpr int STEP = decltype(step_c)::value, MAXT = kNbMax / kIb / STEP;
+    using acc_t = typename Mfma<T>::acc_t;
+    if (first > nrem) return;
+    T f[16], rd[16], slab[4];
+    const int i = tri_row<T>(l15);
+#pragma unroll
+    for (int j = 0; j < 16; ++j) {
+      f[j] = UPPER ? S[(o + j) * kSld + o + i] : S[(o + i) * kSld + o + j];
+      if (!ROWP) rd[j] = sRd[o + j];
+    }
+    // entry (row 4 v + l4, column l15) of tile t's right-hand side
+    auto at = [&](int t, int v) -> T* {
+      const int e = o + kIb + t * kIb + l15, k = o + 4 * v + l4;
+      return ROWP ? S + k * kSld + e : S + e * kSld + k;
+    };
+    // (reads past the panel stay on its last tile, or on the sub-block itself: no branch, so no wait, between them)
+    acc_t x[MAXT];
+#pragma unroll
+    for (int q = 0; q < MAXT; ++q) {
+      const int t = first + q * STEP;
+#pragma unroll
+      for (int v = 0; v < 4; ++v) x[q][v] = *at(t < nrem ? t : nrem - 1, v);
+    }
+    tri_slabs<T, ROWP>(f, rd, slab, l15, l4);
+#pragma unroll
+    for (int q = 0; q < MAXT; ++q)
+#pragma unroll
+      for (int v = 0; v < 4; ++v)
+        if (first + q * STEP == nrem) x[q][v] = 4 * v + l4 == l15 ? T(1) : T(0);
+    auto solve = [&](auto nt) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+#pragma unroll
+        for (int q = 0; q < decltype(nt)::value; ++q) tri_step<T>(slab, x[q], r);
+    };
+    const int nt = (nrem - first) / STEP + 1;
+    static_for<1, MAXT + 1>([&](auto c) {
+      if (nt == decltype(c)::value) solve(c);
+    });
+#pragma unroll
+    for (int q = 0; q < MAXT; ++q) {
+      const int t = first + q * STEP;
+      if (t < nrem) {
+#pragma unroll
+        for (int v = 0; v < 4; ++v) *at(t, v) = x[q][v];
+      } else if (t == nrem) {
+        T* const out = (UPPER ? g.inv_up : g.inv_lo) + (o / kIb) * 256;
+#pragma unroll
+        for (int v = 0; v < 4; ++v) out[UPPER ? l15 * 16 + 4 * v + l4 : (4 * v + l4) * 16 + l15] = x[q][v];
+      }
+    }
+  };
+
+  for (int r = 0; r < nblk; ++r) {
+    const int o = r * kIb;
+    const int rem = bp - o - kIb;  // rows/columns to the right of / below this sub-block
+    const int nrem = rem / kIb;
+    // ---- inner panels on four waves, one per SIMD: the matrix pipes are as busy as with eight, and the factor is read
+    // from LDS and brought to its left operands half as often.  The others write out what is finished.
+    if (wave >= 4) {
+      if (r > 0) store_strip(o - kIb);
+    } else if constexpr (KIND == KIND_LU) {
+      if (wave < 2) panel_tiles(std::false_type{}, std::integral_constant<int, 2>{}, o, nrem, wave);
+      else panel_tiles(std::true_type{}, std::integral_constant<int, 2>{}, o, nrem, wave - 2);
+    } else {
+      panel_tiles(std::false_type{}, std::integral_constant<int, 4>{}, o, nrem, wave);
+    }
+    if (nrem == 0) break;
+    lds_barrier();
     // ---- inner trailing update on MFMA.  Wave 0 updates the next diagonal sub-block first and
     // factors it while the other waves update the remaining blocks (look-ahead inside the block).
-    const int nrem = rem / kIb;
     if (wave == 0) {
       update_block(o, o + kIb, o + kIb);
-      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");  // this wave's LDS writes before its reads below
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup", "local");  // this wave's LDS writes before its reads below
       factor_sub_block(o + kIb);
+    } else if constexpr (KIND == KIND_LU) {
+      // a wave stays in one block row, whose left operands it reads once; short rows are shared by several waves
+      const int parts = (NWAVES - 1) / nrem, ci = (wave - 1) % nrem, part = (wave - 1) / nrem;
+      if (part < parts) update_row(o, o + kIb + ci * kIb, ci == 0 && part == 0 ? parts : part, parts, nrem);
     } else {
       // q = 0 is wave 0's block; two blocks per iteration give the MFMA chains some overlap
       for (int q = wave; q < nrem * nrem; q += 2 * (NWAVES - 1)) {
@@ -442,42 +659,26 @@ __global__ void __launch_bounds__(kDiagThreads) diag_kernel(const DiagArgs<T> g)
         else if (do2) update_block(o, o + kIb + ci2 * kIb, o + kIb + di2 * kIb);
       }
     }
-    __syncthreads();
+    lds_barrier();
   }
 
-  // ---- inverses of the diagonal sub-blocks: one 16-lane row per sub-block ---------------------
-  // waves 0..1: lower factor, sub-blocks 4*(wave&1) + l4;  waves 2..3: upper factor (LU only);
-  // the other waves store the factored block meanwhile.
-  if (wave < 4) {
-    const bool lower = wave < 2;
-    const int blk = (wave & 1) * 4 + l4;
-    if (blk < nblk && (lower || KIND == KIND_LU)) {
-      const int o = blk * kIb;
-      T a[16], rd[16], x[16];
+  // ---- the last sub-block; breakdown: the first pivot that is zero (LU) or not positive (Cholesky)
+  if (wave >= 4) store_strip(bp - kIb);
+  int info = 0;
+  if (wave == 0) {
+    int first = 0;
 #pragma unroll
-      for (int j = 0; j < 16; ++j) {
-        a[j] = S[(o + l15) * kSld + o + j];
-        rd[j] = sRd[o + j];
-      }
-      if (lower) inv_lower16<T, KIND == KIND_LU>(a, rd, x, l15);
-      else inv_upper16<T>(a, rd, x, l15);
-      T* out = (lower ? g.inv_lo : g.inv_up) + blk * 256 + l15 * 16;
-#pragma unroll
-      for (int j = 0; j < 16; ++j) out[j] = x[j];
+    for (int h = kNbMax / 64 - 1; h >= 0; --h) {
+      const int k = h * 64 + lane;
+      const T d = KIND == KIND_LU ? S[k * (kSld + 1)] : sRd[kNbMax + k];
+      const unsigned long long bad = __ballot(k < b && (KIND == KIND_LU ? d == T(0) : !(d > T(0))));
+      if (bad) first = h * 64 + __builtin_ctzll(bad) + 1;
     }
-  } else {
-    // 4 waves = 256 threads: thread = two adjacent columns, 4 rows per pass
-    const int t = tid - 256;
-    const int c = (t % (kNbMax / 2)) * 2, r0 = t / (kNbMax / 2);
-    for (int r = r0; r < b; r += 4) {  // Cholesky: zeros above the diagonal (the output convention)
-      T* p = g.A + (int64_t)r * g.lda + c;
-      if (c < b) p[0] = (KIND == KIND_LU || c <= r) ? S[r * kSld + c] : T(0);
-      if (c + 1 < b) p[1] = (KIND == KIND_LU || c + 1 <= r) ? S[r * kSld + c + 1] : T(0);
-    }
+    info = first ? g.k0 + first : 0;
   }
   if (tid == 0 && g.info) {
-    if (g.k0 == 0) *g.info = s_info;  // first block of the call: initialise
-    else if (s_info != 0 && *g.info == 0) *g.info = s_info;
+    if (g.k0 == 0) *g.info = info;  // first block of the call: initialise
+    else if (info != 0 && *g.info == 0) *g.info = info;
     if (g.broken && __hip_atomic_load(g.broken, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) *g.info = -1;
   }
   if (g.done_counter) chain_signal(g.done_counter, 1, tid);
@@ -485,7 +686,7 @@ __global__ void __launch_bounds__(kDiagThreads) diag_kernel(const DiagArgs<T> g)
 
 template <typename T>
 constexpr int diag_lds_bytes() {
-  return ((kNbMax + 1) * kSld + kNbMax) * (int)sizeof(T);
+  return ((kNbMax + 1) * kSld + 2 * kNbMax) * (int)sizeof(T);
 }
 
 // Zero a few ints (the hand-over counters) with a kernel: usable under stream capture, unlike a memset node.

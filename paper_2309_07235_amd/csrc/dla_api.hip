@@ -34,7 +34,8 @@ int resolve_schedule(dla_dtype dt, const dla_gemm_params* in, int op, GemmSchedu
   GemmSchedule s = {0, 0, 0, 0, 0, 0};
   if (!in || (in->tile_m == 0 && in->tile_n == 0 && in->tile_k == 0 && in->unroll_k == 0 && in->wave_m == 0 && in->wave_n == 0)) {
     s.own = true;
-  } else if (m > 0 && n > 0) {  // dla_default_params() spelled out is the same choice
+  } else if (m > 0 && n > 0 && in->tile_k != 0 && in->wave_m != 0) {  // dla_default_params() spelled out is the same choice
+    // (a default has every field; a partly named schedule differs from it, and the comparison costs the smallest calls 7 %)
     GemmSchedule def;
     s.own = resolve_schedule(dt, nullptr, op, &def, m, n) == DLA_SUCCESS && def.tm == in->tile_m && def.tn == in->tile_n &&
             def.tk == in->tile_k && def.uk == in->unroll_k && def.wm == in->wave_m && def.wn == in->wave_n;

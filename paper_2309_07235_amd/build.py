@@ -2,7 +2,8 @@
 
 The GEMM menu is compiled one translation unit per (element type, macro-tile),
 generated from ``csrc/gemm_inst.hip.in``; objects are cached under ``_build/``
-keyed by a hash of their inputs and compiled in parallel.
+keyed by a hash of their source, of every file it includes and of the flags, and
+compiled in parallel.
 """
 from __future__ import annotations
 
@@ -33,15 +34,27 @@ def _tile_menu():
     return [tuple(int(v) for v in m.groups()) for m in re.finditer(r"X\((\d+), (\d+), (\d+), (\d+)\)", body)]
 
 
-GEMM_HEADERS = ("dla_common.hpp", "gemm_kernel.hpp", "gemm_dispatch.hpp", "dla_codes.hpp")
+def _sources_of(src: Path) -> list:
+    """src and every file of csrc/ and include/ that it includes, directly or through another."""
+    found, todo = [], [src]
+    while todo:
+        p = todo.pop()
+        if p in found:
+            continue
+        found.append(p)
+        for name in re.findall(r'^\s*#\s*include\s+"([^"]+)"', p.read_text(), flags=re.M):
+            hits = [q.resolve() for q in (p.parent / name, CSRC / name) if q.exists()]
+            if not hits:
+                raise RuntimeError(f'{p.name} includes "{name}", which is not in the tree')
+            todo.append(hits[0])
+    return found
 
 
-def _headers_hash(gemm_only: bool = False) -> str:
-    h = hashlib.sha256()
-    headers = [CSRC / n for n in GEMM_HEADERS] if gemm_only else sorted(CSRC.glob("*.hpp"))
-    for p in list(headers) + [HERE.parent / "include" / "dla.h"]:
-        h.update(p.read_bytes())
-    h.update(" ".join(FLAGS).encode())
+def _stamp(src: Path) -> str:
+    """What an object depends on: the text of its source and of all it includes, and the compiler flags."""
+    h = hashlib.sha256(" ".join(FLAGS).encode())
+    for p in sorted(_sources_of(src)):
+        h.update(p.name.encode() + b"\0" + p.read_bytes())
     return h.hexdigest()
 
 
@@ -62,7 +75,6 @@ def _compile(src: Path, obj: Path, stamp: str, verbose: bool) -> str:
 
 def build(verbose: bool = False, jobs: int | None = None) -> Path:
     BUILD.mkdir(exist_ok=True)
-    hh_all, hh_gemm = _headers_hash(False), _headers_hash(True)
     units = []
     template = (CSRC / "gemm_inst.hip.in").read_text()
     for tname, ctype in (("f64", "double"), ("f32", "float")):
@@ -80,10 +92,8 @@ def build(verbose: bool = False, jobs: int | None = None) -> Path:
         futs = []
         for src in units:
             obj = BUILD / (src.stem + ".o")
-            hh = hh_gemm if src.name.startswith("gemm_") else hh_all
-            stamp = hashlib.sha256((hh + src.read_text()).encode()).hexdigest()
             objs.append(obj)
-            futs.append(ex.submit(_compile, src, obj, stamp, verbose))
+            futs.append(ex.submit(_compile, src, obj, _stamp(src), verbose))
         for f in futs:
             msg = f.result()
             if verbose:

@@ -45,12 +45,16 @@ static int launch_wide_tile(int op, GemmGroup<T>& g, hipStream_t st) {
   }
 }
 
-// The kernel's element offsets inside a tile are 32-bit.
+// The kernel's element offsets inside a tile are 32-bit, and what it loads of a row with its columns in memory is whole
+// runs of 16 bytes: rows shorter than one are gemm_kernel's.
 template <typename T>
 bool gemm_wide_fits(int op, const GemmGroup<T>& g) {
+  constexpr int PER = WideVec<T>::PER;
   if (op != OP_ASSIGN && op != OP_SUB && op != OP_SUB_TN) return false;
-  for (int q = 0; q < g.nprob; ++q)
-    if (g.prob[q].lda > (1 << 24) || g.prob[q].ldb > (1 << 24)) return false;
+  for (int q = 0; q < g.nprob; ++q) {
+    const GemmProblem<T>& p = g.prob[q];
+    if (p.lda > (1 << 24) || p.ldb > (1 << 24) || p.N < PER || (op == OP_SUB_TN && p.M < PER)) return false;
+  }
   return true;
 }
 

@@ -12,9 +12,12 @@
 //     row block.  The row stride is odd in units of 16 bytes, so the 8 rows one access cycle serves use all banks;
 //   - adjacent column blocks are interleaved (block b of a pair takes the columns 2 l15 + b), so the right operand is
 //     read and the result stored 16 bytes at a time as well;
-//   - rows and columns past the edge of the matrices are clamped and only reach results that are not stored, so a
-//     ragged tile runs the interior loop without a mask; only a last, partial slab, and a ragged column tile whose
-//     width is not a multiple of 16 bytes, load element by element.
+//   - a ragged tile runs the same pipeline: a row past the edge is clamped to the last one, a run of columns past it to
+//     the last whole run of the row (both only reach results that are not stored); the run that straddles the edge is
+//     moved to its place on the way from the registers to LDS.  The last, partial slab is masked there too.  A mask
+//     where a value is loaded would make it wait for the load: with that, a width that is not a multiple of 16 bytes
+//     took up to 1.67 times as long (Cholesky solve N = 8192, 255 right-hand sides, fp32: 2095 us, now 1126; LU solve
+//     N = 4001, 301, fp64: 1180 us, now 675).
 // Eight waves per workgroup, two on each SIMD, cover each other's barrier.  Measured, back to back (before: gemm_kernel
 // with its default schedule): fp64 E|F of the extralarge 3mm 590 -> 487 us, G 255 -> 208, 4096 x 4096 x 1024 63 ->
 // 72 TFLOP/s (92 % of the matrix-pipe peak); fp32 E|F of the large 3mm 73 -> 43 us, G 57 -> 23.  Whole calls: 847 -> 710
@@ -62,18 +65,34 @@ struct WideShape {
   static constexpr int BYTES = 2 * STAGE * (int)sizeof(T);
 };
 
-// Loads a ROWS x COLS tile (COLS contiguous in memory), 16 bytes per thread and step.
+// A ROWS x COLS tile (COLS contiguous in memory) in passes of NT threads, 16 bytes per thread and pass.
 template <typename T, int ROWS, int COLS, int NT>
 struct WideLoader {
-  using V = typename WideVec<T>::v16;
   static constexpr int PER = WideVec<T>::PER;
   static constexpr int VPR = COLS / PER;
   static constexpr int TOTAL = ROWS * VPR;
-  static constexpr int ITER = (TOTAL + NT - 1) / NT;
+  static constexpr int ITER = TOTAL / NT;
   static_assert(COLS % PER == 0, "tile width");
-  static __device__ __forceinline__ int row_of(int idx) { return (TOTAL % NT == 0 || idx < TOTAL) ? idx / VPR : ROWS - 1; }
+  static __device__ __forceinline__ int row_of(int idx) { return idx / VPR; }
   static __device__ __forceinline__ int col_of(int idx) { return (idx % VPR) * PER; }
 };
+
+// The run that began `by` elements (less than a run) before its place: element e to the front of it is element e + by.
+// What it holds past the edge is not used.
+template <typename T>
+__device__ __forceinline__ typename WideVec<T>::v16 wide_move(typename WideVec<T>::v16 x, int by) {
+  if constexpr (WideVec<T>::PER == 2) {
+    x[0] = by != 0 ? x[1] : x[0];
+  } else {
+    const bool one = (by & 1) != 0, two = (by & 2) != 0;
+    x[0] = one ? x[1] : x[0];
+    x[1] = one ? x[2] : x[1];
+    x[2] = one ? x[3] : x[2];
+    x[0] = two ? x[2] : x[0];
+    x[1] = two ? x[3] : x[1];
+  }
+  return x;
+}
 
 template <typename T, int WM, int WN, int FM, int FN, int TK, int OP>
 __global__ void __launch_bounds__(WM * WN * 64) gemm_wide_kernel(const GemmGroup<T> g) {
@@ -130,24 +149,23 @@ __global__ void __launch_bounds__(WM * WN * 64) gemm_wide_kernel(const GemmGroup
       for (int b = 0; b < FN; ++b) acc[a][b] = acc_t{0, 0, 0, 0};
   }
 
-  // ---- operand loads.  Rows and columns past the edge are clamped into the matrix: what they bring only reaches
-  // results past the edge, which are not stored.
-  const T* const Ag = AT ? P.A + m0 : P.A + (int64_t)m0 * lda;
-  const T* const Bg = P.B + n0;
-  const int a_cols = AT ? M - m0 : K, b_cols = N - n0;   // columns of memory rows that exist
-  const bool a_vec = !AT || a_cols >= LA::VPR * PER || (a_cols % PER == 0), b_vec = b_cols >= TN || (b_cols % PER == 0);
+  // ---- operand loads: 16-byte runs, starting inside the matrix (rows clamped, runs of columns clamped to the last whole
+  // one, which gemm_wide_fits sees to).  `shift`: how far the run that straddles the edge begins before its place.
+  const T* const Ag = AT ? P.A : P.A + (int64_t)m0 * lda;
+  const T* const Bg = P.B;
+  static_assert(LA::TOTAL % NT == 0 && LB::TOTAL % NT == 0 && NT % LA::VPR == 0 && NT % LB::VPR == 0, "whole passes, one column per thread");
+  const int ac = LA::col_of(tid), bc = LB::col_of(tid);  // of every pass
+  const int ma = AT ? (m0 + ac < M - PER ? m0 + ac : M - PER) : ac, nb = n0 + bc < N - PER ? n0 + bc : N - PER;
+  const int ashift = AT ? m0 + ac - ma : 0, bshift = n0 + bc - nb;
+  const bool moved = (n0 + TN > N && N % PER != 0) || (AT && m0 + TM > M && M % PER != 0);  // uniform
   uint32_t aoff[LA::ITER], boff[LB::ITER];               // element offsets of slab 0
 #pragma unroll
   for (int it = 0; it < LA::ITER; ++it) {
-    const int idx = tid + it * NT, r = LA::row_of(idx), c = LA::col_of(idx);
-    if constexpr (AT) aoff[it] = (uint32_t)(r * (uint32_t)lda + (c + PER <= a_cols ? c : (a_cols >= PER ? a_cols - PER : 0)));
-    else aoff[it] = (uint32_t)((m0 + r < M ? r : M - 1 - m0) * (uint32_t)lda + c);
+    const int r = LA::row_of(tid + it * NT);
+    aoff[it] = (uint32_t)(AT || m0 + r < M ? r : M - 1 - m0) * (uint32_t)lda + (uint32_t)ma;
   }
 #pragma unroll
-  for (int it = 0; it < LB::ITER; ++it) {
-    const int idx = tid + it * NT, r = LB::row_of(idx), c = LB::col_of(idx);
-    boff[it] = (uint32_t)(r * (uint32_t)ldb + (c + PER <= b_cols ? c : (b_cols >= PER ? b_cols - PER : 0)));
-  }
+  for (int it = 0; it < LB::ITER; ++it) boff[it] = (uint32_t)LB::row_of(tid + it * NT) * (uint32_t)ldb + (uint32_t)nb;
   V ra[2][LA::ITER], rb[2][LB::ITER];
   auto load_full = [&](auto sc, int s) __attribute__((always_inline)) {
     constexpr int X = decltype(sc)::value;
@@ -158,45 +176,56 @@ __global__ void __launch_bounds__(WM * WN * 64) gemm_wide_kernel(const GemmGroup
 #pragma unroll
     for (int it = 0; it < LB::ITER; ++it) rb[X][it] = *reinterpret_cast<const V*>(pb + boff[it]);
   };
-  // element by element, zero past the edge
-  auto load_edge = [&](auto sc, int s) __attribute__((always_inline)) {
+  // the last, partial slab: k past its end is clamped here and masked in stash
+  auto load_tail = [&](auto sc, int s) __attribute__((always_inline)) {
     constexpr int X = decltype(sc)::value;
     const int kv = K - s * TK;
     const T* const pa = AT ? Ag + (int64_t)s * TK * lda : Ag + (int64_t)s * TK;
     const T* const pb = Bg + (int64_t)s * TK * ldb;
 #pragma unroll
     for (int it = 0; it < LA::ITER; ++it) {
-      const int idx = tid + it * NT, r = LA::row_of(idx), c = LA::col_of(idx);
-      const int rv = AT ? kv : M - m0, cv = AT ? a_cols : kv;
+      if constexpr (AT) {
+        const int r = LA::row_of(tid + it * NT);
+        ra[X][it] = *reinterpret_cast<const V*>(pa + (aoff[it] - (uint32_t)(r < kv ? 0 : r - kv + 1) * (uint32_t)lda));
+      } else {
 #pragma unroll
-      for (int e = 0; e < PER; ++e) {
-        const T x = pa[(int64_t)(r < rv ? r : rv - 1) * lda + (c + e < cv ? c + e : cv - 1)];
-        ra[X][it][e] = (r < rv && c + e < cv) ? x : T(0);
+        for (int e = 0; e < PER; ++e) ra[X][it][e] = pa[aoff[it] - (uint32_t)ac + (uint32_t)(ac + e < kv ? ac + e : kv - 1)];
       }
     }
 #pragma unroll
     for (int it = 0; it < LB::ITER; ++it) {
-      const int idx = tid + it * NT, r = LB::row_of(idx), c = LB::col_of(idx);
-#pragma unroll
-      for (int e = 0; e < PER; ++e) {
-        const T x = pb[(int64_t)(r < kv ? r : kv - 1) * ldb + (c + e < b_cols ? c + e : b_cols - 1)];
-        rb[X][it][e] = (r < kv && c + e < b_cols) ? x : T(0);
-      }
+      const int r = LB::row_of(tid + it * NT);
+      rb[X][it] = *reinterpret_cast<const V*>(pb + (boff[it] - (uint32_t)(r < kv ? 0 : r - kv + 1) * (uint32_t)ldb));
     }
   };
-  auto stash = [&](auto sc, int buf) __attribute__((always_inline)) {
-    constexpr int X = decltype(sc)::value;
+  // registers to LDS.  MODE 0: as loaded; 1: the straddling run moved to its place; 2: that, and zeros past the end of k
+  // (in both operands: what a clamped address brought may be anything)
+  auto stash = [&](auto sc, auto mode, int buf, int s) __attribute__((always_inline)) {
+    constexpr int X = decltype(sc)::value, MODE = decltype(mode)::value;
     T* const sa = smem + buf * S::STAGE;
     T* const sb = sa + S::A_ELEMS;
+    const int kv = K - s * TK;
 #pragma unroll
     for (int it = 0; it < LA::ITER; ++it) {
-      const int idx = tid + it * NT;
-      if (LA::TOTAL % NT == 0 || idx < LA::TOTAL) *reinterpret_cast<__attribute__((aligned(16))) V*>(sa + (idx / LA::VPR) * S::SA + LA::col_of(idx)) = SUB ? -ra[X][it] : ra[X][it];
+      V x = ra[X][it];
+      const int r = LA::row_of(tid + it * NT);
+      if constexpr (AT && MODE > 0) x = wide_move<T>(x, ashift);
+      if constexpr (MODE == 2) {
+#pragma unroll
+        for (int e = 0; e < PER; ++e) x[e] = (AT ? r : ac + e) < kv ? x[e] : T(0);
+      }
+      *reinterpret_cast<__attribute__((aligned(16))) V*>(sa + r * S::SA + ac) = SUB ? -x : x;
     }
 #pragma unroll
     for (int it = 0; it < LB::ITER; ++it) {
-      const int idx = tid + it * NT;
-      if (LB::TOTAL % NT == 0 || idx < LB::TOTAL) *reinterpret_cast<__attribute__((aligned(16))) V*>(sb + (idx / LB::VPR) * S::SB + LB::col_of(idx)) = rb[X][it];
+      V x = rb[X][it];
+      const int r = LB::row_of(tid + it * NT);
+      if constexpr (MODE > 0) x = wide_move<T>(x, bshift);
+      if constexpr (MODE == 2) {
+#pragma unroll
+        for (int e = 0; e < PER; ++e) x[e] = r < kv ? x[e] : T(0);
+      }
+      *reinterpret_cast<__attribute__((aligned(16))) V*>(sb + r * S::SB + bc) = x;
     }
   };
   // k of step kk is KPL * l4 + kk in both operands: a lane's left-operand values of a slab are contiguous
@@ -221,39 +250,47 @@ __global__ void __launch_bounds__(WM * WN * 64) gemm_wide_kernel(const GemmGroup
   };
   using c0 = std::integral_constant<int, 0>;
   using c1 = std::integral_constant<int, 1>;
-  const int nslab = (K + TK - 1) / TK;
-  const int nfull = (a_vec && b_vec) ? K / TK : 0;
+  using c2 = std::integral_constant<int, 2>;
+  const int nslab = (K + TK - 1) / TK, nfull = K / TK;
   auto load_any = [&](auto sc, int s) __attribute__((always_inline)) {
     if (s < nfull) load_full(sc, s);
-    else if (s < nslab) load_edge(sc, s);
+    else if (s < nslab) load_tail(sc, s);
+  };
+  auto stash_any = [&](auto sc, int buf, int s) __attribute__((always_inline)) {
+    if (s < nfull && !moved) stash(sc, c0{}, buf, s);
+    else if (s < nslab) stash(sc, c2{}, buf, s);
   };
   load_any(c0{}, 0);
   load_any(c1{}, 1);
-  stash(c0{}, 0);
+  stash_any(c0{}, 0, 0);
   lds_barrier();
   int s = 0;
-  for (; s + 3 < nfull; s += 2) {
-    load_full(c0{}, s + 2);
-    multiply(0, c0{});
-    stash(c1{}, 1);
-    multiply(0, c1{});
-    lds_barrier();
-    load_full(c1{}, s + 3);
-    multiply(1, c0{});
-    stash(c0{}, 0);
-    multiply(1, c1{});
-    lds_barrier();
-  }
+  auto steady = [&](auto mode) __attribute__((always_inline)) {
+    for (; s + 3 < nfull; s += 2) {
+      load_full(c0{}, s + 2);
+      multiply(0, c0{});
+      stash(c1{}, mode, 1, s + 1);
+      multiply(0, c1{});
+      lds_barrier();
+      load_full(c1{}, s + 3);
+      multiply(1, c0{});
+      stash(c0{}, mode, 0, s + 2);
+      multiply(1, c1{});
+      lds_barrier();
+    }
+  };
+  if (moved) steady(c1{});
+  else steady(c0{});
   for (; s < nslab; s += 2) {
     load_any(c0{}, s + 2);
     multiply(0, c0{});
-    if (s + 1 < nslab) stash(c1{}, 1);
+    stash_any(c1{}, 1, s + 1);
     multiply(0, c1{});
     lds_barrier();
     if (s + 1 >= nslab) break;
     load_any(c1{}, s + 3);
     multiply(1, c0{});
-    if (s + 2 < nslab) stash(c0{}, 0);
+    stash_any(c0{}, 0, s + 2);
     multiply(1, c1{});
     lds_barrier();
   }

@@ -46,3 +46,42 @@ def test_edges_bit_for_bit(op, dtype, pad):
         outside[:m, pad:pad + n] = float("nan")
         assert bool(torch.isnan(outside).all()), "written outside the matrix"
         assert int(torch.isnan(cfull).sum()) == cfull.numel() - m * n
+
+
+def _us(fn):
+    """Device time of one of many calls in a row, best of five rounds."""
+    import torch
+    e0, e1 = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+    for _ in range(5):
+        fn()
+    best = float("inf")
+    for _ in range(5):
+        e0.record()
+        for _ in range(20):
+            fn()
+        e1.record()
+        e1.synchronize()
+        best = min(best, e0.elapsed_time(e1) * 50.0)
+    return best
+
+
+@pytest.mark.parametrize("dtype", ["float64", "float32"])
+@pytest.mark.parametrize("op", [0, 1, 4])
+def test_a_ragged_width_costs_what_its_neighbour_does(op, dtype):
+    """Widths and depths that are no multiple of 16 bytes or of a slab run the same pipeline as those that are.  With
+    loads that waited one by one the first of these took 2 to 3.6 times its neighbour's time; in the same pipeline all are
+    within a fifth of theirs, and 1.3 leaves room for the clock."""
+    import torch
+    from paper_2309_07235_amd import binding as B
+    dt = getattr(torch, dtype)
+
+    def product(m, n, k):
+        a = torch.rand((k, m) if op == 4 else (m, k), dtype=dt, device="cuda")
+        b, c = torch.rand((k, n), dtype=dt, device="cuda"), torch.zeros((m, n), dtype=dt, device="cuda")
+        return lambda: B.dla_gemm(op, a, b, c)
+
+    for whole, ragged in (((256, 304, 4096), (256, 301, 4096)), ((1008, 1008, 1008), (1001, 1001, 1001)), ((456, 3924, 1344), (453, 3923, 1348))):
+        announce(f"gemm op {op} {dtype}: time of {ragged} against {whole}")
+        tw, tr = _us(product(*whole)), _us(product(*ragged))
+        print(f"{whole} {tw:.1f} us, {ragged} {tr:.1f} us")
+        assert tr <= 1.3 * tw

@@ -152,7 +152,7 @@ int run_gemm(const GemmSchedule& s, int op, const T* A, int64_t lda, const T* B,
   g.total_tiles = problem_tiles(s, op, g.prob[0]);
   const double flops = (op == OP_SUB_NT_LOWER ? 1.0 : 2.0) * (double)M * (double)N * (double)K;
   ProfileScope scope(PHASE_GEMM, flops, st);
-  if (s.own && gemm_wide_fits<T>(op, g)) return launch_gemm_wide<T>(op, g, st);
+  if (s.own && gemm_wide_takes<T>(op, g)) return launch_gemm_wide<T>(op, g, st);
   return launch_gemm<T>(s, op, g, st);
 }
 template int run_gemm<double>(const GemmSchedule&, int, const double*, int64_t, const double*, int64_t, double*,
@@ -216,7 +216,7 @@ static int mm3_impl(const T* A, int64_t lda, const T* B, int64_t ldb, const T* C
     g.total_tiles = t0 + problem_tiles(se, OP_ASSIGN, g.prob[1]);
     for (int q = 2; q < kMaxGroup; ++q) g.prob[q] = g.prob[1];
     ProfileScope scope(PHASE_GEMM, 2.0 * ((double)ni * nj * nk + (double)nj * nl * nm), st);
-    rc = se.own && gemm_wide_fits<T>(OP_ASSIGN, g) ? launch_gemm_wide<T>(OP_ASSIGN, g, st) : launch_gemm<T>(se, OP_ASSIGN, g, st);
+    rc = se.own && gemm_wide_takes<T>(OP_ASSIGN, g) ? launch_gemm_wide<T>(OP_ASSIGN, g, st) : launch_gemm<T>(se, OP_ASSIGN, g, st);
     if (rc != DLA_SUCCESS) return rc;
   } else {
     if (nk > 0 && (rc = run_gemm<T>(se, OP_ASSIGN, A, lda, B, ldb, E, L.lde, ni, nj, nk, st)) != DLA_SUCCESS) return rc;

@@ -73,10 +73,10 @@ int launch_gemm_tile(const GemmSchedule& s, int op, const GemmGroup<T>& g, hipSt
 template <typename T>
 int launch_gemm(const GemmSchedule& s, int op, const GemmGroup<T>& g, hipStream_t st);
 
-// gemm_wide_kernel (gemm_wide.hip): C = A*B, C -= A*B and C -= A^T*B with a tile of the library's choice.  fits: the
-// products are within its limits.  launch fills in the tile fields of the group.
+// gemm_wide_kernel (gemm_wide.hip): C = A*B, C -= A*B and C -= A^T*B with a tile of the library's choice.  takes: the
+// products are within its limits and deep enough.  launch fills in the tile fields of the group.
 template <typename T>
-bool gemm_wide_fits(int op, const GemmGroup<T>& g);
+bool gemm_wide_takes(int op, const GemmGroup<T>& g);
 template <typename T>
 int launch_gemm_wide(int op, GemmGroup<T>& g, hipStream_t st);
 

@@ -5,13 +5,14 @@
 
 namespace dla {
 
-// The tiles: X(waves along m, along n, 16 x 16 blocks per wave along m, along n, rate).  rate: TFLOP/s of a
-// 4096 x 4096 x 1024 product in fp64 (fp32 ranks them the same way, 93, 107, 110, 115).
-#define DLA_WIDE_MENU(X) \
-  X(2, 2, 1, 1, 57)      \
-  X(2, 2, 2, 1, 65)      \
-  X(4, 2, 1, 2, 72)      \
-  X(4, 2, 2, 2, 73)
+// The tiles: X(waves along m, along n, 16 x 16 blocks per wave along m, along n, rate in fp64, in fp32, fill).  rate:
+// TFLOP/s of whole rounds of tiles, over the three operations at 3000 x 3000 to 6000 x 6000, k = 1024 to 4096.  fill: what
+// filling and draining a tile costs, in k, more for the waves with two row blocks, of which fewer fit beside each other.
+#define DLA_WIDE_MENU(X)      \
+  X(2, 2, 1, 1, 55, 101, 0)   \
+  X(2, 2, 2, 1, 64, 117, 16)  \
+  X(4, 2, 1, 2, 67, 126, 0)   \
+  X(4, 2, 2, 2, 70, 132, 16)
 
 template <typename T, int WM, int WN, int FM, int FN, int OP>
 static int launch_wide_op(const GemmGroup<T>& g, hipStream_t st) {
@@ -45,51 +46,58 @@ static int launch_wide_tile(int op, GemmGroup<T>& g, hipStream_t st) {
   }
 }
 
-// The kernel's element offsets inside a tile are 32-bit, and what it loads of a row with its columns in memory is whole
-// runs of 16 bytes: rows shorter than one are gemm_kernel's.
+// Which products are the wide kernel's.  Its element offsets inside a tile are 32-bit.  And in fp32 a product no deeper
+// than a slab, which is traffic of C, is gemm_kernel's (C = A*B, C -= A*B, C -= A^T*B, 4000 x 4000, in us, here against
+// there: k = 8 24, 28, 28 against 19, 27, 25; k = 32 20, 26, 26 against 23, 32, 29, but 2047 x 2047 11.3, 11.4, 16.9
+// against 11.0, 11.1, 11.2; k = 64 28, 34, 35 against 34, 42, 37).  fp64, k = 8: 25, 41, 42 against 33, 54, 40.
 template <typename T>
-bool gemm_wide_fits(int op, const GemmGroup<T>& g) {
-  constexpr int PER = WideVec<T>::PER;
+bool gemm_wide_takes(int op, const GemmGroup<T>& g) {
   if (op != OP_ASSIGN && op != OP_SUB && op != OP_SUB_TN) return false;
+  int depth = 0;
   for (int q = 0; q < g.nprob; ++q) {
     const GemmProblem<T>& p = g.prob[q];
-    if (p.lda > (1 << 24) || p.ldb > (1 << 24) || p.N < PER || (op == OP_SUB_TN && p.M < PER)) return false;
+    if (p.lda > (1 << 24) || p.ldb > (1 << 24)) return false;
+    depth = p.K > depth ? p.K : depth;
   }
-  return true;
+  return sizeof(T) == 8 || depth > 32;
 }
 
-// A launch lasts as long as its busiest compute unit: rounds = tiles / 256 rounded up, each one tile at the tile's own
-// rate; the least wins.  (fp64 G of the extralarge 3mm, 1600 x 2200: 64 x 32 tiles, 6.7 per unit, 208 us; 64 x 64, 3.4
-// per unit, 214 us; 128 x 64, 1.8 per unit, 213 us.  E|F: 64 x 64, 6.8 per unit, 487 us; 64 x 32 530; 128 x 64 545.)
+// A launch lasts as long as its busiest compute unit: rounds = tiles / 256 rounded up, each one tile of the group's mean
+// depth, and its fill, at the tile's own rate; the least wins.  Over 140 products of 32 x 400 to 6000 x 6000, k = 8 to 4096,
+// all three operations, the choice costs 1.6 % (fp64) and 1.3 % (fp32) more than the best tile in the mean.
 template <typename T>
 int launch_gemm_wide(int op, GemmGroup<T>& g, hipStream_t st) {
   double best = 0.0;
   int pick = -1, at = 0;
-#define DLA_CASE(WM, WN, FM, FN, RATE)                                                       \
-  {                                                                                          \
-    constexpr int TM = WM * FM * 16, TN = WN * FN * 16;                                      \
-    int64_t tiles = 0;                                                                       \
-    for (int q = 0; q < g.nprob; ++q)                                                        \
-      tiles += (int64_t)((g.prob[q].M + TM - 1) / TM) * ((g.prob[q].N + TN - 1) / TN);       \
-    const double cost = (double)((tiles + 255) / 256) * (TM * TN) / RATE;                    \
-    if (pick < 0 || cost < best) {                                                           \
-      best = cost;                                                                           \
-      pick = at;                                                                             \
-    }                                                                                        \
-    ++at;                                                                                    \
+#define DLA_CASE(WM, WN, FM, FN, RATE64, RATE32, FILL)                                                     \
+  {                                                                                                        \
+    constexpr int TM = WM * FM * 16, TN = WN * FN * 16;                                                    \
+    int64_t tiles = 0;                                                                                     \
+    double depth = 0.0;                                                                                    \
+    for (int q = 0; q < g.nprob; ++q) {                                                                    \
+      const int64_t t = (int64_t)((g.prob[q].M + TM - 1) / TM) * ((g.prob[q].N + TN - 1) / TN);            \
+      tiles += t;                                                                                          \
+      depth += (double)t * (g.prob[q].K + FILL);                                                           \
+    }                                                                                                      \
+    const double cost = (double)((tiles + 255) / 256) * (depth / (double)tiles) * (TM * TN) / (sizeof(T) == 8 ? RATE64 : RATE32); \
+    if (pick < 0 || cost < best) {                                                                         \
+      best = cost;                                                                                         \
+      pick = at;                                                                                           \
+    }                                                                                                      \
+    ++at;                                                                                                  \
   }
   DLA_WIDE_MENU(DLA_CASE)
 #undef DLA_CASE
   at = 0;
-#define DLA_CASE(WM, WN, FM, FN, RATE) \
+#define DLA_CASE(WM, WN, FM, FN, RATE64, RATE32, FILL) \
   if (at++ == pick) return launch_wide_tile<T, WM, WN, FM, FN>(op, g, st);
   DLA_WIDE_MENU(DLA_CASE)
 #undef DLA_CASE
   return DLA_ERR_UNSUPPORTED_PARAMS;
 }
 
-template bool gemm_wide_fits<double>(int, const GemmGroup<double>&);
-template bool gemm_wide_fits<float>(int, const GemmGroup<float>&);
+template bool gemm_wide_takes<double>(int, const GemmGroup<double>&);
+template bool gemm_wide_takes<float>(int, const GemmGroup<float>&);
 template int launch_gemm_wide<double>(int, GemmGroup<double>&, hipStream_t);
 template int launch_gemm_wide<float>(int, GemmGroup<float>&, hipStream_t);
 

@@ -101,7 +101,7 @@ struct ProductList {
     int rc;
     {
       ProfileScope scope(PHASE_GEMM, flops, st);
-      rc = gemm_wide_fits<T>(op, g) ? launch_gemm_wide<T>(op, g, st) : launch_gemm<T>(sch, op, g, st);
+      rc = gemm_wide_takes<T>(op, g) ? launch_gemm_wide<T>(op, g, st) : launch_gemm<T>(sch, op, g, st);
     }
     np = tiles = 0;
     flops = 0.0;
@@ -272,7 +272,7 @@ int solve_impl(const T* F, int64_t n, int64_t lda, T* B, int64_t nrhs, int64_t l
     g.nprob = np;
     g.total_tiles = tiles;
     ProfileScope scope(PHASE_GEMM, flops, st);
-    return gemm_wide_fits<T>(op, g) ? launch_gemm_wide<T>(op, g, st) : launch_gemm<T>(sch, op, g, st);
+    return gemm_wide_takes<T>(op, g) ? launch_gemm_wide<T>(op, g, st) : launch_gemm<T>(sch, op, g, st);
   };
   // ---- forward.  Z_i and then Y_i live in rows i of Y; B is updated in place (part c).
   {

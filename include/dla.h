@@ -64,8 +64,9 @@ enum { DLA_KERNEL_MM3 = 0, DLA_KERNEL_LU = 1, DLA_KERNEL_CHOLESKY = 2 };
  * computes: the paper's split factors of the y and x axes of one 3mm product
  * (code mold, parameters P0..P5).  The remaining fields are the extra knobs of
  * the native kernel.  A field set to 0 means "library default for this
- * macro-tile".  All six 0, or the schedule that dla_default_params() gives for
- * the product's size, leaves tile and kernel to the library.
+ * macro-tile".  A schedule that names any field runs as named; all six 0 (or
+ * a NULL pointer) leaves kernel and tile to the library, which picks them by
+ * the product's size and is faster than any schedule of the menu on most.
  */
 typedef struct {
   int tile_m, tile_n; /* workgroup macro-tile, multiples of 16                                 */
@@ -284,7 +285,8 @@ int dla_block_size_supported(dla_dtype dt, int nb);
 
 /*
  * Fills *out with the default schedule for a kernel (DLA_KERNEL_*) at size n:
- * out points to a dla_mm3_params for DLA_KERNEL_MM3, else to a dla_factor_params.
+ * out points to a dla_mm3_params for DLA_KERNEL_MM3 (all fields 0: every product's
+ * kernel and tile are the library's choice), else to a dla_factor_params.
  */
 int dla_default_params(int kernel, int64_t n, dla_dtype dt, void* out);
 

@@ -31,16 +31,10 @@ static const int kNumKu = (int)(sizeof(kKu) / sizeof(kKu[0]));
 static int esize(dla_dtype dt) { return dt == DLA_F64 ? 8 : 4; }
 
 int resolve_schedule(dla_dtype dt, const dla_gemm_params* in, int op, GemmSchedule* out, int64_t m, int64_t n) {
-  GemmSchedule s = {0, 0, 0, 0, 0, 0};
-  if (!in || (in->tile_m == 0 && in->tile_n == 0 && in->tile_k == 0 && in->unroll_k == 0 && in->wave_m == 0 && in->wave_n == 0)) {
-    s.own = true;
-  } else if (m > 0 && n > 0 && in->tile_k != 0 && in->wave_m != 0) {  // dla_default_params() spelled out is the same choice
-    // (a default has every field; a partly named schedule differs from it, and the comparison costs the smallest calls 7 %)
-    GemmSchedule def;
-    s.own = resolve_schedule(dt, nullptr, op, &def, m, n) == DLA_SUCCESS && def.tm == in->tile_m && def.tn == in->tile_n &&
-            def.tk == in->tile_k && def.uk == in->unroll_k && def.wm == in->wave_m && def.wn == in->wave_n;
-  }
-  if (in) s = GemmSchedule{in->tile_m, in->tile_n, in->tile_k, in->unroll_k, in->wave_m, in->wave_n, s.own};
+  GemmSchedule s = {0, 0, 0, 0, 0, 0, true};
+  // a schedule that names anything runs as named; none at all leaves kernel and tile to the library
+  if (in) s = GemmSchedule{in->tile_m, in->tile_n, in->tile_k, in->unroll_k, in->wave_m, in->wave_n,
+                           !(in->tile_m | in->tile_n | in->tile_k | in->unroll_k | in->wave_m | in->wave_n)};
   if (s.tm < 0 || s.tn < 0 || s.tk < 0 || s.uk < 0 || s.wm < 0 || s.wn < 0) return DLA_ERR_UNSUPPORTED_PARAMS;
   if (s.tm == 0 && s.tn == 0) {
     // A 128x128 macro-tile needs about four tiles per compute unit to balance the 256 of them;
@@ -356,10 +350,7 @@ int dla_default_params(int kernel, int64_t n, dla_dtype dt, void* out) {
   if (!out) return -4;
   if (kernel == DLA_KERNEL_MM3) {
     dla_mm3_params* p = static_cast<dla_mm3_params*>(out);
-    GemmSchedule s;
-    resolve_schedule(dt, nullptr, OP_ASSIGN, &s, n, n);
-    const dla_gemm_params gp = {s.tm, s.tn, s.tk, s.uk, s.wm, s.wn};
-    p->e = p->f = p->g = gp;
+    p->e = p->f = p->g = dla_gemm_params{0, 0, 0, 0, 0, 0};  // kernel and tile by the size of each product
     return DLA_SUCCESS;
   }
   dla_factor_params* p = static_cast<dla_factor_params*>(out);

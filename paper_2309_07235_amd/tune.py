@@ -189,15 +189,16 @@ def _time_ms(fn, reps: int) -> float:
 
 
 def mm3_problem(dims: Dict[str, int], seed: int = 4, reps: int = 5, dtype: str = "f64"):
-    """Search space and objective of 3mm: one schedule of the menu per product (the paper's P0..P5 are the
-    macro-tiles of E, F and G; the native k-slab / unroll / wave-split knobs ride along in the same entry)."""
+    """Search space and objective of 3mm: one schedule per product, entry 0 = the library's own choice, the others =
+    the menu's (the paper's P0..P5 are the macro-tiles of E, F and G; the native k-slab / unroll / wave-split knobs
+    ride along in the same entry)."""
     import torch
     from . import binding as B
     from . import inputs
 
     dt = B.DLA_F64 if dtype == "f64" else B.DLA_F32
     tdt = torch.float64 if dtype == "f64" else torch.float32
-    menu = [t.as_tuple() for t in B.enumerate_tiles(dt)]
+    menu = [(0, 0, 0, 0, 0, 0)] + [t.as_tuple() for t in B.enumerate_tiles(dt)]
     space = SearchSpace(["e", "f", "g"], [menu, menu, menu])
     ops = [torch.from_numpy(x).to("cuda").to(tdt) for x in inputs.mm3_operands(seed, **dims)]
     g = torch.empty((dims["ni"], dims["nl"]), dtype=tdt, device="cuda")

@@ -74,6 +74,7 @@ def test_default_params(B):
     p = B.default_params(B.DLA_KERNEL_MM3, 2000)
     assert p.e.as_tuple() == p.f.as_tuple() == p.g.as_tuple()
     assert B.gemm_params_supported(B.DLA_F64, p.e)
+    assert p.e.as_tuple() == (0, 0, 0, 0, 0, 0)  # kernel and tile are the library's choice, not a schedule of the menu
     for k in (B.DLA_KERNEL_LU, B.DLA_KERNEL_CHOLESKY):
         f = B.default_params(k, 4000)
         assert B.block_size_supported(B.DLA_F64, f.nb)

@@ -68,6 +68,22 @@ def test_every_schedule_in_the_menu(B, oracle):
         assert max_rel_err(to_host(G), want) <= TOL64, repr(t)
 
 
+@pytest.mark.parametrize("dtype", ["float64", "float32"])
+def test_a_schedule_runs_as_named_however_it_is_spelled(B, dtype):
+    """The square tile with all fields written out and with the rest left to the menu's defaults is one schedule: the
+    same kernel, the same order of sums, the same bits, at sizes on both sides of every product's default tile."""
+    import torch
+    dt = getattr(torch, dtype)
+    for m, n, k in ((150, 139, 70), (1000, 1100, 900), (4000, 4000, 257)):
+        announce(f"gemm {dtype} {m} x {n} x {k}, one schedule in two spellings")
+        a, b = (torch.rand(s, dtype=dt, device="cuda") - 0.5 for s in ((m, k), (k, n)))
+        for t, full in ((64, (64, 64, 16, 4, 32, 32)), (128, (128, 128, 16, 4, 64, 64))):
+            c = [torch.zeros((m, n), dtype=dt, device="cuda") for _ in range(2)]
+            B.dla_gemm(0, a, b, c[0], B.GemmParams(*full))
+            B.dla_gemm(0, a, b, c[1], B.GemmParams(t, t, 0, 0, 0, 0))
+            assert torch.equal(*c), (m, n, k, t)
+
+
 def test_mixed_schedules_per_product(B, oracle):
     """The three products may use three different schedules (the six parameters of the code mold)."""
     announce("mm3 mixed schedules")

@@ -196,9 +196,9 @@ static int mm3_impl(const T* A, int64_t lda, const T* B, int64_t ldb, const T* C
   if (ni == 0 || nl == 0) return DLA_SUCCESS;  // G is empty
   int rc;
   if (nj == 0) return fill_zero(G, ldg, ni, nl, st);  // E and F are empty: G = 0
-  // E = A*B and F = C*D are independent: one grouped launch when their schedules coincide.
-  const bool same = se.tm == sf.tm && se.tn == sf.tn && se.tk == sf.tk && se.uk == sf.uk && se.wm == sf.wm &&
-                    se.wn == sf.wn && se.own == sf.own;
+  // E = A*B and F = C*D are independent: one grouped launch when one schedule is meant for both.
+  const bool same = (se.own && sf.own) || (se.own == sf.own && se.tm == sf.tm && se.tn == sf.tn && se.tk == sf.tk &&
+                                           se.uk == sf.uk && se.wm == sf.wm && se.wn == sf.wn);
   if (nk == 0) { if ((rc = fill_zero(E, L.lde, ni, nj, st)) != DLA_SUCCESS) return rc; }
   if (nm == 0) { if ((rc = fill_zero(F, L.ldf, nj, nl, st)) != DLA_SUCCESS) return rc; }
   if (same && nk > 0 && nm > 0) {

@@ -164,6 +164,31 @@ def test_degenerate_dimensions(B, oracle):
     torch.cuda.synchronize()
 
 
+@pytest.mark.parametrize("dtype", ["float64", "float32"])
+def test_two_launches_whatever_the_sizes_of_the_products(B, dtype):
+    """E and F share one launch when the library picks the schedule, also where the menu's default tiles for the two
+    differ (E 4096 x 4096: 128 x 128, F 4096 x 64: 64 x 64); with two named tiles they cannot."""
+    import torch
+    announce(f"mm3 {dtype} 4096x70x4096x40x64, launches counted")
+    dims = (4096, 70, 4096, 40, 64)
+    ops = [torch.randint(-3, 4, s, device="cuda").to(getattr(torch, dtype)) for s in zip(dims[:4], dims[1:])]
+    G = torch.empty((dims[0], dims[4]), dtype=ops[0].dtype, device="cuda")
+
+    def launches(params):
+        torch.cuda.synchronize()
+        B.profile_enable(True)
+        B.mm3(*ops, G, params)
+        B.profile_enable(False)
+        return B.profile_read(B.PHASE_GEMM)[1]
+
+    assert launches(None) == 2
+    if dtype == "float64":  # entries of up to 9 * 70 * 9 * 40 * 4096: exact
+        want = (ops[0].cpu() @ ops[1].cpu()) @ (ops[2].cpu() @ ops[3].cpu())
+        assert torch.equal(G.cpu(), want)
+    assert launches(_params(B, (64, 64))) == 2
+    assert launches(_params(B, (128, 128), (64, 64))) == 3
+
+
 def test_strided_operands_and_stream(B, oracle):
     """Leading dimensions larger than the row length, odd leading dimension, and a non-default stream."""
     import torch

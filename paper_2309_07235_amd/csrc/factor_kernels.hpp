@@ -4,17 +4,19 @@
 //   diag_kernel   one workgroup factors the b x b diagonal block (b <= 128) held
 //                 in LDS, in stages of 16 columns: a wavefront-level 16 x 16
 //                 factorisation in registers (one matrix row per lane, pivot row
-//                 broadcast with DPP row_newbcast), the 16-wide inner panels as
-//                 four dependent MFMAs per tile (tri_slabs), MFMA for the inner
-//                 trailing update.  The identity rides along as one more panel
-//                 tile and comes out as the sub-block's inverse, which goes to
+//                 broadcast with DPP row_newbcast), the 16-wide inner panels by
+//                 substitution, one column or row per lane, MFMA for the inner
+//                 trailing update.  The identity rides along as 16 more columns of
+//                 the panel and comes out as the sub-block's inverse, which goes to
 //                 the workspace.
-// What bounds it is the chain factor -> panels -> next sub-block's update -> factor of its eight stages: about 2900,
-// 2900 and 800 cycles of a stage's 9000 (cycle counter, N = 128, fp64 LU).  fp64 multiply-adds are not the cost (4 cycles
-// each, dependent or not); wait states, selects and compares around them and LDS traffic are.  Measured on whole calls,
-// this form against panels by substitution in one column per lane, pivots tested in every step, inverses and the store
-// behind the last stage, and the first sub-block factored only once the whole block has arrived: LU N = 300 131 -> 125 us,
-// LU N = 4000 1933 -> 1901, Cholesky N = 4000 1615 -> 1560, fp32 Cholesky N = 8192 3865 -> 3770.
+// What bounds it is the chain factor -> panels -> next sub-block's update -> factor of its eight stages.  fp64
+// multiply-adds are not the cost (4 cycles each, dependent or not); wait states, selects and compares around them and LDS
+// traffic are.  Measured on whole calls, against DPP multiply-adds with wait states of their own, pivots tested in every
+// step, inverses and the store behind the last stage, and the first sub-block factored only once the whole block has
+// arrived: N = 128 LU fp64 42.0 -> 37.2 us, Cholesky fp64 44.7 -> 38.9, fp32 40.3 -> 33.6; LU N = 4000 1888 -> 1820.
+// Panels as products with explicit inverses of 4 x 4 blocks on MFMA are no faster (39.8, 39.8, 34.0, 1853) and not
+// substitution: their backward error grows with the condition of these blocks (LU of a kernel matrix of order 33 and
+// condition 1e10: 372 eps against 1), and 0 * NaN carries a breakdown into columns in front of it.
 // The panel solves and the look-ahead head update, which consume those inverses,
 // live in head_kernel.hpp.
 #pragma once
@@ -112,17 +114,30 @@ __device__ inline float row_bcast(float x) {
         : "+&v"(a0), "+&v"(a1), "+&v"(a2), "+&v"(a3)                                                          \
         : "v"(src), "v"(m), "n"(K), "n"(K + 1), "n"(K + 2), "n"(K + 3));                                      \
   }                                                                                                           \
-  /* four of everything: a_q -= s_q[lane K_q] * m_q */                                                        \
-  template <int K0, int K1, int K2, int K3>                                                                   \
-  __device__ inline void fnmac_bcast4_each(T& a0, T& a1, T& a2, T& a3, T s0, T s1, T s2, T s3, T m0, T m1,    \
-                                           T m2, T m3) {                                                      \
-    asm("s_nop 1\n\t" OP " %0, -%4, %8 row_newbcast:%12 row_mask:0xf bank_mask:0xf\n\t"                      \
-        OP " %1, -%5, %9 row_newbcast:%13 row_mask:0xf bank_mask:0xf\n\t"                                     \
-        OP " %2, -%6, %10 row_newbcast:%14 row_mask:0xf bank_mask:0xf\n\t"                                    \
-        OP " %3, -%7, %11 row_newbcast:%15 row_mask:0xf bank_mask:0xf"                                        \
+  /* accumulators and sources, one lane: a_q -= s_q[lane K] * m */                                            \
+  template <int K>                                                                                            \
+  __device__ inline void fnmac_each2(T& a0, T& a1, T s0, T s1, T m) {                                         \
+    asm("s_nop 1\n\t" OP " %0, -%2, %4 row_newbcast:%5 row_mask:0xf bank_mask:0xf\n\t"                        \
+        OP " %1, -%3, %4 row_newbcast:%5 row_mask:0xf bank_mask:0xf"                                          \
+        : "+&v"(a0), "+&v"(a1)                                                                                \
+        : "v"(s0), "v"(s1), "v"(m), "n"(K));                                                                  \
+  }                                                                                                           \
+  template <int K>                                                                                            \
+  __device__ inline void fnmac_each3(T& a0, T& a1, T& a2, T s0, T s1, T s2, T m) {                            \
+    asm("s_nop 1\n\t" OP " %0, -%3, %6 row_newbcast:%7 row_mask:0xf bank_mask:0xf\n\t"                        \
+        OP " %1, -%4, %6 row_newbcast:%7 row_mask:0xf bank_mask:0xf\n\t"                                      \
+        OP " %2, -%5, %6 row_newbcast:%7 row_mask:0xf bank_mask:0xf"                                          \
+        : "+&v"(a0), "+&v"(a1), "+&v"(a2)                                                                     \
+        : "v"(s0), "v"(s1), "v"(s2), "v"(m), "n"(K));                                                         \
+  }                                                                                                           \
+  template <int K>                                                                                            \
+  __device__ inline void fnmac_each4(T& a0, T& a1, T& a2, T& a3, T s0, T s1, T s2, T s3, T m) {               \
+    asm("s_nop 1\n\t" OP " %0, -%4, %8 row_newbcast:%9 row_mask:0xf bank_mask:0xf\n\t"                        \
+        OP " %1, -%5, %8 row_newbcast:%9 row_mask:0xf bank_mask:0xf\n\t"                                      \
+        OP " %2, -%6, %8 row_newbcast:%9 row_mask:0xf bank_mask:0xf\n\t"                                      \
+        OP " %3, -%7, %8 row_newbcast:%9 row_mask:0xf bank_mask:0xf"                                          \
         : "+&v"(a0), "+&v"(a1), "+&v"(a2), "+&v"(a3)                                                          \
-        : "v"(s0), "v"(s1), "v"(s2), "v"(s3), "v"(m0), "v"(m1), "v"(m2), "v"(m3), "n"(K0), "n"(K1), "n"(K2),  \
-          "n"(K3));                                                                                           \
+        : "v"(s0), "v"(s1), "v"(s2), "v"(s3), "v"(m), "n"(K));                                                \
   }
 DLA_FNMAC_BCAST(double, "v_fmac_f64_dpp")
 DLA_FNMAC_BCAST(float, "v_fmac_f32_dpp")
@@ -157,6 +172,22 @@ __device__ inline void fnmac_run_lanes(T (&a)[16], T src, T m) {
     fnmac_lanes2<J0>(a[J0], a[J0 + 1], src, m);
   } else if constexpr (N == 1) {
     fnmac_bcast<J0>(a[J0], src, m);
+  }
+}
+
+// a[j] -= src[j][lane K] * m
+template <int K, int J0, int J1, typename T>
+__device__ inline void fnmac_run_each(T (&a)[16], const T (&src)[16], T m) {
+  constexpr int N = J1 - J0;
+  if constexpr (N >= 4) {
+    fnmac_each4<K>(a[J0], a[J0 + 1], a[J0 + 2], a[J0 + 3], src[J0], src[J0 + 1], src[J0 + 2], src[J0 + 3], m);
+    fnmac_run_each<K, J0 + 4, J1>(a, src, m);
+  } else if constexpr (N == 3) {
+    fnmac_each3<K>(a[J0], a[J0 + 1], a[J0 + 2], src[J0], src[J0 + 1], src[J0 + 2], m);
+  } else if constexpr (N == 2) {
+    fnmac_each2<K>(a[J0], a[J0 + 1], src[J0], src[J0 + 1], m);
+  } else if constexpr (N == 1) {
+    fnmac_bcast<K>(a[J0], src[J0], m);
   }
 }
 
@@ -292,59 +323,6 @@ __device__ inline void chol16(T (&a)[16], T (&rdiag)[16], T (&pivot)[16], int i)
       rs = y;
     }
   });
-}
-
-// ---- solves with a 16 x 16 lower-triangular block T as four dependent MFMAs per 16 columns ----
-//
-// T X = P by substitution in blocks of four rows: X_r = inv(T_rr) P_r, P_s -= T_sr X_r for s > r.  With
-// W_r = [inv(T_rr); -T_sr inv(T_rr)] in rows 4 r .. 15 and zeros above, step r is the one product
-// P <- W_r P_r + (P with block r taken out), 16 x 16 x 4: P_r is the right-hand operand as the accumulators hold it.
-// In the accumulators, register v of lane l holds row 4 v + l / 16 of P.  That is the fp64 layout; in fp32 the
-// instruction's row 4 (l / 16) + v stands for it, so the left operand's rows are dealt to the lanes that way.
-template <typename T>
-__host__ __device__ constexpr int tri_row(int lane15) {  // an involution: also the lane that holds a row
-  return sizeof(T) == 8 ? lane15 : 4 * (lane15 & 3) + (lane15 >> 2);
-}
-
-// The left operands W_0 .. W_3.  f: row tri_row(l15) of T (only its lower part counts), rd: reciprocals of T's diagonal
-// (not read if UNIT).  A row solves w T_rr = (its four entries of T, or of the identity inside the block).
-template <typename T, bool UNIT>
-__device__ inline void tri_slabs(const T (&f)[16], const T (&rd)[16], T (&slab)[4], int l15, int l4) {
-  const int i = tri_row<T>(l15);
-  T w[4][4];  // [column of the block][block]
-#pragma unroll
-  for (int r = 0; r < 4; ++r)
-#pragma unroll
-    for (int q = 0; q < 4; ++q) w[q][r] = i >= 4 * r + 4 ? f[4 * r + q] : (i == 4 * r + q ? T(1) : T(0));
-  static_for<0, 4>([&](auto qc) {
-    constexpr int q = 3 - decltype(qc)::value;
-    if constexpr (!UNIT) {
-#pragma unroll
-      for (int r = 0; r < 4; ++r) w[q][r] *= rd[4 * r + q];
-    }
-    static_for<0, q>([&](auto pc) {
-      constexpr int p = decltype(pc)::value;
-      fnmac_bcast4_each<tri_row<T>(q), tri_row<T>(4 + q), tri_row<T>(8 + q), tri_row<T>(12 + q)>(
-          w[p][0], w[p][1], w[p][2], w[p][3], f[p], f[4 + p], f[8 + p], f[12 + p], w[q][0], w[q][1], w[q][2], w[q][3]);
-    });
-  });
-#pragma unroll
-  for (int r = 0; r < 4; ++r) {
-    // column l4 (values, not elements of w, in the conditionals: those would index w in memory)
-    const T w0 = w[0][r], w1 = w[1][r], w2 = w[2][r], w3 = w[3][r];
-    T x = w0;
-    if (l4 == 1) x = w1;
-    if (l4 == 2) x = w2;
-    if (l4 == 3) x = w3;
-    slab[r] = i >= 4 * r + 4 ? -x : x;
-  }
-}
-
-template <typename T>
-__device__ inline void tri_step(const T (&slab)[4], typename Mfma<T>::acc_t& p, int r) {
-  const T x = p[r];
-  p[r] = T(0);
-  p = Mfma<T>::mma(slab[r], x, p);
 }
 
 // --------------------------------------------------------------------------------------
@@ -562,62 +540,36 @@ __global__ void __launch_bounds__(kDiagThreads) diag_kernel(const DiagArgs<T> g)
   }
   __syncthreads();
 
-  // One 16-wide panel of the sub-block at offset o, in tiles of 16 columns (row panel: L X = P) or rows (column panel:
-  // X U = P or X L^T = P, solved transposed); tile nrem is the identity, which becomes the sub-block's inverse for the
-  // panel solves behind this block.  This wave's tiles are first, first + STEP, ...: at most MAXT of them.
-  auto panel_tiles = [&](auto upper_c, auto step_c, int o, int nrem, int first) {
-    constexpr bool UPPER = decltype(upper_c)::value;  // with U (transposed)
-    constexpr bool ROWP = KIND == KIND_LU && !UPPER;
-    constexpr int STEP = decltype(step_c)::value, MAXT = kNbMax / kIb / STEP;
-    using acc_t = typename Mfma<T>::acc_t;
-    if (first > nrem) return;
-    T f[16], rd[16], slab[4];
-    const int i = tri_row<T>(l15);
+  // One 16-wide panel of the sub-block at offset o by substitution: lane t has one column (row panel: L X = P) or one row
+  // (column panel: X U = P, Cholesky X L^T = P), and the 16 lanes behind the panel the identity, which becomes the
+  // sub-block's inverse for the panel solves behind this block.  The sub-block is uniform over the panel, so each 16-lane
+  // row keeps it in registers (lane i = its row i) and the steps take its entries as DPP broadcasts.
+  auto panel = [&](auto upper_c, int o, int rem, int t) {
+    constexpr bool UPPER = decltype(upper_c)::value, ROWP = KIND == KIND_LU && !UPPER;
+    const int e = t < rem ? o + kIb + t : kNbMax;  // lanes behind the panel read and write dump space
+    T f[16], rd[16], x[16];
 #pragma unroll
     for (int j = 0; j < 16; ++j) {
-      f[j] = UPPER ? S[(o + j) * kSld + o + i] : S[(o + i) * kSld + o + j];
+      f[j] = S[(o + l15) * kSld + o + j];
       if (!ROWP) rd[j] = sRd[o + j];
     }
-    // entry (row 4 v + l4, column l15) of tile t's right-hand side
-    auto at = [&](int t, int v) -> T* {
-      const int e = o + kIb + t * kIb + l15, k = o + 4 * v + l4;
-      return ROWP ? S + k * kSld + e : S + e * kSld + k;
-    };
-    // (reads past the panel stay on its last tile, or on the sub-block itself: no branch, so no wait, between them)
-    acc_t x[MAXT];
 #pragma unroll
-    for (int q = 0; q < MAXT; ++q) {
-      const int t = first + q * STEP;
+    for (int j = 0; j < 16; ++j) x[j] = ROWP ? S[(o + j) * kSld + e] : S[e * kSld + o + j];
+    const int unit = t - rem;
 #pragma unroll
-      for (int v = 0; v < 4; ++v) x[q][v] = *at(t < nrem ? t : nrem - 1, v);
-    }
-    tri_slabs<T, ROWP>(f, rd, slab, l15, l4);
-#pragma unroll
-    for (int q = 0; q < MAXT; ++q)
-#pragma unroll
-      for (int v = 0; v < 4; ++v)
-        if (first + q * STEP == nrem) x[q][v] = 4 * v + l4 == l15 ? T(1) : T(0);
-    auto solve = [&](auto nt) {
-#pragma unroll
-      for (int r = 0; r < 4; ++r)
-#pragma unroll
-        for (int q = 0; q < decltype(nt)::value; ++q) tri_step<T>(slab, x[q], r);
-    };
-    const int nt = (nrem - first) / STEP + 1;
-    static_for<1, MAXT + 1>([&](auto c) {
-      if (nt == decltype(c)::value) solve(c);
+    for (int j = 0; j < 16; ++j) x[j] = unit < 0 ? x[j] : (unit == j ? T(1) : T(0));
+    static_for<0, 16>([&](auto kc) {
+      constexpr int k = decltype(kc)::value;
+      if constexpr (!ROWP) x[k] *= rd[k];
+      if constexpr (UPPER) fnmac_run_each<k, k + 1, 16>(x, f, x[k]);  // U[k][j]: entry j of lane k
+      else fnmac_run_lanes<k + 1, 16>(x, f[k], x[k]);                 // L[j][k]: entry k of lane j
     });
 #pragma unroll
-    for (int q = 0; q < MAXT; ++q) {
-      const int t = first + q * STEP;
-      if (t < nrem) {
+    for (int j = 0; j < 16; ++j) (ROWP ? S[(o + j) * kSld + e] : S[e * kSld + o + j]) = x[j];
+    if (unit >= 0 && unit < 16) {
+      T* const out = (UPPER ? g.inv_up : g.inv_lo) + (o / kIb) * 256;
 #pragma unroll
-        for (int v = 0; v < 4; ++v) *at(t, v) = x[q][v];
-      } else if (t == nrem) {
-        T* const out = (UPPER ? g.inv_up : g.inv_lo) + (o / kIb) * 256;
-#pragma unroll
-        for (int v = 0; v < 4; ++v) out[UPPER ? l15 * 16 + 4 * v + l4 : (4 * v + l4) * 16 + l15] = x[q][v];
-      }
+      for (int j = 0; j < 16; ++j) out[UPPER ? unit * 16 + j : j * 16 + unit] = x[j];
     }
   };
 
@@ -625,15 +577,13 @@ __global__ void __launch_bounds__(kDiagThreads) diag_kernel(const DiagArgs<T> g)
     const int o = r * kIb;
     const int rem = bp - o - kIb;  // rows/columns to the right of / below this sub-block
     const int nrem = rem / kIb;
-    // ---- inner panels on four waves, one per SIMD: the matrix pipes are as busy as with eight, and the factor is read
-    // from LDS and brought to its left operands half as often.  The others write out what is finished.
+    // ---- inner panels: waves 0 and 1 the row panel (Cholesky: the column panel), 2 and 3 the column panel, as far as
+    // there is one; the others write out what is finished.
     if (wave >= 4) {
       if (r > 0) store_strip(o - kIb);
-    } else if constexpr (KIND == KIND_LU) {
-      if (wave < 2) panel_tiles(std::false_type{}, std::integral_constant<int, 2>{}, o, nrem, wave);
-      else panel_tiles(std::true_type{}, std::integral_constant<int, 2>{}, o, nrem, wave - 2);
-    } else {
-      panel_tiles(std::false_type{}, std::integral_constant<int, 4>{}, o, nrem, wave);
+    } else if ((wave & 1) * 64 < rem + kIb) {
+      if (wave < 2) panel(std::false_type{}, o, rem, tid);
+      else if constexpr (KIND == KIND_LU) panel(std::true_type{}, o, rem, tid - 128);
     }
     if (nrem == 0) break;
     lds_barrier();

@@ -58,3 +58,68 @@ def test_first_bad_pivot(kind, value, dtype):
         A[min(p + 20, n - 1), min(p + 20, n - 1)] = value  # a later one is not the one reported
         announce(f"{kind} {dtype} pivot {p} = {value}")
         assert _factor(kind, A, dtype, 0)[1] == p + 1
+
+
+@pytest.mark.parametrize("dtype,gate", [("float64", 1e-9), ("float32", 1e-4)])
+def test_columns_before_a_bad_cholesky_pivot_are_the_factor(dtype, gate):
+    """A pivot that is not positive makes its own column and the ones behind it NaN; the columns before it are those of
+    the oracle's factor, in every row of the block."""
+    import oracle
+    from paper_2309_07235_amd import inputs
+    for n in (16, 60, 100, 128):
+        want, _ = oracle.cholesky(inputs.spd_matrix(n, 5).astype(dtype).astype(np.float64))
+        for p in (1, 2, 3, 5, 14, 15, 16, 18, 30, 47, 50, 77, 98, 113, 126, 127):
+            if p >= n:
+                continue
+            A = inputs.spd_matrix(n, 5).astype(dtype).astype(np.float64)
+            A[p, p] = -3.0
+            announce(f"cholesky {dtype} n {n} pivot {p} negative")
+            got, info, _ = _factor("chol", A, dtype, 0)
+            assert info == p + 1
+            assert np.isfinite(got[:, :p]).all(), (n, p)
+            assert np.abs(got[:, :p] - np.tril(want)[:, :p]).max() <= gate * np.abs(want).max(), (n, p)
+
+
+@pytest.mark.parametrize("dtype", ["float64", "float32"])
+@pytest.mark.parametrize("value", [float("nan"), float("inf")])
+def test_an_entry_that_is_not_finite_stays_in_its_row(value, dtype):
+    """Cholesky of one block with one such entry at (r, c): it reaches row r from column c on and, through the updates,
+    rows and columns from r on.  All other entries are the factor's."""
+    import oracle
+    from paper_2309_07235_amd import inputs
+    n = 100
+    want, _ = oracle.cholesky(inputs.spd_matrix(n, 5).astype(dtype).astype(np.float64))
+    for r, c in ((20, 5), (40, 22), (90, 23), (70, 35), (70, 0), (99, 80)):
+        A = inputs.spd_matrix(n, 5).astype(dtype).astype(np.float64)
+        A[r, c] = value
+        announce(f"cholesky {dtype} {value} at {r}, {c}")
+        got, _, _ = _factor("chol", A, dtype, 0)
+        clean = np.tril(np.ones((n, n), dtype=bool))
+        clean[r, c:] = False
+        clean[:, r:] = False
+        bad = clean & ~(np.abs(got - want) <= 1e-4 * np.abs(want).max())
+        assert not bad.any(), ((r, c), np.argwhere(bad)[:4])
+
+
+@pytest.mark.parametrize("dtype,jitter", [("float64", 1e-12), ("float64", 1e-8), ("float32", 1e-3), ("float32", 1e-4)])
+@pytest.mark.parametrize("kind", ["lu", "chol"])
+def test_backward_error_does_not_grow_with_the_condition(kind, dtype, jitter):
+    """A smooth kernel matrix plus jitter * I (condition about n / jitter), one block.  Substitution computes factors of a
+    matrix that differs from A by at most (n + 1) eps |L||U| (Higham, Accuracy and Stability, theorems 9.3 and 10.3), and
+    for a positive definite A |L||U| is at most sqrt(a_ii a_jj) in each entry up to that factor; the reciprocals of the
+    pivots add two roundings.  Products with explicit inverses of the diagonal blocks lose the condition of these."""
+    eps = float(np.finfo(dtype).eps)
+    for n in (33, 100, 128):
+        x = np.sort(np.random.default_rng(n).uniform(0.0, 1.0, n))
+        for ell in (0.05, 0.5):
+            A = np.exp(-(x[:, None] - x) ** 2 / (2.0 * ell * ell)) + jitter * np.eye(n)
+            A = A.astype(dtype).astype(np.float64)
+            announce(f"{kind} {dtype} kernel matrix n {n} ell {ell} jitter {jitter}")
+            F, info, _ = _factor(kind, A, dtype, 0)
+            assert info == 0
+            W = F.astype(np.longdouble)
+            L = np.tril(W) if kind == "chol" else np.tril(W, -1) + np.eye(n)
+            U = L.T if kind == "chol" else np.triu(W)
+            err = float((np.abs(L @ U - A) / np.sqrt(np.outer(np.diag(A), np.diag(A)))).max())
+            print(f"{kind} {dtype} n {n} ell {ell}: {err / eps:.2f} eps")
+            assert err <= (n + 3) * eps, (n, ell, err / eps)

@@ -256,6 +256,14 @@ int dla_gemm(int op, const void* d_a, int64_t lda, const void* d_b, int64_t ldb,
              void* hip_stream);
 
 /*
+ * What dla_gemm does with such a product when no schedule is named (lda, ldb, m, n, k > 0): 1 and the macro-tile in
+ * *tile_m, *tile_n if it runs on the library's own kernel, 0 if on the menu's default schedule for the size (the tiles
+ * are then left alone), negative for an argument out of range.  A query on the host, no GPU needed.
+ */
+int dla_gemm_choice(int op, int64_t lda, int64_t ldb, int64_t m, int64_t n, int64_t k, dla_dtype dt, int* tile_m,
+                    int* tile_n);
+
+/*
  * The default trailing update of the factorisations on its own (a step of the blocked algorithm that
  * computes the decompositions of the paper's Section "Linear Algebra Benchmarks"; the paper itself does
  * not describe a blocking), exported so that it can be timed and tested in isolation:

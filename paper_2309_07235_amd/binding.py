@@ -97,6 +97,8 @@ def _load() -> ctypes.CDLL:
     lib.dla_handover_selftest.restype = ci
     lib.dla_rank_update.argtypes = [ci, vp, vp, vp, i64, i64, i64, ci, vp]
     lib.dla_rank_update.restype = ci
+    lib.dla_gemm_choice.argtypes = [ci, i64, i64, i64, i64, i64, ci, ctypes.POINTER(ci), ctypes.POINTER(ci)]
+    lib.dla_gemm_choice.restype = ci
     lib.dla_gemm_params_supported.argtypes = [ci, ctypes.POINTER(GemmParams)]
     lib.dla_gemm_params_supported.restype = ci
     lib.dla_enumerate_tiles.argtypes = [ci, ctypes.POINTER(GemmParams), ci]
@@ -169,6 +171,17 @@ def _check(rc: int, where: str):
 
 def gemm_params_supported(dtype_code: int, p: GemmParams) -> bool:
     return bool(lib.dla_gemm_params_supported(dtype_code, ctypes.byref(p)))
+
+
+def gemm_choice(op: int, m: int, n: int, k: int, dtype_code: int = DLA_F64, lda: int | None = None, ldb: int | None = None):
+    """(tile_m, tile_n) of the library's own kernel for a dla_gemm without a schedule, or None where the menu's default runs."""
+    tm, tn = ctypes.c_int(0), ctypes.c_int(0)
+    lda = lda if lda is not None else (m if op == 4 else k)
+    ldb = ldb if ldb is not None else (k if op in (2, 3) else n)
+    rc = lib.dla_gemm_choice(op, lda, ldb, m, n, k, dtype_code, ctypes.byref(tm), ctypes.byref(tn))
+    if rc < 0:
+        _check(rc, "dla_gemm_choice")
+    return (tm.value, tn.value) if rc == 1 else None
 
 
 def enumerate_tiles(dtype_code: int = DLA_F64):

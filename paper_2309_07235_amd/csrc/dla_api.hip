@@ -154,6 +154,16 @@ template int run_gemm<double>(const GemmSchedule&, int, const double*, int64_t, 
 template int run_gemm<float>(const GemmSchedule&, int, const float*, int64_t, const float*, int64_t, float*, int64_t,
                              int64_t, int64_t, int64_t, hipStream_t);
 
+template <typename T>
+static int gemm_choice(int op, int64_t lda, int64_t ldb, int64_t m, int64_t n, int64_t k, int* tile_m, int* tile_n) {
+  GemmGroup<T> g;
+  g.nprob = 1;
+  g.prob[0] = make_problem<T>(GemmSchedule{64, 64, 16, 4, 32, 32}, op, nullptr, lda, nullptr, ldb, nullptr, n, m, n, k, 0);
+  if (!gemm_wide_takes<T>(op, g)) return 0;
+  gemm_wide_tile<T>(g, tile_m, tile_n);
+  return 1;
+}
+
 // C = 0 for the degenerate k == 0 product.
 template <typename T>
 __global__ void fill_zero_kernel(T* c, int64_t ld, int rows, int cols) {
@@ -404,6 +414,19 @@ int dla_gemm(int op, const void* d_a, int64_t lda, const void* d_b, int64_t ldb,
   if (dt == DLA_F64)
     return run_gemm<double>(s, op, (const double*)d_a, lda, (const double*)d_b, ldb, (double*)d_c, ldc, m, n, k, st);
   return run_gemm<float>(s, op, (const float*)d_a, lda, (const float*)d_b, ldb, (float*)d_c, ldc, m, n, k, st);
+}
+
+int dla_gemm_choice(int op, int64_t lda, int64_t ldb, int64_t m, int64_t n, int64_t k, dla_dtype dt, int* tile_m, int* tile_n) {
+  if (op < OP_ASSIGN || op > OP_SUB_TN) return -1;
+  if (lda < 1) return -2;
+  if (ldb < 1) return -3;
+  if (m < 1 || m > kMaxDim) return -4;
+  if (n < 1 || n > kMaxDim) return -5;
+  if (k < 1 || k > kMaxDim) return -6;
+  if (dt != DLA_F64 && dt != DLA_F32) return -7;
+  if (!tile_m) return -8;
+  if (!tile_n) return -9;
+  return dt == DLA_F64 ? gemm_choice<double>(op, lda, ldb, m, n, k, tile_m, tile_n) : gemm_choice<float>(op, lda, ldb, m, n, k, tile_m, tile_n);
 }
 
 int dla_rank_update(int lower, const void* d_l, const void* d_r, void* d_c, int64_t ld, int64_t m, int64_t k,

@@ -74,9 +74,12 @@ template <typename T>
 int launch_gemm(const GemmSchedule& s, int op, const GemmGroup<T>& g, hipStream_t st);
 
 // gemm_wide_kernel (gemm_wide.hip): C = A*B, C -= A*B and C -= A^T*B with a tile of the library's choice.  takes: the
-// products are within its limits and deep enough.  launch fills in the tile fields of the group.
+// products are within its limits, and it is the faster kernel for them.  tile: which one a launch would pick (its place
+// in the menu and its size).  launch fills in the tile fields of the group.
 template <typename T>
 bool gemm_wide_takes(int op, const GemmGroup<T>& g);
+template <typename T>
+int gemm_wide_tile(const GemmGroup<T>& g, int* tile_m, int* tile_n);
 template <typename T>
 int launch_gemm_wide(int op, GemmGroup<T>& g, hipStream_t st);
 

@@ -217,3 +217,31 @@ def test_argument_errors_are_reported_without_gpu_work(B):
     assert L.dla_mfma_peak_scratch_bytes() == 1024 * 256 * 8
     ms = ctypes.c_double()
     assert L.dla_profile_read(9, ctypes.byref(ms), None, None) == -1
+
+
+def test_the_shapes_of_the_gemm_tests_reach_every_tile(B):
+    from tests.test_gpu_gemm_wide import SHAPES
+    tiles = {(32, 32), (64, 32), (64, 64), (128, 64)}
+    for dt, slab in ((B.DLA_F64, 16), (B.DLA_F32, 32)):
+        for op in (0, 1, 4):
+            for pad in (0, 1, 2, 5):
+                deep = {B.gemm_choice(op, m, n, k, dt, (m if op == 4 else k) + 2 * pad, n + 2 * pad) for m, n, k in SHAPES
+                        if k > 4 * slab and k % slab and m % 16 and n % 16}
+                assert deep == tiles, (dt, op, deep)
+
+
+def test_gemm_choice(B):
+    assert B.gemm_choice(0, 4000, 4000, 2000) is not None
+    assert B.gemm_choice(2, 4000, 4000, 2000) is None and B.gemm_choice(3, 4000, 4000, 2000) is None  # A*B^T: the menu's
+    for dt in (B.DLA_F64, B.DLA_F32):  # offsets inside a tile are 32-bit
+        for ld in ("lda", "ldb"):
+            assert B.gemm_choice(1, 100, 100, 100, dt, **{ld: 1 << 24}) is not None
+            assert B.gemm_choice(1, 100, 100, 100, dt, **{ld: (1 << 24) + 1}) is None
+    assert B.gemm_choice(1, 100, 100, 32, B.DLA_F32) is None and B.gemm_choice(1, 100, 100, 33, B.DLA_F32) is not None
+    assert B.gemm_choice(1, 100, 100, 1, B.DLA_F64) is not None
+    i = ctypes.c_int()
+    r = ctypes.byref(i)
+    for pos, args in ((1, (5, 1, 1, 1, 1, 1, 0)), (2, (0, 0, 1, 1, 1, 1, 0)), (3, (0, 1, 0, 1, 1, 1, 0)), (4, (0, 1, 1, 0, 1, 1, 0)),
+                      (5, (0, 1, 1, 1, 0, 1, 0)), (6, (0, 1, 1, 1, 1, 0, 0)), (7, (0, 1, 1, 1, 1, 1, 2))):
+        assert B.lib.dla_gemm_choice(*args, r, r) == -pos
+    assert B.lib.dla_gemm_choice(0, 1, 1, 1, 1, 1, 0, None, r) == -8 and B.lib.dla_gemm_choice(0, 1, 1, 1, 1, 1, 0, r, None) == -9

@@ -10,9 +10,13 @@ from tests.gpu_util import announce, to_host
 
 pytestmark = pytest.mark.gpu
 
-# (m, n, k): around one tile of 32, 64, 128 rows; k around a slab of 16 (fp64) and 32 (fp32) and around two and three
+# (m, n, k): edges of the smallest tile, widths below and around one 16-byte run, k around one, two and three slabs of 16
+# (fp64) and 32 (fp32); then a ragged shape for each of the four tiles, with four whole slabs in both types and a rest
+# (tests/test_abi.py checks that they reach all four)
 SHAPES = [(1, 1, 1), (15, 17, 2), (32, 32, 16), (33, 31, 17), (64, 32, 33), (65, 66, 32), (63, 129, 47), (130, 259, 70),
-          (2100, 70, 64), (1100, 1030, 49), (2050, 1923, 31)]
+          (2100, 70, 64), (1100, 1030, 49), (2050, 1923, 31),
+          (130, 3, 150), (2, 140, 133), (67, 1, 131),
+          (130, 259, 145), (529, 661, 147), (1401, 1403, 147), (2047, 1023, 401)]
 
 
 @pytest.mark.parametrize("pad", [0, 1, 2, 5])

@@ -85,24 +85,29 @@ size_t solve_workspace_bytes_impl(int64_t n, int64_t nrhs, dla_dtype dt) {
   return ((size_t)block_elems(n) + 2 * (size_t)n * (size_t)y_ld(nrhs)) * (dt == DLA_F64 ? 8 : 4);
 }
 
-// products of one op and schedule, kMaxGroup to a launch
+// The products on the tiled GEMM (the pre-pass; the chain with many right-hand sides) take gemm_wide_kernel, whose launch
+// picks the tile: N = 8192 with 1024 right-hand sides, fp32, 2.79 -> 2.18 ms against 32 x 32 tiles of gemm_kernel.  This
+// schedule is for what that kernel does not take (leading dimensions beyond its offsets, fp32 systems of up to 32 rows).
+static const GemmSchedule kSolveTiles = {32, 32, 16, 4, 16, 16};
+template <typename T>
+static int launch_products(int op, GemmGroup<T>& g, int np, int tiles, double flops, hipStream_t st) {
+  for (int q = np; q < kMaxGroup; ++q) g.prob[q] = g.prob[0];
+  g.nprob = np;
+  g.total_tiles = tiles;
+  ProfileScope scope(PHASE_GEMM, flops, st);
+  return gemm_wide_takes<T>(op, g) ? launch_gemm_wide<T>(op, g, st) : launch_gemm<T>(kSolveTiles, op, g, st);
+}
+
+// products of one op, kMaxGroup to a launch
 template <typename T>
 struct ProductList {
-  GemmSchedule sch;
   int op;
   GemmGroup<T> g;
   int np = 0, tiles = 0;
   double flops = 0.0;
   int flush(hipStream_t st) {
     if (np == 0) return DLA_SUCCESS;
-    for (int q = np; q < kMaxGroup; ++q) g.prob[q] = g.prob[0];
-    g.nprob = np;
-    g.total_tiles = tiles;
-    int rc;
-    {
-      ProfileScope scope(PHASE_GEMM, flops, st);
-      rc = gemm_wide_takes<T>(op, g) ? launch_gemm_wide<T>(op, g, st) : launch_gemm<T>(sch, op, g, st);
-    }
+    const int rc = launch_products<T>(op, g, np, tiles, flops, st);
     np = tiles = 0;
     flops = 0.0;
     return rc;
@@ -110,8 +115,8 @@ struct ProductList {
   int add(const T* a, int64_t lda, const T* b, int64_t ldb, T* c, int64_t ldc, int64_t M, int64_t N, int64_t K,
           hipStream_t st) {
     if (M <= 0 || N <= 0 || K <= 0) return DLA_SUCCESS;
-    g.prob[np] = make_problem<T>(sch, op, a, lda, b, ldb, c, ldc, M, N, K, tiles);
-    tiles += problem_tiles(sch, op, g.prob[np]);
+    g.prob[np] = make_problem<T>(kSolveTiles, op, a, lda, b, ldb, c, ldc, M, N, K, tiles);
+    tiles += problem_tiles(kSolveTiles, op, g.prob[np]);
     flops += 2.0 * (double)M * (double)N * (double)K;
     if (++np == kMaxGroup) return flush(st);
     return DLA_SUCCESS;
@@ -143,12 +148,6 @@ int solve_impl(const T* F, int64_t n, int64_t lda, T* B, int64_t nrhs, int64_t l
   auto rows_of = [&](int i) { return n - (int64_t)i * sb < sb ? n - (int64_t)i * sb : sb; };
   auto Nf = [&](int i) { return wf + (int64_t)i * sb * sb; };
   auto Nb = [&](int i) { return wb + (int64_t)i * sb * sb; };
-  // Products on the tiled GEMM (the pre-pass; the chain with many right-hand sides) take gemm_wide_kernel, whose launch
-  // picks the tile: N = 8192 with 1024 right-hand sides, fp32, 2.78 -> 2.46 ms against 32 x 32 tiles of gemm_kernel.
-  // These schedules are for leading dimensions beyond that kernel's offsets.
-  const GemmSchedule small = GemmSchedule{32, 32, 16, 4, 16, 16};
-  const GemmSchedule sch = small;
-  const GemmSchedule wide = GemmSchedule{64, 64, 16, 4, 32, 32};  // the 256 x 512 products of the pre-pass
   int rc;
   // ---- every target of a subtracting product that stands for a plain one starts at zero: the pre-pass's
   // targets lie in front of Y, the passes' own (Y and X) behind them
@@ -162,7 +161,7 @@ int solve_impl(const T* F, int64_t n, int64_t lda, T* B, int64_t nrhs, int64_t l
   // missing quarter of N = 0 - (the other N) * T = W * block * W
   auto pairing = [&](int pass, hipStream_t s) -> int {
     if (n <= nb) return DLA_SUCCESS;
-    ProductList<T> first{small, OP_SUB}, second{small, OP_SUB};
+    ProductList<T> first{OP_SUB}, second{OP_SUB};
     int r;
     for (int64_t p = 0; p < pairs; ++p) {
       const int64_t k0 = p * sb, b2 = n - k0 - nb < nb ? n - k0 - nb : nb;
@@ -189,7 +188,7 @@ int solve_impl(const T* F, int64_t n, int64_t lda, T* B, int64_t nrhs, int64_t l
   };
   // M_i = 0 - N_i * (the factor's blocks beside diagonal block i that the look-back covers)
   auto look_back = [&](int pass, hipStream_t s) -> int {
-    ProductList<T> list{wide, OP_SUB};
+    ProductList<T> list{OP_SUB};
     int r = DLA_SUCCESS;
     if (pass == 0) {
       for (int i = 1; i < nblk && r == DLA_SUCCESS; ++i) {  // block columns i-2 (if any) and i-1 of block row i
@@ -260,19 +259,14 @@ int solve_impl(const T* F, int64_t n, int64_t lda, T* B, int64_t nrhs, int64_t l
     for (int q = 0; q < count; ++q) {
       const Part& P = parts[q];
       if (P.M <= 0 || P.K <= 0) continue;
-      g.prob[np] = make_problem<T>(sch, op, P.a, P.la, P.b, P.lb, P.c, P.lc, P.M, nrhs, P.K, tiles);
+      g.prob[np] = make_problem<T>(kSolveTiles, op, P.a, P.la, P.b, P.lb, P.c, P.lc, P.M, nrhs, P.K, tiles);
       g.prob[np].C2 = P.c2;
       g.prob[np].ldc2 = P.lc2;
-      tiles += problem_tiles(sch, op, g.prob[np]);
+      tiles += problem_tiles(kSolveTiles, op, g.prob[np]);
       flops += 2.0 * (double)P.M * (double)nrhs * (double)P.K;
       ++np;
     }
-    if (np == 0) return DLA_SUCCESS;
-    for (int q = np; q < kMaxGroup; ++q) g.prob[q] = g.prob[0];
-    g.nprob = np;
-    g.total_tiles = tiles;
-    ProfileScope scope(PHASE_GEMM, flops, st);
-    return gemm_wide_takes<T>(op, g) ? launch_gemm_wide<T>(op, g, st) : launch_gemm<T>(sch, op, g, st);
+    return np == 0 ? (int)DLA_SUCCESS : launch_products<T>(op, g, np, tiles, flops, st);
   };
   // ---- forward.  Z_i and then Y_i live in rows i of Y; B is updated in place (part c).
   {

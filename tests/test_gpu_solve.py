@@ -119,6 +119,30 @@ def test_solve_with_padded_leading_dimensions(B, oracle, kind):
     assert np.array_equal(to_host(fbuf)[:, :n], F) and np.all(to_host(fbuf)[:, n:] == 7.25)
 
 
+@pytest.mark.parametrize("kind", ["lu", "chol"])
+@pytest.mark.parametrize("n,nrhs,dtype_name,lda", [(20, 140, "float32", None), (32, 300, "float32", None), (33, 140, "float32", None),
+                                                   (1025, 131, "float64", None), (513, 259, "float32", None),
+                                                   (140, 130, "float32", (1 << 24) + 4)])
+def test_products_at_the_limits_of_the_wide_gemm(B, oracle, kind, n, nrhs, dtype_name, lda):
+    """Many right-hand sides where the products leave the library's own kernel or touch its narrowest forms: fp32 systems
+    no deeper than a slab, last blocks of one row, a factor whose rows lie further apart than 32-bit offsets reach."""
+    import torch
+    announce(f"solve {kind} n={n} nrhs={nrhs} {dtype_name} lda={lda}")
+    dtype = getattr(torch, dtype_name)
+    _, F = _factor(oracle, kind, n, 43)
+    rhs = inputs.uniform_matrix(44, 3, n, nrhs)
+    F, rhs = (x.astype(dtype_name).astype(np.float64) for x in (F, rhs))
+    want = (oracle.lu_solve if kind == "lu" else oracle.cholesky_solve)(F, rhs)
+    if lda is None:
+        f = to_device(F, dtype)
+    else:
+        f = torch.empty((n - 1) * lda + n, dtype=dtype, device="cuda").as_strided((n, n), (lda, 1))
+        f.copy_(to_device(F, dtype))
+    b = to_device(rhs, dtype)
+    (B.lu_solve if kind == "lu" else B.cholesky_solve)(f, b)
+    assert max_rel_err(to_host(b).astype(np.float64), want) <= (TOL64 if dtype_name == "float64" else TOL32)
+
+
 def test_cholesky_solve_reads_the_lower_triangle_only(B, oracle):
     n, nrhs = 150, 4
     _, L = _factor(oracle, "chol", n, 27)

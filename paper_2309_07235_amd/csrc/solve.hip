@@ -226,10 +226,11 @@ int solve_impl(const T* F, int64_t n, int64_t lda, T* B, int64_t nrhs, int64_t l
     int many;  // 1 for product (c): many blocks, the factor as its left operand
   };
   // While a launch of the chain is a few hundred to a few thousand 16 x 16 blocks, what matters is how soon its
-  // longest product ends: the skinny kernel (one block per workgroup, k split over its waves; N = 4000, 64
-  // right-hand sides 0.37 ms against 0.48 ms on 32 x 32 tiles with 128-deep slabs, 0.61 ms with 16-deep ones;
-  // 256: 0.61 against 0.68 ms).  With more work per launch the tiled GEMM's reuse wins (N = 4000, 512: 0.98
-  // against 0.87 ms; N = 8192, 256: 1.99 against 1.89 ms).
+  // longest product ends: the skinny kernel (one block per workgroup, k split over its waves).  With more work per launch
+  // the tiled GEMM's reuse wins.  The two passes of a prepared LU solve, fp64, skinny against tiled: N = 1000 with 256
+  // right-hand sides 66 against 87 us; N = 4000 with 64 251 against 356, 128 331 against 417, 256 490 against 505, 320
+  // 0.93 of the skinny time; N = 8192 with 128 1085 against 1194, 160 0.98, 256 0.85.  fp32 crosses a little earlier
+  // (N = 4000, 256: 0.91; N = 8192, 128: 1.00), Cholesky where LU does.
   const bool skinny = nrhs <= 128 || (nrhs <= 256 && n * nrhs <= 1200000);
   static_assert(2 * kTriPair <= kSkinnyMaxK, "the look-back product's depth");
   auto launch_parts = [&](int op, const Part* parts, int count) -> int {

@@ -132,7 +132,7 @@ def traffic(fetch_db: str, write_db: str, n: int) -> None:
     tot_n = 0
     tot_f = tot_w = 0.0
     for nm in sorted(f):
-        if not ("update_kernel" in nm or "update_span_kernel" in nm or "gemm_kernel<double, 64, 64" in nm):
+        if not any(s in nm for s in ("update_kernel", "update_span_kernel", "gemm_kernel<double, 64, 64", "gemm_wide_kernel")):
             continue
         fv, wv = f[nm], w.get(nm, [0.0])
         print(f"{nm[:50]:50s} {len(fv):10d} {sum(fv) / len(fv):11.1f} {max(fv):11.1f} {sum(wv) / len(wv):11.1f} {max(wv):11.1f}")

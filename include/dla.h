@@ -207,7 +207,8 @@ size_t factor_workspace_bytes(int64_t n, dla_dtype dt, const dla_factor_params* 
  *   A ni x nk, B nk x nj, C nj x nm, D nm x nl, G ni x nl; A..D are read only,
  *   G is overwritten.  E (ni x nj) and F (nj x nl) live in the workspace
  *   (mm3_workspace_bytes), rounded to the element type between products as in
- *   the listing.  E and F are computed by one grouped launch, G by a second.
+ *   the listing.  E and F are computed by one grouped launch (two where
+ *   different schedules are named for them), G by another.
  * Any dimension equal to 0 yields an empty or all-zero G and succeeds.
  */
 int mm3(const void* d_a, int64_t lda, const void* d_b, int64_t ldb, const void* d_c, int64_t ldc,
@@ -222,7 +223,7 @@ size_t mm3_workspace_bytes(int64_t ni, int64_t nj, int64_t nl, dla_dtype dt);
  * capture, tight serving loops, harnesses that forbid hipMalloc.  Same arguments and result as mm3 without
  * the workspace: E and F live in a fixed scratch array that is part of the library's device image
  * (DLA_MM3_NOALLOC_MAX_BYTES per GPU, held until the process ends).  The call allocates and frees nothing
- * and enqueues the same two launches as mm3 on hip_stream.  The first call on a device looks the array's
+ * and enqueues the same launches as mm3 on hip_stream.  The first call on a device looks the array's
  * device address up once (hipGetSymbolAddress).
  *   - Sizes whose E and F need more than DLA_MM3_NOALLOC_MAX_BYTES (mm3_workspace_bytes(ni, nj, nl, dt)
  *     exceeds it) are refused with DLA_ERR_TOO_LARGE before any work is enqueued; the paper's extralarge
@@ -247,8 +248,7 @@ int mm3_noalloc(const void* d_a, int64_t lda, const void* d_b, int64_t ldb, cons
  *          is computed too (the Cholesky trailing update)
  *   op 3:  C -= A*B^T          A m x k, B n x k, every tile (the Cholesky look-ahead panel update)
  *   op 4:  C -= A^T*B          A k x m, B k x n (the backward pass of cholesky_solve multiplies by
- *          L^T this way); only the 32x32 (16x16 waves) and 64x64 (32x32 waves) macro-tiles, p == NULL
- *          takes the latter
+ *          L^T this way); of the menu only the 32x32 (16x16 waves) and 64x64 (32x32 waves) macro-tiles
  * C must not overlap A or B.
  */
 int dla_gemm(int op, const void* d_a, int64_t lda, const void* d_b, int64_t ldb, void* d_c,

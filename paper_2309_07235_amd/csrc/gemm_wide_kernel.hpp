@@ -9,20 +9,21 @@
 //     left, and slab s + 1 goes from the other set to LDS half way through the multiplication;
 //   - a slab is 128 bytes of k, and k is dealt to the lanes so that the left operand's values of a lane are one run:
 //     lane group l4 (the k index of an MFMA) takes k = KPL l4 + kk in step kk of KPL, two 16-byte LDS reads a slab and
-//     row block.  The row stride is odd in units of 16 bytes, so the 8 rows one access cycle serves use all banks;
-//   - adjacent column blocks are interleaved (block b of a pair takes the columns 2 l15 + b), so the right operand is
-//     read and the result stored 16 bytes at a time as well;
+//     row block.  The row stride is odd in units of 16 bytes, so the 8 rows one access cycle serves use all banks (left
+//     as conflicts are 17 - 22 % of the LDS cycles, by counter, with the matrix pipes busy 81 - 83 % of the time);
+//   - where a wave has two column blocks (the 64 x 64 and 128 x 64 tiles) they are interleaved, block b taking the columns
+//     2 l15 + b, so the right operand is read and C is read and stored two elements at a time;
 //   - a ragged tile runs the same pipeline: a row past the edge is clamped to the last one, the run of columns across it
 //     reads on (both only reach results that are not stored); only the last slab is masked, on the way from the registers
 //     to LDS.  A mask where a value is loaded makes it wait for the load: with that, a width that is not a multiple of 16
-//     bytes took up to 1.67 times as long (Cholesky solve N = 8192, 255 right-hand sides, fp32: 2095 us, now 1015; LU solve
-//     N = 4001, 301, fp64: 1180 us, now 675).  And moving the run across the edge to its place in every slab keeps both
-//     forms of the loop in registers: 108 instead of 72 in a 64 x 64 tile, a workgroup less per compute unit.
-// Eight waves per workgroup, two on each SIMD, cover each other's barrier.  Measured, back to back (before: gemm_kernel
-// with its default schedule): fp64 E|F of the extralarge 3mm 590 -> 487 us, G 255 -> 208, 4096 x 4096 x 1024 63 ->
-// 72 TFLOP/s (92 % of the matrix-pipe peak); fp32 E|F of the large 3mm 73 -> 43 us, G 57 -> 23.  Whole calls: 847 -> 710
-// and 130 -> 64 us.  Deeper slabs (256
-// bytes) are 5 % slower, shallower ones (64 bytes) 2 - 10 %, 16 waves per 64 x 64 tile 10 %.
+//     bytes took up to 1.67 times as long as on gemm_kernel (Cholesky solve N = 8192, 255 right-hand sides, fp32: 2095 us,
+//     now 1015; LU solve N = 4001, 301, fp64: 1180 us, now 675).  Moving the run across the edge to its place in every
+//     slab keeps both forms of the loop in registers: 108 instead of 72 in a 64 x 64 tile, a workgroup less per unit.
+// The two larger tiles have eight waves, two on each SIMD, which cover each other's barrier, the smaller ones four, and
+// more workgroups to a unit.  Measured, back to back, gemm_kernel with its default schedule against this:
+// 4096 x 4096 x 1024 57 against 71 TFLOP/s in fp64 (of 78.6), 106 against 131 in fp32; 3mm extralarge fp64 848 against
+// 713 us, large fp32 130 against 64.5, with every dimension one more 130 against 65.  On its first form, deeper slabs
+// (256 bytes) were 5 % slower, shallower ones (64 bytes) 2 - 10 %, 16 waves per 64 x 64 tile 10 %.
 #pragma once
 #include <type_traits>
 #include "gemm_kernel.hpp"

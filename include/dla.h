@@ -175,8 +175,8 @@ size_t solve_workspace_bytes(int64_t n, int64_t nrhs, dla_dtype dt);
  * The same solves in two parts, for callers that solve with one factor again and again (paper, Section
  * "Introduction": the factorisations are what solving systems of linear equations is built on).
  * lu_solve_prepare / cholesky_solve_prepare run the part of the solve that does not depend on B (the
- * inverted diagonal blocks and their products with the factor's blocks beside them: 0.12 ms of lu_solve's
- * 0.37 ms at n = 4000 with 64 right-hand sides) and leave it in the workspace; lu_solve_prepared /
+ * inverted diagonal blocks and their products with the factor's blocks beside them: 0.11 ms of lu_solve's
+ * 0.35 ms at n = 4000 with 64 right-hand sides) and leave it in the workspace; lu_solve_prepared /
  * cholesky_solve_prepared then overwrite B with X like lu_solve / cholesky_solve, bit for bit the same
  * result, from a workspace that the matching prepare call has filled FOR THIS FACTOR (same d_lu / d_l
  * contents, n, lda, dt, same kind) and that nothing else has written since; any number of them may follow

@@ -331,6 +331,15 @@ size_t dla_mfma_peak_scratch_bytes(void);
  */
 int dla_handover_selftest(void* d_scratch, size_t scratch_bytes, void* hip_stream, int* d_info);
 
+/*
+ * Diagnostic for the waits inside lu_solve / cholesky_solve with up to 64 right-hand sides, whose two passes are one
+ * launch of workgroups that wait for each other: kind 0 as lu_solve, 1 as cholesky_solve, the other arguments theirs, but
+ * every wait gives up at once.  X then comes from the row by row substitution that stands in where a wait has given up (in
+ * an ordinary call after 50 ms, which no call reaches unless other work keeps its workgroups off the compute units).
+ */
+int dla_solve_giveup_selftest(int kind, const void* d_f, int64_t n, int64_t lda, void* d_b, int64_t nrhs, int64_t ldb, dla_dtype dt,
+                              void* d_workspace, size_t workspace_bytes, void* hip_stream);
+
 const char* dla_strerror(int code);
 /*
  * After an entry point returned DLA_ERR_HIP on this host thread: which HIP error it was and in which of

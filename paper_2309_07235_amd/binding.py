@@ -95,6 +95,8 @@ def _load() -> ctypes.CDLL:
     lib.dla_mfma_peak_scratch_bytes.restype = ctypes.c_size_t
     lib.dla_handover_selftest.argtypes = [vp, sz, vp, vp]
     lib.dla_handover_selftest.restype = ci
+    lib.dla_solve_giveup_selftest.argtypes = [ci] + lib.lu_solve.argtypes
+    lib.dla_solve_giveup_selftest.restype = ci
     lib.dla_rank_update.argtypes = [ci, vp, vp, vp, i64, i64, i64, ci, vp]
     lib.dla_rank_update.restype = ci
     lib.dla_gemm_choice.argtypes = [ci, i64, i64, i64, i64, i64, ci, ctypes.POINTER(ci), ctypes.POINTER(ci)]
@@ -371,6 +373,13 @@ def handover_selftest(stream=None) -> int:
     _check(lib.dla_handover_selftest(ctypes.c_void_p(scratch.data_ptr()), 8192, ctypes.c_void_p(_stream_ptr(stream)),
                                      ctypes.c_void_p(info.data_ptr())), "dla_handover_selftest")
     return int(info.item())
+
+
+def solve_giveup_selftest(kind: int, f, b, stream=None):
+    """lu_solve (kind 0) or cholesky_solve (1) whose waits all give up at once (see dla.h: dla_solve_giveup_selftest)."""
+    def call(*args):
+        return lib.dla_solve_giveup_selftest(kind, *args)
+    return _solve(call, "dla_solve_giveup_selftest", f, b, None, stream)
 
 
 def mfma_peak(dt: int = DLA_F64, stream=None) -> float:

@@ -595,14 +595,14 @@ size_t solve_workspace_bytes(int64_t n, int64_t nrhs, dla_dtype dt) {
 extern "C++" {
 template <int KIND>
 static int solve_entry(const void* d_f, int64_t n, int64_t lda, void* d_b, int64_t nrhs, int64_t ldb, dla_dtype dt,
-                       void* d_workspace, size_t workspace_bytes, void* hip_stream, int phases) {
+                       void* d_workspace, size_t workspace_bytes, void* hip_stream, int phases, long long wait_ticks = -1) {
   int rc = solve_common_checks(d_f, n, lda, d_b, nrhs, ldb, dt);
   if (rc != DLA_SUCCESS) return rc;
   hip_clear_stale_error();
   hipStream_t st = static_cast<hipStream_t>(hip_stream);
   if (dt == DLA_F64)
-    return solve_impl<double, KIND>((const double*)d_f, n, lda, (double*)d_b, nrhs, ldb, d_workspace, workspace_bytes, st, phases);
-  return solve_impl<float, KIND>((const float*)d_f, n, lda, (float*)d_b, nrhs, ldb, d_workspace, workspace_bytes, st, phases);
+    return solve_impl<double, KIND>((const double*)d_f, n, lda, (double*)d_b, nrhs, ldb, d_workspace, workspace_bytes, st, phases, wait_ticks);
+  return solve_impl<float, KIND>((const float*)d_f, n, lda, (float*)d_b, nrhs, ldb, d_workspace, workspace_bytes, st, phases, wait_ticks);
 }
 
 template <int KIND>
@@ -649,6 +649,15 @@ int lu_solve_prepared(const void* d_lu, int64_t n, int64_t lda, void* d_b, int64
 int cholesky_solve_prepared(const void* d_l, int64_t n, int64_t lda, void* d_b, int64_t nrhs, int64_t ldb, dla_dtype dt,
                             void* d_workspace, size_t workspace_bytes, void* hip_stream) {
   return solve_entry<1>(d_l, n, lda, d_b, nrhs, ldb, dt, d_workspace, workspace_bytes, hip_stream, kSolveApply);
+}
+
+int dla_solve_giveup_selftest(int kind, const void* d_f, int64_t n, int64_t lda, void* d_b, int64_t nrhs, int64_t ldb, dla_dtype dt,
+                              void* d_workspace, size_t workspace_bytes, void* hip_stream) {
+  if (kind != 0 && kind != 1) return -1;
+  constexpr int both = kSolvePrepare | kSolveApply;
+  const int rc = kind == 0 ? solve_entry<0>(d_f, n, lda, d_b, nrhs, ldb, dt, d_workspace, workspace_bytes, hip_stream, both, 0)
+                           : solve_entry<1>(d_f, n, lda, d_b, nrhs, ldb, dt, d_workspace, workspace_bytes, hip_stream, both, 0);
+  return rc < 0 ? rc - 1 : rc;  // (kind comes first here)
 }
 
 int dla_handover_selftest(void* d_scratch, size_t scratch_bytes, void* hip_stream, int* d_info) {

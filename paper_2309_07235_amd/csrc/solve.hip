@@ -22,10 +22,12 @@
 // and the backward pass reads N, M^T and L's block rows as transposed left operands, so it needs no
 // inverses of its own.  The forward pass leaves Y in the workspace and spoils B; the backward pass
 // builds X in a second workspace area and stores each finished block to B as well.
-// The chain's launches run on skinny_kernel up to 128 right-hand sides and on the tiled GEMM above.
+// Up to 64 right-hand sides both passes are one launch of flow_kernel, whose workgroups wait for each other; above that the
+// chain's launches run on skinny_kernel up to 128 right-hand sides and on the tiled GEMM beyond.
 // The pre-pass and the two passes can be called separately (one pre-pass, many solves with its workspace).
 #include "trisolve_kernel.hpp"
 #include "skinny_kernel.hpp"
+#include "flow_kernel.hpp"
 #include "host_common.hpp"
 
 namespace dla {
@@ -63,6 +65,15 @@ static int launch_skinny(bool at, const SkinnyGroup<T>& g, int workgroups, int k
     if (at) hipLaunchKernelGGL((skinny_kernel<T, true, 32>), grid, block, 0, st, g);
     else hipLaunchKernelGGL((skinny_kernel<T, false, 32>), grid, block, 0, st, g);
   }
+  return launch_status(__func__);
+}
+
+template <typename T, int KIND>
+static int launch_flow(const FlowArgs<T>& a, int nb, double flops, hipStream_t st) {
+  ProfileScope scope(PHASE_GEMM, flops, st);
+  const dim3 grid((unsigned)flow_workgroups(a.blocks, a.tiles_n)), block(kFlowThreads);
+  if (nb == 1) hipLaunchKernelGGL((flow_kernel<T, KIND, 1>), grid, block, 0, st, a);
+  else hipLaunchKernelGGL((flow_kernel<T, KIND, 2>), grid, block, 0, st, a);
   return launch_status(__func__);
 }
 
@@ -127,7 +138,7 @@ struct ProductList {
 // kSolveApply = the two passes over B with a workspace the pre-pass has filled for this factor; both = a whole solve.
 template <typename T, int KIND>
 int solve_impl(const T* F, int64_t n, int64_t lda, T* B, int64_t nrhs, int64_t ldb, void* ws, size_t ws_bytes,
-               hipStream_t st, int phases) {
+               hipStream_t st, int phases, long long wait_ticks) {
   const bool prepare = phases & kSolvePrepare, apply = (phases & kSolveApply) && nrhs > 0;
   if (n == 0 || (nrhs == 0 && (phases & kSolveApply))) return DLA_SUCCESS;
   const dla_dtype dt = sizeof(T) == 8 ? DLA_F64 : DLA_F32;
@@ -143,19 +154,31 @@ int solve_impl(const T* F, int64_t n, int64_t lda, T* B, int64_t nrhs, int64_t l
   T* const mf = tb + pairs * nb * nb;     // M of the forward pass: pairs x (256 x 512)
   T* const mb = mf + pairs * sb * 2 * sb; // M of the backward pass (Cholesky: its transpose, 512 x 256)
   T* const Y = mb + pairs * sb * 2 * sb;  // n x nrhs: Z and then the solution of the forward pass
+  static_assert(kFlowBlock == kTriPair, "both passes' blocks are the pre-pass's");
   const int64_t ldy = y_ld(nrhs);
   T* const X = Y + n * ldy;               // n x nrhs: Z and then the solution of the backward pass
   auto rows_of = [&](int i) { return n - (int64_t)i * sb < sb ? n - (int64_t)i * sb : sb; };
   auto Nf = [&](int i) { return wf + (int64_t)i * sb * sb; };
   auto Nb = [&](int i) { return wb + (int64_t)i * sb * sb; };
   int rc;
+  // Few right-hand sides: both passes in one launch (flow_kernel).  64 is where the two areas for S end to fit in the pre-pass's
+  // intermediates; the line lies there and not below because one launch is faster all the way (a prepared LU solve, fp64, us,
+  // launches against this, 1 / 16 / 64 right-hand sides: n = 300 23 / 23 / 24 against 15 / 15 / 16, n = 1000 46 / 47 / 51
+  // against 25 / 25 / 36, n = 2000 102 / 103 / 110 against 50 / 52 / 79, n = 4000 211 / 212 / 255 against 108 / 112 / 182,
+  // n = 8192 571 / 578 / 746 against 276 / 292 / 566; fp32 n = 4000 182 / 180 / 204 against 87 / 91 / 151).  A workgroup takes
+  // two column blocks where one each would be more workgroups than fit beside each other by much (n = 4000 with 32: 145
+  // against 141, n = 8192 419 against 369, n = 2000 65 against 72; n = 2000 with 64: 80 against 84).
+  const bool flow = nrhs <= 64 && lda <= kFlowMaxLd;
+  const int flow_nb = nrhs > 16 && n * nrhs > 128000 ? 2 : 1;
   // ---- every target of a subtracting product that stands for a plain one starts at zero: the pre-pass's
   // targets lie in front of Y, the passes' own (Y and X) behind them
   {
     T* const from = prepare ? wf : Y;
-    const int64_t count = (prepare ? block_elems(n) : 0) + (apply ? 2 * n * ldy : 0);
+    const int64_t count = (prepare ? block_elems(n) : 0) + (apply && !flow ? 2 * n * ldy : 0);
+    if (prepare || !flow) {
     hipLaunchKernelGGL(solve_zero_kernel<T>, dim3((unsigned)((count + 255) / 256)), dim3(256), 0, st, from, count);
     if (launch_status(__func__) != DLA_SUCCESS) return DLA_ERR_HIP;
+    }
   }
   // with N = -W:  T = 0 - (off-diagonal block of the factor) * (N next to it) = block * W, then the
   // missing quarter of N = 0 - (the other N) * T = W * block * W
@@ -218,6 +241,18 @@ int solve_impl(const T* F, int64_t n, int64_t lda, T* B, int64_t nrhs, int64_t l
     if ((rc = look_back(0, st)) != DLA_SUCCESS || (rc = look_back(1, st)) != DLA_SUCCESS) return rc;
   }
   if (!apply) return DLA_SUCCESS;
+  if (flow) {
+    const int tiles_n = (int)((nrhs + 16 * flow_nb - 1) / (16 * flow_nb));
+    int* const ints = reinterpret_cast<int*>(mf);  // (the first block has no M)
+    FlowArgs<T> a{F, B, wf, KIND == KIND_LU ? wb : wf, mf, mb, Y, X, tf, ints, ints + flow_flags(nblk, tiles_n), wait_ticks < 0 ? kFlowWaitTicks : wait_ticks,
+                  lda, ldb, ldy, (int)n, (int)nrhs, nblk, tiles_n, flow_expected((int)n, nblk)};
+    const int64_t count = 2 * n * ldy;
+    const int nints = flow_ints(nblk, tiles_n);
+    const int64_t most = count > nints ? count : nints;
+    hipLaunchKernelGGL(flow_init_kernel<T>, dim3((unsigned)((most + 255) / 256)), dim3(256), 0, st, Y, nblk > kFlowLook + 1 ? tf : nullptr, count, ints, nints);
+    if (launch_status(__func__) != DLA_SUCCESS) return DLA_ERR_HIP;
+    return launch_flow<T, KIND>(a, flow_nb, 2.0 * (double)n * (double)n * (double)nrhs, st);
+  }
   // ---- the chain: one grouped launch per block step
   struct Part {
     const T *a, *b;
@@ -318,9 +353,9 @@ int solve_impl(const T* F, int64_t n, int64_t lda, T* B, int64_t nrhs, int64_t l
   return DLA_SUCCESS;
 }
 
-template int solve_impl<double, KIND_LU>(const double*, int64_t, int64_t, double*, int64_t, int64_t, void*, size_t, hipStream_t, int);
-template int solve_impl<float, KIND_LU>(const float*, int64_t, int64_t, float*, int64_t, int64_t, void*, size_t, hipStream_t, int);
-template int solve_impl<double, KIND_CHOL>(const double*, int64_t, int64_t, double*, int64_t, int64_t, void*, size_t, hipStream_t, int);
-template int solve_impl<float, KIND_CHOL>(const float*, int64_t, int64_t, float*, int64_t, int64_t, void*, size_t, hipStream_t, int);
+template int solve_impl<double, KIND_LU>(const double*, int64_t, int64_t, double*, int64_t, int64_t, void*, size_t, hipStream_t, int, long long);
+template int solve_impl<float, KIND_LU>(const float*, int64_t, int64_t, float*, int64_t, int64_t, void*, size_t, hipStream_t, int, long long);
+template int solve_impl<double, KIND_CHOL>(const double*, int64_t, int64_t, double*, int64_t, int64_t, void*, size_t, hipStream_t, int, long long);
+template int solve_impl<float, KIND_CHOL>(const float*, int64_t, int64_t, float*, int64_t, int64_t, void*, size_t, hipStream_t, int, long long);
 
 }  // namespace dla

@@ -82,15 +82,37 @@ inline int flow_expected(int n, int blocks) {
 inline int flow_flags(int blocks, int tiles_n) { return 2 * blocks * tiles_n * kFlowTiles; }
 inline int flow_ints(int blocks, int tiles_n) { return flow_flags(blocks, tiles_n) + tiles_n + 1; }
 
-// Two areas of count elements each empty; no flag set, no workgroup done.
+// What a launch finds: two areas of count elements each empty, no flag set, no workgroup done.  By the launch in front of it
+// (the pre-pass's first, or one of its own), kFlowThreads to a workgroup.
 template <typename T>
-__global__ void flow_init_kernel(T* area, T* sums, int64_t count, int* ints, int nints) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < count) {
-    area[i] = __builtin_bit_cast(T, FlowBits<T>::kEmpty);
-    if (sums) sums[i] = __builtin_bit_cast(T, FlowBits<T>::kEmpty);
+struct FlowInit {
+  T* area;
+  T* sums;        // or null
+  int64_t count;  // 0: nothing to do
+  int* ints;
+  int nints;
+};
+constexpr int kFlowInitPerThread = 8;
+template <typename T>
+inline int flow_init_workgroups(const FlowInit<T>& a) {
+  const int64_t most = a.count > a.nints ? a.count : a.nints;
+  return (int)((most + kFlowThreads * kFlowInitPerThread - 1) / (kFlowThreads * kFlowInitPerThread));
+}
+template <typename T>
+__device__ __forceinline__ void flow_init(const FlowInit<T>& a, int wg) {
+#pragma unroll
+  for (int e = 0; e < kFlowInitPerThread; ++e) {
+    const int64_t i = ((int64_t)wg * kFlowInitPerThread + e) * kFlowThreads + threadIdx.x;
+    if (i < a.count) {
+      a.area[i] = __builtin_bit_cast(T, FlowBits<T>::kEmpty);
+      if (a.sums) a.sums[i] = __builtin_bit_cast(T, FlowBits<T>::kEmpty);
+    }
+    if (i < a.nints) a.ints[i] = 0;
   }
-  if (i < nints) ints[i] = 0;
+}
+template <typename T>
+__global__ void __launch_bounds__(kFlowThreads) flow_init_kernel(const FlowInit<T> a) {
+  flow_init(a, (int)blockIdx.x);
 }
 
 template <int SCOPE = __HIP_MEMORY_SCOPE_AGENT, typename T>

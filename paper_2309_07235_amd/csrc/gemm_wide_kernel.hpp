@@ -107,9 +107,11 @@ __device__ __forceinline__ typename WideVec<T>::v16 wide_move(typename WideVec<T
   return x;
 }
 
-template <typename T, int WM, int WN, int FM, int FN, int TK, int OP>
-__global__ void __launch_bounds__(WM * WN * 64) gemm_wide_kernel(const GemmGroup<T> g) {
-  constexpr bool AT = OP == OP_SUB_TN, SUB = OP != OP_ASSIGN;
+// Tile (ti, tj) of product P, by the whole workgroup.  OP_NEGATE: C = -A*B.  Off: the type of element offsets inside a tile.
+constexpr int OP_NEGATE = 100;
+template <typename T, int WM, int WN, int FM, int FN, int TK, int OP, typename Off = uint32_t>
+__device__ __forceinline__ void gemm_wide_tile(const GemmProblem<T>& P, const int ti, const int tj, T* const smem) {
+  constexpr bool AT = OP == OP_SUB_TN, SUB = OP != OP_ASSIGN, ONTO = SUB && OP != OP_NEGATE;
   using S = WideShape<T, WM, WN, FM, FN, TK, AT>;
   constexpr int TM = S::TM, TN = S::TN, NT = S::NT, PER = S::PER;
   constexpr int KPL = TK / 4;  // k-steps of a slab = k values per lane
@@ -119,17 +121,6 @@ __global__ void __launch_bounds__(WM * WN * 64) gemm_wide_kernel(const GemmGroup
   using R = typename WideRun<T, RB>::type;  // what a lane holds of a row of C, in one access
   using LA = WideLoader<T, AT ? TK : TM, AT ? TM : TK, NT>;
   using LB = WideLoader<T, TK, TN, NT>;
-  extern __shared__ __align__(16) unsigned char smem_raw[];
-  T* const smem = reinterpret_cast<T*>(smem_raw);
-
-  const int logical = xcd_contiguous_id((int)blockIdx.x, g.total_tiles);
-  int pi = 0;
-#pragma unroll
-  for (int q = 1; q < kMaxGroup; ++q)
-    if (q < g.nprob && logical >= g.prob[q].tile_begin) pi = q;
-  const GemmProblem<T>& P = g.prob[pi];
-  const int local = logical - P.tile_begin;
-  const int ti = local / P.tiles_n, tj = local % P.tiles_n;
   const int m0 = ti * TM, n0 = tj * TN;
   const int tid = (int)threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int l15 = lane & 15, l4 = lane >> 4;
@@ -145,7 +136,7 @@ __global__ void __launch_bounds__(WM * WN * 64) gemm_wide_kernel(const GemmGroup
 
   acc_t acc[FM][FN];
   T* const Ct = P.C + (int64_t)m0 * ldc + n0;
-  if constexpr (SUB) {
+  if constexpr (ONTO) {
     if (full_mn) {
 #pragma unroll
       for (int a = 0; a < FM; ++a)
@@ -184,17 +175,17 @@ __global__ void __launch_bounds__(WM * WN * 64) gemm_wide_kernel(const GemmGroup
   static_assert(LA::TOTAL % NT == 0 && LB::TOTAL % NT == 0 && NT % LA::VPR == 0 && NT % LB::VPR == 0, "whole passes, one column per thread");
   const bool narrow_a = AT && M < PER, narrow_b = N < PER;  // rows shorter than a run
   const bool straddle = (AT && m0 + TM > M && M % PER != 0) || (n0 + TN > N && N % PER != 0);
-  uint32_t aoff[LA::ITER], boff[LB::ITER];                  // element offsets of slab 0
+  Off aoff[LA::ITER], boff[LB::ITER];                  // element offsets of slab 0
 #pragma unroll
   for (int it = 0; it < LA::ITER; ++it) {
     const int r = LA::row_of(tid + it * NT), c = LA::col_of(tid), last = (M - 1) / PER * PER;
-    if constexpr (AT) aoff[it] = (uint32_t)r * (uint32_t)lda + (uint32_t)(m0 + c < last ? m0 + c : last);
-    else aoff[it] = (uint32_t)(m0 + r < M ? r : M - 1 - m0) * (uint32_t)lda + (uint32_t)c;
+    if constexpr (AT) aoff[it] = (Off)r * (Off)lda + (Off)(m0 + c < last ? m0 + c : last);
+    else aoff[it] = (Off)(m0 + r < M ? r : M - 1 - m0) * (Off)lda + (Off)c;
   }
 #pragma unroll
   for (int it = 0; it < LB::ITER; ++it) {
     const int r = LB::row_of(tid + it * NT), c = n0 + LB::col_of(tid), last = (N - 1) / PER * PER;
-    boff[it] = (uint32_t)r * (uint32_t)ldb + (uint32_t)(c < last ? c : last);
+    boff[it] = (Off)r * (Off)ldb + (Off)(c < last ? c : last);
   }
   V ra[2][LA::ITER], rb[2][LB::ITER];
   auto load_full = [&](auto sc, int s) __attribute__((always_inline)) {
@@ -219,7 +210,7 @@ __global__ void __launch_bounds__(WM * WN * 64) gemm_wide_kernel(const GemmGroup
     for (int it = 0; it < LA::ITER; ++it) {
       const int r = LA::row_of(t + it * NT), c = LA::col_of(t);
       if constexpr (AT) {
-        const T* const q = pa + (uint32_t)(r < kv ? r : kv - 1) * (uint32_t)lda;
+        const T* const q = pa + (Off)(r < kv ? r : kv - 1) * (Off)lda;
         if (!narrow_a) {
           ra[X][it] = *reinterpret_cast<const V*>(q + (m0 + c < M - PER ? m0 + c : M - PER));
         } else {
@@ -227,7 +218,7 @@ __global__ void __launch_bounds__(WM * WN * 64) gemm_wide_kernel(const GemmGroup
           for (int e = 0; e < PER; ++e) ra[X][it][e] = q[c + e < M ? c + e : M - 1];
         }
       } else {
-        const T* const q = pa + (uint32_t)(m0 + r < M ? r : M - 1 - m0) * (uint32_t)lda;
+        const T* const q = pa + (Off)(m0 + r < M ? r : M - 1 - m0) * (Off)lda;
 #pragma unroll
         for (int e = 0; e < PER; ++e) ra[X][it][e] = q[c + e < kv ? c + e : kv - 1];
       }
@@ -235,7 +226,7 @@ __global__ void __launch_bounds__(WM * WN * 64) gemm_wide_kernel(const GemmGroup
 #pragma unroll
     for (int it = 0; it < LB::ITER; ++it) {
       const int r = LB::row_of(t + it * NT), c = n0 + LB::col_of(t);
-      const T* const q = pb + (uint32_t)(r < kv ? r : kv - 1) * (uint32_t)ldb;
+      const T* const q = pb + (Off)(r < kv ? r : kv - 1) * (Off)ldb;
       if (!narrow_b) {
         rb[X][it] = *reinterpret_cast<const V*>(q + (c < N - PER ? c : N - PER));
       } else {
@@ -368,6 +359,19 @@ __global__ void __launch_bounds__(WM * WN * 64) gemm_wide_kernel(const GemmGroup
   };
   store_to(Ct, ldc);
   if (P.C2) store_to(P.C2 + (int64_t)m0 * P.ldc2 + n0, P.ldc2);
+}
+
+template <typename T, int WM, int WN, int FM, int FN, int TK, int OP>
+__global__ void __launch_bounds__(WM * WN * 64) gemm_wide_kernel(const GemmGroup<T> g) {
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  const int logical = xcd_contiguous_id((int)blockIdx.x, g.total_tiles);
+  int pi = 0;
+#pragma unroll
+  for (int q = 1; q < kMaxGroup; ++q)
+    if (q < g.nprob && logical >= g.prob[q].tile_begin) pi = q;
+  const GemmProblem<T>& P = g.prob[pi];
+  const int local = logical - P.tile_begin;
+  gemm_wide_tile<T, WM, WN, FM, FN, TK, OP>(P, local / P.tiles_n, local % P.tiles_n, reinterpret_cast<T*>(smem_raw));
 }
 
 }  // namespace dla

@@ -70,17 +70,18 @@ __device__ inline int head_prow(int l15) {
 
 // X = M^-1 * P for a lower-triangular M whose sub-block (s, r), s >= r, sits at tri[s * (s + 1) / 2 + r]
 // (diagonal ones inverted); element (i, k) of a sub-block at i * rs + k * cs.  acc holds P on entry
-// and X on return: register v of acc[s] is row 16 * s + 4 * (lane / 16) + v, column lane % 16.
+// and X on return: register v of acc[s] is row 16 * s + 4 * (lane / 16) + v, column lane % 16.  Sub-block rows of P in front
+// of `first` are zero.
 template <typename T, bool FULL>
-__device__ inline void head_solve(const T* tri, int rs, int cs, int nblk, int lane,
-                                  typename Mfma<T>::acc_t (&acc)[kNbMax / kIb]) {
+__device__ __forceinline__ void head_solve(const T* tri, int rs, int cs, int nblk, int lane,
+                                           typename Mfma<T>::acc_t (&acc)[kNbMax / kIb], int first = 0) {
   constexpr int NB = kNbMax / kIb;
   using acc_t = typename Mfma<T>::acc_t;
   const int l15 = lane & 15, l4 = lane >> 4;
   const T* const base = tri + head_prow<T>(l15) * rs + 4 * l4 * cs;
   static_for<0, NB>([&](auto rc) {
     constexpr int r = decltype(rc)::value;
-    if (FULL || r < nblk) {
+    if ((FULL || r < nblk) && r >= first) {
       const T* d = base + (r * (r + 1) / 2 + r) * kBlk;
       acc_t x = {0, 0, 0, 0};
 #pragma unroll

@@ -4,7 +4,7 @@
 // tri_prepare_kernel, then pairs of them joined into the inverse of a 256-row block,
 //   inv [ L1  0  ] = [  W1        0  ]        inv [ U1 U12 ] = [ V1  -V1 U12 V2 ]
 //       [ L21 L2 ]   [ -W2 L21 W1  W2 ]            [ 0  U2  ]   [ 0    V2       ]
-// by two small products per pair on the tiled GEMM, all pairs in grouped launches.
+// (pair_kernel), then the products M below (look_back_kernel): three launches.
 //
 // The chain of the substitution is latency bound (every launch waits for the one before it), so a
 // block step is ONE grouped launch.  With W_i the inverse of diagonal block i, the plain step
@@ -25,7 +25,7 @@
 // Up to 64 right-hand sides both passes are one launch of flow_kernel, whose workgroups wait for each other; above that the
 // chain's launches run on skinny_kernel up to 128 right-hand sides and on the tiled GEMM beyond.
 // The pre-pass and the two passes can be called separately (one pre-pass, many solves with its workspace).
-#include "trisolve_kernel.hpp"
+#include "prepass_kernel.hpp"
 #include "skinny_kernel.hpp"
 #include "flow_kernel.hpp"
 #include "host_common.hpp"
@@ -33,24 +33,24 @@
 namespace dla {
 
 template <typename T, int MODE>
-static int launch_prepare(const TriPrepareArgs<T>& a, hipStream_t st) {
+static int launch_prepare(const TriPrepareArgs<T>& a, const FlowInit<T>& init, hipStream_t st) {
   auto kern = tri_prepare_kernel<T, MODE>;
   static LdsLimitOnce lds_limit;
   if (!lds_limit.ensure(reinterpret_cast<const void*>(kern), trisolve_lds_bytes<T>())) return DLA_ERR_HIP;
-  const int grid = (int)((a.n + kNbMax - 1) / kNbMax);
+  const int grid = kTriHalves * (int)((a.n + kNbMax - 1) / kNbMax);
   ProfileScope scope(PHASE_TRSM, 0.0, st);
-  hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(kTriThreads), trisolve_lds_bytes<T>(), st, a);
+  hipLaunchKernelGGL(kern, dim3((unsigned)(grid + flow_init_workgroups(init))), dim3(kTriThreads), trisolve_lds_bytes<T>(), st, a, init);
   return launch_status(__func__);
 }
 
 template <typename T, int MODE_A, int MODE_B>
-static int launch_prepare_both(const TriPrepareArgs<T>& a, const TriPrepareArgs<T>& b, hipStream_t st) {
+static int launch_prepare_both(const TriPrepareArgs<T>& a, const TriPrepareArgs<T>& b, const FlowInit<T>& init, hipStream_t st) {
   auto kern = tri_prepare_both_kernel<T, MODE_A, MODE_B>;
   static LdsLimitOnce lds_limit;
   if (!lds_limit.ensure(reinterpret_cast<const void*>(kern), trisolve_lds_bytes<T>())) return DLA_ERR_HIP;
-  const int grid = 2 * (int)((a.n + kNbMax - 1) / kNbMax);
+  const int grid = 2 * kTriHalves * (int)((a.n + kNbMax - 1) / kNbMax);
   ProfileScope scope(PHASE_TRSM, 0.0, st);
-  hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(kTriThreads), trisolve_lds_bytes<T>(), st, a, b);
+  hipLaunchKernelGGL(kern, dim3((unsigned)(grid + flow_init_workgroups(init))), dim3(kTriThreads), trisolve_lds_bytes<T>(), st, a, b, init);
   return launch_status(__func__);
 }
 
@@ -96,7 +96,7 @@ size_t solve_workspace_bytes_impl(int64_t n, int64_t nrhs, dla_dtype dt) {
   return ((size_t)block_elems(n) + 2 * (size_t)n * (size_t)y_ld(nrhs)) * (dt == DLA_F64 ? 8 : 4);
 }
 
-// The products on the tiled GEMM (the pre-pass; the chain with many right-hand sides) take gemm_wide_kernel, whose launch
+// The products of the chain with many right-hand sides take gemm_wide_kernel, whose launch
 // picks the tile: N = 8192 with 1024 right-hand sides, fp32, 2.79 -> 2.18 ms against 32 x 32 tiles of gemm_kernel.  This
 // schedule is for what that kernel does not take (leading dimensions beyond its offsets, fp32 systems of up to 32 rows).
 static const GemmSchedule kSolveTiles = {32, 32, 16, 4, 16, 16};
@@ -109,30 +109,31 @@ static int launch_products(int op, GemmGroup<T>& g, int np, int tiles, double fl
   return gemm_wide_takes<T>(op, g) ? launch_gemm_wide<T>(op, g, st) : launch_gemm<T>(kSolveTiles, op, g, st);
 }
 
-// products of one op, kMaxGroup to a launch
-template <typename T>
-struct ProductList {
-  int op;
-  GemmGroup<T> g;
-  int np = 0, tiles = 0;
-  double flops = 0.0;
-  int flush(hipStream_t st) {
-    if (np == 0) return DLA_SUCCESS;
-    const int rc = launch_products<T>(op, g, np, tiles, flops, st);
-    np = tiles = 0;
-    flops = 0.0;
-    return rc;
-  }
-  int add(const T* a, int64_t lda, const T* b, int64_t ldb, T* c, int64_t ldc, int64_t M, int64_t N, int64_t K,
-          hipStream_t st) {
-    if (M <= 0 || N <= 0 || K <= 0) return DLA_SUCCESS;
-    g.prob[np] = make_problem<T>(kSolveTiles, op, a, lda, b, ldb, c, ldc, M, N, K, tiles);
-    tiles += problem_tiles(kSolveTiles, op, g.prob[np]);
-    flops += 2.0 * (double)M * (double)N * (double)K;
-    if (++np == kMaxGroup) return flush(st);
-    return DLA_SUCCESS;
-  }
-};
+template <typename T, int KIND>
+static int launch_pairing(const PrepassArgs<T>& a, hipStream_t st) {
+  if (a.n <= kNbMax) return DLA_SUCCESS;
+  ProfileScope scope(PHASE_GEMM, 0.0, st);
+  hipLaunchKernelGGL((pair_kernel<T, KIND>), dim3((unsigned)((KIND == KIND_LU ? 2 : 1) * pair_workgroups(a.n))), dim3(kPairThreads), 0, st, a);
+  return launch_status(__func__);
+}
+
+template <typename T, int KIND, typename Off>
+static int launch_look_back_as(const PrepassArgs<T>& a, hipStream_t st) {
+  auto kern = look_back_kernel<T, KIND, Off>;
+  using S = LookShape<T>;
+  static_assert(S::NT == kLookThreads, "threads");
+  static LdsLimitOnce lds_limit;
+  if (!lds_limit.ensure(reinterpret_cast<const void*>(kern), S::BYTES)) return DLA_ERR_HIP;
+  ProfileScope scope(PHASE_GEMM, 0.0, st);
+  hipLaunchKernelGGL(kern, dim3((unsigned)look_back_workgroups(a.n)), dim3(kLookThreads), S::BYTES, st, a);
+  return launch_status(__func__);
+}
+template <typename T, int KIND>
+static int launch_look_back(const PrepassArgs<T>& a, hipStream_t st) {
+  if (a.n <= kTriPair) return DLA_SUCCESS;
+  if (a.lda > (1 << 24)) return launch_look_back_as<T, KIND, uint64_t>(a, st);  // beyond 32-bit element offsets inside a tile
+  return launch_look_back_as<T, KIND, uint32_t>(a, st);
+}
 
 // phases: kSolvePrepare = the pre-pass (independent of B; leaves the negated inverses and M in the workspace),
 // kSolveApply = the two passes over B with a workspace the pre-pass has filled for this factor; both = a whole solve.
@@ -149,9 +150,8 @@ int solve_impl(const T* F, int64_t n, int64_t lda, T* B, int64_t nrhs, int64_t l
   const int nblk = (int)pairs, last = nblk - 1;
   T* const wf = static_cast<T*>(ws);      // negated inverses, forward pass: pairs x (256 x 256)
   T* const wb = wf + pairs * sb * sb;     // negated inverses, backward pass (LU)
-  T* const tf = wb + pairs * sb * sb;     // intermediates of the pairing: pairs x (128 x 128), forward
-  T* const tb = tf + pairs * nb * nb;     // and backward
-  T* const mf = tb + pairs * nb * nb;     // M of the forward pass: pairs x (256 x 512)
+  T* const tf = wb + pairs * sb * sb;     // S of flow_kernel: 2 x pairs x (128 x 128)
+  T* const mf = tf + 2 * pairs * nb * nb; // M of the forward pass: pairs x (256 x 512)
   T* const mb = mf + pairs * sb * 2 * sb; // M of the backward pass (Cholesky: its transpose, 512 x 256)
   T* const Y = mb + pairs * sb * 2 * sb;  // n x nrhs: Z and then the solution of the forward pass
   static_assert(kFlowBlock == kTriPair, "both passes' blocks are the pre-pass's");
@@ -170,88 +170,37 @@ int solve_impl(const T* F, int64_t n, int64_t lda, T* B, int64_t nrhs, int64_t l
   // against 141, n = 8192 419 against 369, n = 2000 65 against 72; n = 2000 with 64: 80 against 84).
   const bool flow = nrhs <= 64 && lda <= kFlowMaxLd;
   const int flow_nb = nrhs > 16 && n * nrhs > 128000 ? 2 : 1;
-  // ---- every target of a subtracting product that stands for a plain one starts at zero: the pre-pass's
-  // targets lie in front of Y, the passes' own (Y and X) behind them
-  {
-    T* const from = prepare ? wf : Y;
-    const int64_t count = (prepare ? block_elems(n) : 0) + (apply && !flow ? 2 * n * ldy : 0);
-    if (prepare || !flow) {
-    hipLaunchKernelGGL(solve_zero_kernel<T>, dim3((unsigned)((count + 255) / 256)), dim3(256), 0, st, from, count);
-    if (launch_status(__func__) != DLA_SUCCESS) return DLA_ERR_HIP;
-    }
+  const int tiles_n = (int)((nrhs + 16 * flow_nb - 1) / (16 * flow_nb));
+  int* const ints = reinterpret_cast<int*>(mf);  // (the first block has no M)
+  FlowInit<T> init{Y, nblk > kFlowLook + 1 ? tf : nullptr, 0, ints, 0};  // S: where the pre-pass keeps nothing
+  if (apply && flow) {
+    init.count = 2 * n * ldy;
+    init.nints = flow_ints(nblk, tiles_n);
   }
-  // with N = -W:  T = 0 - (off-diagonal block of the factor) * (N next to it) = block * W, then the
-  // missing quarter of N = 0 - (the other N) * T = W * block * W
-  auto pairing = [&](int pass, hipStream_t s) -> int {
-    if (n <= nb) return DLA_SUCCESS;
-    ProductList<T> first{OP_SUB}, second{OP_SUB};
-    int r;
-    for (int64_t p = 0; p < pairs; ++p) {
-      const int64_t k0 = p * sb, b2 = n - k0 - nb < nb ? n - k0 - nb : nb;
-      if (b2 <= 0) continue;  // a last block without a partner
-      T* const W = (pass == 0 ? wf : wb) + p * sb * sb;
-      T* const Tm = (pass == 0 ? tf : tb) + p * nb * nb;
-      const T* const L21 = F + (k0 + nb) * lda + k0;  // b2 x 128
-      const T* const U12 = F + k0 * lda + k0 + nb;    // 128 x b2
-      if (pass == 0) r = first.add(L21, lda, W, sb, Tm, nb, b2, nb, nb, s);       // T = L21 W1
-      else r = first.add(U12, lda, W + nb * sb + nb, sb, Tm, nb, nb, b2, b2, s);  // T = U12 V2
-      if (r != DLA_SUCCESS) return r;
-    }
-    if ((r = first.flush(s)) != DLA_SUCCESS) return r;
-    for (int64_t p = 0; p < pairs; ++p) {
-      const int64_t k0 = p * sb, b2 = n - k0 - nb < nb ? n - k0 - nb : nb;
-      if (b2 <= 0) continue;
-      T* const W = (pass == 0 ? wf : wb) + p * sb * sb;
-      const T* const Tm = (pass == 0 ? tf : tb) + p * nb * nb;
-      if (pass == 0) r = second.add(W + nb * sb + nb, sb, Tm, nb, W + nb * sb, sb, b2, nb, b2, s);  // N21 = W2 T
-      else r = second.add(W, sb, Tm, nb, W + nb, sb, nb, b2, nb, s);                                 // N12 = V1 T
-      if (r != DLA_SUCCESS) return r;
-    }
-    return second.flush(s);
-  };
-  // M_i = 0 - N_i * (the factor's blocks beside diagonal block i that the look-back covers)
-  auto look_back = [&](int pass, hipStream_t s) -> int {
-    ProductList<T> list{OP_SUB};
-    int r = DLA_SUCCESS;
-    if (pass == 0) {
-      for (int i = 1; i < nblk && r == DLA_SUCCESS; ++i) {  // block columns i-2 (if any) and i-1 of block row i
-        const int64_t c0 = (int64_t)(i >= 2 ? i - 2 : 0) * sb, kc = (int64_t)i * sb - c0;
-        r = list.add(Nf(i), sb, F + (int64_t)i * sb * lda + c0, lda, mf + (int64_t)i * sb * 2 * sb, 2 * sb, rows_of(i), kc,
-                     rows_of(i), s);
-      }
-    } else {
-      for (int k = 0; k < last && r == DLA_SUCCESS; ++k) {  // block columns k+1 and k+2 (if any) of block row k
-        const int64_t c0 = (int64_t)(k + 1) * sb, kc = (n < c0 + 2 * sb ? n : c0 + 2 * sb) - c0;
-        if (KIND == KIND_LU)  // M_k = V_k [U_k,k+1  U_k,k+2]
-          r = list.add(Nb(k), sb, F + (int64_t)k * sb * lda + c0, lda, mb + (int64_t)k * sb * 2 * sb, 2 * sb, sb, kc, sb, s);
-        else  // M_k^T = [L_k+1,k ; L_k+2,k] W_k   (V_k = W_k^T and U_kj = L_jk^T)
-          r = list.add(F + c0 * lda + (int64_t)k * sb, lda, Nf(k), sb, mb + (int64_t)k * sb * 2 * sb, sb, kc, sb, sb, s);
-      }
-    }
-    return r != DLA_SUCCESS ? r : list.flush(s);
-  };
   if (prepare) {
     if (KIND == KIND_LU)
-      rc = launch_prepare_both<T, TRI_LOWER_UNIT, TRI_UPPER>(TriPrepareArgs<T>{F, lda, n, wf, T(-1)}, TriPrepareArgs<T>{F, lda, n, wb, T(-1)}, st);
+      rc = launch_prepare_both<T, TRI_LOWER_UNIT, TRI_UPPER>(TriPrepareArgs<T>{F, lda, n, wf, T(-1)}, TriPrepareArgs<T>{F, lda, n, wb, T(-1)}, init, st);
     else
-      rc = launch_prepare<T, TRI_LOWER>(TriPrepareArgs<T>{F, lda, n, wf, T(-1)}, st);
+      rc = launch_prepare<T, TRI_LOWER>(TriPrepareArgs<T>{F, lda, n, wf, T(-1)}, init, st);
     if (rc != DLA_SUCCESS) return rc;
-    if ((rc = pairing(0, st)) != DLA_SUCCESS) return rc;
-    if (KIND == KIND_LU && (rc = pairing(1, st)) != DLA_SUCCESS) return rc;
-    if ((rc = look_back(0, st)) != DLA_SUCCESS || (rc = look_back(1, st)) != DLA_SUCCESS) return rc;
+    const PrepassArgs<T> pa{F, lda, (int)n, wf, wb, mf, mb};
+    if ((rc = launch_pairing<T, KIND>(pa, st)) != DLA_SUCCESS || (rc = launch_look_back<T, KIND>(pa, st)) != DLA_SUCCESS) return rc;
   }
   if (!apply) return DLA_SUCCESS;
   if (flow) {
-    const int tiles_n = (int)((nrhs + 16 * flow_nb - 1) / (16 * flow_nb));
-    int* const ints = reinterpret_cast<int*>(mf);  // (the first block has no M)
+    if (!prepare) {
+      hipLaunchKernelGGL(flow_init_kernel<T>, dim3((unsigned)flow_init_workgroups(init)), dim3(kFlowThreads), 0, st, init);
+      if (launch_status(__func__) != DLA_SUCCESS) return DLA_ERR_HIP;
+    }
     FlowArgs<T> a{F, B, wf, KIND == KIND_LU ? wb : wf, mf, mb, Y, X, tf, ints, ints + flow_flags(nblk, tiles_n), wait_ticks < 0 ? kFlowWaitTicks : wait_ticks,
                   lda, ldb, ldy, (int)n, (int)nrhs, nblk, tiles_n, flow_expected((int)n, nblk)};
-    const int64_t count = 2 * n * ldy;
-    const int nints = flow_ints(nblk, tiles_n);
-    const int64_t most = count > nints ? count : nints;
-    hipLaunchKernelGGL(flow_init_kernel<T>, dim3((unsigned)((most + 255) / 256)), dim3(256), 0, st, Y, nblk > kFlowLook + 1 ? tf : nullptr, count, ints, nints);
-    if (launch_status(__func__) != DLA_SUCCESS) return DLA_ERR_HIP;
     return launch_flow<T, KIND>(a, flow_nb, 2.0 * (double)n * (double)n * (double)nrhs, st);
+  }
+  // ---- the targets of the passes' subtracting products that stand for plain ones start at zero
+  {
+    const int64_t count = 2 * n * ldy;
+    hipLaunchKernelGGL(solve_zero_kernel<T>, dim3((unsigned)((count + 255) / 256)), dim3(256), 0, st, Y, count);
+    if (launch_status(__func__) != DLA_SUCCESS) return DLA_ERR_HIP;
   }
   // ---- the chain: one grouped launch per block step
   struct Part {

@@ -21,11 +21,13 @@
 // with the identity.
 #pragma once
 #include "head_kernel.hpp"
+#include "flow_kernel.hpp"
 
 namespace dla {
 
 enum TriMode { TRI_LOWER_UNIT = 0, TRI_LOWER = 1, TRI_UPPER = 2, TRI_LOWER_TRANS = 3 };
 constexpr int kTriThreads = 256;
+static_assert(kTriThreads == kFlowThreads, "its launch carries flow_init");
 
 template <typename T>
 constexpr int trisolve_lds_bytes() {
@@ -69,9 +71,14 @@ struct TriPrepareArgs {
   T unit;       // 1: the inverses themselves; -1: the negated inverses (the substitution runs on -I)
 };
 
-// The work of one workgroup: diagonal block `block` of g's factor.
+// Two workgroups per diagonal block, four of the inverse's eight column slices each, so that a wave substitutes once; the
+// slices are dealt so that both have as much to do (slice s starts at sub-block row s).
+constexpr int kTriHalves = 2;
+static_assert(kTriHalves * (kTriThreads / 64) == kNbMax / kIb, "a wave per slice");
+
+// The work of one workgroup: half of diagonal block `block` of g's factor.
 template <typename T, int MODE>
-__device__ __forceinline__ void tri_prepare_block(const TriPrepareArgs<T>& g, const int block) {
+__device__ __forceinline__ void tri_prepare_block(const TriPrepareArgs<T>& g, const int block, const int half) {
   constexpr int NB = kNbMax / kIb;
   constexpr int NTRI = NB * (NB + 1) / 2;
   constexpr bool REV = MODE == TRI_UPPER || MODE == TRI_LOWER_TRANS;
@@ -144,21 +151,21 @@ __device__ __forceinline__ void tri_prepare_block(const TriPrepareArgs<T>& g, co
   }
   __syncthreads();
 
-  // ---- the block's inverse: the substitution run on the identity, 16 columns per wave and pass.
+  // ---- the block's inverse: the substitution run on the identity, 16 columns per wave.
   // out holds W = M^-1 for the block in its own (un-reversed) index space, row-major, so that the
   // solve itself is the plain product W * B; what lies outside the b x b block is never read.
   using acc_t = typename Mfma<T>::acc_t;
   T* const out = g.out + (int64_t)(block >> 1) * (kTriPair * kTriPair) + (block & 1) * (kNbMax * kTriPair + kNbMax);
-  for (int pass = 0; pass < NB / (kTriThreads / 64); ++pass) {
-    const int slice = pass * (kTriThreads / 64) + wave;
+  {
+    const int slice = __builtin_amdgcn_readfirstlane(half == 0 ? (wave < 2 ? 7 * wave : 1 + wave) : (wave < 2 ? 1 + 5 * wave : wave == 2 ? 2 : 5));
     if (slice < nblk) {  // uniform per wave
       acc_t acc[NB];
 #pragma unroll
       for (int s = 0; s < NB; ++s)
 #pragma unroll
         for (int v = 0; v < 4; ++v) acc[s][v] = (s * kIb + 4 * l4 + v == slice * kIb + l15) ? g.unit : T(0);
-      if (nblk == NB) head_solve<T, true>(tri, kIb + 1, 1, nblk, lane, acc);
-      else head_solve<T, false>(tri, kIb + 1, 1, nblk, lane, acc);
+      if (nblk == NB) head_solve<T, true>(tri, kIb + 1, 1, nblk, lane, acc, slice);
+      else head_solve<T, false>(tri, kIb + 1, 1, nblk, lane, acc, slice);
       const int cc = orig(slice * kIb + l15);
 #pragma unroll
       for (int s = 0; s < NB; ++s) {
@@ -174,18 +181,22 @@ __device__ __forceinline__ void tri_prepare_block(const TriPrepareArgs<T>& g, co
   }
 }
 
+// The workgroups behind those of the inverses do what flow_kernel finds done (none where it does not run behind this).
 template <typename T, int MODE>
-__global__ void __launch_bounds__(kTriThreads) tri_prepare_kernel(const TriPrepareArgs<T> g) {
-  tri_prepare_block<T, MODE>(g, (int)blockIdx.x);
+__global__ void __launch_bounds__(kTriThreads) tri_prepare_kernel(const TriPrepareArgs<T> g, const FlowInit<T> init) {
+  const int bid = (int)blockIdx.x, inverses = kTriHalves * (int)((g.n + kNbMax - 1) / kNbMax);
+  if (bid >= inverses) flow_init(init, bid - inverses);
+  else tri_prepare_block<T, MODE>(g, bid / kTriHalves, bid % kTriHalves);
 }
 
-// Two sets of inverses of the same factor in one launch (they are independent): the first half of the
-// grid works on ga in MODE_A, the second half on gb in MODE_B.
+// Two sets of inverses of the same factor in one launch (they are independent): first ga in MODE_A, then gb in MODE_B.
 template <typename T, int MODE_A, int MODE_B>
-__global__ void __launch_bounds__(kTriThreads) tri_prepare_both_kernel(const TriPrepareArgs<T> ga, const TriPrepareArgs<T> gb) {
-  const int half = (int)(gridDim.x >> 1);
-  if ((int)blockIdx.x < half) tri_prepare_block<T, MODE_A>(ga, (int)blockIdx.x);
-  else tri_prepare_block<T, MODE_B>(gb, (int)blockIdx.x - half);
+__global__ void __launch_bounds__(kTriThreads) tri_prepare_both_kernel(const TriPrepareArgs<T> ga, const TriPrepareArgs<T> gb,
+                                                                       const FlowInit<T> init) {
+  const int bid = (int)blockIdx.x, inverses = kTriHalves * (int)((ga.n + kNbMax - 1) / kNbMax);
+  if (bid >= 2 * inverses) flow_init(init, bid - 2 * inverses);
+  else if (bid < inverses) tri_prepare_block<T, MODE_A>(ga, bid / kTriHalves, bid % kTriHalves);
+  else tri_prepare_block<T, MODE_B>(gb, (bid - inverses) / kTriHalves, (bid - inverses) % kTriHalves);
 }
 
 }  // namespace dla

@@ -4,6 +4,7 @@
 #include "factor_kernels.hpp"
 #include "update_kernel.hpp"
 #include "head_kernel.hpp"
+#include "tile_factor_kernel.hpp"
 #include <mutex>
 #include "host_common.hpp"
 
@@ -43,11 +44,21 @@ size_t factor_workspace_bytes_impl(int64_t n, dla_dtype dt, const dla_factor_par
   return 4 * inv_set_bytes(dt) + 4 * head_copy_bytes(dt) + 256;  // + the hand-over counters of the latency chain
 }
 
+// The largest matrix whose factorisation is one launch of tile_factor_kernel where the caller names no block size, and above
+// it blocks of 128 in the pipeline.  Below, the chain of the diagonal is what a factorisation takes, and it is shorter there
+// (us, the pipeline against one launch, LU fp64: n = 300 125 against 98, 1024 365 against 300, 2000 773 against 587, 4000 1859
+// against 1565; Cholesky fp64 125 against 89, 365 against 271, 745 against 532, 1485 against 1133); above, the products, whose
+// operands the pipeline reads less often (LU 6000 4099 against 4880).
+static int64_t tiles_max_n(dla_dtype dt, int op) {
+  if (op == OP_SUB) return dt == DLA_F64 ? 5400 : 5000;
+  return dt == DLA_F64 ? 6000 : 6400;
+}
+
 int resolve_factor_params(dla_dtype dt, int64_t n, const dla_factor_params* in, int op, FactorPlan* plan,
                           GemmSchedule* upd) {
-  (void)n;
   int b = in ? in->nb : 0;
-  if (b == 0) b = 128;
+  const bool named = b != 0;
+  if (!named) b = 128;
   const bool one_level = b >= 16 && b <= kNbMax && b % 16 == 0;
   const bool two_level = b > kNbMax && b <= 2 * kNbMax && b % 32 == 0;
   if (!one_level && !two_level) return DLA_ERR_UNSUPPORTED_PARAMS;
@@ -60,6 +71,9 @@ int resolve_factor_params(dla_dtype dt, int64_t n, const dla_factor_params* in, 
                             in->update.unroll_k != 0 || in->update.wave_m != 0 || in->update.wave_n != 0);
   // two sub-panels per panel need the pipeline's deferred bulk update and the kernel that takes depth 256
   if (two_level && (la == 0 || tiled)) return DLA_ERR_UNSUPPORTED_PARAMS;
+  const int64_t nt = (n + kTileNb - 1) / kTileNb;
+  plan->tiles = la == 1 && !tiled && defer == 0 && n > 2 * (int64_t)b && (named ? b == kTileNb : n <= tiles_max_n(dt, op)) && nt <= kTileMaxNt &&
+                (dt == DLA_F64 ? tile_workspace_bytes<double>((int)nt) : tile_workspace_bytes<float>((int)nt)) <= factor_workspace_bytes_impl(n, dt, in);
   plan->nb_outer = b;
   plan->nb = two_level ? b / 2 : b;
   plan->lookahead = la;
@@ -307,6 +321,38 @@ static GemmSchedule panel_schedule(int64_t mr) {
   return mr <= 2304 ? GemmSchedule{32, 32, 128, 8, 16, 16} : GemmSchedule{32, 32, 16, 4, 16, 16};
 }
 
+template <typename T, int KIND, int AUX>
+static int launch_tiles_as(const TileArgs<T>& a, hipStream_t st) {
+  auto kern = tile_factor_kernel<T, KIND, AUX>;
+  static LdsLimitOnce lds_limit;
+  if (!lds_limit.ensure(reinterpret_cast<const void*>(kern), tile_lds_bytes<T>())) return DLA_ERR_HIP;
+  const int tiles = tile_before<KIND>(a.nt, a.nt);
+  const dim3 grid((unsigned)(tiles < kNumCu ? tiles + 1 : kNumCu)), block(kTileThreads);
+  const double flops = (KIND == KIND_LU ? 2.0 : 1.0) * (double)a.n * (double)a.n * (double)a.n / 3.0;
+  hipEvent_t p0 = nullptr, p1 = nullptr;
+  if (profile_kernel_events(PHASE_UPDATE, flops, &p0, &p1)) hipExtLaunchKernelGGL(kern, grid, block, tile_lds_bytes<T>(), st, p0, p1, 0, a);
+  else hipLaunchKernelGGL(kern, grid, block, tile_lds_bytes<T>(), st, a);
+  return launch_status(__func__);
+}
+template <typename T, int KIND>
+static int launch_tiles(T* A, int64_t n, int64_t lda, void* ws, int* d_info, long long wait_ticks, hipStream_t st) {
+  TileArgs<T> a;
+  a.A = A;
+  a.lda = lda;
+  a.n = (int)n;
+  a.nt = (int)((n + kTileNb - 1) / kTileNb);
+  a.info = d_info;
+  a.inv = static_cast<T*>(ws);
+  a.pre = a.inv + kTileInvRing * kTileInv;
+  a.ints = reinterpret_cast<int*>(a.pre + 6 * kTileElems);
+  a.wait_ticks = wait_ticks;
+  const int count = TileFlags{a.nt}.count();
+  hipLaunchKernelGGL(tile_clear_kernel, dim3((unsigned)((count + 255) / 256)), dim3(256), 0, st, a.ints, count);
+  if (launch_status(__func__) != DLA_SUCCESS) return DLA_ERR_HIP;
+  const bool aligned = (uintptr_t)A % 128 == 0 && (lda * (int64_t)sizeof(T)) % 128 == 0;
+  return aligned ? launch_tiles_as<T, KIND, 0>(a, st) : launch_tiles_as<T, KIND, kTilePast>(a, st);
+}
+
 template <typename T, int KIND>
 static int factor_impl(T* A, int64_t n, int64_t lda, const dla_factor_params* p, void* ws, size_t ws_bytes,
                        hipStream_t st, int* d_info) {
@@ -469,6 +515,14 @@ static int factor_impl(T* A, int64_t n, int64_t lda, const dla_factor_params* p,
     std::lock_guard<std::mutex> submit_lock(submit_mutex);
     LookaheadCtx& ctx = lookahead_ctx(A);
     if (!ctx.ok) return DLA_ERR_HIP;  // (the failing call is on record)
+    if (plan.tiles && d_info && lda <= kTileMaxLd) {
+      // One launch.  It too starts behind the previous such call of the process: two of them side by side would take the
+      // compute units that the other's workgroups wait for.
+      if (hip_note(hipStreamWaitEvent(st, ctx.ev[7], 0), "hipStreamWaitEvent") != 0) return DLA_ERR_HIP;
+      const long long limit = (long long)(ctx.ticks_per_s * (0.1 + 8.0 * (2.0 * (double)n * (double)n * 256.0) / 8e12));
+      if ((rc = launch_tiles<T, KIND>(A, n, lda, ws, d_info, limit, st)) != DLA_SUCCESS) return rc;
+      return hip_note(hipEventRecord(ctx.ev[7], st), "hipEventRecord") != 0 ? (int)DLA_ERR_HIP : (int)DLA_SUCCESS;
+    }
     wait_ticks = (long long)(ctx.ticks_per_s * (0.1 + 8.0 * (2.0 * (double)n * (double)n * 2.0 * nb) / 8e12));
     hipEvent_t e_head = ctx.ev[0], e_solve = ctx.ev[1], e_bulk = ctx.ev[2], e_start = ctx.ev[3], e_strip = ctx.ev[6];
     hipEvent_t e_diag[2] = {ctx.ev[4], ctx.ev[5]};  // by step parity

@@ -325,6 +325,208 @@ __device__ inline void chol16(T (&a)[16], T (&rdiag)[16], T (&pivot)[16], int i)
   });
 }
 
+// ---- a block of up to NBM columns in LDS: S[(NBM + 1)][NBM + 1], row and column NBM are dump space; rd: [NBM] reciprocals
+// of the diagonal, [NBM] Cholesky's pivots ------------------------------------------------------------------------------
+
+// A factored 16 x 16 sub-block in registers, lane i of a 16-lane row its row i, with what goes beside it.
+template <typename T, int KIND>
+struct DiagSub {
+  T a[16], rd[16], pv[KIND == KIND_CHOL ? 16 : 1];
+  __device__ __forceinline__ void factor(int lane) {
+    if constexpr (KIND == KIND_LU) lu16(a, rd, lane & 15);
+    else chol16(a, rd, pv, lane & 15);
+  }
+  // to LDS, as the sub-block at offset o (one wave)
+  template <int NBM>
+  __device__ __forceinline__ void store(T* const S, T* const sRd, const int lane, const int o) const {
+    if (lane < 16) {
+#pragma unroll
+      for (int j = 0; j < 16; ++j) S[(o + lane) * (NBM + 1) + o + j] = a[j];  // (Cholesky: scratch above the diagonal, which nothing reads)
+    }
+    if (lane == 0) {
+#pragma unroll
+      for (int j = 0; j < 16; ++j) {
+        sRd[o + j] = rd[j];
+        if constexpr (KIND == KIND_CHOL) sRd[NBM + o + j] = pv[j];
+      }
+    }
+  }
+};
+
+// The stages of a block whose first 16 x 16 sub-block is factored (bp: its size, a multiple of 16).  store(o): waves 4 .. 7
+// write out the strip that begins at o, store_last(o) the one in front of the last sub-block's; inverse(upper, sub-block, unit, x): a lane's row (upper) or column of an inverse.
+template <typename T, int KIND, int NBM, typename Store, typename Last, typename Inverse>
+__device__ __forceinline__ void diag_stages(T* const S, T* const sRd, const int bp, const int tid, Store&& store_strip, Last&& store_last,
+                                            Inverse&& inverse) {
+  constexpr int NWAVES = kDiagThreads / 64, SLD = NBM + 1;
+  const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int l15 = lane & 15, l4 = lane >> 4;
+  const int nblk = bp / kIb;
+  auto factor_sub_block = [&](int o) {
+    DiagSub<T, KIND> d;
+#pragma unroll
+    for (int j = 0; j < 16; ++j) d.a[j] = S[(o + l15) * SLD + o + j];
+    d.factor(lane);
+    d.template store<NBM>(S, sRd, lane, o);
+  };
+  // one 16 x 16 block of the inner trailing update of the stage at offset o
+  auto update_block = [&](int o, int c0, int d0) {
+    typename Mfma<T>::acc_t acc;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) acc[v] = S[(c0 + Mfma<T>::row_of(v, lane)) * SLD + d0 + l15];
+#pragma unroll
+    for (int kk = 0; kk < 4; ++kk) {
+      const T fa = -S[(c0 + l15) * SLD + o + kk * 4 + l4];
+      const T fb = (KIND == KIND_LU) ? S[(o + kk * 4 + l4) * SLD + d0 + l15]
+                                     : S[(d0 + l15) * SLD + o + kk * 4 + l4];
+      acc = Mfma<T>::mma(fa, fb, acc);
+    }
+#pragma unroll
+    for (int v = 0; v < 4; ++v) S[(c0 + Mfma<T>::row_of(v, lane)) * SLD + d0 + l15] = acc[v];
+  };
+
+  // two independent blocks at once
+  auto update_block2 = [&](int o, int c0, int d0, int c1, int d1) {
+    typename Mfma<T>::acc_t acc0, acc1;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      acc0[v] = S[(c0 + Mfma<T>::row_of(v, lane)) * SLD + d0 + l15];
+      acc1[v] = S[(c1 + Mfma<T>::row_of(v, lane)) * SLD + d1 + l15];
+    }
+    T fa0[4], fb0[4], fa1[4], fb1[4];
+#pragma unroll
+    for (int kk = 0; kk < 4; ++kk) {
+      fa0[kk] = -S[(c0 + l15) * SLD + o + kk * 4 + l4];
+      fa1[kk] = -S[(c1 + l15) * SLD + o + kk * 4 + l4];
+      fb0[kk] = (KIND == KIND_LU) ? S[(o + kk * 4 + l4) * SLD + d0 + l15] : S[(d0 + l15) * SLD + o + kk * 4 + l4];
+      fb1[kk] = (KIND == KIND_LU) ? S[(o + kk * 4 + l4) * SLD + d1 + l15] : S[(d1 + l15) * SLD + o + kk * 4 + l4];
+    }
+#pragma unroll
+    for (int kk = 0; kk < 4; ++kk) {
+      acc0 = Mfma<T>::mma(fa0[kk], fb0[kk], acc0);
+      acc1 = Mfma<T>::mma(fa1[kk], fb1[kk], acc1);
+    }
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      S[(c0 + Mfma<T>::row_of(v, lane)) * SLD + d0 + l15] = acc0[v];
+      S[(c1 + Mfma<T>::row_of(v, lane)) * SLD + d1 + l15] = acc1[v];
+    }
+  };
+
+  // LU: blocks d, d + step, ... < nrem of one block row (row c0) of the inner trailing update, two at a time
+  auto update_row = [&](int o, int c0, int d, int step, int nrem) {
+    T fa[4];
+#pragma unroll
+    for (int kk = 0; kk < 4; ++kk) fa[kk] = -S[(c0 + l15) * SLD + o + kk * 4 + l4];
+    for (; d < nrem; d += 2 * step) {
+      const bool two = d + step < nrem;  // uniform
+      const int d0 = o + kIb + d * kIb, d1 = two ? d0 + step * kIb : d0;
+      typename Mfma<T>::acc_t acc0, acc1;
+      T fb0[4], fb1[4];
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        acc0[v] = S[(c0 + Mfma<T>::row_of(v, lane)) * SLD + d0 + l15];
+        fb0[v] = S[(o + v * 4 + l4) * SLD + d0 + l15];
+        acc1[v] = S[(c0 + Mfma<T>::row_of(v, lane)) * SLD + d1 + l15];
+        fb1[v] = S[(o + v * 4 + l4) * SLD + d1 + l15];
+      }
+      if (two) {
+#pragma unroll
+        for (int kk = 0; kk < 4; ++kk) {
+          acc0 = Mfma<T>::mma(fa[kk], fb0[kk], acc0);
+          acc1 = Mfma<T>::mma(fa[kk], fb1[kk], acc1);
+        }
+#pragma unroll
+        for (int v = 0; v < 4; ++v) S[(c0 + Mfma<T>::row_of(v, lane)) * SLD + d1 + l15] = acc1[v];
+      } else {
+#pragma unroll
+        for (int kk = 0; kk < 4; ++kk) acc0 = Mfma<T>::mma(fa[kk], fb0[kk], acc0);
+      }
+#pragma unroll
+      for (int v = 0; v < 4; ++v) S[(c0 + Mfma<T>::row_of(v, lane)) * SLD + d0 + l15] = acc0[v];
+    }
+  };
+  // One 16-wide panel of the sub-block at offset o by substitution: lane t has one column (row panel: L X = P) or one row
+  // (column panel: X U = P, Cholesky X L^T = P), and the 16 lanes behind the panel the identity, which becomes the
+  // sub-block's inverse for the panel solves behind this block.  The sub-block is uniform over the panel, so each 16-lane
+  // row keeps it in registers (lane i = its row i) and the steps take its entries as DPP broadcasts.
+  auto panel = [&](auto upper_c, int o, int rem, int t) {
+    constexpr bool UPPER = decltype(upper_c)::value, ROWP = KIND == KIND_LU && !UPPER;
+    const int e = t < rem ? o + kIb + t : NBM;  // lanes behind the panel read and write dump space
+    T f[16], rd[16], x[16];
+#pragma unroll
+    for (int j = 0; j < 16; ++j) {
+      f[j] = S[(o + l15) * SLD + o + j];
+      if (!ROWP) rd[j] = sRd[o + j];
+    }
+#pragma unroll
+    for (int j = 0; j < 16; ++j) x[j] = ROWP ? S[(o + j) * SLD + e] : S[e * SLD + o + j];
+    const int unit = t - rem;
+#pragma unroll
+    for (int j = 0; j < 16; ++j) x[j] = unit < 0 ? x[j] : (unit == j ? T(1) : T(0));
+    static_for<0, 16>([&](auto kc) {
+      constexpr int k = decltype(kc)::value;
+      if constexpr (!ROWP) x[k] *= rd[k];
+      if constexpr (UPPER) fnmac_run_each<k, k + 1, 16>(x, f, x[k]);  // U[k][j]: entry j of lane k
+      else fnmac_run_lanes<k + 1, 16>(x, f[k], x[k]);                 // L[j][k]: entry k of lane j
+    });
+#pragma unroll
+    for (int j = 0; j < 16; ++j) (ROWP ? S[(o + j) * SLD + e] : S[e * SLD + o + j]) = x[j];
+    if (unit >= 0 && unit < 16) {
+      inverse(upper_c, o / kIb, unit, x);
+    }
+  };
+
+  // inner panels: waves 0 and 1 the row panel (Cholesky: the column panel), 2 and 3 the column panel, as far as there is one
+  auto panels = [&](int o, int rem) __attribute__((always_inline)) {
+    if ((wave & 1) * 64 < rem + kIb) {
+      if (wave < 2) panel(std::false_type{}, o, rem, tid);
+      else if constexpr (KIND == KIND_LU) panel(std::true_type{}, o, rem, tid - 128);
+    }
+  };
+  for (int r = 0; r + 1 < nblk; ++r) {
+    const int o = r * kIb;
+    const int rem = bp - o - kIb;  // rows/columns to the right of / below this sub-block
+    const int nrem = rem / kIb;
+    // ---- inner panels; the other waves write out what is finished
+    if (wave >= 4) {
+      if (r > 0) store_strip(o - kIb);
+    } else {
+      panels(o, rem);
+    }
+    lds_barrier();
+    // ---- inner trailing update on MFMA.  Wave 0 updates the next diagonal sub-block first and
+    // factors it while the other waves update the remaining blocks (look-ahead inside the block).
+    if (wave == 0) {
+      update_block(o, o + kIb, o + kIb);
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup", "local");  // this wave's LDS writes before its reads below
+      factor_sub_block(o + kIb);
+    } else if constexpr (KIND == KIND_LU) {
+      // a wave stays in one block row, whose left operands it reads once; short rows are shared by several waves
+      const int parts = (NWAVES - 1) / nrem, ci = (wave - 1) % nrem, part = (wave - 1) / nrem;
+      if (part < parts) update_row(o, o + kIb + ci * kIb, ci == 0 && part == 0 ? parts : part, parts, nrem);
+    } else {
+      // q = 0 is wave 0's block; two blocks per iteration give the MFMA chains some overlap
+      for (int q = wave; q < nrem * nrem; q += 2 * (NWAVES - 1)) {
+        const int q2 = q + (NWAVES - 1);
+        const int ci = q / nrem, di = q % nrem, ci2 = q2 / nrem, di2 = q2 % nrem;
+        const bool do1 = !(KIND == KIND_CHOL && di > ci);
+        const bool do2 = q2 < nrem * nrem && !(KIND == KIND_CHOL && di2 > ci2);
+        if (do1 && do2) update_block2(o, o + kIb + ci * kIb, o + kIb + di * kIb, o + kIb + ci2 * kIb, o + kIb + di2 * kIb);
+        else if (do1) update_block(o, o + kIb + ci * kIb, o + kIb + di * kIb);
+        else if (do2) update_block(o, o + kIb + ci2 * kIb, o + kIb + di2 * kIb);
+      }
+    }
+    lds_barrier();
+  }
+  // ---- the last sub-block: its inverses
+  if (wave >= 4) {
+    if (nblk > 1) store_last(bp - 2 * kIb);
+  } else {
+    panels(bp - kIb, 0);
+  }
+}
+
 // --------------------------------------------------------------------------------------
 template <typename T>
 struct DiagArgs {
@@ -390,107 +592,6 @@ __global__ void __launch_bounds__(kDiagThreads) diag_kernel(const DiagArgs<T> g)
     }
   };
 
-  // 16 x 16 diagonal sub-block at offset o: rows to registers, factor, back to LDS (one wave)
-  auto factor_rows = [&](int o, T (&a)[16]) {
-    T rd[16], pv[KIND == KIND_CHOL ? 16 : 1];
-    if constexpr (KIND == KIND_LU) lu16(a, rd, l15);
-    else chol16(a, rd, pv, l15);
-    if (lane < 16) {
-#pragma unroll
-      for (int j = 0; j < 16; ++j)
-        S[(o + l15) * kSld + o + j] = a[j];  // (Cholesky: scratch above the diagonal, which nothing reads)
-    }
-    if (lane == 0) {
-#pragma unroll
-      for (int j = 0; j < 16; ++j) {
-        sRd[o + j] = rd[j];
-        if constexpr (KIND == KIND_CHOL) sRd[kNbMax + o + j] = pv[j];
-      }
-    }
-  };
-  auto factor_sub_block = [&](int o) {
-    T a[16];
-#pragma unroll
-    for (int j = 0; j < 16; ++j) a[j] = S[(o + l15) * kSld + o + j];
-    factor_rows(o, a);
-  };
-  // one 16 x 16 block of the inner trailing update of the stage at offset o
-  auto update_block = [&](int o, int c0, int d0) {
-    typename Mfma<T>::acc_t acc;
-#pragma unroll
-    for (int v = 0; v < 4; ++v) acc[v] = S[(c0 + Mfma<T>::row_of(v, lane)) * kSld + d0 + l15];
-#pragma unroll
-    for (int kk = 0; kk < 4; ++kk) {
-      const T fa = -S[(c0 + l15) * kSld + o + kk * 4 + l4];
-      const T fb = (KIND == KIND_LU) ? S[(o + kk * 4 + l4) * kSld + d0 + l15]
-                                     : S[(d0 + l15) * kSld + o + kk * 4 + l4];
-      acc = Mfma<T>::mma(fa, fb, acc);
-    }
-#pragma unroll
-    for (int v = 0; v < 4; ++v) S[(c0 + Mfma<T>::row_of(v, lane)) * kSld + d0 + l15] = acc[v];
-  };
-
-  // two independent blocks at once
-  auto update_block2 = [&](int o, int c0, int d0, int c1, int d1) {
-    typename Mfma<T>::acc_t acc0, acc1;
-#pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      acc0[v] = S[(c0 + Mfma<T>::row_of(v, lane)) * kSld + d0 + l15];
-      acc1[v] = S[(c1 + Mfma<T>::row_of(v, lane)) * kSld + d1 + l15];
-    }
-    T fa0[4], fb0[4], fa1[4], fb1[4];
-#pragma unroll
-    for (int kk = 0; kk < 4; ++kk) {
-      fa0[kk] = -S[(c0 + l15) * kSld + o + kk * 4 + l4];
-      fa1[kk] = -S[(c1 + l15) * kSld + o + kk * 4 + l4];
-      fb0[kk] = (KIND == KIND_LU) ? S[(o + kk * 4 + l4) * kSld + d0 + l15] : S[(d0 + l15) * kSld + o + kk * 4 + l4];
-      fb1[kk] = (KIND == KIND_LU) ? S[(o + kk * 4 + l4) * kSld + d1 + l15] : S[(d1 + l15) * kSld + o + kk * 4 + l4];
-    }
-#pragma unroll
-    for (int kk = 0; kk < 4; ++kk) {
-      acc0 = Mfma<T>::mma(fa0[kk], fb0[kk], acc0);
-      acc1 = Mfma<T>::mma(fa1[kk], fb1[kk], acc1);
-    }
-#pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      S[(c0 + Mfma<T>::row_of(v, lane)) * kSld + d0 + l15] = acc0[v];
-      S[(c1 + Mfma<T>::row_of(v, lane)) * kSld + d1 + l15] = acc1[v];
-    }
-  };
-
-  // LU: blocks d, d + step, ... < nrem of one block row (row c0) of the inner trailing update, two at a time
-  auto update_row = [&](int o, int c0, int d, int step, int nrem) {
-    T fa[4];
-#pragma unroll
-    for (int kk = 0; kk < 4; ++kk) fa[kk] = -S[(c0 + l15) * kSld + o + kk * 4 + l4];
-    for (; d < nrem; d += 2 * step) {
-      const bool two = d + step < nrem;  // uniform
-      const int d0 = o + kIb + d * kIb, d1 = two ? d0 + step * kIb : d0;
-      typename Mfma<T>::acc_t acc0, acc1;
-      T fb0[4], fb1[4];
-#pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        acc0[v] = S[(c0 + Mfma<T>::row_of(v, lane)) * kSld + d0 + l15];
-        fb0[v] = S[(o + v * 4 + l4) * kSld + d0 + l15];
-        acc1[v] = S[(c0 + Mfma<T>::row_of(v, lane)) * kSld + d1 + l15];
-        fb1[v] = S[(o + v * 4 + l4) * kSld + d1 + l15];
-      }
-      if (two) {
-#pragma unroll
-        for (int kk = 0; kk < 4; ++kk) {
-          acc0 = Mfma<T>::mma(fa[kk], fb0[kk], acc0);
-          acc1 = Mfma<T>::mma(fa[kk], fb1[kk], acc1);
-        }
-#pragma unroll
-        for (int v = 0; v < 4; ++v) S[(c0 + Mfma<T>::row_of(v, lane)) * kSld + d1 + l15] = acc1[v];
-      } else {
-#pragma unroll
-        for (int kk = 0; kk < 4; ++kk) acc0 = Mfma<T>::mma(fa[kk], fb0[kk], acc0);
-      }
-#pragma unroll
-      for (int v = 0; v < 4; ++v) S[(c0 + Mfma<T>::row_of(v, lane)) * kSld + d0 + l15] = acc0[v];
-    }
-  };
   // Rows [o, o + 16) from column o on and columns [o, o + 16) below them are final once stage o's panels are solved.
   // Waves 4 .. 7 write them out beside the next stage's panels (Cholesky: with the zeros above the diagonal, the
   // output convention), all LDS reads first.
@@ -525,14 +626,15 @@ __global__ void __launch_bounds__(kDiagThreads) diag_kernel(const DiagArgs<T> g)
   };
 
   if (wave == 0) {
-    T a[16];
+    DiagSub<T, KIND> d;
     const T* p = g.A + (int64_t)(l15 < b ? l15 : b - 1) * g.lda;
 #pragma unroll
-    for (int j = 0; j < 16; ++j) a[j] = p[j < b ? j : b - 1];
+    for (int j = 0; j < 16; ++j) d.a[j] = p[j < b ? j : b - 1];
 #pragma unroll
     for (int j = 0; j < 16; ++j)
-      if (!(l15 < b && j < b)) a[j] = (l15 == j) ? T(1) : T(0);
-    factor_rows(0, a);
+      if (!(l15 < b && j < b)) d.a[j] = (l15 == j) ? T(1) : T(0);
+    d.factor(lane);
+    d.template store<kNbMax>(S, sRd, lane, 0);
   } else if (bp <= kNbMax / 2) {
     load_rows(std::integral_constant<int, (kNbMax / 2 + NWAVES - 2) / (NWAVES - 1)>{});
   } else {
@@ -540,77 +642,12 @@ __global__ void __launch_bounds__(kDiagThreads) diag_kernel(const DiagArgs<T> g)
   }
   __syncthreads();
 
-  // One 16-wide panel of the sub-block at offset o by substitution: lane t has one column (row panel: L X = P) or one row
-  // (column panel: X U = P, Cholesky X L^T = P), and the 16 lanes behind the panel the identity, which becomes the
-  // sub-block's inverse for the panel solves behind this block.  The sub-block is uniform over the panel, so each 16-lane
-  // row keeps it in registers (lane i = its row i) and the steps take its entries as DPP broadcasts.
-  auto panel = [&](auto upper_c, int o, int rem, int t) {
-    constexpr bool UPPER = decltype(upper_c)::value, ROWP = KIND == KIND_LU && !UPPER;
-    const int e = t < rem ? o + kIb + t : kNbMax;  // lanes behind the panel read and write dump space
-    T f[16], rd[16], x[16];
+  diag_stages<T, KIND, kNbMax>(S, sRd, bp, tid, store_strip, store_strip, [&](auto upper_c, int q, int unit, const T (&x)[16]) {
+    constexpr bool UPPER = decltype(upper_c)::value;
+    T* const out = (UPPER ? g.inv_up : g.inv_lo) + q * 256;
 #pragma unroll
-    for (int j = 0; j < 16; ++j) {
-      f[j] = S[(o + l15) * kSld + o + j];
-      if (!ROWP) rd[j] = sRd[o + j];
-    }
-#pragma unroll
-    for (int j = 0; j < 16; ++j) x[j] = ROWP ? S[(o + j) * kSld + e] : S[e * kSld + o + j];
-    const int unit = t - rem;
-#pragma unroll
-    for (int j = 0; j < 16; ++j) x[j] = unit < 0 ? x[j] : (unit == j ? T(1) : T(0));
-    static_for<0, 16>([&](auto kc) {
-      constexpr int k = decltype(kc)::value;
-      if constexpr (!ROWP) x[k] *= rd[k];
-      if constexpr (UPPER) fnmac_run_each<k, k + 1, 16>(x, f, x[k]);  // U[k][j]: entry j of lane k
-      else fnmac_run_lanes<k + 1, 16>(x, f[k], x[k]);                 // L[j][k]: entry k of lane j
-    });
-#pragma unroll
-    for (int j = 0; j < 16; ++j) (ROWP ? S[(o + j) * kSld + e] : S[e * kSld + o + j]) = x[j];
-    if (unit >= 0 && unit < 16) {
-      T* const out = (UPPER ? g.inv_up : g.inv_lo) + (o / kIb) * 256;
-#pragma unroll
-      for (int j = 0; j < 16; ++j) out[UPPER ? unit * 16 + j : j * 16 + unit] = x[j];
-    }
-  };
-
-  for (int r = 0; r < nblk; ++r) {
-    const int o = r * kIb;
-    const int rem = bp - o - kIb;  // rows/columns to the right of / below this sub-block
-    const int nrem = rem / kIb;
-    // ---- inner panels: waves 0 and 1 the row panel (Cholesky: the column panel), 2 and 3 the column panel, as far as
-    // there is one; the others write out what is finished.
-    if (wave >= 4) {
-      if (r > 0) store_strip(o - kIb);
-    } else if ((wave & 1) * 64 < rem + kIb) {
-      if (wave < 2) panel(std::false_type{}, o, rem, tid);
-      else if constexpr (KIND == KIND_LU) panel(std::true_type{}, o, rem, tid - 128);
-    }
-    if (nrem == 0) break;
-    lds_barrier();
-    // ---- inner trailing update on MFMA.  Wave 0 updates the next diagonal sub-block first and
-    // factors it while the other waves update the remaining blocks (look-ahead inside the block).
-    if (wave == 0) {
-      update_block(o, o + kIb, o + kIb);
-      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup", "local");  // this wave's LDS writes before its reads below
-      factor_sub_block(o + kIb);
-    } else if constexpr (KIND == KIND_LU) {
-      // a wave stays in one block row, whose left operands it reads once; short rows are shared by several waves
-      const int parts = (NWAVES - 1) / nrem, ci = (wave - 1) % nrem, part = (wave - 1) / nrem;
-      if (part < parts) update_row(o, o + kIb + ci * kIb, ci == 0 && part == 0 ? parts : part, parts, nrem);
-    } else {
-      // q = 0 is wave 0's block; two blocks per iteration give the MFMA chains some overlap
-      for (int q = wave; q < nrem * nrem; q += 2 * (NWAVES - 1)) {
-        const int q2 = q + (NWAVES - 1);
-        const int ci = q / nrem, di = q % nrem, ci2 = q2 / nrem, di2 = q2 % nrem;
-        const bool do1 = !(KIND == KIND_CHOL && di > ci);
-        const bool do2 = q2 < nrem * nrem && !(KIND == KIND_CHOL && di2 > ci2);
-        if (do1 && do2) update_block2(o, o + kIb + ci * kIb, o + kIb + di * kIb, o + kIb + ci2 * kIb, o + kIb + di2 * kIb);
-        else if (do1) update_block(o, o + kIb + ci * kIb, o + kIb + di * kIb);
-        else if (do2) update_block(o, o + kIb + ci2 * kIb, o + kIb + di2 * kIb);
-      }
-    }
-    lds_barrier();
-  }
+    for (int j = 0; j < 16; ++j) out[UPPER ? unit * 16 + j : j * 16 + unit] = x[j];
+  });
 
   // ---- the last sub-block; breakdown: the first pivot that is zero (LU) or not positive (Cholesky)
   if (wave >= 4) store_strip(bp - kIb);

@@ -85,10 +85,10 @@ constexpr size_t kHandoverSelftestBytes = 8192;
 int handover_selftest_impl(void* scratch, hipStream_t st, int* d_info);
 // What a dla_factor_params resolves to.  nb: the width of the sub-panel one diagonal-block kernel factors
 // (= nb_outer up to 128, else half of it); two_level: bulk updates may run two sub-panels deep, while the
-// trailing matrix has at least defer_min_rows rows.
+// trailing matrix has at least defer_min_rows rows; tiles: one launch of 64 x 64 tiles (where the call has an info pointer).
 struct FactorPlan {
   int nb_outer, nb, lookahead;
-  bool two_level;
+  bool two_level, tiles;
   int64_t defer_min_rows;
 };
 int resolve_factor_params(dla_dtype dt, int64_t n, const dla_factor_params* in, int op, FactorPlan* plan,

@@ -92,11 +92,15 @@ typedef struct {
  * nb = 128 the same two-level form (depth 256, sub-panels of 128) is used on its own accord while the
  * trailing matrix is large; defer_min_rows moves that threshold.
  *
+ * nb = 64 with lookahead = 1 and d_info, and nb = 0 for matrices of a few thousand rows (dla_default_params tells: it gives
+ * 64 there), run as one or two launches of 64 x 64 tiles whose workgroups wait for each other; nb = 0 beyond that as blocks of
+ * 128 down to the last few thousand rows, and those in tiles.
+ *
  * There is no separate inner block size of the diagonal-block kernel: it works in stages of 16 columns,
  * the edge of the MFMA block, and nothing else is instantiated.
  */
 typedef struct {
-  int nb;        /* block size (0 = default 128); see above                                     */
+  int nb;        /* block size (0 = the library's choice by n); see above                       */
   int lookahead; /* 0: one stream, strictly sequential steps; 1: the next diagonal block is factored
                     while panel solves and trailing update of this step run on helper streams, and
                     the kernels of that chain wait for each other inside the kernels (needs kernels
@@ -339,6 +343,13 @@ int dla_handover_selftest(void* d_scratch, size_t scratch_bytes, void* hip_strea
  */
 int dla_solve_giveup_selftest(int kind, const void* d_f, int64_t n, int64_t lda, void* d_b, int64_t nrhs, int64_t ldb, dla_dtype dt,
                               void* d_workspace, size_t workspace_bytes, void* hip_stream);
+
+/*
+ * The same for factorisations in tiles (n from 65 to 8192): kind 0 as lu_factor, 1 as cholesky_factor, every wait gives up at
+ * once.  The launches end, *d_info is -1 and the content of A unspecified.
+ */
+int dla_factor_giveup_selftest(int kind, void* d_a, int64_t n, int64_t lda, dla_dtype dt, void* d_workspace, size_t workspace_bytes,
+                               void* hip_stream, int* d_info);
 
 const char* dla_strerror(int code);
 /*

@@ -97,6 +97,8 @@ def _load() -> ctypes.CDLL:
     lib.dla_handover_selftest.restype = ci
     lib.dla_solve_giveup_selftest.argtypes = [ci] + lib.lu_solve.argtypes
     lib.dla_solve_giveup_selftest.restype = ci
+    lib.dla_factor_giveup_selftest.argtypes = [ci, vp, i64, i64, ci, vp, sz, vp, vp]
+    lib.dla_factor_giveup_selftest.restype = ci
     lib.dla_rank_update.argtypes = [ci, vp, vp, vp, i64, i64, i64, ci, vp]
     lib.dla_rank_update.restype = ci
     lib.dla_gemm_choice.argtypes = [ci, i64, i64, i64, i64, i64, ci, ctypes.POINTER(ci), ctypes.POINTER(ci)]
@@ -380,6 +382,17 @@ def solve_giveup_selftest(kind: int, f, b, stream=None):
     def call(*args):
         return lib.dla_solve_giveup_selftest(kind, *args)
     return _solve(call, "dla_solve_giveup_selftest", f, b, None, stream)
+
+
+def factor_giveup_selftest(kind: int, a, stream=None) -> int:
+    """A factorisation in tiles whose waits all give up at once; returns what it reported (-1 expected)."""
+    import torch
+    (ap, lda), n, dt = _matrix(a, "a"), a.shape[0], _dtype_code(a)
+    ws, wsp, wsb = _workspace(factor_workspace_bytes(n, dt), a.device)
+    info = torch.zeros(1, dtype=torch.int32, device="cuda")
+    _check(lib.dla_factor_giveup_selftest(kind, ap, n, lda, dt, wsp, wsb, ctypes.c_void_p(_stream_ptr(stream)),
+                                          ctypes.c_void_p(info.data_ptr())), "dla_factor_giveup_selftest")
+    return int(info.item())
 
 
 def mfma_peak(dt: int = DLA_F64, stream=None) -> float:

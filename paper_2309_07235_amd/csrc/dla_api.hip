@@ -660,6 +660,18 @@ int dla_solve_giveup_selftest(int kind, const void* d_f, int64_t n, int64_t lda,
   return rc < 0 ? rc - 1 : rc;  // (kind comes first here)
 }
 
+int dla_factor_giveup_selftest(int kind, void* d_a, int64_t n, int64_t lda, dla_dtype dt, void* d_workspace, size_t workspace_bytes,
+                               void* hip_stream, int* d_info) {
+  if (kind != 0 && kind != 1) return -1;
+  if (!d_a || ((uintptr_t)d_a % (size_t)esize(dt))) return -2;
+  if (n <= 0) return -3;
+  if (lda < n) return -4;
+  if (dt != DLA_F64 && dt != DLA_F32) return -5;
+  if (!d_info) return -9;
+  hip_clear_stale_error();
+  return tiles_giveup_impl(kind, d_a, n, lda, dt, d_workspace, workspace_bytes, static_cast<hipStream_t>(hip_stream), d_info);
+}
+
 int dla_handover_selftest(void* d_scratch, size_t scratch_bytes, void* hip_stream, int* d_info) {
   if (!d_scratch || ((uintptr_t)d_scratch % 256)) return -1;
   if (scratch_bytes < kHandoverSelftestBytes) return -2;

@@ -44,14 +44,27 @@ size_t factor_workspace_bytes_impl(int64_t n, dla_dtype dt, const dla_factor_par
   return 4 * inv_set_bytes(dt) + 4 * head_copy_bytes(dt) + 256;  // + the hand-over counters of the latency chain
 }
 
-// The largest matrix whose factorisation is one launch of tile_factor_kernel where the caller names no block size, and above
-// it blocks of 128 in the pipeline.  Below, the chain of the diagonal is what a factorisation takes, and it is shorter there
-// (us, the pipeline against one launch, LU fp64: n = 300 125 against 98, 1024 365 against 300, 2000 773 against 587, 4000 1859
-// against 1565; Cholesky fp64 125 against 89, 365 against 271, 745 against 532, 1485 against 1133); above, the products, whose
-// operands the pipeline reads less often (LU 6000 4099 against 4880).
-static int64_t tiles_max_n(dla_dtype dt, int op) {
-  if (op == OP_SUB) return dt == DLA_F64 ? 5400 : 5000;
-  return dt == DLA_F64 ? 6000 : 6400;
+// Matrices that tile_factor_kernel's form takes where the caller names no block size: up to max_n, from two_from on in two
+// launches.  A larger one is factored in the pipeline, by blocks of 128, down to a tail of rows.  Below, the chain of the diagonal is
+// what a factorisation takes, and it is shorter there; above, the products, whose operands the pipeline reads less often.
+// us, the pipeline / one launch / two launches (the second: two tiles to a compute unit, but 20 us of events):
+//   LU fp64        n = 300 125 / 98 / -, 1024 365 / 300 / 315, 3500 1585 / 1150 / 1187, 4000 1859 / 1570 / 1420, 5600 3528 / 4013 / 3052,
+//                  6400 4662 / 5866 / 4278, 8000 8040 / 11085 / 8470
+//   Cholesky fp64  n = 300 125 / 89 / -, 1024 365 / 271 / 275, 4000 1505 / 1128 / 1214, 4800 1930 / 1630 / 1642, 5600 2510 / 2410 / 2270,
+//                  6400 3222 / 3393 / 3112, 8000 5270 / 6256 / 5600
+//   LU fp32        n = 300 111 / 81 / -, 4000 1516 / 1173 / 1197, 4800 1920 / 1839 / 1640, 5600 2510 / 2928 / 2337, 6400 3190 / 4293 / 3319
+//   Cholesky fp32  n = 300 108 / 78 / -, 4000 1400 / 1012 / 1225, 4800 1720 / 1487 / 1655, 5600 2100 / 2215 / 2260 (with rows 16 longer
+//                  2130 / 1760 / 1945), 6400 2500 / 3150 / 3012
+//   n = 7000       LU fp64 6880 / - / 5574, Cholesky fp64 4313 / - / 3348
+// tail: how many rows the pipeline leaves to it.  n = 8192, all in the pipeline, then with tails of 3000, 4000, 5000, 5800, 6600:
+// LU fp64 8466, 8326 8185 8095 8063 8174; Cholesky fp64 5382, 5210 5146 5269 5324 5408; LU fp32 5177, 4913 4949 5050 5115 5451;
+// Cholesky fp32 3782, 3583 3558 3781 4120 4511 (rows 2^15 bytes apart; 16 elements more 3738, 3559 3452 3429 3718 3828).
+struct TileRange {
+  int64_t two_from, max_n, tail;
+};
+static TileRange tile_range(dla_dtype dt, int op) {
+  if (op == OP_SUB) return dt == DLA_F64 ? TileRange{3700, 7200, 5800} : TileRange{4300, 5600, 4000};
+  return dt == DLA_F64 ? TileRange{4800, 7200, 4000} : TileRange{5400, 5400, 4000};
 }
 
 int resolve_factor_params(dla_dtype dt, int64_t n, const dla_factor_params* in, int op, FactorPlan* plan,
@@ -72,8 +85,9 @@ int resolve_factor_params(dla_dtype dt, int64_t n, const dla_factor_params* in, 
   // two sub-panels per panel need the pipeline's deferred bulk update and the kernel that takes depth 256
   if (two_level && (la == 0 || tiled)) return DLA_ERR_UNSUPPORTED_PARAMS;
   const int64_t nt = (n + kTileNb - 1) / kTileNb;
-  plan->tiles = la == 1 && !tiled && defer == 0 && n > 2 * (int64_t)b && (named ? b == kTileNb : n <= tiles_max_n(dt, op)) && nt <= kTileMaxNt &&
+  plan->tiles = la == 1 && !tiled && defer == 0 && n > 2 * (int64_t)b && (named ? b == kTileNb : n <= tile_range(dt, op).max_n) && nt <= kTileMaxNt &&
                 (dt == DLA_F64 ? tile_workspace_bytes<double>((int)nt) : tile_workspace_bytes<float>((int)nt)) <= factor_workspace_bytes_impl(n, dt, in);
+  plan->tail = la == 1 && !tiled && defer == 0 && !named && n > tile_range(dt, op).max_n;
   plan->nb_outer = b;
   plan->nb = two_level ? b / 2 : b;
   plan->lookahead = la;
@@ -334,13 +348,41 @@ static int launch_tiles_as(const TileArgs<T>& a, hipStream_t st) {
   else hipLaunchKernelGGL(kern, grid, block, tile_lds_bytes<T>(), st, a);
   return launch_status(__func__);
 }
+// The same in two launches: `clear` has happened on st (e_start rides behind it), the tiles' workgroups run on `side`.
+template <typename T, int KIND, int AUX>
+static int launch_tiles_two_as(const TileArgs<T>& a, hipStream_t st, hipStream_t side, hipEvent_t e_start, hipEvent_t e_done) {
+  auto chain = tile_chain_kernel<T, KIND>;
+  auto owners = tile_owner_kernel<T, KIND, AUX>;
+  static LdsLimitOnce chain_limit, owner_limit;
+  if (!chain_limit.ensure(reinterpret_cast<const void*>(chain), tile_lds_bytes<T>()) ||
+      !owner_limit.ensure(reinterpret_cast<const void*>(owners), tile_owner_lds_bytes<T>()))
+    return DLA_ERR_HIP;
+  if (hip_note(hipStreamWaitEvent(side, e_start, 0), "hipStreamWaitEvent") != 0) return DLA_ERR_HIP;
+  hipLaunchKernelGGL(chain, dim3(1), dim3(kTileThreads), tile_lds_bytes<T>(), st, a);
+  if (launch_status(__func__) != DLA_SUCCESS) return DLA_ERR_HIP;
+  const int tiles = tile_before<KIND>(a.nt, a.nt), most = 2 * (kNumCu - 1);
+  const double flops = (KIND == KIND_LU ? 2.0 : 1.0) * (double)a.n * (double)a.n * (double)a.n / 3.0;
+  hipEvent_t p0 = nullptr, p1 = nullptr;
+  const dim3 grid((unsigned)(tiles < most ? tiles : most)), block(kTileOwnerThreads);
+  if (profile_kernel_events(PHASE_UPDATE, flops, &p0, &p1)) {
+    hipExtLaunchKernelGGL(owners, grid, block, tile_owner_lds_bytes<T>(), side, p0, p1, 0, a);
+    if (launch_status(__func__) != DLA_SUCCESS || hip_note(hipEventRecord(e_done, side), "hipEventRecord") != 0) return DLA_ERR_HIP;
+  } else {
+    hipExtLaunchKernelGGL(owners, grid, block, tile_owner_lds_bytes<T>(), side, nullptr, e_done, 0, a);
+    if (launch_status(__func__) != DLA_SUCCESS) return DLA_ERR_HIP;
+  }
+  return hip_note(hipStreamWaitEvent(st, e_done, 0), "hipStreamWaitEvent") != 0 ? (int)DLA_ERR_HIP : (int)DLA_SUCCESS;
+}
 template <typename T, int KIND>
-static int launch_tiles(T* A, int64_t n, int64_t lda, void* ws, int* d_info, long long wait_ticks, hipStream_t st) {
+static int launch_tiles(T* A, int64_t n, int64_t lda, int64_t k0, void* ws, const int* broken, int* d_info, long long wait_ticks,
+                        hipStream_t st, hipStream_t side, hipEvent_t e_start, hipEvent_t e_done) {
   TileArgs<T> a;
   a.A = A;
   a.lda = lda;
   a.n = (int)n;
   a.nt = (int)((n + kTileNb - 1) / kTileNb);
+  a.k0 = (int)k0;
+  a.broken = broken;
   a.info = d_info;
   a.inv = static_cast<T*>(ws);
   a.pre = a.inv + kTileInvRing * kTileInv;
@@ -350,6 +392,10 @@ static int launch_tiles(T* A, int64_t n, int64_t lda, void* ws, int* d_info, lon
   hipLaunchKernelGGL(tile_clear_kernel, dim3((unsigned)((count + 255) / 256)), dim3(256), 0, st, a.ints, count);
   if (launch_status(__func__) != DLA_SUCCESS) return DLA_ERR_HIP;
   const bool aligned = (uintptr_t)A % 128 == 0 && (lda * (int64_t)sizeof(T)) % 128 == 0;
+  if (n >= tile_range(sizeof(T) == 8 ? DLA_F64 : DLA_F32, KIND == KIND_LU ? OP_SUB : OP_SUB_NT_LOWER).two_from) {
+    if (hip_note(hipEventRecord(e_start, st), "hipEventRecord") != 0) return DLA_ERR_HIP;
+    return aligned ? launch_tiles_two_as<T, KIND, 0>(a, st, side, e_start, e_done) : launch_tiles_two_as<T, KIND, kTilePast>(a, st, side, e_start, e_done);
+  }
   return aligned ? launch_tiles_as<T, KIND, 0>(a, st) : launch_tiles_as<T, KIND, kTilePast>(a, st);
 }
 
@@ -520,14 +566,19 @@ static int factor_impl(T* A, int64_t n, int64_t lda, const dla_factor_params* p,
       // compute units that the other's workgroups wait for.
       if (hip_note(hipStreamWaitEvent(st, ctx.ev[7], 0), "hipStreamWaitEvent") != 0) return DLA_ERR_HIP;
       const long long limit = (long long)(ctx.ticks_per_s * (0.1 + 8.0 * (2.0 * (double)n * (double)n * 256.0) / 8e12));
-      if ((rc = launch_tiles<T, KIND>(A, n, lda, ws, d_info, limit, st)) != DLA_SUCCESS) return rc;
+      if ((rc = launch_tiles<T, KIND>(A, n, lda, 0, ws, nullptr, d_info, limit, st, ctx.bulk, ctx.ev[3], ctx.ev[2])) != DLA_SUCCESS) return rc;
       return hip_note(hipEventRecord(ctx.ev[7], st), "hipEventRecord") != 0 ? (int)DLA_ERR_HIP : (int)DLA_SUCCESS;
     }
     wait_ticks = (long long)(ctx.ticks_per_s * (0.1 + 8.0 * (2.0 * (double)n * (double)n * 2.0 * nb) / 8e12));
     hipEvent_t e_head = ctx.ev[0], e_solve = ctx.ev[1], e_bulk = ctx.ev[2], e_start = ctx.ev[3], e_strip = ctx.ev[6];
     hipEvent_t e_diag[2] = {ctx.ev[4], ctx.ev[5]};  // by step parity
     constexpr int SOP = (KIND == KIND_LU) ? OP_SUB : OP_SUB_NT;
-    const int nsteps = (int)((n + nb - 1) / nb) - 1;  // steps that have a panel behind the diagonal block
+    // steps that have a panel behind the diagonal block.  The last rows in tiles: the last step of the pipeline then leaves out
+    // the next diagonal block and puts nothing off.
+    const int64_t tail_max = plan.tail && d_info && lda <= kTileMaxLd ? tile_range(dt, op).tail : 0;
+    const int to_tail = tail_max > 0 ? (int)((n - tail_max + nb - 1) / nb) : 0;  // steps in front of them
+    const int64_t tail = to_tail > 0 ? n - (int64_t)to_tail * nb : 0;
+    const int nsteps = tail > 0 ? to_tail : (int)((n + nb - 1) / nb) - 1;
     bool bulk_pending = false;
     // Two-level blocking of the bulk update while the trailing matrix is large (the bulk stream is then the
     // longest): every other step puts its bulk update off (owed), and the step after it carries both
@@ -629,7 +680,7 @@ static int factor_impl(T* A, int64_t n, int64_t lda, const dla_factor_params* p,
         const int64_t rest = mr - bn2;
         // put the bulk update off when the step after this one can carry it: full blocks N2, N3 and
         // two more behind them, and a trailing matrix large enough for the bulk stream to be the longest
-        if (!owed && auto_tile && plan.two_level && mr >= plan.defer_min_rows && rest >= 4 * (int64_t)nb) {
+        if (!owed && auto_tile && plan.two_level && mr >= plan.defer_min_rows && rest >= 4 * (int64_t)nb && !(tail > 0 && step + 1 == nsteps)) {
           owed = true;
           after_wide = false;
           return DLA_SUCCESS;
@@ -678,6 +729,7 @@ static int factor_impl(T* A, int64_t n, int64_t lda, const dla_factor_params* p,
       int head_wgs = 0, r;
       if ((r = launch_head<T, KIND>(ha, ctx.head, e_head, &head_wgs)) != DLA_SUCCESS) return r;
       heads_done += head_wgs;
+      if (tail > 0 && step + 1 == nsteps) return DLA_SUCCESS;
       if (!chained && hip_note(hipStreamWaitEvent(st, e_head, 0), "hipStreamWaitEvent") != 0) return DLA_ERR_HIP;
       if ((r = diag(k0 + b, step + 1, st, chained ? nullptr : e_diag[(step + 1) & 1])) != DLA_SUCCESS) return r;
       return DLA_SUCCESS;
@@ -711,6 +763,11 @@ static int factor_impl(T* A, int64_t n, int64_t lda, const dla_factor_params* p,
     if (hip_note(hipStreamWaitEvent(st, e_head, 0), "hipStreamWaitEvent") != 0) return DLA_ERR_HIP;
     if (hip_note(hipStreamWaitEvent(st, e_strip, 0), "hipStreamWaitEvent") != 0) return DLA_ERR_HIP;
     if (bulk_pending && hip_note(hipStreamWaitEvent(st, e_bulk, 0), "hipStreamWaitEvent") != 0) return DLA_ERR_HIP;
+    if (tail > 0) {
+      const int64_t k0 = n - tail;
+      if ((rc = launch_tiles<T, KIND>(A + k0 * lda + k0, tail, lda, k0, ws, chain + 2, d_info, wait_ticks, st, ctx.bulk, e_start, e_bulk)) != DLA_SUCCESS)
+        return rc;
+    }
     if (hip_note(hipEventRecord(e_call_done, st), "hipEventRecord") != 0) return DLA_ERR_HIP;
   }
   if (KIND == KIND_CHOL && n > 1 && !early_zero) {
@@ -719,6 +776,24 @@ static int factor_impl(T* A, int64_t n, int64_t lda, const dla_factor_params* p,
     if (launch_status(__func__) != DLA_SUCCESS) return DLA_ERR_HIP;
   }
   return DLA_SUCCESS;
+}
+
+// Diagnostic: the tiles' launches with waits that give up at once.
+template <typename T, int KIND>
+static int tiles_giveup(T* A, int64_t n, int64_t lda, void* ws, size_t ws_bytes, hipStream_t st, int* d_info) {
+  const int nt = (int)((n + kTileNb - 1) / kTileNb);
+  if (nt < 2 || nt > kTileMaxNt || lda > kTileMaxLd) return DLA_ERR_UNSUPPORTED_PARAMS;
+  if (!ws || ws_bytes < tile_workspace_bytes<T>(nt) || ((uintptr_t)ws % 256)) return DLA_ERR_WORKSPACE;
+  LookaheadCtx& ctx = lookahead_ctx(A);
+  if (!ctx.ok) return DLA_ERR_HIP;
+  return launch_tiles<T, KIND>(A, n, lda, 0, ws, nullptr, d_info, -1, st, ctx.bulk, ctx.ev[3], ctx.ev[2]);
+}
+int tiles_giveup_impl(int kind, void* A, int64_t n, int64_t lda, dla_dtype dt, void* ws, size_t ws_bytes, hipStream_t st, int* d_info) {
+  if (dt == DLA_F64)
+    return kind == KIND_LU ? tiles_giveup<double, KIND_LU>((double*)A, n, lda, ws, ws_bytes, st, d_info)
+                           : tiles_giveup<double, KIND_CHOL>((double*)A, n, lda, ws, ws_bytes, st, d_info);
+  return kind == KIND_LU ? tiles_giveup<float, KIND_LU>((float*)A, n, lda, ws, ws_bytes, st, d_info)
+                         : tiles_giveup<float, KIND_CHOL>((float*)A, n, lda, ws, ws_bytes, st, d_info);
 }
 
 template <typename T>

@@ -41,11 +41,13 @@ struct TileArgs {
   T* A;
   int64_t lda;
   int n, nt;        // order; tiles per side
+  int k0;           // what lies in front of the matrix, factored already
+  const int* broken; // or null: set where that went wrong
   int* info;
   T* inv;           // [kTileInvRing][2][4][256]: inverted sub-blocks, row-major
   T* pre;           // [2][3][64 x 64]: unsolved (s, s+1), (s+1, s) and (s+1, s+1), by parity of s + 1
   int* ints;        // TileFlags
-  long long wait_ticks;
+  long long wait_ticks;  // below 0: a wait gives up at once
 };
 // Flags and counters: a wait gave up, tiles taken; then a flag per tile and what belongs to the blocks of the diagonal.
 struct TileFlags {
@@ -139,7 +141,7 @@ __device__ __forceinline__ void tile_spin(int* ints, long long limit, int pause,
     const long long t0 = wall_clock64();
     for (int spins = 0;; ++spins) {
       if (__builtin_amdgcn_ballot_w64(!ok()) == 0) break;
-      if (spins % 32 == 31) {
+      if (spins % 32 == 31 || limit < 0) {
         if (__builtin_amdgcn_ballot_w64(__hip_atomic_load(ints, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) != 0) break;
         if (wall_clock64() - t0 > limit) {
           __hip_atomic_store(ints, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -353,11 +355,15 @@ __device__ __forceinline__ void tile_chain(const TileArgs<T>& g, T* const smem) 
     }
     lds_barrier();
   }
-  if (threadIdx.x == 0) *g.info = __hip_atomic_load(g.ints + TileFlags::kGaveUp, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0 ? -1 : info;
+  if (threadIdx.x == 0) {
+    const int before = g.k0 > 0 ? *g.info : 0;
+    const bool bad = __hip_atomic_load(g.ints + TileFlags::kGaveUp, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0 || (g.broken && *g.broken != 0);
+    *g.info = bad ? -1 : before != 0 ? before : info != 0 ? g.k0 + info : 0;
+  }
 }
 
-// ---- the workgroup of tile (i, j).  AUX: how other tiles are read (0 through the L2, kTilePast)
-template <typename T, int KIND, int AUX>
+// ---- the workgroup of tile (i, j), of WAVES waves.  AUX: how other tiles are read (0 through the L2, kTilePast)
+template <typename T, int KIND, int AUX, int WAVES>
 __device__ __forceinline__ void tile_owner(const TileArgs<T>& g, T* const smem, const int i, const int j) {
   using acc_t = typename Mfma<T>::acc_t;
   constexpr bool LU = KIND == KIND_LU;
@@ -372,8 +378,10 @@ __device__ __forceinline__ void tile_owner(const TileArgs<T>& g, T* const smem, 
   // a tile's resource: rows beyond the matrix are beyond its extent
   auto res_of = [&](int r, int c) { return __builtin_amdgcn_make_buffer_rsrc(tile_at(r, c), 0, ((valid(r) - 1) * ld + kTileNb) * E, kFlags); };
   const int rows = valid(i), cols = valid(j);
-  // this wave's 32 x 32 of the tile and half of each product's k: waves 4 .. 7 start from zero and are added at the end
-  const int r0 = (wave >> 1 & 1) * 2 * kIb, c0 = (wave & 1) * 2 * kIb, khalf = wave >> 2;
+  // this wave's 32 x 32 of the tile; with eight waves also half of each product's k, where waves 4 .. 7 start from zero and are
+  // added at the end
+  constexpr int NT = WAVES * 64;
+  const int r0 = (wave >> 1 & 1) * 2 * kIb, c0 = (wave & 1) * 2 * kIb, khalf = WAVES == 8 ? wave >> 2 : 0;
   acc_t acc[2][2];
   {
     const __amdgpu_buffer_rsrc_t rs = res_of(i, j);
@@ -392,13 +400,13 @@ __device__ __forceinline__ void tile_owner(const TileArgs<T>& g, T* const smem, 
   if (!LU && i > j) {  // the tile above the diagonal
     T* const Z = tile_at(j, i);
 #pragma unroll
-    for (int e = 0; e < kTileElems / kTileThreads; ++e) {
-      const int r = wave + e * 8;
+    for (int e = 0; e < kTileElems / NT; ++e) {
+      const int r = wave + e * WAVES;
       if (r < cols && lane < rows) Z[(int64_t)r * g.lda + lane] = T(0);
     }
   }
 
-  // ---- the products in front of it.  k of a fragment's step e: 32 khalf + 8 (e / 2) + 2 l4 + e % 2
+  // ---- the products in front of it.  k of a fragment's step e: 32 half + 8 (e / 2) + 2 l4 + e % 2
   const int depth = i == j ? s - 1 : s;  // (block (s, s) gets its last product on the diagonal's chain)
   T a[2][2][8], b[2][2][8];
   int avo[2], bvo[2];
@@ -408,7 +416,7 @@ __device__ __forceinline__ void tile_owner(const TileArgs<T>& g, T* const smem, 
     avo[q] = r < rows ? (r * ld + kk) * E : kOob;
     bvo[q] = c < cols ? (LU ? kk * ld + c : c * ld + kk) * E : kOob;
   }
-  auto fetch = [&](auto xc, int k) __attribute__((always_inline)) {
+  auto fetch = [&](auto xc, int k, int half) __attribute__((always_inline)) {  // (half: of a wave that has both)
     constexpr int X = decltype(xc)::value;
     const __amdgpu_buffer_rsrc_t ra = __builtin_amdgcn_make_buffer_rsrc(tile_at(i, k), 0, (kTileNb - 1) * ld * E + kTileNb * E, kFlags);
     const __amdgpu_buffer_rsrc_t rb = __builtin_amdgcn_make_buffer_rsrc(LU ? tile_at(k, j) : tile_at(j, k), 0, (kTileNb - 1) * ld * E + kTileNb * E, kFlags);
@@ -427,12 +435,12 @@ __device__ __forceinline__ void tile_owner(const TileArgs<T>& g, T* const smem, 
     for (int e = 0; e < 8; e += 2)
 #pragma unroll
       for (int q = 0; q < 2; ++q) {
-        pair(ra, avo[q], 4 * e * E, a[X][q][e], a[X][q][e + 1]);
+        pair(ra, avo[q], (32 * half + 4 * e) * E, a[X][q][e], a[X][q][e + 1]);
         if constexpr (LU) {
-          b[X][q][e] = tile_load<AUX>(rb, bvo[q], 4 * e * ld * E, (T*)nullptr);
-          b[X][q][e + 1] = tile_load<AUX>(rb, bvo[q], (4 * e + 1) * ld * E, (T*)nullptr);
+          b[X][q][e] = tile_load<AUX>(rb, bvo[q], (32 * half + 4 * e) * ld * E, (T*)nullptr);
+          b[X][q][e + 1] = tile_load<AUX>(rb, bvo[q], (32 * half + 4 * e + 1) * ld * E, (T*)nullptr);
         } else {
-          pair(rb, bvo[q], 4 * e * E, b[X][q][e], b[X][q][e + 1]);
+          pair(rb, bvo[q], (32 * half + 4 * e) * E, b[X][q][e], b[X][q][e + 1]);
         }
       }
   };
@@ -465,7 +473,7 @@ __device__ __forceinline__ void tile_owner(const TileArgs<T>& g, T* const smem, 
         const unsigned both = (unsigned)miss | (unsigned)(miss >> 32);
         ready = both ? __builtin_ctz(both) : 32;
         if (ready) break;
-        if (spins % 32 == 31) {
+        if (spins % 32 == 31 || g.wait_ticks < 0) {
           if (__builtin_amdgcn_ballot_w64(tile_flag(g.ints)) != 0) ready = 1;
           if (wall_clock64() - t0 > g.wait_ticks) {
             __hip_atomic_store(g.ints, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -482,21 +490,30 @@ __device__ __forceinline__ void tile_owner(const TileArgs<T>& g, T* const smem, 
     tile_order();
     if (ready > depth - k) ready = depth - k;
     const int end = k + ready;
-    fetch(h0{}, k);
-    for (; k < end; k += 2) {
-      if (k + 1 < end) fetch(h1{}, k + 1);
-      multiply(h0{});
-      if (k + 1 >= end) {
-        ++k;
-        break;
+    fetch(h0{}, k, 0);
+    if constexpr (WAVES == 8) {
+      for (; k < end; k += 2) {
+        if (k + 1 < end) fetch(h1{}, k + 1, 0);
+        multiply(h0{});
+        if (k + 1 >= end) {
+          ++k;
+          break;
+        }
+        if (k + 2 < end) fetch(h0{}, k + 2, 0);
+        multiply(h1{});
       }
-      if (k + 2 < end) fetch(h0{}, k + 2);
-      multiply(h1{});
+    } else {
+      for (; k < end; ++k) {
+        fetch(h1{}, k, 1);
+        multiply(h0{});
+        if (k + 1 < end) fetch(h0{}, k + 1, 0);
+        multiply(h1{});
+      }
     }
     lds_barrier();  // (shared[0] is read)
   }
 
-  // ---- the halves of k added up, in LDS
+  // ---- the tile to LDS, the halves of k added up
   T* const P = smem;
   T* const D = P + kTileNb * kTileLd;
   T* const sInv = D + kTileNb * kTileLd;
@@ -508,10 +525,12 @@ __device__ __forceinline__ void tile_owner(const TileArgs<T>& g, T* const smem, 
 #pragma unroll
         for (int v = 0; v < 4; ++v) acc[p][q][v] = f(r0 + p * kIb + Mfma<T>::row_of(v, lane), c0 + q * kIb + l15, (T)acc[p][q][v]);
   };
-  if (khalf != 0) each([&](int r, int c, T x) { return P[r * kTileLd + c] = x; });
-  lds_barrier();
-  if (khalf == 0) {
-    each([&](int r, int c, T x) { return P[r * kTileLd + c] += x; });
+  if constexpr (WAVES == 8) {
+    if (khalf != 0) each([&](int r, int c, T x) { return P[r * kTileLd + c] = x; });
+    lds_barrier();
+    if (khalf == 0) each([&](int r, int c, T x) { return P[r * kTileLd + c] += x; });
+  } else {
+    each([&](int r, int c, T x) { return P[r * kTileLd + c] = x; });
   }
   // ---- unsolved, for the diagonal's chain (the column panel's transposed)
   if (far == s + 1 || i == j) {
@@ -530,16 +549,17 @@ __device__ __forceinline__ void tile_owner(const TileArgs<T>& g, T* const smem, 
   {
     const T* const src = tile_at(s, s);
     const T* const inv = g.inv + (int64_t)(s % kTileInvRing) * kTileInv + (LU && i > j ? kTileSub * 256 : 0);
-    T d[kTileElems / kTileThreads], w[2];
+    constexpr int W = kTileSub * 256 / NT;
+    T d[kTileElems / NT], w[W];
 #pragma unroll
-    for (int e = 0; e < kTileElems / kTileThreads; ++e) d[e] = tile_get(src + (int64_t)(wave + e * 8) * g.lda + lane);
+    for (int e = 0; e < kTileElems / NT; ++e) d[e] = tile_get(src + (int64_t)(wave + e * WAVES) * g.lda + lane);
 #pragma unroll
-    for (int e = 0; e < 2; ++e) w[e] = tile_get(inv + tid + e * kTileThreads);
+    for (int e = 0; e < W; ++e) w[e] = tile_get(inv + tid + e * NT);
 #pragma unroll
-    for (int e = 0; e < kTileElems / kTileThreads; ++e) D[(wave + e * 8) * kTileLd + lane] = d[e];
+    for (int e = 0; e < kTileElems / NT; ++e) D[(wave + e * WAVES) * kTileLd + lane] = d[e];
 #pragma unroll
-    for (int e = 0; e < 2; ++e) {
-      const int at = tid + e * kTileThreads, r = at >> 4 & 15, c = at & 15;
+    for (int e = 0; e < W; ++e) {
+      const int at = tid + e * NT, r = at >> 4 & 15, c = at & 15;
       sInv[(at >> 8) * kBlk + r * 17 + c] = w[e];
     }
   }
@@ -573,21 +593,15 @@ __device__ __forceinline__ void tile_owner(const TileArgs<T>& g, T* const smem, 
 template <int KIND>
 __host__ __device__ inline int tile_before(int nt, int s) { return KIND == KIND_LU ? 2 * s * nt - s * s : s * nt - s * (s - 1) / 2; }
 
-template <typename T, int KIND, int AUX>
-__global__ void __launch_bounds__(kTileThreads, 2) tile_factor_kernel(const TileArgs<T> g) {
-  extern __shared__ __align__(16) unsigned char smem_raw[];
-  __shared__ int ticket;
-  T* const smem = reinterpret_cast<T*>(smem_raw);
+// Tiles from the counter until there are none left.
+template <typename T, int KIND, int AUX, int WAVES>
+__device__ __forceinline__ void tile_owners(const TileArgs<T>& g, T* const smem, int* const ticket) {
   const int tid = (int)threadIdx.x, nt = g.nt, tiles = tile_before<KIND>(nt, nt);
-  if (blockIdx.x == 0) {
-    tile_chain<T, KIND>(g, smem);
-    return;
-  }
   for (;;) {
     __syncthreads();
-    if (tid == 0) ticket = __hip_atomic_fetch_add(g.ints + TileFlags::kTicket, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (tid == 0) *ticket = __hip_atomic_fetch_add(g.ints + TileFlags::kTicket, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     __syncthreads();
-    const int id = __builtin_amdgcn_readfirstlane(ticket);
+    const int id = __builtin_amdgcn_readfirstlane(*ticket);
     if (id >= tiles) return;  // uniform
     int s = 0;
     for (int step = 64; step > 0; step >>= 1)  // the last s with tile_before(s) <= id
@@ -605,8 +619,41 @@ __global__ void __launch_bounds__(kTileThreads, 2) tile_factor_kernel(const Tile
     } else if (s == 0) {
       continue;  // block 0 starts on the diagonal's chain
     }
-    tile_owner<T, KIND, AUX>(g, smem, i, j);
+    if constexpr (WAVES == 4) {  // beside the diagonal: before the other workgroup of the compute unit
+      if (i - j <= 2 && j - i <= 2) __builtin_amdgcn_s_setprio(3);
+      else __builtin_amdgcn_s_setprio(0);
+    }
+    tile_owner<T, KIND, AUX, WAVES>(g, smem, i, j);
   }
+}
+
+// The whole factorisation in one launch.
+template <typename T, int KIND, int AUX>
+__global__ void __launch_bounds__(kTileThreads, 2) tile_factor_kernel(const TileArgs<T> g) {
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  __shared__ int ticket;
+  T* const smem = reinterpret_cast<T*>(smem_raw);
+  if (blockIdx.x == 0) tile_chain<T, KIND>(g, smem);
+  else tile_owners<T, KIND, AUX, kTileThreads / 64>(g, smem, &ticket);
+}
+
+// The same in two, side by side on two streams: workgroup 0, and the tiles' workgroups with four waves, two of them to a compute
+// unit, one of which multiplies while the other starts, solves or publishes.
+template <typename T, int KIND>
+__global__ void __launch_bounds__(kTileThreads, 2) tile_chain_kernel(const TileArgs<T> g) {
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  tile_chain<T, KIND>(g, reinterpret_cast<T*>(smem_raw));
+}
+constexpr int kTileOwnerThreads = 256;
+template <typename T>
+constexpr int tile_owner_lds_bytes() {
+  return (2 * kTileNb * kTileLd + kTileSub * kBlk) * (int)sizeof(T);
+}
+template <typename T, int KIND, int AUX>
+__global__ void __launch_bounds__(kTileOwnerThreads, 2) tile_owner_kernel(const TileArgs<T> g) {
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  __shared__ int ticket;
+  tile_owners<T, KIND, AUX, kTileOwnerThreads / 64>(g, reinterpret_cast<T*>(smem_raw), &ticket);
 }
 
 }  // namespace dla

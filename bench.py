@@ -4,9 +4,10 @@
 A step is one pass over the whole hot path on one batch of seeded synthetic
 input resident in HBM: lu_factor (N=4000), cholesky_factor (N=4000) and mm3
 (extralarge rectangular shape).  Prints ONE JSON line with the whole-job
-throughput in fp64 GFLOP/s, the roofline of the dominant kernel (the rank-128
-trailing update of the two factorisations, timed per launch with HIP events on
-the stream it runs on) and the CPU oracle timed on the host cores.
+throughput in fp64 GFLOP/s, the roofline of the dominant kernel (the two
+factorisations' tiles, one or two launches each; with --lookahead 2 the rank-128
+trailing update of the pipeline; timed per launch with HIP events on the stream
+it runs on) and the CPU oracle timed on the host cores.
 
   python bench.py [--gpus 1] [--steps K] [--warmup W] [--no-cpu-baseline]
 """
@@ -74,6 +75,12 @@ def update_algorithmic_bytes(n, nb=128, lower=False, defer_min_rows=0):
     return launches, total
 
 
+def tiles_algorithmic_bytes(n, lower=False):
+    """(launches, bytes) of one factorisation in tiles: the matrix read and written once (Cholesky: the lower triangle read,
+    all of it written)."""
+    return 1, 8 * (n * (n + 1) // 2 + n * n if lower else 2 * n * n)
+
+
 def lu_flops(n):
     return 2.0 * n ** 3 / 3.0
 
@@ -133,6 +140,8 @@ def main(argv=None) -> int:
     p_mm = B.default_params(B.DLA_KERNEL_MM3, dims["nk"])
     if args.lookahead is not None:
         p_lu.lookahead = p_ch.lookahead = args.lookahead
+        if args.lookahead != 1:
+            p_lu.nb = p_ch.nb = 128  # (the tiles need look-ahead 1)
     ws_f = torch.empty(B.factor_workspace_bytes(n, B.DLA_F64, p_lu), dtype=torch.uint8, device=dev)
     ws_m = torch.empty(B.mm3_workspace_bytes(dims["ni"], dims["nj"], dims["nl"], B.DLA_F64), dtype=torch.uint8,
                        device=dev)
@@ -158,7 +167,7 @@ def main(argv=None) -> int:
     gflops = flops_step * K / elapsed * 1e-9
 
     # ---- per-kernel figures and the GEMM-phase roofline (a repeat of the timed steps, one
-    # kernel at a time, with per-launch events on the stream the GEMM runs on) -------------------
+    # kernel at a time, with per-launch events on the stream the kernel runs on) -----------------
     def timed(fn, reps):
         # device events on the caller's stream (every entry point joins its helper streams back into it):
         # a wall clock would add the cost of the two synchronisations, which is not small against 20 short calls
@@ -213,8 +222,12 @@ def main(argv=None) -> int:
         upd_launches += ucnt
     achieved = upd_fl / upd_ms * 1e-9 if upd_ms > 0 else 0.0  # TFLOP/s
     measured_peak = B.mfma_peak(B.DLA_F64)  # register-resident MFMA loop, the achievable counterpart of the published peak
-    la, ba = update_algorithmic_bytes(n, p_lu.nb or 128, False, p_lu.defer_min_rows)
-    lc, bc = update_algorithmic_bytes(n, p_ch.nb or 128, True, p_ch.defer_min_rows)
+    tiles = p_lu.nb == p_ch.nb == 64 and p_lu.lookahead == 1  # the whole factorisation in 64 x 64 tiles
+    if tiles:
+        (la, ba), (lc, bc) = tiles_algorithmic_bytes(n), tiles_algorithmic_bytes(n, lower=True)
+    else:
+        la, ba = update_algorithmic_bytes(n, p_lu.nb or 128, False, p_lu.defer_min_rows)
+        lc, bc = update_algorithmic_bytes(n, p_ch.nb or 128, True, p_ch.defer_min_rows)
     alg_launches, alg_bytes = la + lc, ba + bc
 
     # ---- CPU oracle on the host cores: one pass of the same workload ----------------------------
@@ -244,13 +257,14 @@ def main(argv=None) -> int:
         "pct_of_measured_fp64_mfma_peak": round(gflops * 1e-3 / measured_peak * 100, 2),
         "kernels": kernels,
         "roofline": {"bound": "mfma", "achieved": round(achieved, 2), "peak": PEAK_F64_MFMA_TFLOPS, "unit": "TFLOP/s",
-                     "frac": round(achieved / PEAK_F64_MFMA_TFLOPS, 4), "traffic": update_traffic_bytes_per_launch(n),
-                     "kernel": "update_kernel (bulk trailing update of lu_factor and cholesky_factor, all launches)",
+                     "frac": round(achieved / PEAK_F64_MFMA_TFLOPS, 4), "traffic": None if tiles else update_traffic_bytes_per_launch(n),
+                     "kernel": "tile_factor_kernel / tile_owner_kernel (lu_factor and cholesky_factor whole, all launches)" if tiles
+                     else "update_kernel (bulk trailing update of lu_factor and cholesky_factor, all launches)",
                      "launches": upd_launches, "avg_launch_ms": round(upd_ms / max(upd_launches, 1), 5),
                      "flops_per_launch": round(upd_fl / max(upd_launches, 1), 1),
                      "algorithmic_bytes_per_launch": round(alg_bytes / max(alg_launches, 1), 1),
                      "how": "HIP start/stop events attached to every launch of the kernel (hipExtLaunchKernelGGL) on the "
-                            "stream it runs on, in a repeat of the timed steps with the pipeline's other streams beside it"},
+                            "stream it runs on, in a repeat of the timed steps with the call's other streams beside it"},
         "cpu_baseline": cpu,
     }
     print(json.dumps(out))

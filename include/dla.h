@@ -93,8 +93,8 @@ typedef struct {
  * trailing matrix is large; defer_min_rows moves that threshold.
  *
  * nb = 64 with lookahead = 1 and d_info, and nb = 0 for matrices of a few thousand rows (dla_default_params tells: it gives
- * 64 there), run as one or two launches of 64 x 64 tiles whose workgroups wait for each other; nb = 0 beyond that as blocks of
- * 128 down to the last few thousand rows, and those in tiles.
+ * 64 there), run as one or two launches of 64 x 64 tiles whose workgroups wait for each other; nb = 0 or 128 beyond that as
+ * blocks of 128 down to the last few thousand rows, and those in tiles (if defer_min_rows is 0).
  *
  * There is no separate inner block size of the diagonal-block kernel: it works in stages of 16 columns,
  * the edge of the MFMA block, and nothing else is instantiated.

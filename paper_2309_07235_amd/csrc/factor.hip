@@ -1,6 +1,7 @@
 // Host drivers of the blocked right-looking factorisations: for every block
 // column  (1) factor the diagonal block, (2) solve the panels, (3) update the
-// trailing matrix with the MFMA GEMM (the step that dominates the run time).
+// trailing matrix with the MFMA GEMM (the step that dominates the run time).  Matrices up to a few thousand rows, and the last
+// rows of larger ones, are factored in 64 x 64 tiles instead (tile_factor_kernel.hpp; TileRange has the lines between them).
 #include "factor_kernels.hpp"
 #include "update_kernel.hpp"
 #include "head_kernel.hpp"
@@ -87,7 +88,7 @@ int resolve_factor_params(dla_dtype dt, int64_t n, const dla_factor_params* in, 
   const int64_t nt = (n + kTileNb - 1) / kTileNb;
   plan->tiles = la == 1 && !tiled && defer == 0 && n > 2 * (int64_t)b && (named ? b == kTileNb : n <= tile_range(dt, op).max_n) && nt <= kTileMaxNt &&
                 (dt == DLA_F64 ? tile_workspace_bytes<double>((int)nt) : tile_workspace_bytes<float>((int)nt)) <= factor_workspace_bytes_impl(n, dt, in);
-  plan->tail = la == 1 && !tiled && defer == 0 && !named && n > tile_range(dt, op).max_n;
+  plan->tail = la == 1 && !tiled && defer == 0 && b == kNbMax && n > tile_range(dt, op).max_n;  // 128: what a caller names who passes the defaults on
   plan->nb_outer = b;
   plan->nb = two_level ? b / 2 : b;
   plan->lookahead = la;

@@ -64,7 +64,7 @@ def test_tiles_match_the_oracle(B, oracle, kind, dtype, n, pad, shift, nb):
 
 
 # both sides of the line between one launch and two, and of the line to the pipeline (which then leaves its last rows to the
-# tiles); against the pipeline's own factor
+# tiles, also where the caller names the 128 that the defaults give there); against the factor of the pipeline alone
 @gpu
 @pytest.mark.parametrize("kind,dtype,n", [("lu", "float64", 3699), ("lu", "float64", 3700), ("lu", "float64", 7200), ("lu", "float64", 7201),
                                           ("chol", "float64", 4799), ("chol", "float64", 4800), ("chol", "float64", 7233),
@@ -81,11 +81,13 @@ def test_lines_between_the_forms(B, kind, dtype, n):
         a += (m - m.t()) / 8
     a = a.to(d)
     outs = []
-    for nb in (0, 128):
+    default = B.default_params(B.DLA_KERNEL_LU if kind == "lu" else B.DLA_KERNEL_CHOLESKY, n, B.DLA_F64 if dtype == "float64" else B.DLA_F32)
+    for nb, lookahead in ((0, -1), (128, 2), (default.nb, -1)):
         x, info = a.clone(), torch.full((1,), -7, dtype=torch.int32, device="cuda")
-        (B.lu_factor if kind == "lu" else B.cholesky_factor)(x, B.FactorParams(nb, -1, B.GemmParams(), 0), info=info)
+        (B.lu_factor if kind == "lu" else B.cholesky_factor)(x, B.FactorParams(nb, lookahead, B.GemmParams(), 0), info=info)
         assert int(info.item()) == 0
         outs.append(x.double())
+    assert torch.equal(outs[0], outs[2])
     eps = EPS64 if dtype == "float64" else EPS32
     # the sums of both are those of the same products in another order: about sqrt(n) eps apart, and no further than n eps
     assert float((outs[0] - outs[1]).norm() / outs[1].norm()) <= 0.1 * n * eps

@@ -10,7 +10,9 @@
 // result depends neither on timing nor on the launch.
 //
 // What bounds it is the hop X_{i-1} -> X_i, 2 n / 256 of them in sequence: a store to the device's point of coherence, a
-// load from it, 16 dependent MFMAs a wave, a rendezvous in LDS.
+// load from it, 16 dependent MFMAs a wave, a rendezvous in LDS.  Measured 3.2 - 4 us a hop with few right-hand sides, where a
+// launch per hop takes 6.6 - 8: prepared LU solves, fp64, n = 4000 with 1 right-hand side 211 -> 108 us, with 64 255 -> 182,
+// n = 8192 571 -> 276 and 746 -> 566.
 //
 // Hand-over.  A piece of X is its own signal: the areas the passes publish in are filled with a bit pattern that is never
 // published (kEmpty, a NaN; a result with these bits is stored as another NaN), every element is stored and loaded as an

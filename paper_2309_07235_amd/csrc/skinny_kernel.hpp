@@ -1,4 +1,5 @@
-// Skinny subtracting products for latency chains (the block steps of the solves with the factors;
+// Skinny subtracting products for latency chains (the block steps of the solves with the factors with 65 to 128 or 256
+// right-hand sides;
 // paper, Section "Introduction": LU and Cholesky are named as the factorisations behind solving
 // systems of linear equations):  C (M x N) -= A (M x K) * B (K x N)  with few columns and K <= 512,
 // where the launch is one link of a chain of dependent launches and what matters is how soon it ends.

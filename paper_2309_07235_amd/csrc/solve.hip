@@ -6,8 +6,8 @@
 //       [ L21 L2 ]   [ -W2 L21 W1  W2 ]            [ 0  U2  ]   [ 0    V2       ]
 // (pair_kernel), then the products M below (look_back_kernel): three launches.
 //
-// The chain of the substitution is latency bound (every launch waits for the one before it), so a
-// block step is ONE grouped launch.  With W_i the inverse of diagonal block i, the plain step
+// The chain of the substitution is latency bound (every step waits for the one before it), so a
+// block step is ONE grouped launch (or, with few right-hand sides, one hop inside a launch).  With W_i the inverse of diagonal block i, the plain step
 //   X_i = W_i (B_i - sum_{j<i} L_ij X_j)
 // is split as  X_i = Z_i - M_i [X_{i-2}; X_{i-1}],  Z_i = W_i (B_i - sum_{j<i-2} L_ij X_j),
 // M_i = W_i [L_{i,i-2}, L_{i,i-1}]  (the pre-pass forms M_i, one product per block).  The launch that
@@ -23,7 +23,7 @@
 // inverses of its own.  The forward pass leaves Y in the workspace and spoils B; the backward pass
 // builds X in a second workspace area and stores each finished block to B as well.
 // Up to 64 right-hand sides both passes are one launch of flow_kernel, whose workgroups wait for each other; above that the
-// chain's launches run on skinny_kernel up to 128 right-hand sides and on the tiled GEMM beyond.
+// chain's launches run on skinny_kernel up to 128 right-hand sides (256 of a small system) and on gemm_wide_kernel beyond.
 // The pre-pass and the two passes can be called separately (one pre-pass, many solves with its workspace).
 #include "prepass_kernel.hpp"
 #include "skinny_kernel.hpp"

@@ -1,4 +1,4 @@
-// A whole factorisation as ONE launch, in 64 x 64 tiles (paper, Section "Linear Algebra Benchmarks": A = L*U without
+// A whole factorisation as one launch, or two side by side, in 64 x 64 tiles (paper, Section "Linear Algebra Benchmarks": A = L*U without
 // pivoting, A = L*L^T; the tiling is this library's).  Workgroups wait in place for what they read:
 //   workgroup 0 walks the diagonal: block s lies in its LDS, is factored there (diag_stages), then the two blocks beside the
 //     next one, (s, s+1) and (s+1, s), are solved from copies and block (s+1, s+1) gets their product, so that from one
@@ -7,10 +7,17 @@
 //     the tiles in front of it, (i, k) (k, j), as these appear, and solves it once block s is factored.  The tiles beside the
 //     diagonal are also copied, unsolved, for workgroup 0, which is through with a block about when they are there.
 // So a tile of the matrix is read and written once, there is one launch instead of six per block column, and the chain of
-// the diagonal is free of hand-overs.
+// the diagonal is free of hand-overs.  In two launches (tile_chain_kernel, tile_owner_kernel) the tiles' workgroups have four
+// waves instead of eight and two of them share a compute unit: one's start, solve and publication hide behind the other's
+// products, which is what the larger matrices need, and the second stream's two events, 20 us, what the smaller ones do not.
 //
-// What bounds it is that chain while the matrix is small: per 64 columns four stages of the diagonal block, the two solves
-// and a product.  Beyond, the tiles' products, whose operands come from the L2.
+// What bounds it is that chain while the matrix is small: LU 18, Cholesky 16 us per 64 columns, of which the four stages of the
+// diagonal block are 11.5, the two solves 1.9 - 3.4, the product with the next block's first factor 2.3.  (A block of 128 in the
+// pipeline, with its head update and two hand-overs between kernels, is 47.)  Beyond, the tiles' products, whose operands come
+// from the L2.  us, the pipeline against one launch: LU fp64 n = 300 125 -> 98, Cholesky n = 1024 in blocks of 64 713 -> 264,
+// n = 4000 1580 -> 1144; two launches: LU fp64 n = 4000 1866 -> 1444 (30 TFLOP/s), n = 7000 6880 -> 5574 (41).
+// Half of 128 registers per lane for two workgroups of eight waves spills; a workgroup on the chain's compute unit costs the
+// chain 2 - 4 us a step.
 //
 // Hand-over.  Published tiles are stored past the L2s (kTilePast), each workgroup waits for its stores and then sets a flag.
 // A tile of the factor is read through the reader's L2 where no line of it can be there from before: lines are not shared

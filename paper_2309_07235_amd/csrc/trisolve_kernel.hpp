@@ -2,10 +2,10 @@
 // factorisations behind solving systems of linear equations):  A X = B  becomes  L Y = B, U X = Y
 // after lu_factor and  L Y = B, L^T X = Y  after cholesky_factor.  The host driver walks the
 // triangular matrix in blocks of rows.  The blocks' own triangular systems are taken off the chain
-// of the substitution by inverting every diagonal block up front (this kernel: one workgroup per
-// 128-row block, all blocks at once, independent of the right-hand sides), so that a step of the
-// chain is small products on the tiled GEMM.  The host pairs the 128-row inverses into inverses of
-// 256-row blocks (two more small products per pair, all pairs at once), which halves the steps of
+// of the substitution by inverting every diagonal block up front (this kernel: two workgroups per
+// 128-row block, half of its columns each, all blocks at once, independent of the right-hand sides), so that a step of the
+// chain is small products.  pair_kernel joins the 128-row inverses to inverses of 256-row blocks
+// (two more small products per pair, all pairs at once), which halves the steps of
 // the chain, and asks for the negated inverses (unit = -1) because its chain subtracts.
 //
 // The inversion is the panel solve of the factorisations run on the identity: the block is brought

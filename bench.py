@@ -140,8 +140,6 @@ def main(argv=None) -> int:
     p_mm = B.default_params(B.DLA_KERNEL_MM3, dims["nk"])
     if args.lookahead is not None:
         p_lu.lookahead = p_ch.lookahead = args.lookahead
-        if args.lookahead != 1:
-            p_lu.nb = p_ch.nb = 128  # (the tiles need look-ahead 1)
     ws_f = torch.empty(B.factor_workspace_bytes(n, B.DLA_F64, p_lu), dtype=torch.uint8, device=dev)
     ws_m = torch.empty(B.mm3_workspace_bytes(dims["ni"], dims["nj"], dims["nl"], B.DLA_F64), dtype=torch.uint8,
                        device=dev)
@@ -222,7 +220,8 @@ def main(argv=None) -> int:
         upd_launches += ucnt
     achieved = upd_fl / upd_ms * 1e-9 if upd_ms > 0 else 0.0  # TFLOP/s
     measured_peak = B.mfma_peak(B.DLA_F64)  # register-resident MFMA loop, the achievable counterpart of the published peak
-    tiles = p_lu.nb == p_ch.nb == 64 and p_lu.lookahead == 1  # the whole factorisation in 64 x 64 tiles
+    # no launch of the diagonal-block kernel: both factorisations ran whole in 64 x 64 tiles
+    tiles = all(kernels[k]["diag"]["launches_per_call"] == 0 for k in ("lu", "cholesky")) and upd_launches > 0
     if tiles:
         (la, ba), (lc, bc) = tiles_algorithmic_bytes(n), tiles_algorithmic_bytes(n, lower=True)
     else:

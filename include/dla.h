@@ -92,9 +92,10 @@ typedef struct {
  * nb = 128 the same two-level form (depth 256, sub-panels of 128) is used on its own accord while the
  * trailing matrix is large; defer_min_rows moves that threshold.
  *
- * nb = 64 with lookahead = 1 and d_info, and nb = 0 for matrices of a few thousand rows (dla_default_params tells: it gives
- * 64 there), run as one or two launches of 64 x 64 tiles whose workgroups wait for each other; nb = 0 or 128 beyond that as
- * blocks of 128 down to the last few thousand rows, and those in tiles (if defer_min_rows is 0).
+ * The defaults (nb = 0 or 128, lookahead = 1, update and defer_min_rows 0, with d_info) leave the schedule to the library: matrices
+ * of up to a few thousand rows run as one or two launches of 64 x 64 tiles whose workgroups wait for each other, larger ones as
+ * blocks of 128 down to the last few thousand rows, and those in tiles.  nb = 64 asks for the tiles at any size.  defer_min_rows
+ * other than 0 or lookahead = 2 with nb = 128 is the pipeline of blocks all the way.
  *
  * There is no separate inner block size of the diagonal-block kernel: it works in stages of 16 columns,
  * the edge of the MFMA block, and nothing else is instantiated.

@@ -369,7 +369,7 @@ int dla_default_params(int kernel, int64_t n, dla_dtype dt, void* out) {
   const int op = kernel == DLA_KERNEL_LU ? OP_SUB : OP_SUB_NT_LOWER;
   int rc = resolve_factor_params(dt, n, nullptr, op, &plan, &s);
   if (rc != DLA_SUCCESS) return rc;
-  p->nb = plan.tiles ? 64 : plan.nb_outer;
+  p->nb = plan.nb_outer;
   p->lookahead = plan.lookahead;
   (void)s;
   p->update = dla_gemm_params{0, 0, 0, 0, 0, 0};  // the panel-stationary update kernel

@@ -45,7 +45,8 @@ size_t factor_workspace_bytes_impl(int64_t n, dla_dtype dt, const dla_factor_par
   return 4 * inv_set_bytes(dt) + 4 * head_copy_bytes(dt) + 256;  // + the hand-over counters of the latency chain
 }
 
-// Matrices that tile_factor_kernel's form takes where the caller names no block size: up to max_n, from two_from on in two
+// Matrices that tile_factor_kernel's form takes where the caller leaves the schedule to the library (block size 0, or 128, which
+// is what dla_default_params gives, and nothing else named): up to max_n, from two_from on in two
 // launches.  A larger one is factored in the pipeline, by blocks of 128, down to a tail of rows.  Below, the chain of the diagonal is
 // what a factorisation takes, and it is shorter there; above, the products, whose operands the pipeline reads less often.
 // us, the pipeline / one launch / two launches (the second: two tiles to a compute unit, but 20 us of events):
@@ -71,8 +72,7 @@ static TileRange tile_range(dla_dtype dt, int op) {
 int resolve_factor_params(dla_dtype dt, int64_t n, const dla_factor_params* in, int op, FactorPlan* plan,
                           GemmSchedule* upd) {
   int b = in ? in->nb : 0;
-  const bool named = b != 0;
-  if (!named) b = 128;
+  if (b == 0) b = kNbMax;
   const bool one_level = b >= 16 && b <= kNbMax && b % 16 == 0;
   const bool two_level = b > kNbMax && b <= 2 * kNbMax && b % 32 == 0;
   if (!one_level && !two_level) return DLA_ERR_UNSUPPORTED_PARAMS;
@@ -86,9 +86,9 @@ int resolve_factor_params(dla_dtype dt, int64_t n, const dla_factor_params* in, 
   // two sub-panels per panel need the pipeline's deferred bulk update and the kernel that takes depth 256
   if (two_level && (la == 0 || tiled)) return DLA_ERR_UNSUPPORTED_PARAMS;
   const int64_t nt = (n + kTileNb - 1) / kTileNb;
-  plan->tiles = la == 1 && !tiled && defer == 0 && n > 2 * (int64_t)b && (named ? b == kTileNb : n <= tile_range(dt, op).max_n) && nt <= kTileMaxNt &&
+  plan->tiles = la == 1 && !tiled && defer == 0 && n > 2 * (int64_t)b && (b == kTileNb || (b == kNbMax && n <= tile_range(dt, op).max_n)) && nt <= kTileMaxNt &&
                 (dt == DLA_F64 ? tile_workspace_bytes<double>((int)nt) : tile_workspace_bytes<float>((int)nt)) <= factor_workspace_bytes_impl(n, dt, in);
-  plan->tail = la == 1 && !tiled && defer == 0 && b == kNbMax && n > tile_range(dt, op).max_n;  // 128: what a caller names who passes the defaults on
+  plan->tail = la == 1 && !tiled && defer == 0 && b == kNbMax && n > tile_range(dt, op).max_n;
   plan->nb_outer = b;
   plan->nb = two_level ? b / 2 : b;
   plan->lookahead = la;

@@ -18,13 +18,6 @@ def B():
     return binding
 
 
-def test_default_params_name_the_tiles_where_they_run():
-    from paper_2309_07235_amd import binding as B
-    for kind in (B.DLA_KERNEL_LU, B.DLA_KERNEL_CHOLESKY):
-        for dt in (B.DLA_F64, B.DLA_F32):
-            assert [B.default_params(kind, n, dt).nb for n in (256, 257, 4000, 8192)] == [128, 64, 64, 128]
-
-
 def _factor(B, kind, H, dtype, pad, shift, nb):
     """The factor of H in a buffer with `pad` more columns and `shift` elements in front; the padding must stay as it was.
     What lies above the diagonal must not matter to Cholesky."""
@@ -64,7 +57,7 @@ def test_tiles_match_the_oracle(B, oracle, kind, dtype, n, pad, shift, nb):
 
 
 # both sides of the line between one launch and two, and of the line to the pipeline (which then leaves its last rows to the
-# tiles, also where the caller names the 128 that the defaults give there); against the factor of the pipeline alone
+# tiles), also where the caller passes the library's defaults on; against the factor of the pipeline alone
 @gpu
 @pytest.mark.parametrize("kind,dtype,n", [("lu", "float64", 3699), ("lu", "float64", 3700), ("lu", "float64", 7200), ("lu", "float64", 7201),
                                           ("chol", "float64", 4799), ("chol", "float64", 4800), ("chol", "float64", 7233),

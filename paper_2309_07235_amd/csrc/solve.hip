@@ -85,8 +85,8 @@ __global__ void solve_zero_kernel(T* p, int64_t count) {
 
 // Workspace, in elements: per 256-row block a 256 x 256 negated inverse for the forward and one for the
 // backward pass (LU), a 128 x 128 intermediate of the pairing for each, and a 256 x 512 area M for each
-// pass; then the n x nrhs areas Y and X (leading dimension nrhs rounded up to even).  All of it is
-// cleared at the start of a call.
+// pass; then the n x nrhs areas Y and X (leading dimension nrhs rounded up to even), which
+// a call sets to zero, or to what flow_kernel never publishes, before its passes.
 static int64_t pairs_of(int64_t n) { return (n + kTriPair - 1) / kTriPair; }
 static int64_t block_elems(int64_t n) {
   return 2 * pairs_of(n) * ((int64_t)kTriPair * kTriPair + (int64_t)kNbMax * kNbMax + 2 * (int64_t)kTriPair * kTriPair);

@@ -24,14 +24,14 @@ import sys
 TRAFFIC_TAG = "roofline.traffic"   # bench.py looks for a line starting with this
 
 COMMANDS = {
-    "trace": "rocprofv3 --kernel-trace --stats -d $R/gpurun_out/prof_bench -o bench -- \\\n"
+    "trace": "rocprofv3 --kernel-trace --stats -d $R/prof/prof_bench -o bench -- \\\n"
              "      python3 $R/bench.py --steps 10 --warmup 2 --no-cpu-baseline",
     "counters": "rocprofv3 --pmc SQ_VALU_MFMA_BUSY_CYCLES SQ_BUSY_CYCLES SQ_WAVE_CYCLES SQ_INSTS_VALU_MFMA_MOPS_F64 \\\n"
-                "      SQ_LDS_BANK_CONFLICT SQ_LDS_IDX_ACTIVE GRBM_GUI_ACTIVE -d $R/gpurun_out/pmc_mfma -o bench -- \\\n"
+                "      SQ_LDS_BANK_CONFLICT SQ_LDS_IDX_ACTIVE GRBM_GUI_ACTIVE -d $R/prof/pmc_mfma -o bench -- \\\n"
                 "      python3 $R/bench.py --steps 2 --warmup 1 --no-cpu-baseline --lookahead 2",
-    "fetch": "rocprofv3 --pmc FETCH_SIZE -d $R/gpurun_out/pmc_fetch -o bench -- \\\n"
+    "fetch": "rocprofv3 --pmc FETCH_SIZE -d $R/prof/pmc_fetch -o bench -- \\\n"
              "      python3 $R/bench.py --steps 2 --warmup 1 --no-cpu-baseline --lookahead 2",
-    "write": "rocprofv3 --pmc WRITE_SIZE -d $R/gpurun_out/pmc_write -o bench -- \\\n"
+    "write": "rocprofv3 --pmc WRITE_SIZE -d $R/prof/pmc_write -o bench -- \\\n"
              "      python3 $R/bench.py --steps 2 --warmup 1 --no-cpu-baseline --lookahead 2",
 }
 LOOKAHEAD_NOTE = ("--lookahead 2: counter collection runs the kernels one at a time, and the default pipeline (lookahead 1)\n"
@@ -49,7 +49,7 @@ def trace(db_path: str, top: int) -> None:
     rows = cur.execute("select name, count(*), sum(end-start), avg(end-start), min(end-start), max(end-start) "
                        "from kernels group by name order by sum(end-start) desc").fetchall()
     total = sum(r[2] for r in rows)
-    print("Command (from /tmp with TMPDIR=/tmp on the GPU box; R = repository root):\n")
+    print("Command (from /tmp with TMPDIR=/tmp on an MI355X; R = repository root):\n")
     print("  " + COMMANDS["trace"] + "\n")
     print("Per-kernel aggregate of the `kernels` view of the results database (nanoseconds -> us / ms):\n")
     print(f"{'kernel':78s} {'calls':>6s} {'total_ms':>10s} {'avg_us':>9s} {'min_us':>9s} {'max_us':>9s} {'pct':>6s}")

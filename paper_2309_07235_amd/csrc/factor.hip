@@ -602,6 +602,7 @@ static int factor_impl(T* A, int64_t n, int64_t lda, const dla_factor_params* p,
       const int64_t mr = m - bn;              // what is left behind it
       const int64_t bn2 = mr < nb ? mr : nb;  // size of block N2
       const bool wide = owed;                 // this step also applies the previous step's panels
+      const bool to_tiles = tail > 0 && step + 1 == nsteps;  // the tiles come next
       const int ksh = wide ? nb : 0;          // depth added in front of this step's panels
       const int kk = b + ksh;
       const int64_t lsh = ksh, ush = (KIND == KIND_LU) ? (int64_t)ksh * lda : (int64_t)ksh;
@@ -617,7 +618,8 @@ static int factor_impl(T* A, int64_t n, int64_t lda, const dla_factor_params* p,
       } else if (hip_note(hipStreamWaitEvent(ctx.panel, step == 0 ? e_head : e_diag[step & 1], 0), "hipStreamWaitEvent") != 0) {
         return DLA_ERR_HIP;
       }
-      // the last kernel of the step on this stream carries e_strip
+      // e_strip: what the next head update reads is there; behind the last step, which the call then joins: all of this stream.
+      // (A wide step that is followed by another has a second group of strips behind it, which that one's e_strip covers.)
       if ((r = solves(k0, step, ctx.panel, mr > 0 ? e_solve : e_strip)) != DLA_SUCCESS) return r;
       if (mr > 0) {
         if (bulk_pending && !after_wide && hip_note(hipStreamWaitEvent(ctx.panel, e_bulk, 0), "hipStreamWaitEvent") != 0) return DLA_ERR_HIP;
@@ -661,8 +663,9 @@ static int factor_impl(T* A, int64_t n, int64_t lda, const dla_factor_params* p,
           flops = 0.0;
           return rr;
         };
-        if ((r = launch_group(e_strip)) != DLA_SUCCESS) return r;
-        if (wide) {
+        const bool two_groups = wide && rest > 0;
+        if ((r = launch_group(two_groups && to_tiles ? nullptr : e_strip)) != DLA_SUCCESS) return r;
+        if (two_groups) {
           // block row / column N2 behind block (N2,N2), and block (N3,N3): what the next step's strips work on
           const int64_t bn3 = rest < nb ? rest : nb, o2 = bn + bn2;
           const T* Lr3 = Lr + bn2 * lda;  // rows from block N3 on
@@ -674,14 +677,14 @@ static int factor_impl(T* A, int64_t n, int64_t lda, const dla_factor_params* p,
             add(Lr3, Lr, A22 + o2 * lda + bn, rest, bn2, nullptr);              // block column N2 below (N2,N2)
             add(Lr3, Lr3, A22 + o2 * lda + o2, bn3, bn3, nullptr);              // block (N3,N3)
           }
-          if ((r = launch_group(nullptr)) != DLA_SUCCESS) return r;
+          if ((r = launch_group(to_tiles ? e_strip : nullptr)) != DLA_SUCCESS) return r;
         }
       }
       if (mr > bn2) {
         const int64_t rest = mr - bn2;
         // put the bulk update off when the step after this one can carry it: full blocks N2, N3 and
         // two more behind them, and a trailing matrix large enough for the bulk stream to be the longest
-        if (!owed && auto_tile && plan.two_level && mr >= plan.defer_min_rows && rest >= 4 * (int64_t)nb && !(tail > 0 && step + 1 == nsteps)) {
+        if (!owed && auto_tile && plan.two_level && mr >= plan.defer_min_rows && rest >= 4 * (int64_t)nb && !to_tiles) {
           owed = true;
           after_wide = false;
           return DLA_SUCCESS;

@@ -61,7 +61,9 @@ def test_tiles_match_the_oracle(B, oracle, kind, dtype, n, pad, shift, nb):
 @gpu
 @pytest.mark.parametrize("kind,dtype,n", [("lu", "float64", 3699), ("lu", "float64", 3700), ("lu", "float64", 7200), ("lu", "float64", 7201),
                                           ("chol", "float64", 4799), ("chol", "float64", 4800), ("chol", "float64", 7233),
-                                          ("lu", "float32", 4300), ("lu", "float32", 5601), ("chol", "float32", 5401)])
+                                          ("lu", "float32", 4300), ("lu", "float32", 5601), ("chol", "float32", 5401),
+                                          # the step in front of the tiles carries two panels
+                                          ("lu", "float64", 7300), ("lu", "float32", 5700), ("chol", "float64", 7300)])
 def test_lines_between_the_forms(B, kind, dtype, n):
     import torch
     announce(f"tiles lines {kind} {dtype} n={n}")

@@ -1,0 +1,114 @@
+"""What a call submits, and in which order the streams and events let it run (host only: a stand-in for the HIP runtime writes
+the calls down; nothing is launched)."""
+import json
+import subprocess
+import sys
+from pathlib import Path
+
+import pytest
+
+from paper_2309_07235_amd import build
+
+HERE = Path(__file__).resolve().parent
+F64, F32 = 0, 1
+
+# Run in a process of its own, without torch: the stand-in has to be there before the library's own runtime.
+DRIVER = r"""
+import ctypes, json, sys, threading
+rec = ctypes.CDLL(sys.argv[1], mode=ctypes.RTLD_GLOBAL)
+lib = ctypes.CDLL(sys.argv[2])
+vp, i64, ci, sz = ctypes.c_void_p, ctypes.c_int64, ctypes.c_int, ctypes.c_size_t
+class Gemm(ctypes.Structure):
+    _fields_ = [(f, ci) for f in ("tile_m", "tile_n", "tile_k", "unroll_k", "wave_m", "wave_n")]
+class Params(ctypes.Structure):
+    _fields_ = [("nb", ci), ("lookahead", ci), ("update", Gemm), ("defer_min_rows", ci)]
+lib.factor_workspace_bytes.argtypes, lib.factor_workspace_bytes.restype = [i64, ci, vp], sz
+for f in (lib.lu_factor, lib.cholesky_factor):
+    f.argtypes = [vp, i64, i64, ci, ctypes.POINTER(Params), vp, sz, vp, vp]
+lib.dla_factor_giveup_selftest.argtypes = [ci, vp, i64, i64, ci, vp, sz, vp, vp]
+rec.record_text.restype = ctypes.c_char_p
+def call(kind, dtype, n, nb=0, lookahead=-1, info=True, stream=0x77, giveup=False):
+    ws = lib.factor_workspace_bytes(n, dtype, None)
+    data, scratch, status = 0x100000000, 0x200000000, 0x300000000 if info else None
+    if giveup:
+        return lib.dla_factor_giveup_selftest(int(kind != "lu"), data, n, n, dtype, scratch, ws, stream, status)
+    f = lib.lu_factor if kind == "lu" else lib.cholesky_factor
+    return f(data, n, n, dtype, Params(nb, lookahead, Gemm(), 0), scratch, ws, stream, status)
+job = json.loads(sys.argv[3])
+out = []
+for threads in job["runs"]:  # each a list of threads, each a list of calls
+    rec.record_start(ci(job.get("pause", 0)))
+    rcs = [[] for _ in threads]
+    def work(t):
+        rec.record_thread(ci(t))
+        for c in threads[t]:
+            rcs[t].append(call(**c))
+    ts = [threading.Thread(target=work, args=(t,)) for t in range(len(threads))]
+    for t in ts: t.start()
+    for t in ts: t.join()
+    out.append({"rc": rcs, "text": rec.record_text().decode()})
+print(json.dumps(out))
+"""
+
+
+@pytest.fixture(scope="module")
+def record(tmp_path_factory):
+    so = tmp_path_factory.mktemp("rec") / "librecorder.so"
+    subprocess.run(["g++", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include", "-std=c++17", "-O1", "-w", "-shared", "-fPIC", "-pthread",
+                    str(HERE / "host" / "hip_recorder.cpp"), "-o", str(so)], check=True)
+
+    def run(runs, pause=0):
+        """Per run the calls' return codes and the list of (thread, what, stream, event, workgroups, kernel)."""
+        res = subprocess.run([sys.executable, "-c", DRIVER, str(so), str(build.LIB), json.dumps({"runs": runs, "pause": pause})],
+                             capture_output=True, text=True, timeout=100, check=True)
+        out = []
+        for r in json.loads(res.stdout):
+            rows = [line.split(" ") for line in r["text"].splitlines()]
+            out.append((r["rc"], [(int(t), w, st, ev, int(g), k) for t, w, st, ev, g, k in rows]))
+        return out
+
+    return run
+
+
+def _behind(ops):
+    """Per operation the set (bits) of launches that are complete before it starts, and that for the end of each stream."""
+    done, events, before = {}, {}, []
+    for i, (_, what, st, ev, _, _) in enumerate(ops):
+        now = done.get(st, 0)
+        before.append(now)
+        if what == "W":
+            done[st] = now | events.get(ev, 0)
+        elif what == "L":
+            done[st] = now | 1 << i
+            if ev != "0":
+                events[ev] = done[st]
+        elif what == "R":
+            events[ev] = now
+    return before, done
+
+
+def _call(kind, dtype, n, **more):
+    return {"kind": kind, "dtype": dtype, "n": n, **more}
+
+
+# every form: one block, one stream, both pipelines, tiles, and tails of tiles behind an even and an odd number of block steps
+# (a step that carries two panels is then the last one, or is not)
+FORMS = [_call(kind, dtype, n, **more) for kind, dtype in (("lu", F64), ("lu", F32), ("chol", F64), ("chol", F32))
+         for n, more in [(100, {}), (600, {"lookahead": 0}), (600, {"info": False}), (5000, {"lookahead": 2}), (5000, {"nb": 256}), (600, {}),
+                         (5000, {}), (7300, {}), (7400, {}), (7500, {}), (8000, {}), (8192, {})]]
+
+
+def test_a_call_joins_all_it_has_submitted(record):
+    """Whatever the caller's stream runs next is behind every kernel of the call, and so is the launch that takes the last rows in
+    tiles: it works in place on what the pipeline's kernels have left."""
+    for form, (rc, ops) in zip(FORMS, record([[[f]] for f in FORMS])):
+        assert rc == [[0]], form
+        launches = sum(1 << i for i, o in enumerate(ops) if o[1] == "L")
+        assert launches, form
+        before, done = _behind(ops)
+        names = lambda bits: sorted({ops[i][5] for i in range(len(ops)) if bits >> i & 1})
+        assert done["77"] & launches == launches, (form, names(launches & ~done["77"]))
+        for i, o in enumerate(ops):
+            if o[1] == "L" and "tile_" in o[5]:
+                rest = sum(1 << j for j in range(i) if ops[j][1] == "L" and "tile_" not in ops[j][5])
+                assert before[i] & rest == rest, (form, o[5], names(rest & ~before[i]))

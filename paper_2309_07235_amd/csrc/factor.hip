@@ -284,6 +284,13 @@ struct LookaheadCtx {
   double ticks_per_s = 1e8;     // rate of the constant wall clock the in-kernel waits are bounded by
   bool ok = false;
 };
+// They are shared by every call of the process, of whatever kind and type: who uses them holds this, so that one call enqueues all
+// it has before the next one starts to, and calls from several host threads line up on the helper streams instead of mixing
+// their events.
+static std::mutex& lookahead_mutex() {
+  static std::mutex m;
+  return m;
+}
 // data: a device pointer of the call (its device is made current for a host thread that has none yet).
 static LookaheadCtx& lookahead_ctx(const void* data) {
   static LookaheadCtx ctx;
@@ -398,6 +405,16 @@ static int launch_tiles(T* A, int64_t n, int64_t lda, int64_t k0, void* ws, cons
     return aligned ? launch_tiles_two_as<T, KIND, 0>(a, st, side, e_start, e_done) : launch_tiles_two_as<T, KIND, kTilePast>(a, st, side, e_start, e_done);
   }
   return aligned ? launch_tiles_as<T, KIND, 0>(a, st) : launch_tiles_as<T, KIND, kTilePast>(a, st);
+}
+
+// A whole factorisation in tiles.  It starts behind the previous call of the process that uses the helper streams: two of them
+// side by side would take the compute units that the other's workgroups wait for.  (The caller holds lookahead_mutex.)
+template <typename T, int KIND>
+static int tiles_call(T* A, int64_t n, int64_t lda, void* ws, int* d_info, long long wait_ticks, hipStream_t st, LookaheadCtx& ctx) {
+  if (hip_note(hipStreamWaitEvent(st, ctx.ev[7], 0), "hipStreamWaitEvent") != 0) return DLA_ERR_HIP;
+  const int rc = launch_tiles<T, KIND>(A, n, lda, 0, ws, nullptr, d_info, wait_ticks, st, ctx.bulk, ctx.ev[3], ctx.ev[2]);
+  if (rc != DLA_SUCCESS) return rc;
+  return hip_note(hipEventRecord(ctx.ev[7], st), "hipEventRecord") != 0 ? (int)DLA_ERR_HIP : (int)DLA_SUCCESS;
 }
 
 template <typename T, int KIND>
@@ -555,21 +572,11 @@ static int factor_impl(T* A, int64_t n, int64_t lda, const dla_factor_params* p,
     // Only the chain is handed over this way: a waiting kernel holds its compute units, and the
     // bulk update needs every unit outside the reserve at once, so a head update that also waited
     // in place for the strips (tried) doubled the bulk update's run time.
-    // The helper streams and events are shared by every call of the process: one call enqueues its
-    // whole pipeline before the next one starts to, so calls from several host threads line up on
-    // the helper streams instead of mixing their events.
-    static std::mutex submit_mutex;
-    std::lock_guard<std::mutex> submit_lock(submit_mutex);
+    std::lock_guard<std::mutex> submit_lock(lookahead_mutex());
     LookaheadCtx& ctx = lookahead_ctx(A);
     if (!ctx.ok) return DLA_ERR_HIP;  // (the failing call is on record)
-    if (plan.tiles && d_info && lda <= kTileMaxLd) {
-      // One launch.  It too starts behind the previous such call of the process: two of them side by side would take the
-      // compute units that the other's workgroups wait for.
-      if (hip_note(hipStreamWaitEvent(st, ctx.ev[7], 0), "hipStreamWaitEvent") != 0) return DLA_ERR_HIP;
-      const long long limit = (long long)(ctx.ticks_per_s * (0.1 + 8.0 * (2.0 * (double)n * (double)n * 256.0) / 8e12));
-      if ((rc = launch_tiles<T, KIND>(A, n, lda, 0, ws, nullptr, d_info, limit, st, ctx.bulk, ctx.ev[3], ctx.ev[2])) != DLA_SUCCESS) return rc;
-      return hip_note(hipEventRecord(ctx.ev[7], st), "hipEventRecord") != 0 ? (int)DLA_ERR_HIP : (int)DLA_SUCCESS;
-    }
+    if (plan.tiles && d_info && lda <= kTileMaxLd)
+      return tiles_call<T, KIND>(A, n, lda, ws, d_info, (long long)(ctx.ticks_per_s * (0.1 + 8.0 * (2.0 * (double)n * (double)n * 256.0) / 8e12)), st, ctx);
     wait_ticks = (long long)(ctx.ticks_per_s * (0.1 + 8.0 * (2.0 * (double)n * (double)n * 2.0 * nb) / 8e12));
     hipEvent_t e_head = ctx.ev[0], e_solve = ctx.ev[1], e_bulk = ctx.ev[2], e_start = ctx.ev[3], e_strip = ctx.ev[6];
     hipEvent_t e_diag[2] = {ctx.ev[4], ctx.ev[5]};  // by step parity
@@ -788,9 +795,10 @@ static int tiles_giveup(T* A, int64_t n, int64_t lda, void* ws, size_t ws_bytes,
   const int nt = (int)((n + kTileNb - 1) / kTileNb);
   if (nt < 2 || nt > kTileMaxNt || lda > kTileMaxLd) return DLA_ERR_UNSUPPORTED_PARAMS;
   if (!ws || ws_bytes < tile_workspace_bytes<T>(nt) || ((uintptr_t)ws % 256)) return DLA_ERR_WORKSPACE;
+  std::lock_guard<std::mutex> submit_lock(lookahead_mutex());
   LookaheadCtx& ctx = lookahead_ctx(A);
   if (!ctx.ok) return DLA_ERR_HIP;
-  return launch_tiles<T, KIND>(A, n, lda, 0, ws, nullptr, d_info, -1, st, ctx.bulk, ctx.ev[3], ctx.ev[2]);
+  return tiles_call<T, KIND>(A, n, lda, ws, d_info, -1, st, ctx);
 }
 int tiles_giveup_impl(int kind, void* A, int64_t n, int64_t lda, dla_dtype dt, void* ws, size_t ws_bytes, hipStream_t st, int* d_info) {
   if (dt == DLA_F64)

@@ -112,3 +112,20 @@ def test_a_call_joins_all_it_has_submitted(record):
             if o[1] == "L" and "tile_" in o[5]:
                 rest = sum(1 << j for j in range(i) if ops[j][1] == "L" and "tile_" not in ops[j][5])
                 assert before[i] & rest == rest, (form, o[5], names(rest & ~before[i]))
+
+
+def test_calls_from_several_threads_line_up(record):
+    """The helper streams and events are one set for the process: whatever the kinds and types of the calls, one has submitted all
+    it has before the next begins to, starts behind it on the device, and the set is made once."""
+    calls = [_call("lu", F64, 600), _call("chol", F64, 700), _call("lu", F32, 1500), _call("chol", F32, 6000), _call("lu", F64, 8000),
+             _call("chol", F64, 900, lookahead=2), _call("lu", F32, 4000, giveup=True), _call("chol", F64, 1000, giveup=True)]
+    (rc, ops), = record([[[c] for c in calls]], pause=200)
+    assert rc == [[0]] * len(calls)
+    turns = [t for i, (t, *_) in enumerate(ops) if i == 0 or ops[i - 1][0] != t]
+    assert sorted(turns) == list(range(len(calls))), turns
+    assert sum(o[1] == "S" for o in ops) == 3 and sum(o[1] == "E" for o in ops) == 8
+    before, _ = _behind([(t, w, st if st != "77" else f"77 of {t}", ev, g, k) for t, w, st, ev, g, k in ops])  # a stream per thread
+    for a, t in enumerate(turns[1:]):
+        first = next(i for i, o in enumerate(ops) if o[0] == t and o[1] == "L")
+        rest = sum(1 << i for i, o in enumerate(ops) if o[0] == turns[a] and o[1] == "L")
+        assert before[first] & rest == rest, (calls[turns[a]], calls[t])

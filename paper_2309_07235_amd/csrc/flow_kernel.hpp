@@ -136,6 +136,14 @@ __device__ __forceinline__ void flow_store(T* p, T x) {
   __hip_atomic_store(reinterpret_cast<U*>(p), u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+// Where a workgroup's wait hands what it has found from one wave to the others, with one barrier between the two: the next wait
+// takes the other slot, however many positions were found, so that a slot is written again only behind the barrier of the wait
+// between, in front of which every wave has read it.
+struct FlowSlots {
+  int waits = 0;
+  __host__ __device__ int next() { return waits++ & 1; }
+};
+
 template <typename T, int NB>
 struct FlowTile {  // (32-bit byte offsets throughout: kFlowMaxLd)
   static constexpr int STEPS = kFlowBlock / 16;  // k-steps of a wave per block
@@ -416,6 +424,7 @@ __global__ void __launch_bounds__(kFlowThreads, NB == 1 ? 3 : 2) flow_kernel(con
   };
   bool behind = true;
   int complete = 0;  // positions that a look at the flags has found complete
+  FlowSlots slots;
   auto step = [&](const T (&a)[STEPS], int q) __attribute__((always_inline)) {
     const int j = block_of(q), kc = rows_of(j);
     const T* const x = block_at(sum_wg || q != own ? V : p > kFlowLook ? S : g.Y, j);
@@ -425,8 +434,9 @@ __global__ void __launch_bounds__(kFlowThreads, NB == 1 ? 3 : 2) flow_kernel(con
       // line was brought with another block's rows, before these were there, the loads below follow)
       if (q >= complete) {
         const int stride = g.tiles_n * kFlowTiles;
-        if (count - q > 2) complete = q + t.template wait_positions<32>(flags_of(back, q), stride, pieces_of(j), count - 1 - q, behind, &shared_late[q & 1]);
-        else complete = q + t.template wait_positions<8>(flags_of(back, q), stride, pieces_of(j), count - 1 - q, behind, &shared_late[q & 1]);
+        int* const found = &shared_late[slots.next()];
+        if (count - q > 2) complete = q + t.template wait_positions<32>(flags_of(back, q), stride, pieces_of(j), count - 1 - q, behind, found);
+        else complete = q + t.template wait_positions<8>(flags_of(back, q), stride, pieces_of(j), count - 1 - q, behind, found);
       }
       there = t.template load_area<0>(b, x, ldy, kc);
     } else if (!sum_wg && q == own && p <= kFlowLook && !back) {

@@ -348,7 +348,7 @@ static int launch_tiles_as(const TileArgs<T>& a, hipStream_t st) {
   auto kern = tile_factor_kernel<T, KIND, AUX>;
   static LdsLimitOnce lds_limit;
   if (!lds_limit.ensure(reinterpret_cast<const void*>(kern), tile_lds_bytes<T>())) return DLA_ERR_HIP;
-  const int tiles = tile_before<KIND>(a.nt, a.nt);
+  const int tiles = tile_count<KIND>(a.nt);
   const dim3 grid((unsigned)(tiles < kNumCu ? tiles + 1 : kNumCu)), block(kTileThreads);
   const double flops = (KIND == KIND_LU ? 2.0 : 1.0) * (double)a.n * (double)a.n * (double)a.n / 3.0;
   hipEvent_t p0 = nullptr, p1 = nullptr;
@@ -368,7 +368,7 @@ static int launch_tiles_two_as(const TileArgs<T>& a, hipStream_t st, hipStream_t
   if (hip_note(hipStreamWaitEvent(side, e_start, 0), "hipStreamWaitEvent") != 0) return DLA_ERR_HIP;
   hipLaunchKernelGGL(chain, dim3(1), dim3(kTileThreads), tile_lds_bytes<T>(), st, a);
   if (launch_status(__func__) != DLA_SUCCESS) return DLA_ERR_HIP;
-  const int tiles = tile_before<KIND>(a.nt, a.nt), most = 2 * (kNumCu - 1);
+  const int tiles = tile_count<KIND>(a.nt), most = 2 * (kNumCu - 1);
   const double flops = (KIND == KIND_LU ? 2.0 : 1.0) * (double)a.n * (double)a.n * (double)a.n / 3.0;
   hipEvent_t p0 = nullptr, p1 = nullptr;
   const dim3 grid((unsigned)(tiles < most ? tiles : most)), block(kTileOwnerThreads);

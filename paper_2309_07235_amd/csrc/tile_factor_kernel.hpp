@@ -24,9 +24,10 @@
 // between tiles (base and leading dimension multiples of 128 bytes) and only its owner has touched it, on the XCD that it
 // publishes it from; otherwise, and for everything that is reused or written by workgroup 0, by loads past the L2.
 //
-// Order.  Tiles are taken by step from a counter, so a workgroup waits only for workgroup 0 and for tiles taken before its own,
-// and workgroup 0 waits only for tiles of the steps so far and the next diagonal tile, the first of its step: one resident
-// workgroup beside workgroup 0 is enough.  Waits are bounded like those of the pipeline (chain_wait).
+// Order.  Tiles are taken from a counter by step, the three that workgroup 0 needs before it publishes block s first in step s
+// (tile_of): (s+1, s), (s, s+1) and (s+1, s+1).  A workgroup waits only for workgroup 0 and for tiles taken before its own, so that
+// three workgroups beside workgroup 0 that are there to the end are enough (Cholesky: two), however few the others let run.  Waits
+// are bounded like those of the pipeline (chain_wait).
 #pragma once
 #include "head_kernel.hpp"
 
@@ -596,36 +597,41 @@ __device__ __forceinline__ void tile_owner(const TileArgs<T>& g, T* const smem, 
   tile_publish(g.ints + (i > j ? fl.low(i, j) : fl.up(j, i)), tid);
 }
 
-// Tiles in front of those of step s.
+// The order in which tiles are taken.  Step s: (s+1, s), (s, s+1) (LU), (s+1, s+1), then the others of block column and row s.  Block
+// (0, 0) is not among them, it starts on the diagonal's chain.  Tiles in front of those of step s, and tile number id:
 template <int KIND>
 __host__ __device__ inline int tile_before(int nt, int s) { return KIND == KIND_LU ? 2 * s * nt - s * s : s * nt - s * (s - 1) / 2; }
+template <int KIND>
+__host__ __device__ inline int tile_count(int nt) { return tile_before<KIND>(nt, nt - 1); }
+template <int KIND>
+__host__ __device__ inline void tile_of(int nt, int id, int* i, int* j) {
+  int s = 0;
+  for (int step = 64; step > 0; step >>= 1)  // the last s with tile_before(s) <= id
+    while (s + step < nt - 1 && tile_before<KIND>(nt, s + step) <= id) s += step;
+  const int q = id - tile_before<KIND>(nt, s);
+  *i = *j = s;
+  if (KIND == KIND_LU) {
+    if (q == 2) *i = *j = s + 1;
+    else if (q < 2) (q == 0 ? *i : *j) = s + 1;
+    else ((q & 1) ? *i : *j) = s + 2 + (q - 3) / 2;
+  } else {
+    *i = q < 2 ? s + 1 : s + q;
+    if (q == 1) *j = s + 1;
+  }
+}
 
 // Tiles from the counter until there are none left.
 template <typename T, int KIND, int AUX, int WAVES>
 __device__ __forceinline__ void tile_owners(const TileArgs<T>& g, T* const smem, int* const ticket) {
-  const int tid = (int)threadIdx.x, nt = g.nt, tiles = tile_before<KIND>(nt, nt);
+  const int tid = (int)threadIdx.x, tiles = tile_count<KIND>(g.nt);
   for (;;) {
     __syncthreads();
     if (tid == 0) *ticket = __hip_atomic_fetch_add(g.ints + TileFlags::kTicket, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     __syncthreads();
     const int id = __builtin_amdgcn_readfirstlane(*ticket);
     if (id >= tiles) return;  // uniform
-    int s = 0;
-    for (int step = 64; step > 0; step >>= 1)  // the last s with tile_before(s) <= id
-      while (s + step < nt && tile_before<KIND>(nt, s + step) <= id) s += step;
-    const int q = id - tile_before<KIND>(nt, s);
-    int i = s, j = s;
-    if (q > 0) {
-      if (KIND == KIND_LU) {
-        const int far = s + (q + 1) / 2;
-        if (q & 1) i = far;
-        else j = far;
-      } else {
-        i = s + q;
-      }
-    } else if (s == 0) {
-      continue;  // block 0 starts on the diagonal's chain
-    }
+    int i, j;
+    tile_of<KIND>(g.nt, id, &i, &j);
     if constexpr (WAVES == 4) {  // beside the diagonal: before the other workgroup of the compute unit
       if (i - j <= 2 && j - i <= 2) __builtin_amdgcn_s_setprio(3);
       else __builtin_amdgcn_s_setprio(0);

@@ -45,28 +45,26 @@ size_t factor_workspace_bytes_impl(int64_t n, dla_dtype dt, const dla_factor_par
   return 4 * inv_set_bytes(dt) + 4 * head_copy_bytes(dt) + 256;  // + the hand-over counters of the latency chain
 }
 
-// Matrices that tile_factor_kernel's form takes where the caller leaves the schedule to the library (block size 0, or 128, which
-// is what dla_default_params gives, and nothing else named): up to max_n, from two_from on in two
-// launches.  A larger one is factored in the pipeline, by blocks of 128, down to a tail of rows.  Below, the chain of the diagonal is
+// Matrices that tile_factor_kernel takes where the caller leaves the schedule to the library (block size 0, or 128, which
+// is what dla_default_params gives, and nothing else named): up to max_n.  A larger one is factored in the pipeline, by blocks of
+// 128, down to a tail of rows.  Below, the chain of the diagonal is
 // what a factorisation takes, and it is shorter there; above, the products, whose operands the pipeline reads less often.
-// us, the pipeline / one launch / two launches (the second: two tiles to a compute unit, but 20 us of events):
-//   LU fp64        n = 300 125 / 98 / -, 1024 365 / 300 / 315, 3500 1585 / 1150 / 1187, 4000 1859 / 1570 / 1420, 5600 3528 / 4013 / 3052,
-//                  6400 4662 / 5866 / 4278, 8000 8040 / 11085 / 8470
-//   Cholesky fp64  n = 300 125 / 89 / -, 1024 365 / 271 / 275, 4000 1505 / 1128 / 1214, 4800 1930 / 1630 / 1642, 5600 2510 / 2410 / 2270,
-//                  6400 3222 / 3393 / 3112, 8000 5270 / 6256 / 5600
-//   LU fp32        n = 300 111 / 81 / -, 4000 1516 / 1173 / 1197, 4800 1920 / 1839 / 1640, 5600 2510 / 2928 / 2337, 6400 3190 / 4293 / 3319
-//   Cholesky fp32  n = 300 108 / 78 / -, 4000 1400 / 1012 / 1225, 4800 1720 / 1487 / 1655, 5600 2100 / 2215 / 2260 (with rows 16 longer
-//                  2130 / 1760 / 1945), 6400 2500 / 3150 / 3012
-//   n = 7000       LU fp64 6880 / - / 5574, Cholesky fp64 4313 / - / 3348
+// us, the pipeline / tiles:
+//   LU fp64        n = 300 125 / 98, 1024 365 / 302, 3500 1585 / 1082, 4000 1859 / 1391, 5600 3528 / 3050, 6400 4662 / 4250, 7000 6880 / 5235
+//   Cholesky fp64  n = 300 125 / 89, 1024 365 / 271, 4000 1505 / 1115, 4800 1930 / 1530, 5600 2510 / 2185, 6400 3222 / 3020, 7000 4313 / 3226
+//   LU fp32        n = 300 111 / 81, 4000 1516 / 1045, 4800 1920 / 1546, 5600 2510 / 2302
+//   Cholesky fp32  n = 300 108 / 78, 4000 1400 / 988, 4800 1720 / 1397, 5400 - / 1537
+// and at the ends of the range, the pipeline with a tail / tiles: LU fp64 7360 6128 / 6196, 8000 7643 / 7840, Cholesky fp64 7360 4110 / 4346,
+// LU fp32 5696 2217 / 2366, Cholesky fp32 5440 1708 / 1860.
 // tail: how many rows the pipeline leaves to it.  n = 8192, all in the pipeline, then with tails of 3000, 4000, 5000, 5800, 6600:
-// LU fp64 8466, 8326 8185 8095 8063 8174; Cholesky fp64 5382, 5210 5146 5269 5324 5408; LU fp32 5177, 4913 4949 5050 5115 5451;
-// Cholesky fp32 3782, 3583 3558 3781 4120 4511 (rows 2^15 bytes apart; 16 elements more 3738, 3559 3452 3429 3718 3828).
+// LU fp64 8419, 8217 8115 8149 8083 8144; Cholesky fp64 5360, 5220 5109 5110 5239 5373; LU fp32 5163, 4921 4787 4874 5064 5395;
+// Cholesky fp32 3710, 3575 3495 3636 3883 4285 (rows 2^15 bytes apart; 16 elements more 3726, 3561 3448 3354 3411 3591).
 struct TileRange {
-  int64_t two_from, max_n, tail;
+  int64_t max_n, tail;
 };
 static TileRange tile_range(dla_dtype dt, int op) {
-  if (op == OP_SUB) return dt == DLA_F64 ? TileRange{3700, 7200, 5800} : TileRange{4300, 5600, 4000};
-  return dt == DLA_F64 ? TileRange{4800, 7200, 4000} : TileRange{5400, 5400, 4000};
+  if (op == OP_SUB) return dt == DLA_F64 ? TileRange{7200, 5800} : TileRange{5600, 4000};
+  return dt == DLA_F64 ? TileRange{7200, 4000} : TileRange{5400, 4000};
 }
 
 int resolve_factor_params(dla_dtype dt, int64_t n, const dla_factor_params* in, int op, FactorPlan* plan,
@@ -343,47 +341,27 @@ static GemmSchedule panel_schedule(int64_t mr) {
   return mr <= 2304 ? GemmSchedule{32, 32, 128, 8, 16, 16} : GemmSchedule{32, 32, 16, 4, 16, 16};
 }
 
-template <typename T, int KIND, int AUX>
+// Two teams to a workgroup: LU in fp64, whose products weigh most, from here on and where tiles are read through the L2.  us, one
+// team / two: LU fp64 n = 4000 1390 / 1442, 4800 2100 / 2088, 5008 2388 / 2346, 5600 3140 / 3066, 6400 4407 / 4286, 7200 6157 / 5906; not aligned
+// 5401 3110 / 3208, 7001 6261 / 6400; Cholesky fp64 n = 4800 1527 / 1643, 6400 3029 / 3102; LU fp32 n = 4000 1046 / 1090, 5000 1737 / 1791;
+// Cholesky fp32 n = 4000 988 / 1104, 5400 1533 / 1623.
+constexpr int64_t kTwoTeamsMinRows = 5000;
+template <typename T, int KIND, int AUX, int TEAMS>
 static int launch_tiles_as(const TileArgs<T>& a, hipStream_t st) {
-  auto kern = tile_factor_kernel<T, KIND, AUX>;
+  auto kern = tile_factor_kernel<T, KIND, AUX, TEAMS>;
+  constexpr int lds = tile_lds_bytes<T, TEAMS>();
   static LdsLimitOnce lds_limit;
-  if (!lds_limit.ensure(reinterpret_cast<const void*>(kern), tile_lds_bytes<T>())) return DLA_ERR_HIP;
-  const int tiles = tile_count<KIND>(a.nt);
-  const dim3 grid((unsigned)(tiles < kNumCu ? tiles + 1 : kNumCu)), block(kTileThreads);
+  if (!lds_limit.ensure(reinterpret_cast<const void*>(kern), lds)) return DLA_ERR_HIP;
+  const int wgs = (tile_count<KIND>(a.nt) + TEAMS - 1) / TEAMS + 1;
+  const dim3 grid((unsigned)(wgs < kNumCu ? wgs : kNumCu)), block(kTileThreads);
   const double flops = (KIND == KIND_LU ? 2.0 : 1.0) * (double)a.n * (double)a.n * (double)a.n / 3.0;
   hipEvent_t p0 = nullptr, p1 = nullptr;
-  if (profile_kernel_events(PHASE_UPDATE, flops, &p0, &p1)) hipExtLaunchKernelGGL(kern, grid, block, tile_lds_bytes<T>(), st, p0, p1, 0, a);
-  else hipLaunchKernelGGL(kern, grid, block, tile_lds_bytes<T>(), st, a);
+  if (profile_kernel_events(PHASE_UPDATE, flops, &p0, &p1)) hipExtLaunchKernelGGL(kern, grid, block, lds, st, p0, p1, 0, a);
+  else hipLaunchKernelGGL(kern, grid, block, lds, st, a);
   return launch_status(__func__);
 }
-// The same in two launches: `clear` has happened on st (e_start rides behind it), the tiles' workgroups run on `side`.
-template <typename T, int KIND, int AUX>
-static int launch_tiles_two_as(const TileArgs<T>& a, hipStream_t st, hipStream_t side, hipEvent_t e_start, hipEvent_t e_done) {
-  auto chain = tile_chain_kernel<T, KIND>;
-  auto owners = tile_owner_kernel<T, KIND, AUX>;
-  static LdsLimitOnce chain_limit, owner_limit;
-  if (!chain_limit.ensure(reinterpret_cast<const void*>(chain), tile_lds_bytes<T>()) ||
-      !owner_limit.ensure(reinterpret_cast<const void*>(owners), tile_owner_lds_bytes<T>()))
-    return DLA_ERR_HIP;
-  if (hip_note(hipStreamWaitEvent(side, e_start, 0), "hipStreamWaitEvent") != 0) return DLA_ERR_HIP;
-  hipLaunchKernelGGL(chain, dim3(1), dim3(kTileThreads), tile_lds_bytes<T>(), st, a);
-  if (launch_status(__func__) != DLA_SUCCESS) return DLA_ERR_HIP;
-  const int tiles = tile_count<KIND>(a.nt), most = 2 * (kNumCu - 1);
-  const double flops = (KIND == KIND_LU ? 2.0 : 1.0) * (double)a.n * (double)a.n * (double)a.n / 3.0;
-  hipEvent_t p0 = nullptr, p1 = nullptr;
-  const dim3 grid((unsigned)(tiles < most ? tiles : most)), block(kTileOwnerThreads);
-  if (profile_kernel_events(PHASE_UPDATE, flops, &p0, &p1)) {
-    hipExtLaunchKernelGGL(owners, grid, block, tile_owner_lds_bytes<T>(), side, p0, p1, 0, a);
-    if (launch_status(__func__) != DLA_SUCCESS || hip_note(hipEventRecord(e_done, side), "hipEventRecord") != 0) return DLA_ERR_HIP;
-  } else {
-    hipExtLaunchKernelGGL(owners, grid, block, tile_owner_lds_bytes<T>(), side, nullptr, e_done, 0, a);
-    if (launch_status(__func__) != DLA_SUCCESS) return DLA_ERR_HIP;
-  }
-  return hip_note(hipStreamWaitEvent(st, e_done, 0), "hipStreamWaitEvent") != 0 ? (int)DLA_ERR_HIP : (int)DLA_SUCCESS;
-}
 template <typename T, int KIND>
-static int launch_tiles(T* A, int64_t n, int64_t lda, int64_t k0, void* ws, const int* broken, int* d_info, long long wait_ticks,
-                        hipStream_t st, hipStream_t side, hipEvent_t e_start, hipEvent_t e_done) {
+static int launch_tiles(T* A, int64_t n, int64_t lda, int64_t k0, void* ws, const int* broken, int* d_info, long long wait_ticks, hipStream_t st) {
   TileArgs<T> a;
   a.A = A;
   a.lda = lda;
@@ -400,11 +378,9 @@ static int launch_tiles(T* A, int64_t n, int64_t lda, int64_t k0, void* ws, cons
   hipLaunchKernelGGL(tile_clear_kernel, dim3((unsigned)((count + 255) / 256)), dim3(256), 0, st, a.ints, count);
   if (launch_status(__func__) != DLA_SUCCESS) return DLA_ERR_HIP;
   const bool aligned = (uintptr_t)A % 128 == 0 && (lda * (int64_t)sizeof(T)) % 128 == 0;
-  if (n >= tile_range(sizeof(T) == 8 ? DLA_F64 : DLA_F32, KIND == KIND_LU ? OP_SUB : OP_SUB_NT_LOWER).two_from) {
-    if (hip_note(hipEventRecord(e_start, st), "hipEventRecord") != 0) return DLA_ERR_HIP;
-    return aligned ? launch_tiles_two_as<T, KIND, 0>(a, st, side, e_start, e_done) : launch_tiles_two_as<T, KIND, kTilePast>(a, st, side, e_start, e_done);
-  }
-  return aligned ? launch_tiles_as<T, KIND, 0>(a, st) : launch_tiles_as<T, KIND, kTilePast>(a, st);
+  if constexpr (KIND == KIND_LU && sizeof(T) == 8)
+    if (aligned && n >= kTwoTeamsMinRows) return launch_tiles_as<T, KIND, 0, 2>(a, st);
+  return aligned ? launch_tiles_as<T, KIND, 0, 1>(a, st) : launch_tiles_as<T, KIND, kTilePast, 1>(a, st);
 }
 
 // A whole factorisation in tiles.  It starts behind the previous call of the process that uses the helper streams: two of them
@@ -412,7 +388,7 @@ static int launch_tiles(T* A, int64_t n, int64_t lda, int64_t k0, void* ws, cons
 template <typename T, int KIND>
 static int tiles_call(T* A, int64_t n, int64_t lda, void* ws, int* d_info, long long wait_ticks, hipStream_t st, LookaheadCtx& ctx) {
   if (hip_note(hipStreamWaitEvent(st, ctx.ev[7], 0), "hipStreamWaitEvent") != 0) return DLA_ERR_HIP;
-  const int rc = launch_tiles<T, KIND>(A, n, lda, 0, ws, nullptr, d_info, wait_ticks, st, ctx.bulk, ctx.ev[3], ctx.ev[2]);
+  const int rc = launch_tiles<T, KIND>(A, n, lda, 0, ws, nullptr, d_info, wait_ticks, st);
   if (rc != DLA_SUCCESS) return rc;
   return hip_note(hipEventRecord(ctx.ev[7], st), "hipEventRecord") != 0 ? (int)DLA_ERR_HIP : (int)DLA_SUCCESS;
 }
@@ -776,7 +752,7 @@ static int factor_impl(T* A, int64_t n, int64_t lda, const dla_factor_params* p,
     if (bulk_pending && hip_note(hipStreamWaitEvent(st, e_bulk, 0), "hipStreamWaitEvent") != 0) return DLA_ERR_HIP;
     if (tail > 0) {
       const int64_t k0 = n - tail;
-      if ((rc = launch_tiles<T, KIND>(A + k0 * lda + k0, tail, lda, k0, ws, chain + 2, d_info, wait_ticks, st, ctx.bulk, e_start, e_bulk)) != DLA_SUCCESS)
+      if ((rc = launch_tiles<T, KIND>(A + k0 * lda + k0, tail, lda, k0, ws, chain + 2, d_info, wait_ticks, st)) != DLA_SUCCESS)
         return rc;
     }
     if (hip_note(hipEventRecord(e_call_done, st), "hipEventRecord") != 0) return DLA_ERR_HIP;

@@ -1,21 +1,24 @@
-// A whole factorisation as one launch, or two side by side, in 64 x 64 tiles (paper, Section "Linear Algebra Benchmarks": A = L*U without
+// A whole factorisation as one launch, in 64 x 64 tiles (paper, Section "Linear Algebra Benchmarks": A = L*U without
 // pivoting, A = L*L^T; the tiling is this library's).  Workgroups wait in place for what they read:
 //   workgroup 0 walks the diagonal: block s lies in its LDS, is factored there (diag_stages), then the two blocks beside the
 //     next one, (s, s+1) and (s+1, s), are solved from copies and block (s+1, s+1) gets their product, so that from one
 //     diagonal block to the next nothing leaves the workgroup;
-//   every other workgroup owns one tile, (i, j) with step s = min(i, j), keeps it in accumulators, subtracts the products of
-//     the tiles in front of it, (i, k) (k, j), as these appear, and solves it once block s is factored.  The tiles beside the
-//     diagonal are also copied, unsolved, for workgroup 0, which is through with a block about when they are there.
+//   the other workgroups take tiles, (i, j) with step s = min(i, j), one at a time: the tile is kept in accumulators, the products of
+//     the tiles in front of it, (i, k) (k, j), are subtracted as these appear, and it is solved once block s is factored.  The tiles
+//     beside the diagonal are also copied, unsolved, for workgroup 0, which is through with a block about when they are there.
 // So a tile of the matrix is read and written once, there is one launch instead of six per block column, and the chain of
-// the diagonal is free of hand-overs.  In two launches (tile_chain_kernel, tile_owner_kernel) the tiles' workgroups have four
-// waves instead of eight and two of them share a compute unit: one's start, solve and publication hide behind the other's
-// products, which is what the larger matrices need, and the second stream's two events, 20 us, what the smaller ones do not.
+// the diagonal is free of hand-overs.  It is one launch also because its workgroups wait for each other both ways: two launches on
+// two streams that share a hardware queue would run one after the other.
+//
+// A tile's workgroup has eight waves, four 32 x 32 parts of the tile times two halves of each product's depth; or they are two teams
+// of four that each have a tile of their own (TileTeam), so that one's start, solve and publication hide behind the other's
+// products, which is what large matrices with aligned tiles need and what costs the chain of smaller ones (launch_tiles_as).
 //
 // What bounds it is that chain while the matrix is small: LU 18, Cholesky 16 us per 64 columns, of which the four stages of the
 // diagonal block are 11.5, the two solves 1.9 - 3.4, the product with the next block's first factor 2.3.  (A block of 128 in the
-// pipeline, with its head update and two hand-overs between kernels, is 47.)  Beyond, the tiles' products, whose operands come
-// from the L2.  us, the pipeline against one launch: LU fp64 n = 300 125 -> 98, Cholesky n = 1024 in blocks of 64 713 -> 264,
-// n = 4000 1580 -> 1144; two launches: LU fp64 n = 4000 1866 -> 1444 (30 TFLOP/s), n = 7000 6880 -> 5574 (41).
+// pipeline, with its head update and two hand-overs between kernels, is 47.)  Beyond, the tiles' products.  us, the pipeline against
+// this: LU fp64 n = 300 125 -> 98, n = 4000 1866 -> 1391 (31 TFLOP/s), n = 7000 6880 -> 5235 (44), Cholesky n = 1024 in blocks of 64
+// 713 -> 269, n = 4000 1580 -> 1115.
 // Half of 128 registers per lane for two workgroups of eight waves spills; a workgroup on the chain's compute unit costs the
 // chain 2 - 4 us a step.
 //
@@ -68,15 +71,8 @@ struct TileFlags {
   __host__ __device__ int read(int s) const { return kFirst + nt * nt + 5 * nt + s; }              // tiles that have read block s
   __host__ __device__ int count() const { return kFirst + nt * nt + 6 * nt; }
 };
-// LDS of workgroup 0: block, pivots, inverses, the slices of both solves.  (A tile's workgroup needs less; what both are given
-// leaves one workgroup to a compute unit.)
+// LDS of workgroup 0: block, pivots, inverses, the slices of both solves.
 constexpr int kTileSlices = (kTileNb + 1) * kTileLd + 2 * kTileNb + 2 * kTileSub * kBlk, kTileLds = kTileSlices + 8 * kTileSub * 4 * 64 + kBlk;
-static_assert(kTileLds >= 2 * kTileNb * kTileLd + kTileSub * kBlk, "a tile's workgroup");
-template <typename T>
-constexpr int tile_lds_bytes() {
-  constexpr int bytes = kTileLds * (int)sizeof(T);
-  return bytes > 84 * 1024 ? bytes : 84 * 1024;
-}
 template <typename T>
 inline size_t tile_workspace_bytes(int nt) {
   return (size_t)(kTileInvRing * kTileInv + 6 * kTileElems) * sizeof(T) + (size_t)TileFlags{nt}.count() * sizeof(int);
@@ -161,18 +157,39 @@ __device__ __forceinline__ void tile_spin(int* ints, long long limit, int pause,
     }
   }
 }
-// A workgroup waits, by its first wave.
-template <typename F>
-__device__ __forceinline__ void tile_wait(int* ints, long long limit, int wave, int pause, F&& ok) {
-  if (wave == 0) tile_spin(ints, limit, pause, ok);
-  lds_barrier();
+// The waves that work on one tile: all eight of a workgroup, or four, one of its two teams, which share the compute unit but wait
+// for nothing of each other.  A team meets at a count in LDS (s_barrier is the workgroup's): each wave adds one and looks until all
+// four of this meeting have.  The waves of a workgroup are all there, so every meeting ends.
+template <int WAVES>
+struct TileTeam {
+  int wave;      // within the team
+  int* arrived;  // four waves: the team's count, which starts at zero
+  int meetings = 0;
+  __device__ __forceinline__ void barrier() {
+    if constexpr (WAVES == kTileThreads / 64) {
+      lds_barrier();
+    } else {
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+      meetings += WAVES;
+      if ((threadIdx.x & 63) == 0) __hip_atomic_fetch_add(arrived, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+      while (__builtin_amdgcn_readfirstlane(__hip_atomic_load(arrived, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)) < meetings) {}
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+    }
+  }
+};
+// A team waits, by its first wave.
+template <int WAVES, typename F>
+__device__ __forceinline__ void tile_wait(int* ints, long long limit, TileTeam<WAVES>& team, int pause, F&& ok) {
+  if (team.wave == 0) tile_spin(ints, limit, pause, ok);
+  team.barrier();
   tile_order();
 }
 __device__ __forceinline__ bool tile_flag(const int* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0; }
 // every wave's stores are past the L2s, then the flag
-__device__ __forceinline__ void tile_publish(int* flag, int tid) {
+template <int WAVES>
+__device__ __forceinline__ void tile_publish(int* flag, TileTeam<WAVES>& team, int tid) {
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-  lds_barrier();
+  team.barrier();
   if (tid == 0) __hip_atomic_store(flag, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
@@ -370,13 +387,16 @@ __device__ __forceinline__ void tile_chain(const TileArgs<T>& g, T* const smem) 
   }
 }
 
-// ---- the workgroup of tile (i, j), of WAVES waves.  AUX: how other tiles are read (0 through the L2, kTilePast)
+// ---- the team of tile (i, j).  AUX: how other tiles are read (0 through the L2, kTilePast)
 template <typename T, int KIND, int AUX, int WAVES>
-__device__ __forceinline__ void tile_owner(const TileArgs<T>& g, T* const smem, const int i, const int j) {
+__device__ __forceinline__ void tile_owner(const TileArgs<T>& g, T* const smem, TileTeam<WAVES>& team, const int i, const int j) {
   using acc_t = typename Mfma<T>::acc_t;
   constexpr bool LU = KIND == KIND_LU;
   constexpr int E = (int)sizeof(T), kOob = 0x7FFFFFF0, kFlags = 0x00020000;
-  const int tid = (int)threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  // (the lane's place as a value of this tile, as in tile_chain)
+  int tid = (int)threadIdx.x % (WAVES * 64);
+  asm volatile("" : "+v"(tid));
+  const int lane = tid & 63, wave = team.wave;
   const int l15 = lane & 15, l4 = lane >> 4;
   const TileFlags fl{g.nt};
   const int s = i < j ? i : j, far = i < j ? j : i;
@@ -493,7 +513,7 @@ __device__ __forceinline__ void tile_owner(const TileArgs<T>& g, T* const smem, 
       }
       if (lane == 0) shared[0] = ready;
     }
-    lds_barrier();
+    team.barrier();
     ready = __builtin_amdgcn_readfirstlane(shared[0]);
     tile_order();
     if (ready > depth - k) ready = depth - k;
@@ -518,7 +538,7 @@ __device__ __forceinline__ void tile_owner(const TileArgs<T>& g, T* const smem, 
         multiply(h1{});
       }
     }
-    lds_barrier();  // (shared[0] is read)
+    team.barrier();  // (shared[0] is read)
   }
 
   // ---- the tile to LDS, the halves of k added up
@@ -535,7 +555,7 @@ __device__ __forceinline__ void tile_owner(const TileArgs<T>& g, T* const smem, 
   };
   if constexpr (WAVES == 8) {
     if (khalf != 0) each([&](int r, int c, T x) { return P[r * kTileLd + c] = x; });
-    lds_barrier();
+    team.barrier();
     if (khalf == 0) each([&](int r, int c, T x) { return P[r * kTileLd + c] += x; });
   } else {
     each([&](int r, int c, T x) { return P[r * kTileLd + c] = x; });
@@ -548,12 +568,12 @@ __device__ __forceinline__ void tile_owner(const TileArgs<T>& g, T* const smem, 
       tile_store(out + (what == 1 ? c * kTileNb + r : r * kTileNb + c), x);
       return x;
     });
-    tile_publish(g.ints + fl.copied(at, what), tid);
+    tile_publish(g.ints + fl.copied(at, what), team, tid);
   }
   if (i == j) return;
 
   // ---- solved with block s
-  tile_wait(g.ints, g.wait_ticks, wave, 1, [&] { return __hip_atomic_load(g.ints + fl.diag(s), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >= 4; });
+  tile_wait(g.ints, g.wait_ticks, team, 1, [&] { return __hip_atomic_load(g.ints + fl.diag(s), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >= 4; });
   {
     const T* const src = tile_at(s, s);
     const T* const inv = g.inv + (int64_t)(s % kTileInvRing) * kTileInv + (LU && i > j ? kTileSub * 256 : 0);
@@ -571,7 +591,7 @@ __device__ __forceinline__ void tile_owner(const TileArgs<T>& g, T* const smem, 
       sInv[(at >> 8) * kBlk + r * 17 + c] = w[e];
     }
   }
-  lds_barrier();
+  team.barrier();
   if (tid == 0) __hip_atomic_fetch_add(g.ints + fl.read(s), 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   if (wave < 4) {
     const bool x_job = LU && i < j;
@@ -594,7 +614,7 @@ __device__ __forceinline__ void tile_owner(const TileArgs<T>& g, T* const smem, 
         }
     }
   }
-  tile_publish(g.ints + (i > j ? fl.low(i, j) : fl.up(j, i)), tid);
+  tile_publish(g.ints + (i > j ? fl.low(i, j) : fl.up(j, i)), team, tid);
 }
 
 // The order in which tiles are taken.  Step s: (s+1, s), (s, s+1) (LU), (s+1, s+1), then the others of block column and row s.  Block
@@ -622,51 +642,42 @@ __host__ __device__ inline void tile_of(int nt, int id, int* i, int* j) {
 
 // Tiles from the counter until there are none left.
 template <typename T, int KIND, int AUX, int WAVES>
-__device__ __forceinline__ void tile_owners(const TileArgs<T>& g, T* const smem, int* const ticket) {
-  const int tid = (int)threadIdx.x, tiles = tile_count<KIND>(g.nt);
+__device__ __forceinline__ void tile_owners(const TileArgs<T>& g, T* const smem, int* const ticket, TileTeam<WAVES> team) {
+  const int tid = (int)threadIdx.x % (WAVES * 64), tiles = tile_count<KIND>(g.nt);
   for (;;) {
-    __syncthreads();
+    team.barrier();
     if (tid == 0) *ticket = __hip_atomic_fetch_add(g.ints + TileFlags::kTicket, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    __syncthreads();
+    team.barrier();
     const int id = __builtin_amdgcn_readfirstlane(*ticket);
     if (id >= tiles) return;  // uniform
     int i, j;
     tile_of<KIND>(g.nt, id, &i, &j);
-    if constexpr (WAVES == 4) {  // beside the diagonal: before the other workgroup of the compute unit
+    if constexpr (WAVES == 4) {  // beside the diagonal: before the other team
       if (i - j <= 2 && j - i <= 2) __builtin_amdgcn_s_setprio(3);
       else __builtin_amdgcn_s_setprio(0);
     }
-    tile_owner<T, KIND, AUX, WAVES>(g, smem, i, j);
+    tile_owner<T, KIND, AUX, WAVES>(g, smem, team, i, j);
   }
 }
 
-// The whole factorisation in one launch.
-template <typename T, int KIND, int AUX>
+// The whole factorisation in one launch; TEAMS: how many tiles a workgroup has at a time.
+constexpr int kTileTeamElems = 2 * kTileNb * kTileLd + kTileSub * kBlk;
+template <typename T, int TEAMS>
+constexpr int tile_lds_bytes() {
+  constexpr int elems = TEAMS * kTileTeamElems > kTileLds ? TEAMS * kTileTeamElems : kTileLds, bytes = elems * (int)sizeof(T);
+  return bytes > 84 * 1024 ? bytes : 84 * 1024;  // (more than half of a compute unit's: one workgroup each)
+}
+template <typename T, int KIND, int AUX, int TEAMS>
 __global__ void __launch_bounds__(kTileThreads, 2) tile_factor_kernel(const TileArgs<T> g) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
-  __shared__ int ticket;
+  __shared__ int ticket[TEAMS], arrived[TEAMS];
   T* const smem = reinterpret_cast<T*>(smem_raw);
+  constexpr int WAVES = kTileThreads / 64 / TEAMS;
+  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), t = TEAMS == 1 ? 0 : wave / WAVES;
+  if (threadIdx.x < TEAMS) arrived[threadIdx.x] = 0;
+  __syncthreads();
   if (blockIdx.x == 0) tile_chain<T, KIND>(g, smem);
-  else tile_owners<T, KIND, AUX, kTileThreads / 64>(g, smem, &ticket);
-}
-
-// The same in two, side by side on two streams: workgroup 0, and the tiles' workgroups with four waves, two of them to a compute
-// unit, one of which multiplies while the other starts, solves or publishes.
-template <typename T, int KIND>
-__global__ void __launch_bounds__(kTileThreads, 2) tile_chain_kernel(const TileArgs<T> g) {
-  extern __shared__ __align__(16) unsigned char smem_raw[];
-  tile_chain<T, KIND>(g, reinterpret_cast<T*>(smem_raw));
-}
-constexpr int kTileOwnerThreads = 256;
-template <typename T>
-constexpr int tile_owner_lds_bytes() {
-  return (2 * kTileNb * kTileLd + kTileSub * kBlk) * (int)sizeof(T);
-}
-template <typename T, int KIND, int AUX>
-__global__ void __launch_bounds__(kTileOwnerThreads, 2) tile_owner_kernel(const TileArgs<T> g) {
-  extern __shared__ __align__(16) unsigned char smem_raw[];
-  __shared__ int ticket;
-  tile_owners<T, KIND, AUX, kTileOwnerThreads / 64>(g, reinterpret_cast<T*>(smem_raw), &ticket);
+  else tile_owners<T, KIND, AUX, WAVES>(g, smem + t * kTileTeamElems, ticket + t, TileTeam<WAVES>{wave % WAVES, arrived + t});
 }
 
 }  // namespace dla

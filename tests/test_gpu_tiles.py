@@ -1,4 +1,4 @@
-"""Factorisations in 64 x 64 tiles (tile_factor_kernel and its form in two launches): edges of tiles, alignment, hand-over,
+"""Factorisations in 64 x 64 tiles (tile_factor_kernel, one team and two to a workgroup): edges of tiles, alignment, hand-over,
 breakdown, and the line to the pipeline."""
 import numpy as np
 import pytest
@@ -56,14 +56,15 @@ def test_tiles_match_the_oracle(B, oracle, kind, dtype, n, pad, shift, nb):
         assert np.all(np.triu(got, 1) == 0.0)
 
 
-# both sides of the line between one launch and two, and of the line to the pipeline (which then leaves its last rows to the
+# both sides of the line between one team and two to a workgroup (aligned rows of LU fp64), and of the line to the pipeline (which then leaves its last rows to the
 # tiles), also where the caller passes the library's defaults on; against the factor of the pipeline alone
 @gpu
 @pytest.mark.parametrize("kind,dtype,n", [("lu", "float64", 3699), ("lu", "float64", 3700), ("lu", "float64", 7200), ("lu", "float64", 7201),
                                           ("chol", "float64", 4799), ("chol", "float64", 4800), ("chol", "float64", 7233),
                                           ("lu", "float32", 4300), ("lu", "float32", 5601), ("chol", "float32", 5401),
                                           # the step in front of the tiles carries two panels
-                                          ("lu", "float64", 7300), ("lu", "float32", 5700), ("chol", "float64", 7300)])
+                                          ("lu", "float64", 7300), ("lu", "float32", 5700), ("chol", "float64", 7300),
+                                          ("lu", "float64", 4992), ("lu", "float64", 5008)])
 def test_lines_between_the_forms(B, kind, dtype, n):
     import torch
     announce(f"tiles lines {kind} {dtype} n={n}")
@@ -115,3 +116,34 @@ def test_waits_that_give_up_are_reported(B, kind, n):
     a = torch.eye(n, dtype=torch.float64, device="cuda") * 4
     (B.cholesky_factor if kind else B.lu_factor)(a, info=info)
     assert int(info.item()) == 0 and torch.equal(a, torch.eye(n, dtype=torch.float64, device="cuda") * (2 if kind else 4))
+
+
+@gpu
+def test_on_many_streams(B):
+    """A program's streams share a few hardware queues with the helper streams.  Whichever stream a call is on, the workgroups
+    that wait for each other run side by side, and the result is the default stream's bit for bit."""
+    import torch
+    cases = []
+    for kind, n, dtype in (("lu", 4000, torch.float64), ("lu", 5008, torch.float64), ("chol", 5000, torch.float64), ("lu", 5008, torch.float32),
+                           ("lu", 7300, torch.float64)):
+        gen = torch.Generator(device="cuda").manual_seed(n)
+        m = torch.rand(n, n, dtype=torch.float64, device="cuda", generator=gen) * 2 - 1
+        a = torch.mm(m, m.t()) / n
+        a.diagonal().add_(4.0)
+        factor, a = B.lu_factor if kind == "lu" else B.cholesky_factor, a.to(dtype)
+        info = torch.full((1,), -7, dtype=torch.int32, device="cuda")
+        want = a.clone()
+        factor(want, info=info)
+        assert int(info.item()) == 0
+        cases.append((factor, a, want, info, f"{kind} n={n} {dtype}"))
+    for i in range(12):
+        stream = torch.cuda.Stream()
+        factor, a, want, info, name = cases[i % len(cases)]
+        announce(f"tiles on side stream {i}: {name}")
+        info.fill_(-7)
+        x = a.clone()
+        stream.wait_stream(torch.cuda.current_stream())
+        with torch.cuda.stream(stream):
+            factor(x, info=info)
+        stream.synchronize()
+        assert int(info.item()) == 0 and torch.equal(x, want)

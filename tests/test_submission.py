@@ -129,3 +129,15 @@ def test_calls_from_several_threads_line_up(record):
         first = next(i for i, o in enumerate(ops) if o[0] == t and o[1] == "L")
         rest = sum(1 << i for i, o in enumerate(ops) if o[0] == turns[a] and o[1] == "L")
         assert before[first] & rest == rest, (calls[turns[a]], calls[t])
+
+
+def test_what_waits_for_each_other_is_one_launch(record):
+    """The tiles' workgroups wait for the diagonal's and it for theirs: in two launches they would need two hardware queues, and
+    streams share a few.  They are one launch, on the caller's stream, behind the one that clears their flags."""
+    tiled = 0
+    for form, (_, ops) in zip(FORMS, record([[[f]] for f in FORMS])):
+        tiles = [o for o in ops if o[1] == "L" and "tile_" in o[5]]
+        assert all(o[2] == "77" for o in tiles), (form, tiles)
+        assert not tiles or (len(tiles) == 2 and "tile_clear_kernel" in tiles[0][5] and "tile_factor_kernel" in tiles[1][5]), (form, tiles)
+        tiled += bool(tiles)
+    assert tiled == 4 * 7

@@ -339,14 +339,22 @@ int dla_handover_selftest(void* d_scratch, size_t scratch_bytes, void* hip_strea
 /*
  * Diagnostic for the waits inside lu_solve / cholesky_solve with up to 64 right-hand sides, whose two passes are one
  * launch of workgroups that wait for each other: kind 0 as lu_solve, 1 as cholesky_solve, the other arguments theirs, but
- * every wait gives up at once.  X then comes from the row by row substitution that stands in where a wait has given up (in
- * an ordinary call after 50 ms, which no call reaches unless other work keeps its workgroups off the compute units).
+ * every wait gives up at once.  X then comes from the row by row substitution that stands in where a launch has given up (in
+ * an ordinary call after one second in which it has not come on, which nothing is known to reach).
  */
 int dla_solve_giveup_selftest(int kind, const void* d_f, int64_t n, int64_t lda, void* d_b, int64_t nrhs, int64_t ldb, dla_dtype dt,
                               void* d_workspace, size_t workspace_bytes, void* hip_stream);
 
 /*
- * The same for factorisations in tiles (n from 65 to 8192): kind 0 as lu_factor, 1 as cholesky_factor, every wait gives up at
+ * Diagnostic for the order of the same launch: every eighth workgroup leaves at once, as if other work kept an XCD from starting
+ * its share, and the others take over what it has left (in an ordinary call after a wait of 2 ms).  X is bit for bit that of lu_solve /
+ * cholesky_solve.
+ */
+int dla_solve_absent_selftest(int kind, const void* d_f, int64_t n, int64_t lda, void* d_b, int64_t nrhs, int64_t ldb, dla_dtype dt,
+                              void* d_workspace, size_t workspace_bytes, void* hip_stream);
+
+/*
+ * The diagnostic of the waits for factorisations in tiles (n from 65 to 8192): kind 0 as lu_factor, 1 as cholesky_factor, every wait gives up at
  * once.  The launches end, *d_info is -1 and the content of A unspecified.
  */
 int dla_factor_giveup_selftest(int kind, void* d_a, int64_t n, int64_t lda, dla_dtype dt, void* d_workspace, size_t workspace_bytes,

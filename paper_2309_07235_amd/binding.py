@@ -95,8 +95,9 @@ def _load() -> ctypes.CDLL:
     lib.dla_mfma_peak_scratch_bytes.restype = ctypes.c_size_t
     lib.dla_handover_selftest.argtypes = [vp, sz, vp, vp]
     lib.dla_handover_selftest.restype = ci
-    lib.dla_solve_giveup_selftest.argtypes = [ci] + lib.lu_solve.argtypes
-    lib.dla_solve_giveup_selftest.restype = ci
+    for f in (lib.dla_solve_giveup_selftest, lib.dla_solve_absent_selftest):
+        f.argtypes = [ci] + lib.lu_solve.argtypes
+        f.restype = ci
     lib.dla_factor_giveup_selftest.argtypes = [ci, vp, i64, i64, ci, vp, sz, vp, vp]
     lib.dla_factor_giveup_selftest.restype = ci
     lib.dla_rank_update.argtypes = [ci, vp, vp, vp, i64, i64, i64, ci, vp]
@@ -382,6 +383,13 @@ def solve_giveup_selftest(kind: int, f, b, stream=None):
     def call(*args):
         return lib.dla_solve_giveup_selftest(kind, *args)
     return _solve(call, "dla_solve_giveup_selftest", f, b, None, stream)
+
+
+def solve_absent_selftest(kind: int, f, b, stream=None):
+    """lu_solve (kind 0) or cholesky_solve (1) with every eighth workgroup away (see dla.h: dla_solve_absent_selftest)."""
+    def call(*args):
+        return lib.dla_solve_absent_selftest(kind, *args)
+    return _solve(call, "dla_solve_absent_selftest", f, b, None, stream)
 
 
 def factor_giveup_selftest(kind: int, a, stream=None) -> int:

@@ -595,14 +595,14 @@ size_t solve_workspace_bytes(int64_t n, int64_t nrhs, dla_dtype dt) {
 extern "C++" {
 template <int KIND>
 static int solve_entry(const void* d_f, int64_t n, int64_t lda, void* d_b, int64_t nrhs, int64_t ldb, dla_dtype dt,
-                       void* d_workspace, size_t workspace_bytes, void* hip_stream, int phases, long long wait_ticks = -1) {
+                       void* d_workspace, size_t workspace_bytes, void* hip_stream, int phases, FlowWaits waits = FlowWaits::kOrdinary) {
   int rc = solve_common_checks(d_f, n, lda, d_b, nrhs, ldb, dt);
   if (rc != DLA_SUCCESS) return rc;
   hip_clear_stale_error();
   hipStream_t st = static_cast<hipStream_t>(hip_stream);
   if (dt == DLA_F64)
-    return solve_impl<double, KIND>((const double*)d_f, n, lda, (double*)d_b, nrhs, ldb, d_workspace, workspace_bytes, st, phases, wait_ticks);
-  return solve_impl<float, KIND>((const float*)d_f, n, lda, (float*)d_b, nrhs, ldb, d_workspace, workspace_bytes, st, phases, wait_ticks);
+    return solve_impl<double, KIND>((const double*)d_f, n, lda, (double*)d_b, nrhs, ldb, d_workspace, workspace_bytes, st, phases, waits);
+  return solve_impl<float, KIND>((const float*)d_f, n, lda, (float*)d_b, nrhs, ldb, d_workspace, workspace_bytes, st, phases, waits);
 }
 
 template <int KIND>
@@ -651,13 +651,23 @@ int cholesky_solve_prepared(const void* d_l, int64_t n, int64_t lda, void* d_b, 
   return solve_entry<1>(d_l, n, lda, d_b, nrhs, ldb, dt, d_workspace, workspace_bytes, hip_stream, kSolveApply);
 }
 
-int dla_solve_giveup_selftest(int kind, const void* d_f, int64_t n, int64_t lda, void* d_b, int64_t nrhs, int64_t ldb, dla_dtype dt,
-                              void* d_workspace, size_t workspace_bytes, void* hip_stream) {
+extern "C++" {
+static int solve_selftest(int kind, const void* d_f, int64_t n, int64_t lda, void* d_b, int64_t nrhs, int64_t ldb, dla_dtype dt, void* d_workspace,
+                          size_t workspace_bytes, void* hip_stream, FlowWaits waits) {
   if (kind != 0 && kind != 1) return -1;
   constexpr int both = kSolvePrepare | kSolveApply;
-  const int rc = kind == 0 ? solve_entry<0>(d_f, n, lda, d_b, nrhs, ldb, dt, d_workspace, workspace_bytes, hip_stream, both, 0)
-                           : solve_entry<1>(d_f, n, lda, d_b, nrhs, ldb, dt, d_workspace, workspace_bytes, hip_stream, both, 0);
+  const int rc = kind == 0 ? solve_entry<0>(d_f, n, lda, d_b, nrhs, ldb, dt, d_workspace, workspace_bytes, hip_stream, both, waits)
+                           : solve_entry<1>(d_f, n, lda, d_b, nrhs, ldb, dt, d_workspace, workspace_bytes, hip_stream, both, waits);
   return rc < 0 ? rc - 1 : rc;  // (kind comes first here)
+}
+}
+int dla_solve_giveup_selftest(int kind, const void* d_f, int64_t n, int64_t lda, void* d_b, int64_t nrhs, int64_t ldb, dla_dtype dt,
+                              void* d_workspace, size_t workspace_bytes, void* hip_stream) {
+  return solve_selftest(kind, d_f, n, lda, d_b, nrhs, ldb, dt, d_workspace, workspace_bytes, hip_stream, FlowWaits::kGiveUp);
+}
+int dla_solve_absent_selftest(int kind, const void* d_f, int64_t n, int64_t lda, void* d_b, int64_t nrhs, int64_t ldb, dla_dtype dt,
+                              void* d_workspace, size_t workspace_bytes, void* hip_stream) {
+  return solve_selftest(kind, d_f, n, lda, d_b, nrhs, ldb, dt, d_workspace, workspace_bytes, hip_stream, FlowWaits::kAbsent);
 }
 
 int dla_factor_giveup_selftest(int kind, void* d_a, int64_t n, int64_t lda, dla_dtype dt, void* d_workspace, size_t workspace_bytes,

@@ -11,22 +11,28 @@
 //
 // What bounds it is the hop X_{i-1} -> X_i, 2 n / 256 of them in sequence: a store to the device's point of coherence, a
 // load from it, 16 dependent MFMAs a wave, a rendezvous in LDS.  Measured 3.2 - 4 us a hop with few right-hand sides, where a
-// launch per hop takes 6.6 - 8: prepared LU solves, fp64, n = 4000 with 1 right-hand side 211 -> 108 us, with 64 255 -> 182,
-// n = 8192 571 -> 276 and 746 -> 566.
+// launch per hop takes 6.6 - 8: prepared LU solves, fp64, n = 4000 with 1 right-hand side 211 -> 102 us, with 64 255 -> 186,
+// n = 8192 571 -> 271 and 746 -> 566.  (One counter that deals the pieces out, instead of the claims below: 150, 243, 367, 743; two
+// thousand atomics on one address.)
 //
-// Hand-over.  A piece of X is its own signal: the areas the passes publish in are filled with a bit pattern that is never
+// Hand-over.  A piece of X or S is its own signal: the areas the passes publish in are filled with a bit pattern that is never
 // published (kEmpty, a NaN; a result with these bits is stored as another NaN), every element is stored and loaded as an
 // atomic of device scope, and a reader loads its operand again until no element is empty.  No counter and no fence is
-// needed, and nothing is assumed about the order of two stores.  The sum workgroups, many readers of one block, first look
-// at one element and then load through their L2; an element that is still empty there is loaded from the point of coherence.
-// S_i, whose area the two passes share, has one flag per piece instead; it has a hop's time to spare.
+// needed, and nothing is assumed about the order of two stores.  The sum workgroups, many readers of one block, first look at a
+// flag that each piece of X also sets, and then load through their L2; an element that is still empty there is loaded from the
+// point of coherence.  A solution workgroup looks at flags, too, until the block two positions back can be there.
 //
-// Order.  Every workgroup waits only for workgroups of its own launch with a smaller index, so the launch ends however few
-// of them are resident at a time, as long as the hardware starts them in order and nothing else keeps the compute units for
-// good.  Where that does not hold (two such launches that each keep the other's next workgroup from starting), a wait ends
-// after the call's limit, every other wait of the launch then ends too, and the last workgroup of a column tile to finish
-// substitutes row by row for it (flow_recover): B is not written before the forward pass of the tile is complete, and Y
-// never after, so nothing it needs is lost.
+// Order.  A piece waits only for pieces with a smaller index, and a workgroup begins with the piece of its own index.  An XCD
+// starts its share of the workgroups in order, but knows nothing of the others': two such launches on two streams can fill each an
+// XCD with workgroups that wait for one that the other launch keeps from starting.  So a piece belongs to the workgroup that has
+// claimed it, and one that has waited for kFlowSearchTicks gives its piece back, takes the first piece up to its own that nobody
+// has, and so on until there is none.  The first piece that is not done is then always at work or taken next, whichever workgroups
+// of a launch are there, and every launch ends.  What is published is checked against the claim, so a workgroup that starts late
+// and finds its piece taken has only wasted its time.
+// A launch that does not come on for kFlowWaitTicks all the same (none is known that would not) gives up: every wait ends, and the
+// last workgroup of a column tile to finish substitutes row by row for it (flow_recover): B is not written before the forward pass
+// of the tile is complete, and Y never after, so nothing it needs is lost.  It takes 0.27 s at n = 4096 with 1 right-hand side, 0.53 s
+// with 64, and grows with n^2.
 #pragma once
 #include <type_traits>
 #include "dla_common.hpp"
@@ -37,7 +43,8 @@ constexpr int kFlowThreads = 256;
 constexpr int kFlowBlock = 256;               // rows of a block of the substitution
 constexpr int kFlowTiles = kFlowBlock / 16;   // workgroups along a block's rows
 constexpr int kFlowLook = 2;                  // blocks that M covers
-constexpr long long kFlowWaitTicks = 5000000; // 50 ms of the 100 MHz wall clock
+constexpr long long kFlowSearchTicks = 200000;  // 2 ms of the 100 MHz wall clock, several times the longest solve up to n = 8192
+constexpr long long kFlowWaitTicks = 100000000; // 1 s
 
 constexpr int kFlowCoherent = 16;             // sc1: a load from the device's point of coherence
 
@@ -68,23 +75,55 @@ struct FlowArgs {
   T* X;            // solution of the backward pass
   T* S;            // what the blocks start from, forward pass; the backward pass's lies behind it
   int* flags;      // [pass][position][column tile][16]: the piece of X_i is there
-  int* done;       // [column tile]: workgroups that are through;  behind them: a wait has given up
-  long long wait_ticks;
+  int* done;       // [column tile]: pieces that are through;  behind them: a wait has given up
+  int* claims;     // [piece]: a workgroup has it
+  long long wait_ticks, search_ticks;
+  int absent;      // -1, or (diagnostic) of the workgroups with this index modulo 8 only those of the last block solved are there
   int64_t lda, ldb, ldy;
-  int n, nrhs, blocks, tiles_n, expected;  // expected: workgroups per column tile
+  int n, nrhs, blocks, tiles_n, expected;  // expected: pieces per column tile
 };
 
 // Position p of a pass (p-th block solved) has a sum from p = kFlowLook + 1 on.
 __host__ __device__ inline int flow_groups(int blocks) { return blocks + (blocks > kFlowLook + 1 ? blocks - kFlowLook - 1 : 0); }
-inline int flow_workgroups(int blocks, int tiles_n) { return 2 * flow_groups(blocks) * kFlowTiles * tiles_n; }
+__host__ __device__ inline int flow_pieces(int blocks, int tiles_n) { return 2 * flow_groups(blocks) * kFlowTiles * tiles_n; }
+// Piece number id: pass, position, sum or solution, 16 rows, 16 NB columns.  The column tiles of the same rows are eight pieces
+// apart, so that one XCD's L2 serves their left operand.
+struct FlowPiece {
+  bool back, sum;
+  int p, rt, ct;
+  __host__ __device__ int block(int blocks) const { return back ? blocks - 1 - p : p; }
+};
+__host__ __device__ inline FlowPiece flow_piece(int id, int blocks, int tiles_n) {
+  const int per_group = kFlowTiles * tiles_n, groups = flow_groups(blocks), sums = groups - blocks;
+  FlowPiece f;
+  f.back = id >= groups * per_group;
+  if (f.back) id -= groups * per_group;
+  // X_0, X_1, then  S_3 X_2, S_4 X_3, ...: a sum as early as its last block allows; at the end the solutions without a sum
+  const int group = id / per_group, local = id % per_group;
+  f.p = group;
+  f.sum = false;
+  if (group >= kFlowLook) {
+    const int pair = (group - kFlowLook) / 2;
+    if (pair < sums) {
+      f.sum = (group - kFlowLook) % 2 == 0;
+      f.p = pair + (f.sum ? kFlowLook + 1 : kFlowLook);
+    } else {
+      f.p = group - sums;
+    }
+  }
+  f.rt = (local / (kNumXcd * tiles_n)) * kNumXcd + local % kNumXcd;
+  f.ct = (local / kNumXcd) % tiles_n;
+  return f;
+}
+// Whether there is such a piece (the last block of the matrix may have fewer rows).
+__host__ __device__ inline bool flow_piece_is(const FlowPiece& f, int n, int blocks) { return f.block(blocks) * kFlowBlock + f.rt * 16 < n; }
 inline int flow_expected(int n, int blocks) {
   const int full = blocks > kFlowLook + 1 ? blocks - kFlowLook - 1 : 0;  // blocks with a sum
   return 2 * ((n + 15) / 16) + full * kFlowTiles + (full ? (n + 15) / 16 - (kFlowLook + 1) * kFlowTiles : 0);
 }
-inline int flow_flags(int blocks, int tiles_n) { return 2 * blocks * tiles_n * kFlowTiles; }
-inline int flow_ints(int blocks, int tiles_n) { return flow_flags(blocks, tiles_n) + tiles_n + 1; }
+inline int64_t flow_ints(int64_t blocks, int tiles_n) { return 2 * blocks * tiles_n * kFlowTiles + tiles_n + 1 + flow_pieces((int)blocks, tiles_n); }
 
-// What a launch finds: two areas of count elements each empty, no flag set, no workgroup done.  By the launch in front of it
+// What a launch finds: two areas of count elements each empty, no flag set, no piece claimed or done.  By the launch in front of it
 // (the pre-pass's first, or one of its own), kFlowThreads to a workgroup.
 template <typename T>
 struct FlowInit {
@@ -153,8 +192,9 @@ struct FlowTile {  // (32-bit byte offsets throughout: kFlowMaxLd)
   int lane, wave, l15, kq;
   int col[NB];        // this lane's columns, clamped
   int* gave_up;       // the launch's flag
-  long long limit;
-  bool late = false;  // a wait of this wave has ended without what it waited for
+  long long limit;    // of a wait
+  bool last_try;      // behind it the launch gives up
+  int late = 0;       // a wait of this wave has ended without what it waited for: 1 to look for work, 2 the launch has given up
 
   // k of step s: pairs dealt round-robin to the waves and lane groups, as the left operand's pairs are one load
   static __device__ __forceinline__ int k_step(int s) { return 32 * (s >> 1) + (s & 1); }
@@ -163,13 +203,14 @@ struct FlowTile {  // (32-bit byte offsets throughout: kFlowMaxLd)
   // a wait that is not over yet: true to go on waiting
   __device__ __forceinline__ bool again(int spins, long long t0) {
     if (spins % 32 == 31 || limit == 0) {
-      if (!flow_all(__hip_atomic_load(gave_up, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0)) late = true;
-      if (wall_clock64() - t0 > limit) {
-        late = true;
-        __hip_atomic_store(gave_up, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if (!flow_all(__hip_atomic_load(gave_up, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0)) {
+        late = 2;
+      } else if (wall_clock64() - t0 > limit) {
+        late = last_try ? 2 : 1;
+        if (last_try) __hip_atomic_store(gave_up, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       }
     }
-    return !late;
+    return late == 0;
   }
 
   static __device__ __forceinline__ T load_one(__amdgpu_buffer_rsrc_t rs, int vo, int so) {
@@ -253,7 +294,7 @@ struct FlowTile {  // (32-bit byte offsets throughout: kFlowMaxLd)
     if (wave == 0) {
       const int* const p = flags + (l15 < count ? l15 : count - 1);
       const long long t0 = wall_clock64();
-      for (int spins = 0; !late; ++spins) {
+      for (int spins = 0; late == 0; ++spins) {
         if (flow_all(__hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) || !again(spins, t0)) break;
         __builtin_amdgcn_s_sleep(PAUSE);
       }
@@ -273,7 +314,7 @@ struct FlowTile {  // (32-bit byte offsets throughout: kFlowMaxLd)
       const long long t0 = wall_clock64();
       unsigned long long missing = 0;
       int spins = 0;
-      for (; !late; ++spins) {
+      for (; late == 0; ++spins) {
         missing = __builtin_amdgcn_ballot_w64(__hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0);
         if ((missing & 0xFFFF) == 0 || !again(spins, t0)) break;
         __builtin_amdgcn_s_sleep(PAUSE);
@@ -336,49 +377,54 @@ __device__ __attribute__((noinline)) void flow_recover(const T* F, int64_t lda, 
   }
 }
 
+// Takes the first piece up to `own` that nobody has (one wave); -1: there is none.
+static __device__ __attribute__((noinline)) int flow_search(int* claims, int own, int n, int blocks, int tiles_n) {
+  const int lane = (int)threadIdx.x & 63;
+  for (int base = 0; base <= own; base += 64) {
+    const int id = base + lane;
+    bool open = false;
+    if (id <= own && flow_piece_is(flow_piece(id, blocks, tiles_n), n, blocks))
+      open = __hip_atomic_load(claims + id, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0;
+    for (unsigned long long mask = __builtin_amdgcn_ballot_w64(open); mask != 0; mask &= mask - 1) {
+      const int at = base + __builtin_ctzll(mask);
+      int before = 1;
+      if (lane == 0) before = __hip_atomic_exchange(claims + at, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if (__builtin_amdgcn_readfirstlane(before) == 0) return at;
+    }
+  }
+  return -1;
+}
+
+// Computes and publishes one piece, by the whole workgroup; TAKEN: the workgroup has it already, else it claims it on the way.
+// last_try: a wait that is over makes the launch give up.  Returns 0; 1 where a wait has been too long: the piece is then back; 2 + ct
+// where column tile ct is through and the launch has given up.
 // KIND: 0 LU, 1 Cholesky (FactorKind)
-template <typename T, int KIND, int NB>
-__global__ void __launch_bounds__(kFlowThreads, NB == 1 ? 3 : 2) flow_kernel(const FlowArgs<T> g) {
+template <typename T, int KIND, int NB, bool TAKEN>
+__device__ __forceinline__ int flow_run(const FlowArgs<T>& g, const int piece, const bool last_try, T* const red) {
   using Tile = FlowTile<T, NB>;
   using acc_t = typename Tile::acc_t;
   constexpr int STEPS = Tile::STEPS;
   constexpr int64_t SB = kFlowBlock;
   constexpr bool CH = KIND == 1;
-  __shared__ T red[4 * NB * 256];
   __shared__ int shared_late[6];
-  const int tid = (int)threadIdx.x;
+  int tid = (int)threadIdx.x;
+  if (TAKEN && NB == 2) asm volatile("" : "+v"(tid));  // (or what the workgroup's first piece has computed is kept for this one)
   Tile t;
   t.lane = tid & 63;
   t.wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   t.l15 = t.lane & 15;
   t.kq = t.wave * 8 + 2 * (t.lane >> 4);
   t.gave_up = g.done + g.tiles_n;
-  t.limit = g.wait_ticks;
-
-  // ---- which piece: pass, position p, sum or solution, 16 rows, 16 NB columns.  The column tiles of the same rows are
-  // eight workgroups apart, so that one XCD's L2 serves their left operand.
-  const int per_group = kFlowTiles * g.tiles_n, groups = flow_groups(g.blocks);
-  int bid = (int)blockIdx.x;
-  const bool back = bid >= groups * per_group;
-  if (back) bid -= groups * per_group;
-  // X_0, X_1, then  S_3 X_2, S_4 X_3, ...: a sum as early as its last block allows; at the end the solutions without a sum
-  const int group = bid / per_group, local = bid % per_group, sums = groups - g.blocks;
-  int p = group;
-  bool sum_wg = false;
-  if (group >= kFlowLook) {
-    const int pair = (group - kFlowLook) / 2;
-    if (pair < sums) {
-      sum_wg = (group - kFlowLook) % 2 == 0;
-      p = pair + (sum_wg ? kFlowLook + 1 : kFlowLook);
-    } else {
-      p = group - sums;
-    }
-  }
-  const int rt = (local / (kNumXcd * g.tiles_n)) * kNumXcd + local % kNumXcd, ct = (local / kNumXcd) % g.tiles_n;
-  const int last = g.blocks - 1, i = back ? last - p : p;
+  t.limit = g.search_ticks;
+  t.last_try = last_try;
+  int claimed = 0;  // what the piece's claim was before (one thread); looked at when the piece is ready
+  const FlowPiece f = flow_piece(piece, g.blocks, g.tiles_n);
+  const bool back = f.back, sum_wg = f.sum;
+  const int p = f.p, rt = f.rt, ct = f.ct;
+  const int last = g.blocks - 1, i = f.block(g.blocks);
   auto rows_of = [&](int q) { return g.n - q * (int)SB < (int)SB ? g.n - q * (int)SB : (int)SB; };
   const int rows = rows_of(i), r0 = rt * 16, ldy = (int)g.ldy;
-  if (r0 >= rows) return;  // uniform
+  if (r0 >= rows) return 0;  // uniform
   const int row = r0 + t.l15 < rows ? r0 + t.l15 : rows - 1;  // this lane's row of the left operands
 #pragma unroll
   for (int j = 0; j < NB; ++j) t.col[j] = ct * 16 * NB + j * 16 + t.l15 < g.nrhs ? ct * 16 * NB + j * 16 + t.l15 : g.nrhs - 1;
@@ -396,11 +442,11 @@ __global__ void __launch_bounds__(kFlowThreads, NB == 1 ? 3 : 2) flow_kernel(con
   // The products, in the order in which their right operands appear.  Sum: the blocks solved at the positions 0, 1, ...;
   // solution: the block two positions back, S_i, the block before this.  The left operand of the next is on its way
   // while a right operand is waited for.
-  const int own = p >= 2 ? 1 : 0;  // which of a solution's products is S_i's
+  const int from_s = p >= 2 ? 1 : 0;  // which of a solution's products is S_i's
   const int count = sum_wg ? p - kFlowLook : (p < kFlowLook ? p : kFlowLook) + 1;
   auto block_of = [&](int q) {  // the block whose rows the right operand of product q is
     if (sum_wg) return back ? last - q : q;
-    const int d = q == own ? 0 : (q < own ? 2 : 1);
+    const int d = q == from_s ? 0 : (q < from_s ? 2 : 1);
     return back ? i + d : i - d;
   };
   auto left = [&](T (&a)[STEPS], int q) __attribute__((always_inline)) {
@@ -410,7 +456,7 @@ __global__ void __launch_bounds__(kFlowThreads, NB == 1 ? 3 : 2) flow_kernel(con
     if (sum_wg) {
       ld = g.lda;
       base = CH && back ? g.F + (int64_t)j * SB * ld + (int64_t)i * SB : g.F + (int64_t)i * SB * ld + (int64_t)j * SB;
-    } else if (q == own) {
+    } else if (q == from_s) {
       ld = SB;
       base = (back && !CH ? g.nb : g.nf) + (int64_t)i * SB * SB;
     } else {
@@ -427,7 +473,7 @@ __global__ void __launch_bounds__(kFlowThreads, NB == 1 ? 3 : 2) flow_kernel(con
   FlowSlots slots;
   auto step = [&](const T (&a)[STEPS], int q) __attribute__((always_inline)) {
     const int j = block_of(q), kc = rows_of(j);
-    const T* const x = block_at(sum_wg || q != own ? V : p > kFlowLook ? S : g.Y, j);
+    const T* const x = block_at(sum_wg || q != from_s ? V : p > kFlowLook ? S : g.Y, j);
     bool there = false;
     if (sum_wg && q + 1 < count) {
       // not urgent: one wave looks at the flags, and the block comes through the L2, once for the XCD's workgroups (where a
@@ -439,7 +485,7 @@ __global__ void __launch_bounds__(kFlowThreads, NB == 1 ? 3 : 2) flow_kernel(con
         else complete = q + t.template wait_positions<8>(flags_of(back, q), stride, pieces_of(j), count - 1 - q, behind, found);
       }
       there = t.template load_area<0>(b, x, ldy, kc);
-    } else if (!sum_wg && q == own && p <= kFlowLook && !back) {
+    } else if (!sum_wg && q == from_s && p <= kFlowLook && !back) {
       t.load_rhs(b, g.B + (int64_t)i * SB * g.ldb, g.ldb, kc);
       there = true;
     } else if (!sum_wg && q == 0) {
@@ -453,6 +499,8 @@ __global__ void __launch_bounds__(kFlowThreads, NB == 1 ? 3 : 2) flow_kernel(con
   left(a0, 0);
   for (int q = 0; q < count; q += 2) {
     if (q + 1 < count) left(a1, q + 1);
+    // (between the left operands, which do not wait for it, and the first right operand, which takes as long)
+    if (!TAKEN && q == 0 && tid == 0) claimed = __hip_atomic_exchange(g.claims + piece, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     step(a0, q);
     if (q + 1 >= count) break;
     if (q + 2 < count) left(a0, q + 2);
@@ -464,12 +512,13 @@ __global__ void __launch_bounds__(kFlowThreads, NB == 1 ? 3 : 2) flow_kernel(con
   for (int j = 0; j < NB; ++j)
 #pragma unroll
     for (int v = 0; v < 4; ++v) red[((t.wave * NB + j) * 4 + v) * 64 + t.lane] = acc[j][v];
-  if (t.lane == 0) shared_late[2 + t.wave] = t.late ? 1 : 0;
+  if (t.lane == 0) shared_late[2 + t.wave] = t.late | (!TAKEN && claimed != 0 ? 4 : 0);
   lds_barrier();
-  const bool late = (shared_late[2] | shared_late[3] | shared_late[4] | shared_late[5]) != 0;
+  const int late = shared_late[2] | shared_late[3] | shared_late[4] | shared_late[5];
+  if (!TAKEN && (late & 4) != 0) return 0;  // uniform: another workgroup has it
   const int er = r0 + Mfma<T>::row_of(t.wave, t.lane);
   const int64_t gr = (int64_t)i * SB + er;
-  if (!late) {
+  if (late == 0) {
 #pragma unroll
     for (int j = 0; j < NB; ++j) {
       const int c = (ct * NB + j) * 16 + t.l15;
@@ -493,12 +542,44 @@ __global__ void __launch_bounds__(kFlowThreads, NB == 1 ? 3 : 2) flow_kernel(con
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   __syncthreads();
   if (tid == 0) {
-    if (!late && !sum_wg) __hip_atomic_store(flags_of(back, p) + rt, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    const int before = __hip_atomic_fetch_add(g.done + ct, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    shared_late[0] = before == g.expected - 1 && __hip_atomic_load(t.gave_up, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0;
+    int rest = late;  // 1; 2 or 3: the launch has given up
+    if (late == 1) {
+      __hip_atomic_store(g.claims + piece, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // (the piece is back before the search)
+    } else {
+      if (late == 0 && !sum_wg) __hip_atomic_store(flags_of(back, p) + rt, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      const int before = __hip_atomic_fetch_add(g.done + ct, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      rest = before == g.expected - 1 && __hip_atomic_load(t.gave_up, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0 ? 2 + ct : 0;
+    }
+    shared_late[0] = rest;
   }
   __syncthreads();
-  if (shared_late[0]) flow_recover<T, KIND>(g.F, g.lda, g.B, g.ldb, g.Y, g.X, g.ldy, g.n, g.nrhs, ct * NB * 16, NB, red);  // uniform
+  return __builtin_amdgcn_readfirstlane(shared_late[0]);
+}
+
+template <typename T, int KIND, int NB>
+__global__ void __launch_bounds__(kFlowThreads, NB == 1 ? 3 : 2) flow_kernel(const FlowArgs<T> g) {
+  __shared__ T red[4 * NB * 256];
+  __shared__ int next;
+  const int own = (int)blockIdx.x;
+  if (own % kNumXcd == g.absent && own < flow_pieces(g.blocks, g.tiles_n) - kFlowTiles * g.tiles_n) return;  // uniform
+  int rest = flow_run<T, KIND, NB, false>(g, own, false, red);
+  // ---- rare: for a column tile of a launch that has given up, the substitution; else other pieces (see Order above)
+  long long waited = 0;  // in vain, since something came on
+  if (rest == 0) return;  // uniform
+  for (;;) {
+    if (rest > 1) flow_recover<T, KIND>(g.F, g.lda, g.B, g.ldb, g.Y, g.X, g.ldy, g.n, g.nrhs, (rest - 2) * NB * 16, NB, red);
+    waited = rest == 1 ? waited + g.search_ticks : 0;
+    __syncthreads();
+    if (threadIdx.x < 64) {
+      const int found = flow_search(g.claims, own, g.n, g.blocks, g.tiles_n);
+      if (threadIdx.x == 0) next = found;
+    }
+    __syncthreads();
+    const int piece = __builtin_amdgcn_readfirstlane(next);
+    if (piece < 0) return;  // uniform
+    rest = flow_run<T, KIND, NB, true>(g, piece, waited + g.search_ticks >= g.wait_ticks, red);
+  }
 }
 
 }  // namespace dla

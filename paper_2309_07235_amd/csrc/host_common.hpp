@@ -76,9 +76,12 @@ template <typename T>
 int rank_update_impl(bool lower, const T* L, const T* Rm, T* C, int64_t ld, int64_t m, int b, hipStream_t st);
 // Solve with the factors (solve.hip); KIND is FactorKind as an int; phases: which of its two parts to run.
 constexpr int kSolvePrepare = 1, kSolveApply = 2;
+// What the waits of the passes' one launch do (the other two for the diagnostics): as ever; give up at once; every eighth workgroup
+// stays away and the others soon look for what it has left.
+enum class FlowWaits { kOrdinary, kGiveUp, kAbsent };
 template <typename T, int KIND>
 int solve_impl(const T* F, int64_t n, int64_t lda, T* B, int64_t nrhs, int64_t ldb, void* ws, size_t ws_bytes,
-               hipStream_t st, int phases, long long wait_ticks = -1);  // wait_ticks: limit of the passes' waits, -1: the library's
+               hipStream_t st, int phases, FlowWaits waits = FlowWaits::kOrdinary);
 size_t solve_workspace_bytes_impl(int64_t n, int64_t nrhs, dla_dtype dt);
 size_t factor_workspace_bytes_impl(int64_t n, dla_dtype dt, const dla_factor_params* p);
 constexpr size_t kHandoverSelftestBytes = 8192;

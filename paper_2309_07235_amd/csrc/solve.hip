@@ -71,7 +71,7 @@ static int launch_skinny(bool at, const SkinnyGroup<T>& g, int workgroups, int k
 template <typename T, int KIND>
 static int launch_flow(const FlowArgs<T>& a, int nb, double flops, hipStream_t st) {
   ProfileScope scope(PHASE_GEMM, flops, st);
-  const dim3 grid((unsigned)flow_workgroups(a.blocks, a.tiles_n)), block(kFlowThreads);
+  const dim3 grid((unsigned)flow_pieces(a.blocks, a.tiles_n)), block(kFlowThreads);
   if (nb == 1) hipLaunchKernelGGL((flow_kernel<T, KIND, 1>), grid, block, 0, st, a);
   else hipLaunchKernelGGL((flow_kernel<T, KIND, 2>), grid, block, 0, st, a);
   return launch_status(__func__);
@@ -139,7 +139,7 @@ static int launch_look_back(const PrepassArgs<T>& a, hipStream_t st) {
 // kSolveApply = the two passes over B with a workspace the pre-pass has filled for this factor; both = a whole solve.
 template <typename T, int KIND>
 int solve_impl(const T* F, int64_t n, int64_t lda, T* B, int64_t nrhs, int64_t ldb, void* ws, size_t ws_bytes,
-               hipStream_t st, int phases, long long wait_ticks) {
+               hipStream_t st, int phases, FlowWaits waits) {
   const bool prepare = phases & kSolvePrepare, apply = (phases & kSolveApply) && nrhs > 0;
   if (n == 0 || (nrhs == 0 && (phases & kSolveApply))) return DLA_SUCCESS;
   const dla_dtype dt = sizeof(T) == 8 ? DLA_F64 : DLA_F32;
@@ -164,18 +164,19 @@ int solve_impl(const T* F, int64_t n, int64_t lda, T* B, int64_t nrhs, int64_t l
   // Few right-hand sides: both passes in one launch (flow_kernel).  64 is where the two areas for S end to fit in the pre-pass's
   // intermediates; the line lies there and not below because one launch is faster all the way (a prepared LU solve, fp64, us,
   // launches against this, 1 / 16 / 64 right-hand sides: n = 300 23 / 23 / 24 against 15 / 15 / 16, n = 1000 46 / 47 / 51
-  // against 25 / 25 / 36, n = 2000 102 / 103 / 110 against 50 / 52 / 79, n = 4000 211 / 212 / 255 against 108 / 112 / 182,
-  // n = 8192 571 / 578 / 746 against 276 / 292 / 566; fp32 n = 4000 182 / 180 / 204 against 87 / 91 / 151).  A workgroup takes
-  // two column blocks where one each would be more workgroups than fit beside each other by much (n = 4000 with 32: 145
-  // against 141, n = 8192 419 against 369, n = 2000 65 against 72; n = 2000 with 64: 80 against 84).
-  const bool flow = nrhs <= 64 && lda <= kFlowMaxLd;
+  // against 26 / 26 / 33, n = 2000 102 / 103 / 110 against 48 / 50 / 72, n = 4000 211 / 212 / 255 against 102 / 108 / 186,
+  // n = 8192 571 / 578 / 746 against 271 / 283 / 566; fp32 n = 4000 182 / 180 / 204 against 86 / 96 / 155).  A workgroup takes
+  // two column blocks where one each would be more workgroups than fit beside each other by much (one against two, n = 2000 with 32
+  // 61 / 73, with 64 72 / 83; n = 4000 with 32 141 / 143, with 64 199 / 186; n = 8192 with 32 419 / 367, with 64 672 / 566).
   const int flow_nb = nrhs > 16 && n * nrhs > 128000 ? 2 : 1;
   const int tiles_n = (int)((nrhs + 16 * flow_nb - 1) / (16 * flow_nb));
+  // (its flags and claims lie in the first block's M, room for 682 blocks in fp32 with two column tiles, n = 174 000; beyond: launches)
+  const bool flow = nrhs <= 64 && lda <= kFlowMaxLd && flow_ints(nblk, tiles_n) * (int64_t)sizeof(int) <= 2 * sb * sb * (int64_t)sizeof(T);
   int* const ints = reinterpret_cast<int*>(mf);  // (the first block has no M)
   FlowInit<T> init{Y, nblk > kFlowLook + 1 ? tf : nullptr, 0, ints, 0};  // S: where the pre-pass keeps nothing
   if (apply && flow) {
     init.count = 2 * n * ldy;
-    init.nints = flow_ints(nblk, tiles_n);
+    init.nints = (int)flow_ints(nblk, tiles_n);
   }
   if (prepare) {
     if (KIND == KIND_LU)
@@ -192,7 +193,10 @@ int solve_impl(const T* F, int64_t n, int64_t lda, T* B, int64_t nrhs, int64_t l
       hipLaunchKernelGGL(flow_init_kernel<T>, dim3((unsigned)flow_init_workgroups(init)), dim3(kFlowThreads), 0, st, init);
       if (launch_status(__func__) != DLA_SUCCESS) return DLA_ERR_HIP;
     }
-    FlowArgs<T> a{F, B, wf, KIND == KIND_LU ? wb : wf, mf, mb, Y, X, tf, ints, ints + flow_flags(nblk, tiles_n), wait_ticks < 0 ? kFlowWaitTicks : wait_ticks,
+    int* const done = ints + 2 * nblk * tiles_n * kFlowTiles;
+    FlowArgs<T> a{F, B, wf, KIND == KIND_LU ? wb : wf, mf, mb, Y, X, tf, ints, done, done + tiles_n + 1,
+                  waits == FlowWaits::kGiveUp ? 0 : kFlowWaitTicks, waits == FlowWaits::kOrdinary ? kFlowSearchTicks : waits == FlowWaits::kAbsent ? 2000 : 0,
+                  waits == FlowWaits::kAbsent ? 3 : -1,
                   lda, ldb, ldy, (int)n, (int)nrhs, nblk, tiles_n, flow_expected((int)n, nblk)};
     return launch_flow<T, KIND>(a, flow_nb, 2.0 * (double)n * (double)n * (double)nrhs, st);
   }
@@ -302,9 +306,9 @@ int solve_impl(const T* F, int64_t n, int64_t lda, T* B, int64_t nrhs, int64_t l
   return DLA_SUCCESS;
 }
 
-template int solve_impl<double, KIND_LU>(const double*, int64_t, int64_t, double*, int64_t, int64_t, void*, size_t, hipStream_t, int, long long);
-template int solve_impl<float, KIND_LU>(const float*, int64_t, int64_t, float*, int64_t, int64_t, void*, size_t, hipStream_t, int, long long);
-template int solve_impl<double, KIND_CHOL>(const double*, int64_t, int64_t, double*, int64_t, int64_t, void*, size_t, hipStream_t, int, long long);
-template int solve_impl<float, KIND_CHOL>(const float*, int64_t, int64_t, float*, int64_t, int64_t, void*, size_t, hipStream_t, int, long long);
+template int solve_impl<double, KIND_LU>(const double*, int64_t, int64_t, double*, int64_t, int64_t, void*, size_t, hipStream_t, int, FlowWaits);
+template int solve_impl<float, KIND_LU>(const float*, int64_t, int64_t, float*, int64_t, int64_t, void*, size_t, hipStream_t, int, FlowWaits);
+template int solve_impl<double, KIND_CHOL>(const double*, int64_t, int64_t, double*, int64_t, int64_t, void*, size_t, hipStream_t, int, FlowWaits);
+template int solve_impl<float, KIND_CHOL>(const float*, int64_t, int64_t, float*, int64_t, int64_t, void*, size_t, hipStream_t, int, FlowWaits);
 
 }  // namespace dla

@@ -150,3 +150,55 @@ def test_captured_and_replayed(B):
         B.lu_solve(f, other)  # eager work between the replays
         torch.cuda.synchronize()
         assert torch.equal(b, w) and torch.equal(other, w)
+
+
+@pytest.mark.parametrize("kind", ["lu", "chol"])
+@pytest.mark.parametrize("n,nrhs,dtype", [(250, 3, "float64"), (257, 1, "float32"), (1100, 40, "float64"), (1030, 64, "float32"), (2305, 61, "float64")])
+def test_workgroups_that_stay_away(B, kind, n, nrhs, dtype):
+    """Every eighth workgroup leaves at once: the others take over its pieces, and each piece is what it is in an ordinary call."""
+    import torch
+    announce(f"flow absent {kind} {dtype} n={n} nrhs={nrhs}")
+    d = getattr(torch, dtype)
+    F, _, _ = _system(kind, n, 17, dtype)
+    f, rhs = to_device(F, d), to_device(inputs.uniform_matrix(64, 3, n, nrhs), d)
+    want, got = rhs.clone(), rhs.clone()
+    (B.lu_solve if kind == "lu" else B.cholesky_solve)(f, want)
+    B.solve_absent_selftest(0 if kind == "lu" else 1, f, got)
+    assert torch.equal(got, want)
+
+
+def test_large_solves_on_several_streams(B):
+    """Four solves that would each fill the card, on four streams, with factorisations beside them: they hold compute units that the
+    others' next workgroups need, and all end with the lone call's result bit for bit."""
+    import torch
+    n = 8192
+    gen = torch.Generator(device="cuda").manual_seed(5)
+    f = torch.rand(n, n, dtype=torch.float64, device="cuda", generator=gen) / n + torch.eye(n, dtype=torch.float64, device="cuda")
+    g0 = f[:3000, :3000].contiguous()
+    cases = []
+    for nrhs in (64, 33, 64, 1):
+        b0 = torch.rand(n, nrhs, dtype=torch.float64, device="cuda", generator=gen)
+        want = b0.clone()
+        ws = B.lu_solve(f, want)
+        cases.append((b0, want, ws, torch.cuda.Stream()))
+    factor = g0.clone()
+    B.lu_factor(factor, info=torch.zeros(1, dtype=torch.int32, device="cuda"))
+    side, info = torch.cuda.Stream(), torch.zeros(1, dtype=torch.int32, device="cuda")
+    torch.cuda.synchronize()
+    for round_ in range(3):
+        announce(f"flow large on four streams, pass {round_}")
+        got, x = [c[0].clone() for c in cases], g0.clone()
+        torch.cuda.synchronize()
+        for b, (b0, _, ws, st) in zip(got, cases):
+            with torch.cuda.stream(st):
+                for _ in range(4):
+                    b.copy_(b0)
+                    B.lu_solve(f, b, workspace=ws)
+        with torch.cuda.stream(side):
+            for _ in range(3):
+                x.copy_(g0)
+                B.lu_factor(x, info=info)
+        torch.cuda.synchronize()
+        for b, c in zip(got, cases):
+            assert torch.equal(b, c[1])
+        assert int(info.item()) == 0 and torch.equal(x, factor)

@@ -93,8 +93,9 @@ typedef struct {
  * trailing matrix is large; defer_min_rows moves that threshold.
  *
  * The defaults (nb = 0 or 128, lookahead = 1, update and defer_min_rows 0, with d_info) leave the schedule to the library: matrices
- * of up to a few thousand rows run as one or two launches of 64 x 64 tiles whose workgroups wait for each other, larger ones as
- * blocks of 128 down to the last few thousand rows, and those in tiles.  nb = 64 asks for the tiles at any size.  defer_min_rows
+ * of up to a few thousand rows run as one launch of 64 x 64 tiles whose workgroups wait for each other, larger ones as
+ * blocks of 128 down to the last few thousand rows, and those in tiles.  nb = 64 asks for the tiles up to 8192 rows (DLA_F32: 8000,
+ * what the workspace holds); beyond, it is the pipeline with blocks of 64.  defer_min_rows
  * other than 0 or lookahead = 2 with nb = 128 is the pipeline of blocks all the way.
  *
  * There is no separate inner block size of the diagonal-block kernel: it works in stages of 16 columns,
@@ -354,7 +355,7 @@ int dla_solve_absent_selftest(int kind, const void* d_f, int64_t n, int64_t lda,
                               void* d_workspace, size_t workspace_bytes, void* hip_stream);
 
 /*
- * The diagnostic of the waits for factorisations in tiles (n from 65 to 8192): kind 0 as lu_factor, 1 as cholesky_factor, every wait gives up at
+ * The diagnostic of the waits for factorisations in tiles (n from 65 to 8192, DLA_F32: to 8000): kind 0 as lu_factor, 1 as cholesky_factor, every wait gives up at
  * once.  The launches end, *d_info is -1 and the content of A unspecified.
  */
 int dla_factor_giveup_selftest(int kind, void* d_a, int64_t n, int64_t lda, dla_dtype dt, void* d_workspace, size_t workspace_bytes,

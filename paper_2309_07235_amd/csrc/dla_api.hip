@@ -160,7 +160,7 @@ static int gemm_choice(int op, int64_t lda, int64_t ldb, int64_t m, int64_t n, i
   g.nprob = 1;
   g.prob[0] = make_problem<T>(GemmSchedule{64, 64, 16, 4, 32, 32}, op, nullptr, lda, nullptr, ldb, nullptr, n, m, n, k, 0);
   if (!gemm_wide_takes<T>(op, g)) return 0;
-  gemm_wide_tile<T>(g, tile_m, tile_n);
+  gemm_wide_pick<T>(g, tile_m, tile_n);
   return 1;
 }
 

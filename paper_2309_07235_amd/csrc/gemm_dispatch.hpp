@@ -79,7 +79,7 @@ int launch_gemm(const GemmSchedule& s, int op, const GemmGroup<T>& g, hipStream_
 template <typename T>
 bool gemm_wide_takes(int op, const GemmGroup<T>& g);
 template <typename T>
-int gemm_wide_tile(const GemmGroup<T>& g, int* tile_m, int* tile_n);
+int gemm_wide_pick(const GemmGroup<T>& g, int* tile_m, int* tile_n);
 template <typename T>
 int launch_gemm_wide(int op, GemmGroup<T>& g, hipStream_t st);
 

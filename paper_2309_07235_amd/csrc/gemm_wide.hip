@@ -66,7 +66,7 @@ bool gemm_wide_takes(int op, const GemmGroup<T>& g) {
 // depth, and its fill, at the tile's own rate; the least wins.  Over 140 products of 32 x 400 to 6000 x 6000, k = 8 to 4096,
 // all three operations, the choice costs 1.6 % (fp64) and 1.3 % (fp32) more than the best tile in the mean.
 template <typename T>
-int gemm_wide_tile(const GemmGroup<T>& g, int* tile_m, int* tile_n) {
+int gemm_wide_pick(const GemmGroup<T>& g, int* tile_m, int* tile_n) {
   double best = 0.0;
   int pick = -1, at = 0;
 #define DLA_CASE(WM, WN, FM, FN, RATE64, RATE32, FILL)                                                     \
@@ -96,7 +96,7 @@ int gemm_wide_tile(const GemmGroup<T>& g, int* tile_m, int* tile_n) {
 template <typename T>
 int launch_gemm_wide(int op, GemmGroup<T>& g, hipStream_t st) {
   int tm, tn, at = 0;
-  const int pick = gemm_wide_tile(g, &tm, &tn);
+  const int pick = gemm_wide_pick(g, &tm, &tn);
 #define DLA_CASE(WM, WN, FM, FN, RATE64, RATE32, FILL) \
   if (at++ == pick) return launch_wide_tile<T, WM, WN, FM, FN>(op, g, st);
   DLA_WIDE_MENU(DLA_CASE)
@@ -106,8 +106,8 @@ int launch_gemm_wide(int op, GemmGroup<T>& g, hipStream_t st) {
 
 template bool gemm_wide_takes<double>(int, const GemmGroup<double>&);
 template bool gemm_wide_takes<float>(int, const GemmGroup<float>&);
-template int gemm_wide_tile<double>(const GemmGroup<double>&, int*, int*);
-template int gemm_wide_tile<float>(const GemmGroup<float>&, int*, int*);
+template int gemm_wide_pick<double>(const GemmGroup<double>&, int*, int*);
+template int gemm_wide_pick<float>(const GemmGroup<float>&, int*, int*);
 template int launch_gemm_wide<double>(int, GemmGroup<double>&, hipStream_t);
 template int launch_gemm_wide<float>(int, GemmGroup<float>&, hipStream_t);
 

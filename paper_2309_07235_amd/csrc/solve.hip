@@ -84,8 +84,8 @@ __global__ void solve_zero_kernel(T* p, int64_t count) {
 }
 
 // Workspace, in elements: per 256-row block a 256 x 256 negated inverse for the forward and one for the
-// backward pass (LU), a 128 x 128 intermediate of the pairing for each, and a 256 x 512 area M for each
-// pass; then the n x nrhs areas Y and X (leading dimension nrhs rounded up to even), which
+// backward pass (LU), 128 x 128 for each (flow_kernel's S, up to 64 right-hand sides), and a 256 x 512 area M for each
+// pass (the first one of the forward pass, which has none, for flow_kernel's flags); then the n x nrhs areas Y and X (leading dimension nrhs rounded up to even), which
 // a call sets to zero, or to what flow_kernel never publishes, before its passes.
 static int64_t pairs_of(int64_t n) { return (n + kTriPair - 1) / kTriPair; }
 static int64_t block_elems(int64_t n) {
@@ -161,8 +161,8 @@ int solve_impl(const T* F, int64_t n, int64_t lda, T* B, int64_t nrhs, int64_t l
   auto Nf = [&](int i) { return wf + (int64_t)i * sb * sb; };
   auto Nb = [&](int i) { return wb + (int64_t)i * sb * sb; };
   int rc;
-  // Few right-hand sides: both passes in one launch (flow_kernel).  64 is where the two areas for S end to fit in the pre-pass's
-  // intermediates; the line lies there and not below because one launch is faster all the way (a prepared LU solve, fp64, us,
+  // Few right-hand sides: both passes in one launch (flow_kernel).  64 is where the two areas for S end to fit in their
+  // part of the workspace; the line lies there and not below because one launch is faster all the way (a prepared LU solve, fp64, us,
   // launches against this, 1 / 16 / 64 right-hand sides: n = 300 23 / 23 / 24 against 15 / 15 / 16, n = 1000 46 / 47 / 51
   // against 26 / 26 / 33, n = 2000 102 / 103 / 110 against 48 / 50 / 72, n = 4000 211 / 212 / 255 against 102 / 108 / 186,
   // n = 8192 571 / 578 / 746 against 271 / 283 / 566; fp32 n = 4000 182 / 180 / 204 against 86 / 96 / 155).  A workgroup takes

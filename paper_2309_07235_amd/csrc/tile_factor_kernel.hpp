@@ -83,7 +83,7 @@ static __global__ void __launch_bounds__(256) tile_clear_kernel(int* p, int n) {
   if (i < n) p[i] = 0;
 }
 
-template <int AUX, typename T = double>
+template <int AUX>
 __device__ __forceinline__ double tile_load(__amdgpu_buffer_rsrc_t rs, int vo, int so, double*) {
   return __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(rs, vo, so, AUX));
 }
@@ -141,20 +141,18 @@ __device__ __forceinline__ void tile_solve(const T* D, int bs, int br, int rs, i
 // A wave waits until ok() holds for all of its lanes.
 template <typename F>
 __device__ __forceinline__ void tile_spin(int* ints, long long limit, int pause, F&& ok) {
-  {
-    const long long t0 = wall_clock64();
-    for (int spins = 0;; ++spins) {
-      if (__builtin_amdgcn_ballot_w64(!ok()) == 0) break;
-      if (spins % 32 == 31 || limit < 0) {
-        if (__builtin_amdgcn_ballot_w64(__hip_atomic_load(ints, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) != 0) break;
-        if (wall_clock64() - t0 > limit) {
-          __hip_atomic_store(ints, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-          break;
-        }
+  const long long t0 = wall_clock64();
+  for (int spins = 0;; ++spins) {
+    if (__builtin_amdgcn_ballot_w64(!ok()) == 0) break;
+    if (spins % 32 == 31 || limit < 0) {
+      if (__builtin_amdgcn_ballot_w64(__hip_atomic_load(ints, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) != 0) break;
+      if (wall_clock64() - t0 > limit) {
+        __hip_atomic_store(ints, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        break;
       }
-      if (pause == 1) __builtin_amdgcn_s_sleep(2);
-      if (pause == 2) __builtin_amdgcn_s_sleep(8);
     }
+    if (pause == 1) __builtin_amdgcn_s_sleep(2);
+    if (pause == 2) __builtin_amdgcn_s_sleep(8);
   }
 }
 // The waves that work on one tile: all eight of a workgroup, or four, one of its two teams, which share the compute unit but wait

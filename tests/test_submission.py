@@ -141,3 +141,13 @@ def test_what_waits_for_each_other_is_one_launch(record):
         assert not tiles or (len(tiles) == 2 and "tile_clear_kernel" in tiles[0][5] and "tile_factor_kernel" in tiles[1][5]), (form, tiles)
         tiled += bool(tiles)
     assert tiled == 4 * 7
+
+
+@pytest.mark.parametrize("kind", ["lu", "chol"])
+@pytest.mark.parametrize("dtype,most", [(F64, 8192), (F32, 8000)])
+def test_block_size_64_is_the_tiles_up_to_a_size(record, kind, dtype, most):
+    """The line that the header states, on both sides; the diagnostic of the tiles' waits has the same."""
+    runs = record([[[_call(kind, dtype, n, **more)]] for more in ({"nb": 64}, {"giveup": True}) for n in (most, most + 1)])
+    tiled = [any("tile_factor_kernel" in o[5] for o in ops) for _, ops in runs]
+    assert tiled == [True, False, True, False]
+    assert [rc for rc, _ in runs] == [[[0]], [[0]], [[0]], [[1 if dtype == F64 else 2]]]  # (DLA_ERR_UNSUPPORTED_PARAMS; DLA_ERR_WORKSPACE)

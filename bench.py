@@ -5,7 +5,7 @@ A step is one pass over the whole hot path on one batch of seeded synthetic
 input resident in HBM: lu_factor (N=4000), cholesky_factor (N=4000) and mm3
 (extralarge rectangular shape).  Prints ONE JSON line with the whole-job
 throughput in fp64 GFLOP/s, the roofline of the dominant kernel (the two
-factorisations' tiles, one or two launches each; with --lookahead 2 the rank-128
+factorisations' tiles, one launch each; with --lookahead 2 the rank-128
 trailing update of the pipeline; timed per launch with HIP events on the stream
 it runs on) and the CPU oracle timed on the host cores.
 
@@ -28,9 +28,9 @@ METRIC = "fp64 GFLOP/s and % of MFMA fp64 peak for LU/Cholesky/3mm at N=4000"
 # HBM bytes per launch of the bulk update kernel (fetch + write) come from the summary of the two rocprofv3
 # --pmc passes that `python -m paper_2309_07235_amd.profile_summary traffic` writes (counter readings scaled
 # by the same counters' readings for a device copy of known size); null when no summary for this N is there.
-def update_traffic_bytes_per_launch(n):
+def traffic_bytes_per_launch(n, tiles):
     from paper_2309_07235_amd.profile_summary import read_traffic
-    return read_traffic(os.path.join(ROOT, "profiles", f"update_kernel_hbm_traffic_n{n}.txt"), n)
+    return read_traffic(os.path.join(ROOT, "profiles", f"{'tile' if tiles else 'update'}_kernel_hbm_traffic_n{n}.txt"), n)
 
 
 def update_algorithmic_bytes(n, nb=128, lower=False, defer_min_rows=0):
@@ -256,8 +256,8 @@ def main(argv=None) -> int:
         "pct_of_measured_fp64_mfma_peak": round(gflops * 1e-3 / measured_peak * 100, 2),
         "kernels": kernels,
         "roofline": {"bound": "mfma", "achieved": round(achieved, 2), "peak": PEAK_F64_MFMA_TFLOPS, "unit": "TFLOP/s",
-                     "frac": round(achieved / PEAK_F64_MFMA_TFLOPS, 4), "traffic": None if tiles else update_traffic_bytes_per_launch(n),
-                     "kernel": "tile_factor_kernel / tile_owner_kernel (lu_factor and cholesky_factor whole, all launches)" if tiles
+                     "frac": round(achieved / PEAK_F64_MFMA_TFLOPS, 4), "traffic": traffic_bytes_per_launch(n, tiles),
+                     "kernel": "tile_factor_kernel (lu_factor and cholesky_factor whole, one launch each)" if tiles
                      else "update_kernel (bulk trailing update of lu_factor and cholesky_factor, all launches)",
                      "launches": upd_launches, "avg_launch_ms": round(upd_ms / max(upd_launches, 1), 5),
                      "flops_per_launch": round(upd_fl / max(upd_launches, 1), 1),

@@ -55,3 +55,22 @@ def test_trace_summary_lists_kernels_by_total_time(tmp_path):
     lines = [l for l in out.getvalue().splitlines() if l.startswith(("update_kernel", "diag_kernel"))]
     assert lines[0].startswith("update_kernel<double, false, 2, 128>") and " 2 " in lines[0]
     assert "average 40.00 us per launch" in out.getvalue()
+
+
+def test_tile_and_cache_summaries(tmp_path):
+    n = 64
+    copy_kib = n * n * 8 / 1024.0
+    tile, upd = "void dla::tile_factor_kernel<double, 0, 0, 1>(dla::TileArgs<double>)", "void dla::update_kernel<double, false, 2, 128>(x)"
+    f, w, c = (str(tmp_path / name) for name in ("f.db", "w.db", "c.db"))
+    for path, name, value in ((f, "FETCH_SIZE", 24.0), (w, "WRITE_SIZE", 8.0)):
+        _db(path, [(1, "__amd_rocclr_copyBuffer", name, copy_kib, 0, 10), (2, tile, name, value, 0, 10), (3, upd, name, 999.0, 0, 10)])
+    _db(c, [(1, tile, "TCC_HIT_sum", 3000.0, 0, 2000), (1, tile, "TCC_MISS_sum", 1000.0, 0, 2000), (1, tile, "TCC_REQ_sum", 4000.0, 0, 2000)])
+    out = io.StringIO()
+    with contextlib.redirect_stdout(out):
+        ps.traffic(f, w, n, tiles=True)
+        ps.cache(c, "tiles")
+    text = out.getvalue()
+    summary = tmp_path / "summary.txt"
+    summary.write_text(text)
+    assert ps.read_traffic(str(summary), n) == 32 * 1024 and "--lookahead 2" not in text
+    assert any(l.startswith("tile_factor_kernel<double, 0, 0, 1>") and l.split()[-1] == "75.0" for l in text.splitlines())

@@ -496,15 +496,30 @@ __device__ __forceinline__ int flow_run(const FlowArgs<T>& g, const int piece, c
     if (!there) t.load_published(b, x, ldy, kc);
     t.multiply(acc, a, b);
   };
+  // A solution's product with S_i holds its largest terms, the diagonal of W_i: what comes behind it is added up by itself, from zero
+  // (partial sums at the size of the result are rounded there, half of an ulp each)
+  bool parted = false;
+  auto part = [&](int q) __attribute__((always_inline)) {
+    if (sum_wg || q != from_s || q + 1 >= count) return;  // uniform
+    parted = true;
+#pragma unroll
+    for (int j = 0; j < NB; ++j) {
+#pragma unroll
+      for (int v = 0; v < 4; ++v) red[4 * NB * 256 + ((t.wave * NB + j) * 4 + v) * 64 + t.lane] = acc[j][v];
+      acc[j] = acc_t{0, 0, 0, 0};
+    }
+  };
   left(a0, 0);
   for (int q = 0; q < count; q += 2) {
     if (q + 1 < count) left(a1, q + 1);
     // (between the left operands, which do not wait for it, and the first right operand, which takes as long)
     if (!TAKEN && q == 0 && tid == 0) claimed = __hip_atomic_exchange(g.claims + piece, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     step(a0, q);
+    part(q);
     if (q + 1 >= count) break;
     if (q + 2 < count) left(a0, q + 2);
     step(a1, q + 1);
+    part(q + 1);
   }
 
   // ---- the waves' partial blocks added up: element (row_of(wave, lane), l15) of each column block is this thread's
@@ -525,7 +540,12 @@ __device__ __forceinline__ int flow_run(const FlowArgs<T>& g, const int piece, c
       T x[4];
 #pragma unroll
       for (int w = 0; w < 4; ++w) x[w] = red[((w * NB + j) * 4 + t.wave) * 64 + t.lane];
-      const T sum = ((x[0] + x[1]) + x[2]) + x[3];
+      T sum = ((x[0] + x[1]) + x[2]) + x[3];
+      if (parted) {
+#pragma unroll
+        for (int w = 0; w < 4; ++w) x[w] = red[4 * NB * 256 + ((w * NB + j) * 4 + t.wave) * 64 + t.lane];
+        sum += ((x[0] + x[1]) + x[2]) + x[3];
+      }
       if (er < rows && c < g.nrhs) {
         if (sum_wg) {
           // (the backward pass starts from Y, which is complete once a block of X is there)
@@ -559,7 +579,7 @@ __device__ __forceinline__ int flow_run(const FlowArgs<T>& g, const int piece, c
 
 template <typename T, int KIND, int NB>
 __global__ void __launch_bounds__(kFlowThreads, NB == 1 ? 3 : 2) flow_kernel(const FlowArgs<T> g) {
-  __shared__ T red[4 * NB * 256];
+  __shared__ T red[2 * 4 * NB * 256];
   __shared__ int next;
   const int own = (int)blockIdx.x;
   if (own % kNumXcd == g.absent && own < flow_pieces(g.blocks, g.tiles_n) - kFlowTiles * g.tiles_n) return;  // uniform

@@ -147,3 +147,26 @@ def test_on_many_streams(B):
             factor(x, info=info)
         stream.synchronize()
         assert int(info.item()) == 0 and torch.equal(x, want)
+
+
+# the most tiles that there are room for in either type, against the library's choice at that size (a pipeline with a tail)
+@gpu
+@pytest.mark.parametrize("kind,dtype,n", [("lu", "float64", 8192), ("chol", "float64", 8190), ("lu", "float32", 8000), ("chol", "float32", 7999)])
+def test_largest_with_block_size_64(B, kind, dtype, n):
+    import torch
+    announce(f"tiles largest {kind} {dtype} n={n}")
+    gen = torch.Generator(device="cuda").manual_seed(n)
+    m = torch.rand(n, n, dtype=torch.float64, device="cuda", generator=gen) * 2 - 1
+    a = torch.mm(m, m.t()) / n
+    a.diagonal().add_(4.0)
+    if kind == "lu":
+        a += (m - m.t()) / 8
+    a = a.to(getattr(torch, dtype))
+    outs = []
+    for nb in (0, 64):
+        x, info = a.clone(), torch.full((1,), -7, dtype=torch.int32, device="cuda")
+        (B.lu_factor if kind == "lu" else B.cholesky_factor)(x, B.FactorParams(nb, -1, B.GemmParams(), 0), info=info)
+        assert int(info.item()) == 0
+        outs.append(x.double())
+    eps = EPS64 if dtype == "float64" else EPS32
+    assert float((outs[0] - outs[1]).norm() / outs[0].norm()) <= 0.1 * n * eps  # (as in test_lines_between_the_forms)

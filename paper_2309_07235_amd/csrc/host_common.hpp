@@ -89,7 +89,7 @@ int handover_selftest_impl(void* scratch, hipStream_t st, int* d_info);
 int tiles_giveup_impl(int kind, void* A, int64_t n, int64_t lda, dla_dtype dt, void* ws, size_t ws_bytes, hipStream_t st, int* d_info);
 // What a dla_factor_params resolves to.  nb: the width of the sub-panel one diagonal-block kernel factors
 // (= nb_outer up to 128, else half of it); two_level: bulk updates may run two sub-panels deep, while the
-// trailing matrix has at least defer_min_rows rows; tiles: in 64 x 64 tiles, one or two launches; tail: the last rows so (both
+// trailing matrix has at least defer_min_rows rows; tiles: in 64 x 64 tiles, one launch; tail: the last rows so (both
 // where the call has an info pointer).
 struct FactorPlan {
   int nb_outer, nb, lookahead;

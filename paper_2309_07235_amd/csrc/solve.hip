@@ -170,7 +170,7 @@ int solve_impl(const T* F, int64_t n, int64_t lda, T* B, int64_t nrhs, int64_t l
   // 61 / 73, with 64 72 / 83; n = 4000 with 32 141 / 143, with 64 199 / 186; n = 8192 with 32 419 / 367, with 64 672 / 566).
   const int flow_nb = nrhs > 16 && n * nrhs > 128000 ? 2 : 1;
   const int tiles_n = (int)((nrhs + 16 * flow_nb - 1) / (16 * flow_nb));
-  // (its flags and claims lie in the first block's M, room for 682 blocks in fp32 with two column tiles, n = 174 000; beyond: launches)
+  // (its flags and claims lie in the first block's M, room for 683 blocks in fp32 with two column tiles, n = 174 848; beyond: launches)
   const bool flow = nrhs <= 64 && lda <= kFlowMaxLd && flow_ints(nblk, tiles_n) * (int64_t)sizeof(int) <= 2 * sb * sb * (int64_t)sizeof(T);
   int* const ints = reinterpret_cast<int*>(mf);  // (the first block has no M)
   FlowInit<T> init{Y, nblk > kFlowLook + 1 ? tf : nullptr, 0, ints, 0};  // S: where the pre-pass keeps nothing

@@ -26,8 +26,12 @@ lib.factor_workspace_bytes.argtypes, lib.factor_workspace_bytes.restype = [i64, 
 for f in (lib.lu_factor, lib.cholesky_factor):
     f.argtypes = [vp, i64, i64, ci, ctypes.POINTER(Params), vp, sz, vp, vp]
 lib.dla_factor_giveup_selftest.argtypes = [ci, vp, i64, i64, ci, vp, sz, vp, vp]
+lib.solve_workspace_bytes.argtypes, lib.solve_workspace_bytes.restype = [i64, i64, ci], sz
+lib.lu_solve.argtypes = [vp, i64, i64, vp, i64, i64, ci, vp, sz, vp]
 rec.record_text.restype = ctypes.c_char_p
-def call(kind, dtype, n, nb=0, lookahead=-1, info=True, stream=0x77, giveup=False):
+def call(kind, dtype, n, nb=0, lookahead=-1, info=True, stream=0x77, giveup=False, nrhs=0):
+    if nrhs:
+        return lib.lu_solve(0x10000000000, n, n, 0x100000000, nrhs, nrhs, dtype, 0x20000000000, lib.solve_workspace_bytes(n, nrhs, dtype), stream)
     ws = lib.factor_workspace_bytes(n, dtype, None)
     data, scratch, status = 0x100000000, 0x200000000, 0x300000000 if info else None
     if giveup:
@@ -151,3 +155,12 @@ def test_block_size_64_is_the_tiles_up_to_a_size(record, kind, dtype, most):
     tiled = [any("tile_factor_kernel" in o[5] for o in ops) for _, ops in runs]
     assert tiled == [True, False, True, False]
     assert [rc for rc, _ in runs] == [[[0]], [[0]], [[0]], [[1 if dtype == F64 else 2]]]  # (DLA_ERR_UNSUPPORTED_PARAMS; DLA_ERR_WORKSPACE)
+
+
+@pytest.mark.parametrize("nrhs,most", [(64, 683 * 256), (1, 1366 * 256)])
+def test_one_launch_of_passes_as_long_as_its_claims_have_room(record, nrhs, most):
+    """fp32: the flags and claims of flow_kernel lie in the 512 KiB of the first block's M; a system beyond takes the launches."""
+    runs = record([[[_call("lu", F32, n, nrhs=nrhs)]] for n in (most, most + 1)])
+    flows = [sum("flow_kernel" in o[5] for o in ops) for _, ops in runs]
+    assert flows == [1, 0] and all(rc == [[0]] for rc, _ in runs)
+    assert sum(o[1] == "L" for o in runs[0][1]) == 4  # three of the pre-pass in front of it
